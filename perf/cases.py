@@ -140,9 +140,10 @@ def prepare(case, seed):
     if s.stream is not None:
         s.buf.set_stream(s.stream)
         s.pipe = rb.Pipeline(s.buf)
+    s.results = [{"reps": s.out_x[q], "labels": s.out_y[q], "stored": s.buf.buf_x, "stored_labels": s.buf.buf_y} for q in range(2)]
     s.first = s.t
-    s.px = [s.x[i].data_ptr() for i in range(RING)]
-    s.py = [s.y[i].data_ptr() for i in range(RING)]
+    s.bx, s.by = list(s.x), list(s.y)
+    s.px, s.py = [x.data_ptr() for x in s.bx], [y.data_ptr() for y in s.by]
     s.ox = [[s.out_x[q, i].data_ptr() for i in range(n)] for q in range(2)]
     s.oy = [[s.out_y[q, i].data_ptr() for i in range(n)] for q in range(2)]
     s.passes = 0
@@ -175,11 +176,11 @@ def run(s):
             _ok(rb.rb_update_sample_many(h, n, px, py, b, c, r, LIB_SEED, t, s.ox[q], s.oy[q]))
         else:
             train = torch.cuda.current_stream()
-            s.pipe.step_many([s.x[k] for k in now], [s.y[k] for k in now], c, r, LIB_SEED, t, s.ox[q], s.oy[q], train)
+            s.pipe.step_many([s.bx[k] for k in now], [s.by[k] for k in now], c, r, LIB_SEED, t, s.ox[q], s.oy[q], train)
             s.pipe.drain(train)
     s.t += n
     s.passes += 1
-    return {"reps": s.out_x[q], "labels": s.out_y[q], "stored": s.buf.buf_x, "stored_labels": s.buf.buf_y}
+    return s.results[q]
 
 
 def _row_bytes(case):
