@@ -98,18 +98,14 @@ int rb_bind(rb_buffer *rb, void *buf_x, int64_t *buf_y, void *workspace, void *h
  * binary32, which is exact, by rb_sample_augment.  Mini-batches and outputs
  * keep the full row size; buf_x rows shrink to half: call this BEFORE
  * rb_query_sizes / rb_bind (RB_ESTATE once bound).  The sample's byte size
- * must be a multiple of 32.  Served by the general kernels (two launches per
- * step), by the plan-ahead forms of the single launch (rb_announce_next) and
- * by the several-steps launch (rb_update_sample_many).
+ * must be a multiple of 32.  Served by every launch form.
  * RB_STORE_U8: samples are binary32 with values meant to lie in [0, 1] (image
  * tensors); an element x is stored as the byte nearest to 255 * x - product
  * and rounding in binary32, ties to even; x <= 0 and NaN give 0, 255 * x >= 255
  * gives 255 - and handed out as byte / 255 (binary32 division, correctly
  * rounded): a quarter of the memory, an absolute error of at most 1/510 for
  * values in [0, 1].  The sample's byte size must be a multiple of 64.  Served
- * by the general kernels, by the plan-ahead forms of the single launch and by
- * the several-steps launches of rb_update_sample_many; every call form gives
- * the same bytes.
+ * by every launch form; every call form gives the same bytes.
  */
 enum rb_storage { RB_STORE_SAME = 0, RB_STORE_BF16 = 1, RB_STORE_U8 = 2 };
 int rb_set_storage(rb_buffer *rb, int32_t storage);
@@ -127,9 +123,9 @@ int rb_set_storage(rb_buffer *rb, int32_t storage);
  * offered to a full class replaces a uniformly drawn slot with probability
  * slots_per_class / n and is dropped otherwise (exact while a class has been
  * offered fewer than 2^31 - 1 samples).
- * With a variant selected a plain rb_update_sample enqueues the two general
- * kernels.  The plan-ahead forms of the single launch (rb_announce_next) serve
- * every variant (the Bernoulli selection for b <= 1024), and so do the
+ * FIFO and reservoir replacement are served by every launch form, the Bernoulli
+ * selection by the general kernels (two launches per rb_update_sample).  The
+ * plan-ahead forms of the single launch (rb_announce_next) serve every variant (the Bernoulli selection for b <= 1024), and so do the
  * several-steps launches of rb_update_sample_many (the form for small counts
  * with the exact selection only; the form for large counts takes over for the
  * Bernoulli selection, again for b <= 1024).  RB_EINVAL: unknown value.  RB_ESTATE: an rb_update was already
@@ -207,8 +203,8 @@ int rb_sample_augment(rb_buffer *rb, int64_t r, uint64_t seed, uint64_t step,
  * representatives): rb_update(rb, batch_x, batch_y, b, c, seed, step) followed
  * by rb_sample_augment(rb, r, seed, step, out_x, out_y), as one call with the
  * same arguments, meaning, errors and, bit for bit, the same results.  When
- * 1 <= c <= 64, 1 <= r <= 64 and classes <= 1024 both halves run as ONE kernel
- * launch (a representative whose slot is being written in this very step is
+ * 1 <= c <= 64, 1 <= r <= 64, classes <= 1024 and the selection is the exact one
+ * (any replacement strategy and storage form) both halves run as ONE kernel launch (a representative whose slot is being written in this very step is
  * copied from the mini-batch row stored there); otherwise the two kernels are
  * enqueued one after the other.  out_x must not overlap batch_x.
  */

@@ -118,6 +118,9 @@ struct Shape {
 // Split `rows` rows of `row_vec` vectors into tiles of at most width * unroll vectors, where `width`
 // is the number of threads that share a tile: TPB in the small-count kernels (a workgroup per tile),
 // WAVE in the general ones (a wavefront per tile).
+// (With 8-bit storage a vector stands for four accesses of a thread: one is enough in flight.  Measured on MI355X, update and
+// sampling in one launch: 8 + 8 rows of 602 KB stored in 8 bits 7.06 us with one vector per thread, 7.33 with two, 9.5 with
+// four; 32 + 32 rows of 49 KB 6.65, 7.42, 9.5; 64 + 64 rows of 602 KB 25.6, 24.5, 27.7.)
 // most: the most vectors per thread the caller's kernel can hold (the converting movers hold several accesses per
 // vector); preferred: what the caller's kernel does best with, taken when the option leaves the choice open.
 Shape plan_shape(const rb_buffer* rb, int64_t rows, int width, int most = 8, int preferred = 0)
@@ -130,7 +133,8 @@ Shape plan_shape(const rb_buffer* rb, int64_t rows, int width, int most = 8, int
         // the small-count kernels, four wavefronts in the general ones); never below two vectors in
         // flight per thread (one was slower at every size measured) unless the row is shorter.
         u = 8;
-        while (u > 2 && rows * ((row_vec + (int64_t)width * u - 1) / ((int64_t)width * u)) < 1024) u >>= 1;
+        const int least = rb->storage == RB_STORE_U8 ? 1 : 2;
+        while (u > least && rows * ((row_vec + (int64_t)width * u - 1) / ((int64_t)width * u)) < 1024) u >>= 1;
         while (u > 1 && (int64_t)width * (u / 2) >= row_vec) u >>= 1;
     }
     if (u > most) u = most;
@@ -154,18 +158,65 @@ Shape plan_shape(const rb_buffer* rb, int64_t rows, int width, int most = 8, int
     return s;
 }
 
-template <bool NT>
-hipError_t launch_update(const UpdateArgs& a, bool small, int narrow, int unroll, dim3 grid, size_t lds, hipStream_t st)
+// The small-count kernels: vectors per thread (8-bit storage: at most two, a thread holds four accesses per vector),
+// storage form and whether the replacement strategy keeps per-class state are template parameters.
+template <bool NT, int ST, bool AUX>
+hipError_t launch_update_small_s(const UpdateArgs& a, int unroll, dim3 grid, size_t lds, hipStream_t st)
 {
-    if (small) {
-        switch (unroll) {
-        case 1: rb_update_small_kernel<1, NT><<<grid, TPB, lds, st>>>(a); break;
-        case 2: rb_update_small_kernel<2, NT><<<grid, TPB, lds, st>>>(a); break;
-        case 4: rb_update_small_kernel<4, NT><<<grid, TPB, lds, st>>>(a); break;
-        default: rb_update_small_kernel<8, NT><<<grid, TPB, lds, st>>>(a); break;
-        }
-        return hipGetLastError();
+    switch (unroll) {
+    case 1: rb_update_small_kernel<1, NT, ST, AUX><<<grid, TPB, lds, st>>>(a); break;
+    case 2: rb_update_small_kernel<2, NT, ST, AUX><<<grid, TPB, lds, st>>>(a); break;
+    default:
+        if constexpr (ST == RB_STORE_U8) return hipErrorInvalidValue;
+        else if (unroll == 4) rb_update_small_kernel<4, NT, ST, AUX><<<grid, TPB, lds, st>>>(a);
+        else rb_update_small_kernel<8, NT, ST, AUX><<<grid, TPB, lds, st>>>(a);
+        break;
     }
+    return hipGetLastError();
+}
+
+template <bool NT>
+hipError_t launch_update_small(const UpdateArgs& a, int storage, int unroll, dim3 grid, size_t lds, hipStream_t st)
+{
+    const bool aux = a.eviction != RB_EVICT_UNIFORM;
+    switch (storage) {
+    case RB_STORE_BF16:
+        return aux ? launch_update_small_s<NT, RB_STORE_BF16, true>(a, unroll, grid, lds, st) : launch_update_small_s<NT, RB_STORE_BF16, false>(a, unroll, grid, lds, st);
+    case RB_STORE_U8:
+        return aux ? launch_update_small_s<NT, RB_STORE_U8, true>(a, unroll, grid, lds, st) : launch_update_small_s<NT, RB_STORE_U8, false>(a, unroll, grid, lds, st);
+    default:
+        return aux ? launch_update_small_s<NT, RB_STORE_SAME, true>(a, unroll, grid, lds, st) : launch_update_small_s<NT, RB_STORE_SAME, false>(a, unroll, grid, lds, st);
+    }
+}
+
+template <bool NT, int ST>
+hipError_t launch_sample_small_s(const SampleArgs& a, int unroll, dim3 grid, hipStream_t st)
+{
+    switch (unroll) {
+    case 1: rb_sample_small_kernel<1, NT, ST><<<grid, TPB, 0, st>>>(a); break;
+    case 2: rb_sample_small_kernel<2, NT, ST><<<grid, TPB, 0, st>>>(a); break;
+    default:
+        if constexpr (ST == RB_STORE_U8) return hipErrorInvalidValue;
+        else if (unroll == 4) rb_sample_small_kernel<4, NT, ST><<<grid, TPB, 0, st>>>(a);
+        else rb_sample_small_kernel<8, NT, ST><<<grid, TPB, 0, st>>>(a);
+        break;
+    }
+    return hipGetLastError();
+}
+
+template <bool NT>
+hipError_t launch_sample_small(const SampleArgs& a, int storage, int unroll, dim3 grid, hipStream_t st)
+{
+    switch (storage) {
+    case RB_STORE_BF16: return launch_sample_small_s<NT, RB_STORE_BF16>(a, unroll, grid, st);
+    case RB_STORE_U8: return launch_sample_small_s<NT, RB_STORE_U8>(a, unroll, grid, st);
+    default: return launch_sample_small_s<NT, RB_STORE_SAME>(a, unroll, grid, st);
+    }
+}
+
+template <bool NT>
+hipError_t launch_update(const UpdateArgs& a, int narrow, int unroll, dim3 grid, size_t lds, hipStream_t st)
+{
     if (narrow == 2) {                  // 8 bits per element: a lane holds four accesses per vector of the tile (at most four vectors)
         if (unroll == 1) rb_update_kernel<1, NT, 2><<<grid, TPB, lds, st>>>(a);
         else if (unroll == 2) rb_update_kernel<2, NT, 2><<<grid, TPB, lds, st>>>(a);
@@ -191,17 +242,8 @@ hipError_t launch_update(const UpdateArgs& a, bool small, int narrow, int unroll
 }
 
 template <bool NT>
-hipError_t launch_sample(const SampleArgs& a, bool small, int widen, int unroll, dim3 grid, size_t lds, hipStream_t st)
+hipError_t launch_sample(const SampleArgs& a, int widen, int unroll, dim3 grid, size_t lds, hipStream_t st)
 {
-    if (small) {
-        switch (unroll) {
-        case 1: rb_sample_small_kernel<1, NT><<<grid, TPB, lds, st>>>(a); break;
-        case 2: rb_sample_small_kernel<2, NT><<<grid, TPB, lds, st>>>(a); break;
-        case 4: rb_sample_small_kernel<4, NT><<<grid, TPB, lds, st>>>(a); break;
-        default: rb_sample_small_kernel<8, NT><<<grid, TPB, lds, st>>>(a); break;
-        }
-        return hipGetLastError();
-    }
     if (widen == 2) {
         if (unroll == 1) rb_sample_kernel<1, NT, 2><<<grid, TPB, lds, st>>>(a);
         else if (unroll == 2) rb_sample_kernel<2, NT, 2><<<grid, TPB, lds, st>>>(a);
@@ -226,16 +268,33 @@ hipError_t launch_sample(const SampleArgs& a, bool small, int widen, int unroll,
     return hipGetLastError();
 }
 
-template <bool NT>
-hipError_t launch_step(const StepArgs& a, int unroll, dim3 grid, size_t lds, hipStream_t st)
+template <bool NT, int ST, bool AUX>
+hipError_t launch_step_s(const StepArgs& a, int unroll, dim3 grid, size_t lds, hipStream_t st)
 {
     switch (unroll) {
-    case 1: rb_step_small_kernel<1, NT><<<grid, TPB, lds, st>>>(a); break;
-    case 2: rb_step_small_kernel<2, NT><<<grid, TPB, lds, st>>>(a); break;
-    case 4: rb_step_small_kernel<4, NT><<<grid, TPB, lds, st>>>(a); break;
-    default: rb_step_small_kernel<8, NT><<<grid, TPB, lds, st>>>(a); break;
+    case 1: rb_step_small_kernel<1, NT, ST, AUX><<<grid, TPB, lds, st>>>(a); break;
+    case 2: rb_step_small_kernel<2, NT, ST, AUX><<<grid, TPB, lds, st>>>(a); break;
+    default:
+        if constexpr (ST == RB_STORE_U8) return hipErrorInvalidValue;
+        else if (unroll == 4) rb_step_small_kernel<4, NT, ST, AUX><<<grid, TPB, lds, st>>>(a);
+        else rb_step_small_kernel<8, NT, ST, AUX><<<grid, TPB, lds, st>>>(a);
+        break;
     }
     return hipGetLastError();
+}
+
+template <bool NT>
+hipError_t launch_step(const StepArgs& a, int storage, int unroll, dim3 grid, size_t lds, hipStream_t st)
+{
+    const bool aux = a.u.eviction != RB_EVICT_UNIFORM;
+    switch (storage) {
+    case RB_STORE_BF16:
+        return aux ? launch_step_s<NT, RB_STORE_BF16, true>(a, unroll, grid, lds, st) : launch_step_s<NT, RB_STORE_BF16, false>(a, unroll, grid, lds, st);
+    case RB_STORE_U8:
+        return aux ? launch_step_s<NT, RB_STORE_U8, true>(a, unroll, grid, lds, st) : launch_step_s<NT, RB_STORE_U8, false>(a, unroll, grid, lds, st);
+    default:
+        return aux ? launch_step_s<NT, RB_STORE_SAME, true>(a, unroll, grid, lds, st) : launch_step_s<NT, RB_STORE_SAME, false>(a, unroll, grid, lds, st);
+    }
 }
 
 template <bool NT, int PACE>
@@ -1140,9 +1199,8 @@ int rb_update(rb_buffer* rb, const void* batch_x, const int64_t* batch_y,
     discard_plan(rb);
     if (c == 0) return RB_OK;
 
-    const bool variant = rb->selection != RB_SELECT_EXACT || rb->eviction != RB_EVICT_UNIFORM;
     const int narrow = rb->storage == RB_STORE_BF16 ? 1 : rb->storage == RB_STORE_U8 ? 2 : 0;
-    const bool small = c <= WAVE && !variant && !narrow;
+    const bool small = c <= WAVE && rb->selection == RB_SELECT_EXACT;
     // Rows the grid is sized for.  The Bernoulli selection yields a random number of candidates
     // (mean c, at most b); the movers loop over the work items, so any number is handled, and
     // the grid only has to be large enough for the usual case.
@@ -1152,7 +1210,7 @@ int rb_update(rb_buffer* rb, const void* batch_x, const int64_t* batch_y,
         while (slack * slack < 36 * c) ++slack;          // about six standard deviations
         rows = c + slack < b ? c + slack : b;
     }
-    const Shape sh = plan_shape(rb, rows, small ? TPB : WAVE, narrow == 2 ? 4 : 8);   // (the 8-bit mover holds at most four vectors per lane)
+    const Shape sh = plan_shape(rb, rows, small ? TPB : WAVE, narrow == 2 ? (small ? 2 : 4) : 8);   // (see plan_shape)
     UpdateArgs a;
     a.batch_x = static_cast<const vec16*>(batch_x);
     a.batch_y = batch_y;
@@ -1174,8 +1232,10 @@ int rb_update(rb_buffer* rb, const void* batch_x, const int64_t* batch_y,
     a.aux_new = reinterpret_cast<int32_t*>(rb->ws + rb->off_aux[rb->cur ^ 1]);
     const dim3 grid((unsigned)(rb->nchunks + (small ? sh.groups * sh.tpr : (rows * sh.tpr + NWAVE - 1) / NWAVE)));
     const size_t lds = small ? (size_t)b * 8 : (size_t)b * 4 + (size_t)a.cap * 8;
-    hipError_t e = rb->opt_nt ? launch_update<true>(a, small, narrow, sh.unroll, grid, lds, rb->stream)
-                              : launch_update<false>(a, small, narrow, sh.unroll, grid, lds, rb->stream);
+    const hipError_t e = small ? (rb->opt_nt ? launch_update_small<true>(a, rb->storage, sh.unroll, grid, lds, rb->stream)
+                                             : launch_update_small<false>(a, rb->storage, sh.unroll, grid, lds, rb->stream))
+                               : (rb->opt_nt ? launch_update<true>(a, narrow, sh.unroll, grid, lds, rb->stream)
+                                             : launch_update<false>(a, narrow, sh.unroll, grid, lds, rb->stream));
     if (e != hipSuccess) return RB_EHIP;
     rb->cur ^= 1;
     rb->updates += 1;
@@ -1191,8 +1251,8 @@ int rb_sample_augment(rb_buffer* rb, int64_t r, uint64_t seed, uint64_t step, vo
     if (r == 0) return RB_OK;
 
     const int widen = rb->storage == RB_STORE_BF16 ? 1 : rb->storage == RB_STORE_U8 ? 2 : 0;
-    const bool small = r <= WAVE && rb->nchunks <= WAVE && !widen;
-    const Shape sh = plan_shape(rb, r, small ? TPB : WAVE, widen == 2 ? 4 : 8);
+    const bool small = r <= WAVE && rb->nchunks <= WAVE;
+    const Shape sh = plan_shape(rb, r, small ? TPB : WAVE, widen == 2 ? (small ? 2 : 4) : 8);
     SampleArgs a;
     a.buf_x = static_cast<const vec16*>(rb->buf_x);
     a.out_x = static_cast<vec16*>(out_x);
@@ -1208,8 +1268,10 @@ int rb_sample_augment(rb_buffer* rb, int64_t r, uint64_t seed, uint64_t step, vo
     a.tpr = sh.tpr; a.tile_vec = sh.tile_vec; a.tile_rem = sh.tile_rem; a.rpb = sh.rpb;
     const dim3 grid((unsigned)(small ? sh.groups * sh.tpr : (r * sh.tpr + NWAVE - 1) / NWAVE));
     const size_t lds = small ? 0 : ((size_t)rb->nchunks + (size_t)r) * 4;
-    hipError_t e = rb->opt_nt ? launch_sample<true>(a, small, widen, sh.unroll, grid, lds, rb->stream)
-                              : launch_sample<false>(a, small, widen, sh.unroll, grid, lds, rb->stream);
+    const hipError_t e = small ? (rb->opt_nt ? launch_sample_small<true>(a, rb->storage, sh.unroll, grid, rb->stream)
+                                             : launch_sample_small<false>(a, rb->storage, sh.unroll, grid, rb->stream))
+                               : (rb->opt_nt ? launch_sample<true>(a, widen, sh.unroll, grid, lds, rb->stream)
+                                             : launch_sample<false>(a, widen, sh.unroll, grid, lds, rb->stream));
     return e == hipSuccess ? RB_OK : RB_EHIP;
 }
 
@@ -1224,7 +1286,7 @@ int rb_update_sample(rb_buffer* rb, const void* batch_x, const int64_t* batch_y,
     // the plan-ahead form covers both storage forms; the kernel that plans and moves in one launch only the plain one
     const bool plannable = c >= 1 && c <= WAVE && r >= 1 && r <= WAVE && rb->nchunks <= DIRECT_CHUNKS && rb->opt_fuse &&
                            rb->selection == RB_SELECT_EXACT;
-    const bool fused = plannable && rb->storage == RB_STORE_SAME && rb->eviction == RB_EVICT_UNIFORM;
+    const bool fused = plannable;
     // larger counts have a plan-ahead form of their own
     // (with the Bernoulli selection, whose number of candidates is only bounded by b, for mini-batches of at most BIG_MAX)
     const bool big = !plannable && c >= 1 && c <= BIG_MAX && r >= 1 && r <= BIG_MAX && b <= BIG_BATCH &&
@@ -1244,7 +1306,7 @@ int rb_update_sample(rb_buffer* rb, const void* batch_x, const int64_t* batch_y,
         if (rc != RB_OK) return rc;
         return rb_sample_augment(rb, r, seed, step, out_x, out_y);
     }
-    const Shape sh = plan_shape(rb, c + r, TPB);
+    const Shape sh = plan_shape(rb, c + r, TPB, rb->storage == RB_STORE_U8 ? 2 : 8);
     StepArgs sa;
     UpdateArgs& a = sa.u;
     a.batch_x = static_cast<const vec16*>(batch_x);
@@ -1261,16 +1323,17 @@ int rb_update_sample(rb_buffer* rb, const void* batch_x, const int64_t* batch_y,
     a.S = rb->S;
     a.row_vec = rb->row_vec;
     a.tpr = sh.tpr; a.tile_vec = sh.tile_vec; a.tile_rem = sh.tile_rem; a.rpb = 1;
-    a.selection = RB_SELECT_EXACT; a.eviction = RB_EVICT_UNIFORM; a.cap = (int32_t)c;
-    a.aux_old = nullptr; a.aux_new = nullptr;
+    a.selection = RB_SELECT_EXACT; a.eviction = rb->eviction; a.cap = (int32_t)c;
+    a.aux_old = reinterpret_cast<const int32_t*>(rb->ws + rb->off_aux[rb->cur]);
+    a.aux_new = reinterpret_cast<int32_t*>(rb->ws + rb->off_aux[rb->cur ^ 1]);
     sa.out_x = static_cast<vec16*>(out_x);
     sa.out_y = out_y;
     sa.r = (int32_t)r;
     sa.first_gather = (int32_t)(rb->nchunks + c * sh.tpr);
     const dim3 grid((unsigned)(rb->nchunks + (c + r) * sh.tpr));
     const size_t lds = (((size_t)b * 2 + 3) & ~(size_t)3) * 4 + (size_t)DIRECT_CHUNKS * CH * 8;
-    hipError_t e = rb->opt_nt ? launch_step<true>(sa, sh.unroll, grid, lds, rb->stream)
-                              : launch_step<false>(sa, sh.unroll, grid, lds, rb->stream);
+    const hipError_t e = rb->opt_nt ? launch_step<true>(sa, rb->storage, sh.unroll, grid, lds, rb->stream)
+                                    : launch_step<false>(sa, rb->storage, sh.unroll, grid, lds, rb->stream);
     if (e != hipSuccess) return RB_EHIP;
     rb->cur ^= 1;
     rb->updates += 1;

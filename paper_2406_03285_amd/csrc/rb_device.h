@@ -54,6 +54,21 @@ struct Seed {
     uint32_t seed_lo, seed_hi, step_lo, step_hi;
 };
 
+// Requests every 64-byte line of the kernel's arguments at once and waits for them together.  A launch's arguments are in
+// no cache, and the compiler reads them in batches as it comes to need them: each batch that starts a new line is one more
+// trip to memory (measured on MI355X: about 0.5 us) before the wavefront goes on.
+template <size_t BYTES>
+__device__ __forceinline__ void fetch_args()
+{
+    constexpr int LINES = (int)((BYTES + 63) / 64);
+    const __attribute__((address_space(4))) uint32_t* args = (const __attribute__((address_space(4))) uint32_t*)__builtin_amdgcn_kernarg_segment_ptr();
+    uint32_t v[LINES];
+#pragma unroll
+    for (int i = 0; i < LINES; ++i) v[i] = args[16 * i];
+#pragma unroll
+    for (int i = 0; i < LINES; ++i) asm volatile("" : : "s"(v[i]));
+}
+
 // ---------------------------------------------------------------------------
 // Counter-based random draws: Philox4x32-10 (Salmon et al., SC'11).  Counter =
 // (index, purpose, step), key = seed; the low two output words form one 64-bit
@@ -78,9 +93,16 @@ __device__ __forceinline__ uint64_t draw64(const Seed& sd, uint32_t purpose, uin
     return (uint64_t)x0 | ((uint64_t)x1 << 32);
 }
 
+// The high half of bits * n, for an n of 32 bits: two 32x32->64 multiply-adds (a 64-bit high product takes four and the carries).
+__device__ __forceinline__ uint32_t reduce32(uint64_t bits, uint32_t n)
+{
+    return (uint32_t)(((bits >> 32) * n + (((bits & 0xFFFFFFFFu) * n) >> 32)) >> 32);
+}
+
+// Every range drawn from is below 2^32: mini-batch positions, slots, stored samples, and a class's offers (counted up to 2^31).
 __device__ __forceinline__ uint64_t below(const Seed& sd, uint32_t purpose, uint32_t index, uint64_t n)
 {
-    return __umul64hi(draw64(sd, purpose, index), n);
+    return reduce32(draw64(sd, purpose, index), (uint32_t)n);
 }
 
 // ---------------------------------------------------------------------------
@@ -209,15 +231,19 @@ constexpr int stored_wide(int storage)
 // the destination row is binary32, converted from the tile's bfloat16 while it is stored; CV_BOTH -
 // binary32 to binary32 through the bfloat16 a stored copy would hold.  Tile indices always count
 // vectors of the narrow (stored) row.
-template <int U, bool NT, int W = TPB, int PACED = 1, int CV = CV_NONE>
+// LATE (CV_NARROW only): the binary32 vectors are kept as they come and converted when they are stored, so that load()
+// does not wait for them.
+template <int U, bool NT, int W = TPB, int PACED = 1, int CV = CV_NONE, bool LATE = false>
 struct Tile {
+    static constexpr bool RAW = LATE && CV != CV_NONE;       // load() moves vectors of the binary32 row
+    static constexpr int PARTS = CV & CV_Q8 ? 4 : CV ? 2 : 1;
     // Without conversion a lane holds U vectors.  With one, it holds 2 U half vectors (four bfloat16 each):
     // a lane then touches 8 bytes of the narrow row and 16 bytes of the binary32 row per access, so every
     // instruction of a wavefront covers one contiguous run of bytes on either side.
-    vec16 v[CV ? 1 : U];
-    vec8 h[CV && !(CV & CV_Q8) ? 2 * U : 1];
+    vec16 v[RAW ? PARTS * U : CV ? 1 : U];
+    vec8 h[CV && !(CV & CV_Q8) && !RAW ? 2 * U : 1];
     // 8-bit storage: 4 U quarter vectors (four bytes of the stored row against 16 bytes of the binary32 row per access)
-    uint32_t q[CV & CV_Q8 ? 4 * U : 1];
+    uint32_t q[CV & CV_Q8 && !RAW ? 4 * U : 1];
 
     // Requires lo < hi.  No lane is ever masked off: a lane whose index falls past the end of
     // the tile moves the tile's last vector again (same source, same destination, same bytes as
@@ -226,6 +252,15 @@ struct Tile {
     // to drain these - and keeps the compiler from moving loads down into a guarded store.
     __device__ __forceinline__ void load(const vec16* __restrict__ src, int64_t lo, int64_t hi)
     {
+        if constexpr (RAW) {
+#pragma unroll
+            for (int u = 0; u < PARTS * U; ++u) {
+                int64_t j = PARTS * lo + (int64_t)u * W + (threadIdx.x & (W - 1));
+                j = j < PARTS * hi ? j : PARTS * hi - 1;
+                v[u] = NT ? __builtin_nontemporal_load(src + j) : src[j];
+            }
+            return;
+        }
         if (CV & CV_Q8) {
 #pragma unroll
             for (int u = 0; u < 4 * U; ++u) {
@@ -278,13 +313,14 @@ struct Tile {
                 int64_t j = 4 * lo + (int64_t)u * W + (threadIdx.x & (W - 1));
                 j = j < 4 * hi ? j : 4 * hi - 1;
                 if (CV & CV_WIDEN) {
-                    const vec16 a = unpack4_u8(q[u]);
+                    const vec16 a = unpack4_u8(q[RAW ? 0 : u]);
                     if (NT) __builtin_nontemporal_store(a, dst + j);
                     else dst[j] = a;
                 } else {
                     uint32_t* quarter = reinterpret_cast<uint32_t*>(dst);
-                    if (NT) __builtin_nontemporal_store(q[u], quarter + j);
-                    else quarter[j] = q[u];
+                    const uint32_t a = RAW ? pack4_u8(v[RAW ? u : 0]) : q[RAW ? 0 : u];
+                    if (NT) __builtin_nontemporal_store(a, quarter + j);
+                    else quarter[j] = a;
                 }
                 if (PACED && (u + 1) % PACED == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             }
@@ -296,13 +332,14 @@ struct Tile {
                 int64_t j = 2 * lo + (int64_t)u * W + (threadIdx.x & (W - 1));
                 j = j < 2 * hi ? j : 2 * hi - 1;
                 if (CV & CV_WIDEN) {
-                    const vec16 a = widen4(h[u]);
+                    const vec16 a = widen4(h[RAW ? 0 : u]);
                     if (NT) __builtin_nontemporal_store(a, dst + j);
                     else dst[j] = a;
                 } else {
                     vec8* half = reinterpret_cast<vec8*>(dst);
-                    if (NT) __builtin_nontemporal_store(h[u], half + j);
-                    else half[j] = h[u];
+                    const vec8 a = RAW ? narrow4(v[RAW ? u : 0]) : h[RAW ? 0 : u];
+                    if (NT) __builtin_nontemporal_store(a, half + j);
+                    else half[j] = a;
                 }
                 if (PACED && (u + 1) % PACED == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             }

@@ -67,22 +67,66 @@ __device__ __forceinline__ int wave_select(const Seed& sd, int b, int c, uint32_
     return active ? (taken ? base + lane : (int)t) : 0;
 }
 
+// Slot of class-mate number `rank` (at mini-batch position x) of a class that held fill0 samples: appended while there is
+// room, else what the replacement strategy overwrites; -1: not kept (reservoir).  aux0: the strategy's state of the class.
+__device__ __forceinline__ int mate_slot(const UpdateArgs& a, int x, int rank, int64_t fill0, int64_t aux0)
+{
+    const int64_t at = fill0 + rank;
+    if (at < a.S) return (int)at;
+    if (a.eviction == RB_EVICT_FIFO) return (int)((aux0 + at - a.S) % a.S);
+    const bool reservoir = a.eviction == RB_EVICT_RESERVOIR;
+    const int64_t offers = aux0 + rank < INT32_MAX ? aux0 + rank : INT32_MAX;      // to the class, before this one
+    const int64_t draw = (int64_t)below(a.sd, PURPOSE_EVICT, (uint32_t)x, reservoir ? (uint64_t)offers + 1 : (uint64_t)a.S);
+    return draw < a.S ? (int)draw : -1;
+}
+
+// The strategy's state of a class after a step that offers it `count` candidates (old: samples it held, aux: state before).
+__device__ __forceinline__ int32_t next_aux(const UpdateArgs& a, int64_t old, int64_t aux, int64_t count)
+{
+    if (a.eviction == RB_EVICT_FIFO) {
+        const int64_t over = old + count > a.S ? old + count - a.S : 0;            // the oldest sample moves on by the overwrites
+        return (int32_t)((aux + over) % a.S);
+    }
+    const int64_t seen = aux + count;
+    return (int32_t)(seen < INT32_MAX ? seen : INT32_MAX);
+}
+
+// For every lane of `mask`: how many other lanes of it hold a smaller x.
+__device__ __forceinline__ int rank_among(uint64_t mask, int x)
+{
+    int rank = 0;
+    while (mask != 0) {
+        const int m = __builtin_ctzll(mask);
+        mask &= mask - 1;
+        rank += (int)(__builtin_amdgcn_readlane(x, m) < x);
+    }
+    return rank;
+}
+
 // Where candidate i (mini-batch position p, class ki, fill0 samples of that class stored before
 // the step) is stored: row index ki*S + slot, or -1 if it is not stored (label outside [0, K),
 // or a later class-mate overwrites its slot).  Lane l holds candidate l: position x, class k.
-__device__ __forceinline__ int64_t wave_place(const Seed& sd, bool active, int x, int32_t k, int i, int p,
-                                              int32_t ki, int64_t fill0, int64_t S)
+// AUX: FIFO or reservoir replacement.
+template <bool AUX>
+__device__ __forceinline__ int64_t wave_place(const UpdateArgs& a, bool active, int x, int32_t k, int i, int p, int32_t ki)
 {
     if (ki < 0) return -1;
+    const int64_t fill0 = a.fill_old[ki], S = a.S;
     // candidates of class ki; in mini-batch order the one with `rank` class-mates
     // before it is insertion number fill0 + rank of the class
     const bool same = active && k == ki;
     const int total = __popcll(__ballot(same));
     const int rank = __popcll(__ballot(same && x < p));
     if (fill0 + total <= S) return (int64_t)ki * S + fill0 + rank;     // all append: distinct slots
+    if (AUX) {
+        // a later class-mate may take the slot, or (reservoir) it may not be kept
+        const int slot = same ? mate_slot(a, x, rank_among(__ballot(same), x), fill0, a.aux_old[ki]) : -1;
+        const int own = lane_read(slot, i);
+        return own < 0 || __ballot(same && x > p && slot == own) != 0 ? -1 : (int64_t)ki * S + own;
+    }
     // Insertions beyond the capacity overwrite a uniformly drawn slot.  This
     // candidate is not stored if a later class-mate overwrites its slot.
-    const int draw = same ? (int)below(sd, PURPOSE_EVICT, (uint32_t)x, (uint64_t)S) : -1;
+    const int draw = same ? (int)below(a.sd, PURPOSE_EVICT, (uint32_t)x, (uint64_t)S) : -1;
     const int own = fill0 + rank < S ? (int)(fill0 + rank) : lane_read(draw, i);
     uint64_t rivals = __ballot(same && x > p && draw == own);
     while (rivals != 0) {
@@ -96,7 +140,7 @@ __device__ __forceinline__ int64_t wave_place(const Seed& sd, bool active, int x
 }
 
 // ---------------------------------------------------------------------------
-// rb_update for c <= WAVE candidates: the plan is computed by the first
+// rb_update for c <= WAVE candidates, exact selection, any replacement strategy and storage form: the plan is computed by the first
 // wavefront of each workgroup alone, one lane per candidate, with ballots and
 // lane reads instead of workgroup scans; the other three wavefronts only move
 // data.  Same grid and arguments as rb_update_kernel.
@@ -104,7 +148,7 @@ __device__ __forceinline__ int64_t wave_place(const Seed& sd, bool active, int x
 // LDS (dynamic): s_first[b] u32 (lowest lane that drew a value), s_y[b] i32
 // (label of every mini-batch position, LAB_INVALID when outside [0, K)).
 // ---------------------------------------------------------------------------
-template <int U, bool NT>
+template <int U, bool NT, int ST, bool AUX>     // ST: RB_STORE_*, the form binary32 samples are stored in; AUX: FIFO or reservoir replacement
 __global__ void __launch_bounds__(TPB) rb_update_small_kernel(const UpdateArgs a)
 {
     extern __shared__ uint32_t lds[];
@@ -151,6 +195,7 @@ __global__ void __launch_bounds__(TPB) rb_update_small_kernel(const UpdateArgs a
             int64_t v = (int64_t)a.fill_old[kk] + s_hist[tid];
             nf = (int32_t)(v < a.S ? v : a.S);
             a.fill_new[kk] = nf;
+            if (AUX) a.aux_new[kk] = next_aux(a, a.fill_old[kk], a.aux_old[kk], s_hist[tid]);
         }
         int total;
         block_scan_excl(nf, total, s_wave);
@@ -178,14 +223,14 @@ __global__ void __launch_bounds__(TPB) rb_update_small_kernel(const UpdateArgs a
         const int p = s_p[0];
         // The row is requested as soon as its position is known: before the labels have
         // arrived, and long before wavefront 0 has worked out where it goes.
-        Tile<U, NT> t;
-        t.load(a.batch_x + (int64_t)p * a.row_vec, v_lo, v_hi);
+        Tile<U, NT, TPB, 1, stored_cv(ST, CV_NARROW), true> t;
+        t.load(a.batch_x + (int64_t)p * a.row_vec * stored_wide(ST), v_lo, v_hi);
         park_labels(yv, a.batch_y, b, a.K, s_y);
         __syncthreads();
         if (w0) {
             k = active ? s_y[x] : LAB_UNSELECTED;
             const int32_t ki = lane_read(k, i);
-            const int64_t dst = wave_place(a.sd, active, x, k, i, p, ki, ki >= 0 ? a.fill_old[ki] : 0, a.S);
+            const int64_t dst = wave_place<AUX>(a, active, x, k, i, p, ki);
             if (lane == 0) s_dst[0] = dst;
         }
         __syncthreads();
@@ -205,11 +250,11 @@ __global__ void __launch_bounds__(TPB) rb_update_small_kernel(const UpdateArgs a
         }
         __syncthreads();
         const int p = s_p[par];
-        Tile<U, NT> t;
-        t.load(a.batch_x + (int64_t)p * a.row_vec, v_lo, v_hi);
+        Tile<U, NT, TPB, 1, stored_cv(ST, CV_NARROW), true> t;
+        t.load(a.batch_x + (int64_t)p * a.row_vec * stored_wide(ST), v_lo, v_hi);
         if (w0) {
             const int32_t ki = lane_read(k, i);
-            const int64_t dst = wave_place(a.sd, active, x, k, i, p, ki, ki >= 0 ? a.fill_old[ki] : 0, a.S);
+            const int64_t dst = wave_place<AUX>(a, active, x, k, i, p, ki);
             if (lane == 0) s_dst[par] = dst;
         }
         __syncthreads();
@@ -231,7 +276,7 @@ __global__ void __launch_bounds__(TPB) rb_update_small_kernel(const UpdateArgs a
 // ---------------------------------------------------------------------------
 constexpr int DIRECT_CHUNKS = 4;
 
-template <int U, bool NT>
+template <int U, bool NT, int ST>
 __global__ void __launch_bounds__(TPB) rb_sample_small_kernel(const SampleArgs a)
 {
     __shared__ int s_pick[2][2];    // (class, slot) of the current row, double-buffered over rows
@@ -332,16 +377,25 @@ __global__ void __launch_bounds__(TPB) rb_sample_small_kernel(const SampleArgs a
             continue;
         }
         const int pk = s_pick[par][0], ps = s_pick[par][1];
-        Tile<U, NT> t2;
+        Tile<U, NT, TPB, 1, stored_cv(ST, CV_WIDEN)> t2;
         t2.load(a.buf_x + ((int64_t)pk * a.S + ps) * a.row_vec, v_lo, v_hi);
-        t2.store(a.out_x + (int64_t)j * a.row_vec, v_lo, v_hi);
+        t2.store(a.out_x + (int64_t)j * a.row_vec * stored_wide(ST), v_lo, v_hi);
         if (tile == 0 && tid == 0) { a.out_y[j] = pk; count_moved(a.state); }
     }
 }
 
 // ---------------------------------------------------------------------------
 // rb_update_sample, c <= WAVE, r <= WAVE, at most DIRECT_CHUNKS chunks of
-// classes: update and sampling of one step in ONE launch.
+// classes, exact selection: update and sampling of one step in ONE launch, with
+// any replacement strategy and storage form.  What bounds it is the chain from
+// the labels to the rows' addresses and the launch itself, so a second dependent
+// launch is the thing to avoid.  Measured on MI355X, this launch against the two
+// general ones: 8 + 8 rows of 602 KB stored in 8 bits 7.1 : 14.2 us, as bfloat16
+// 7.4 : 10.7; 32 + 32 rows as bfloat16 12.5 : 20.9; 16 + 16 rows of 12 KB in
+// 8 bits 6.3 : 13.7; FIFO 8 + 8 rows of 602 KB 7.6 : 11.0; reservoir 16 + 16 rows
+// of 12 KB 5.7 : 9.0.  With binary32 samples stored in fewer bits the vectors
+// are converted when they are stored: a conversion at the load would wait for
+// the row before its destination is worked out.
 //
 // Grid: bookkeeping workgroups, then the movers of the c candidate rows
 // (exactly as in rb_update_small_kernel), then the movers of the r
@@ -357,9 +411,10 @@ __global__ void __launch_bounds__(TPB) rb_sample_small_kernel(const SampleArgs a
 // s_cnt[DIRECT_CHUNKS*CH] (candidates of each class in this step).
 // ---------------------------------------------------------------------------
 
-template <int U, bool NT>
+template <int U, bool NT, int ST, bool AUX>
 __global__ void __launch_bounds__(TPB) rb_step_small_kernel(const StepArgs sa)
 {
+    fetch_args<sizeof(StepArgs)>();
     const UpdateArgs& a = sa.u;
     constexpr int NCLS = DIRECT_CHUNKS * CH;
     extern __shared__ uint32_t lds[];
@@ -418,6 +473,7 @@ __global__ void __launch_bounds__(TPB) rb_step_small_kernel(const StepArgs sa)
             int64_t v = (int64_t)a.fill_old[kk] + s_hist[tid];
             nf = (int32_t)(v < a.S ? v : a.S);
             a.fill_new[kk] = nf;
+            if (AUX) a.aux_new[kk] = next_aux(a, a.fill_old[kk], a.aux_old[kk], s_hist[tid]);
         }
         int total;
         block_scan_excl(nf, total, s_wave);
@@ -438,14 +494,14 @@ __global__ void __launch_bounds__(TPB) rb_step_small_kernel(const StepArgs sa)
         __syncthreads();
         const int p = s_p;
         // requested as soon as the position is known, before the labels have arrived
-        Tile<U, NT> t;
-        t.load(a.batch_x + (int64_t)p * a.row_vec, v_lo, v_hi);
+        Tile<U, NT, TPB, 1, stored_cv(ST, CV_NARROW), true> t;
+        t.load(a.batch_x + (int64_t)p * a.row_vec * stored_wide(ST), v_lo, v_hi);
         park_labels(yv, a.batch_y, b, a.K, s_y);
         __syncthreads();
         if (w0) {
             const int32_t k = active ? s_y[x] : LAB_UNSELECTED;
             const int32_t ki = lane_read(k, i);
-            const int64_t dst = wave_place(a.sd, active, x, k, i, p, ki, ki >= 0 ? a.fill_old[ki] : 0, a.S);
+            const int64_t dst = wave_place<AUX>(a, active, x, k, i, p, ki);
             if (lane == 0) s_dst = dst;
         }
         __syncthreads();
@@ -523,18 +579,9 @@ __global__ void __launch_bounds__(TPB) rb_step_small_kernel(const StepArgs sa)
             const int64_t fill0 = s_old[pk];
             int fwd = -1;
             if (same_mask != 0 && (ps >= fill0 || fill0 + __popcll(same_mask) > a.S)) {
-                int my_rank = 0;                       // class-mates earlier in the mini-batch
-                uint64_t sm = same_mask;
-                while (sm != 0) {
-                    const int m = __builtin_ctzll(sm);
-                    sm &= sm - 1;
-                    my_rank += (int)(__builtin_amdgcn_readlane(x, m) < x);
-                }
+                const int my_rank = rank_among(same_mask, x);          // class-mates earlier in the mini-batch
                 int slot = -1;
-                if (same) {
-                    const int64_t at = fill0 + my_rank;
-                    slot = (int)(at < a.S ? at : (int64_t)below(a.sd, PURPOSE_EVICT, (uint32_t)x, (uint64_t)a.S));
-                }
+                if (same) slot = mate_slot(a, x, my_rank, fill0, AUX ? a.aux_old[pk] : 0);
                 uint64_t writers = __ballot(same && slot == ps);
                 while (writers != 0) {                 // the one latest in the mini-batch is what the slot holds
                     const int m = __builtin_ctzll(writers);
@@ -552,11 +599,19 @@ __global__ void __launch_bounds__(TPB) rb_step_small_kernel(const StepArgs sa)
         return;
     }
     const int pk = s_pick[0], ps = s_pick[1], fwd = s_pick[2];
-    const vec16* src = fwd >= 0 ? a.batch_x + (int64_t)fwd * a.row_vec
-                                : a.buf_x + ((int64_t)pk * a.S + ps) * a.row_vec;
-    Tile<U, NT> t;
-    t.load(src, v_lo, v_hi);
-    t.store(sa.out_x + (int64_t)j * a.row_vec, v_lo, v_hi);
+    vec16* dst = sa.out_x + (int64_t)j * a.row_vec * stored_wide(ST);
+    if (ST != RB_STORE_SAME && fwd >= 0) {
+        // from the mini-batch: what the slot will hold is the row in its stored form
+        Tile<U, NT, TPB, 1, stored_cv(ST, CV_BOTH)> t;
+        t.load(a.batch_x + (int64_t)fwd * a.row_vec * stored_wide(ST), v_lo, v_hi);
+        t.store(dst, v_lo, v_hi);
+    } else {
+        const vec16* src = fwd >= 0 ? a.batch_x + (int64_t)fwd * a.row_vec
+                                    : a.buf_x + ((int64_t)pk * a.S + ps) * a.row_vec;
+        Tile<U, NT, TPB, 1, stored_cv(ST, CV_WIDEN)> t;
+        t.load(src, v_lo, v_hi);
+        t.store(dst, v_lo, v_hi);
+    }
     if (tile == 0 && tid == 0) { sa.out_y[j] = pk; count_moved(a.state); }
 }
 

@@ -115,6 +115,48 @@ def test_policy_variant_through_the_single_call_and_at_full_size():
     run_parity(wl.C4, steps=30, policy=POLICIES["bernoulli-fifo"], single_call=True, progress=10)
 
 
+# The single call without a plan: small counts (one launch, any strategy and storage form) and the shapes beyond them.
+@pytest.mark.parametrize("policy", ["exact-uniform"] + sorted(POLICIES))
+@pytest.mark.parametrize("K,S,vecs,b,c,r,store,labels", [
+    (10, 3, 64, 40, 9, 12, "bf16", "uniform"),              # both counts within a wavefront, classes fill at once
+    (300, 4, 133, 200, 64, 64, "u8", "zipf"),               # the last counts one wavefront selects; ragged rows
+    (300, 4, 133, 200, 65, 63, "same", "zipf"),             # ... and the first ones the workgroup does
+    (2, 700, 1, 4096, 4096, 4096, "same", "uniform"),       # every count at its limit, ~2048 class-mates, one vector per row
+    (1, 37, 4, 1100, 1024, 1025, "bf16", "uniform"),        # one class: thousands of rivals, r above what is stored
+    (1024, 9, 192, 1025, 500, 128, "u8", "active50"),       # ~10 class-mates, more positions than threads
+    (10240, 2, 64, 300, 90, 200, "same", "uniform"),        # most classes this launch serves
+    (10241, 2, 64, 300, 90, 200, "same", "uniform"),        # one more: two launches
+    (1025, 6, 9408, 64, 8, 8, "same", "uniform"),           # long rows: several tiles per row
+    (50, 5, 1176, 1000, 700, 900, "bf16", "zipf"),          # more tiles than wavefronts: they take several each
+])
+def test_single_call_without_a_plan(K, S, vecs, b, c, r, store, labels, policy):
+    shape = (vecs * {"same": 4, "bf16": 8, "u8": 16}[store],)       # vecs: 16-byte vectors of a stored row
+    w = wl.Workload(f"one-K{K}-b{b}-c{c}-r{r}-{store}", 9, K, S, shape, "f32", b, c, r, 4, "uniform", labels)
+    run_parity(w, check_state_every=2, single_call=True, policy=POLICIES.get(policy),
+               store_bf16=store == "bf16", store_u8=store == "u8")
+
+
+def test_single_call_without_a_plan_drops_and_flags_bad_labels():
+    rb = _rb()
+    K, S, b, c, r = 1500, 3, 300, 200, 70
+    buf = rb.RehearsalBuffer(K, S, (64,), torch.float32)
+    orc = rbo.Buffer(K, S, 256)
+    x = torch.randn((b, 64), device="cuda:0")
+    out_x, out_y = torch.zeros((r, 64), device="cuda:0"), torch.full((r,), -7, dtype=torch.int64, device="cuda:0")
+    for step in range(3):
+        y = torch.randint(0, 40, (b,), device="cuda:0")
+        if step == 1:
+            y[::3] = torch.tensor([-1, K, 1 << 40, -(1 << 40)], device="cuda:0").repeat(25)
+        buf.update_sample(x, y, c, r, 5, step, out_x, out_y)
+        hx = x.cpu().numpy().view(np.uint8).reshape(b, 256)
+        orc.update(hx, y.cpu().numpy(), c, 5, step)
+        n, want_x, want_y = orc.sample_augment(r, 5, step, out_x=np.zeros((r, 256), dtype=np.uint8))
+        assert np.array_equal(out_y.cpu().numpy(), want_y)
+        assert np.array_equal(out_x.cpu().numpy().view(np.uint8).reshape(r, 256)[:n], want_x[:n])
+        assert buf.read_state()[2] == orc.flags == (0 if step == 0 else rb.RB_FLAG_BAD_LABEL)
+    compare_buffers(buf, orc, "bad labels, single call")
+
+
 def test_policy_cannot_change_after_an_update():
     rb = _rb()
     w = wl.C1
