@@ -123,9 +123,8 @@ int rb_set_storage(rb_buffer *rb, int32_t storage);
  * offered to a full class replaces a uniformly drawn slot with probability
  * slots_per_class / n and is dropped otherwise (exact while a class has been
  * offered fewer than 2^31 - 1 samples).
- * FIFO and reservoir replacement are served by every launch form, the Bernoulli
- * selection by the general kernels (two launches per rb_update_sample).  The
- * plan-ahead forms of the single launch (rb_announce_next) serve every variant (the Bernoulli selection for b <= 1024), and so do the
+ * rb_update_sample serves every variant in one launch (up to 10240 classes).
+ * The plan-ahead forms of the single launch (rb_announce_next) serve every variant (the Bernoulli selection for b <= 1024), and so do the
  * several-steps launches of rb_update_sample_many (the form for small counts
  * with the exact selection only; the form for large counts takes over for the
  * Bernoulli selection, again for b <= 1024).  RB_EINVAL: unknown value.  RB_ESTATE: an rb_update was already
@@ -202,11 +201,11 @@ int rb_sample_augment(rb_buffer *rb, int64_t r, uint64_t seed, uint64_t step,
  * step 2: update the buffer with the mini-batch, then sample the next
  * representatives): rb_update(rb, batch_x, batch_y, b, c, seed, step) followed
  * by rb_sample_augment(rb, r, seed, step, out_x, out_y), as one call with the
- * same arguments, meaning, errors and, bit for bit, the same results.  When
- * 1 <= c <= 64, 1 <= r <= 64, classes <= 1024 and the selection is the exact one
- * (any replacement strategy and storage form) both halves run as ONE kernel launch (a representative whose slot is being written in this very step is
- * copied from the mini-batch row stored there); otherwise the two kernels are
- * enqueued one after the other.  out_x must not overlap batch_x.
+ * same arguments, meaning, errors and, bit for bit, the same results.  With
+ * c >= 1, r >= 1 and up to 10240 classes both halves run as ONE kernel launch (a
+ * representative whose slot is being written in this very step is copied from
+ * the mini-batch row stored there); otherwise the two kernels are enqueued one
+ * after the other.  out_x must not overlap batch_x.
  */
 int rb_update_sample(rb_buffer *rb, const void *batch_x, const int64_t *batch_y, int64_t b, int64_t c,
                      int64_t r, uint64_t seed, uint64_t step, void *out_x, int64_t *out_y);
@@ -226,8 +225,8 @@ int rb_update_sample(rb_buffer *rb, const void *batch_x, const int64_t *batch_y,
  * the call after the announcing step does not match what was planned, or any
  * other call comes first, the plan is dropped and nothing is lost but the time
  * it took.  The match is by address: memory that held announced labels must
- * not be given other contents and passed as the next step's labels.  Used when the step is
- * eligible for the single launch (see rb_update_sample), and also for up to
+ * not be given other contents and passed as the next step's labels.  Used for 1 <= c <= 64,
+ * 1 <= r <= 64, classes <= 1024 and the exact selection, and also for up to
  * 1024 candidates and representatives, b <= 4096 (b <= 1024 with the Bernoulli
  * selection) and up to 10240 classes (the step is then one launch that moves
  * rows by the plan, instead of two kernels); ignored otherwise.

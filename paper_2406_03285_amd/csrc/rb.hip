@@ -15,6 +15,7 @@
 // When the labels of the next mini-batch are known in advance (rb_announce_next)
 // the plan is not recomputed per workgroup at all: one workgroup of the previous
 // launch leaves it as a table in the workspace and the step's launch only moves rows.
+// rb_kernels_one.h holds the single launch of the shapes that the small-count kernels do not serve.
 //
 // Per-class fill counts are kept twice (ping-pong): an update reads the "old"
 // copy everywhere and a few bookkeeping workgroups write the "new" one, so no
@@ -36,6 +37,7 @@
 #include "rb_kernels_window.h"
 #include "rb_kernels_big.h"
 #include "rb_kernels_bigwin.h"
+#include "rb_kernels_one.h"
 #include "rb_kernels_aux.h"
 
 // ===========================================================================
@@ -465,15 +467,14 @@ int step_planned(rb_buffer* rb, const void* batch_x, const int64_t* batch_y, int
 }
 
 // The 1024-thread kernels ask for more dynamic LDS than a kernel gets by default: allowed once per kernel and device.
-template <auto kernel>
+template <auto kernel, int bytes = (int)BIG_LDS_BYTES>
 hipError_t allow_big_lds()
 {
     static bool allowed[64] = {};
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return hipErrorInvalidDevice;
     if (dev < 0 || dev >= 64 || !allowed[dev]) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 (int)BIG_LDS_BYTES);
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
         if (e != hipSuccess) return e;
         if (dev >= 0 && dev < 64) allowed[dev] = true;
     }
@@ -1000,6 +1001,117 @@ int many_form(const rb_buffer* rb, int64_t b, int64_t c, int64_t r, int64_t& ste
     return form;
 }
 
+template <int U, bool NT, int ST>
+hipError_t launch_one_u(const OneArgs& a, dim3 grid, size_t lds, hipStream_t st)
+{
+    if constexpr (ST == RB_STORE_U8 && U > 4) {
+        return hipErrorInvalidValue;           // (a lane holds four accesses per vector: step_one)
+    } else {
+        constexpr int most = 4 * (ONE_CLASSES + ONE_TPB + (int)ONE_MATE_WORDS + 4 * RB_MAX_BATCH) + 2 * RB_MAX_BATCH;      // one_lds_bytes at its largest
+        static_assert(most <= 156 * 1024, "a compute unit has 160 KB of LDS");
+        const hipError_t e = allow_big_lds<&rb_step_one_kernel<U, NT, ST>, most>();
+        if (e != hipSuccess) return e;
+        rb_step_one_kernel<U, NT, ST><<<grid, ONE_TPB, lds, st>>>(a);
+        return hipGetLastError();
+    }
+}
+
+template <bool NT, int ST>
+hipError_t launch_one_s(const OneArgs& a, int unroll, dim3 grid, size_t lds, hipStream_t st)
+{
+    switch (unroll) {
+    case 1: return launch_one_u<1, NT, ST>(a, grid, lds, st);
+    case 2: return launch_one_u<2, NT, ST>(a, grid, lds, st);
+    case 4: return launch_one_u<4, NT, ST>(a, grid, lds, st);
+    default: return launch_one_u<8, NT, ST>(a, grid, lds, st);
+    }
+}
+
+template <bool NT>
+hipError_t launch_one(const OneArgs& a, int storage, int unroll, dim3 grid, size_t lds, hipStream_t st)
+{
+    switch (storage) {
+    case RB_STORE_BF16: return launch_one_s<NT, RB_STORE_BF16>(a, unroll, grid, lds, st);
+    case RB_STORE_U8: return launch_one_s<NT, RB_STORE_U8>(a, unroll, grid, lds, st);
+    default: return launch_one_s<NT, RB_STORE_SAME>(a, unroll, grid, lds, st);
+    }
+}
+
+// Tiles of `rows` rows for `waves` wavefronts that take one tile after the other: as many tiles per row as make the
+// wavefronts' shares equal, with at most `most` vectors per lane.  Returns the vectors per lane they need.
+int one_tiles(const rb_buffer* rb, int64_t rows, int64_t waves, int most, int32_t& tpr, int32_t& tile_vec, int32_t& tile_rem)
+{
+    const int64_t units = (rb->row_vec + TILE_UNIT - 1) / TILE_UNIT;
+    int64_t n = (units + most - 1) / most;
+    if (rb->opt_unroll == 0) {
+        const int64_t rounds = (rows * n + waves - 1) / waves;
+        n = std::max(n, std::min(units, rounds * waves / rows));
+    }
+    tpr = (int32_t)n;
+    tile_vec = (int32_t)(units / n);
+    tile_rem = (int32_t)(units % n);
+    return (int)((units + n - 1) / n);
+}
+
+// Update and sampling of one step in one launch without a plan (rb_kernels_one.h).
+int step_one(rb_buffer* rb, const void* batch_x, const int64_t* batch_y, int64_t b, int64_t c, int64_t r,
+             uint64_t seed, uint64_t step, void* out_x, int64_t* out_y)
+{
+    OneArgs oa;
+    UpdateArgs& a = oa.u;
+    a.batch_x = static_cast<const vec16*>(batch_x);
+    a.batch_y = batch_y;
+    a.buf_x = static_cast<vec16*>(rb->buf_x);
+    a.buf_y = rb->buf_y;
+    a.fill_old = reinterpret_cast<const int32_t*>(rb->ws + rb->off_fill[rb->cur]);
+    a.fill_new = reinterpret_cast<int32_t*>(rb->ws + rb->off_fill[rb->cur ^ 1]);
+    a.chunk_new = reinterpret_cast<int32_t*>(rb->ws + rb->off_chunk[rb->cur ^ 1]);
+    a.state = reinterpret_cast<DevState*>(rb->ws);
+    a.sd = make_seed(seed, step);
+    a.b = (int32_t)b; a.c = (int32_t)c;
+    a.K = (int32_t)rb->K; a.nchunks = rb->nchunks;
+    a.S = rb->S;
+    a.row_vec = rb->row_vec;
+    a.rpb = 1;
+    a.selection = rb->selection; a.eviction = rb->eviction;
+    a.cap = (int32_t)(rb->selection == RB_SELECT_BERNOULLI ? b : c);
+    a.aux_old = reinterpret_cast<const int32_t*>(rb->ws + rb->off_aux[rb->cur]);
+    a.aux_new = reinterpret_cast<int32_t*>(rb->ws + rb->off_aux[rb->cur ^ 1]);
+    oa.out_x = static_cast<vec16*>(out_x);
+    oa.out_y = out_y;
+    oa.r = (int32_t)r;
+    // rows the grid is sized for (Bernoulli selection: the mean and about one standard deviation; the movers loop, and a grid
+    // sized for more leaves that many more wavefronts without work)
+    int64_t rows = c;
+    if (rb->selection == RB_SELECT_BERNOULLI) {
+        int64_t slack = 0;
+        while (slack * slack < c) ++slack;
+        rows = std::min(b, c + slack);
+    }
+    constexpr int64_t CUS = 256;                // one workgroup per compute unit, dealt to the two sides by their rows
+    const int64_t most_r = std::min<int64_t>(CUS - 1, std::max<int64_t>(1, (CUS * r + (rows + r) / 2) / (rows + r)));
+    int limit = rb->storage == RB_STORE_U8 ? 4 : 8;
+    if (rb->opt_unroll != 0) limit = std::min(limit, rb->opt_unroll);
+    const int uc = one_tiles(rb, rows, (CUS - most_r) * ONE_NWAVE, limit, a.tpr, a.tile_vec, a.tile_rem);
+    const int ur = one_tiles(rb, r, most_r * ONE_NWAVE, limit, oa.tpr, oa.tile_vec, oa.tile_rem);
+    int unroll = 1;
+    while (unroll < std::max(uc, ur)) unroll <<= 1;
+    const int64_t nc = std::min(CUS - most_r, (rows * a.tpr + ONE_NWAVE - 1) / ONE_NWAVE);
+    const int64_t nr = std::min(most_r, (r * oa.tpr + ONE_NWAVE - 1) / ONE_NWAVE);
+    oa.first_cand = (int32_t)nr;
+    oa.share = (int32_t)((r * oa.tpr + nr - 1) / nr);
+    oa.cshare = rb->selection == RB_SELECT_BERNOULLI ? 0 : (int32_t)((c * a.tpr + nc - 1) / nc);
+    oa.nwg = (int32_t)(nr + nc);
+    const dim3 grid((unsigned)(nr + nc));
+    const size_t lds = one_lds_bytes((int)b, a.cap, (int)r, rb->nchunks);
+    const hipError_t e = rb->opt_nt ? launch_one<true>(oa, rb->storage, unroll, grid, lds, rb->stream)
+                                    : launch_one<false>(oa, rb->storage, unroll, grid, lds, rb->stream);
+    if (e != hipSuccess) return RB_EHIP;
+    rb->cur ^= 1;
+    rb->updates += 1;
+    return RB_OK;
+}
+
 // What the host can check of the arguments of one update + sample step.
 int check_step(const rb_buffer* rb, const void* batch_x, const int64_t* batch_y, int64_t b, int64_t c, int64_t r,
                const void* out_x, const int64_t* out_y)
@@ -1301,6 +1413,10 @@ int rb_update_sample(rb_buffer* rb, const void* batch_x, const int64_t* batch_y,
         return step_planned(rb, batch_x, batch_y, b, c, r, seed, step, out_x, out_y, next_y);
     if (big && (rb->plan_valid || next_y))
         return step_big(rb, batch_x, batch_y, b, c, r, seed, step, out_x, out_y, next_y);
+    // every other shape in one launch as well, as long as the fill counts fit LDS and work items are counted in 32 bits
+    if (!fused && c >= 1 && r >= 1 && rb->K <= ONE_CLASSES && rb->opt_fuse &&
+        (rb->row_vec + TILE_UNIT - 1) / TILE_UNIT <= INT32_MAX / 2 / RB_MAX_BATCH)
+        return step_one(rb, batch_x, batch_y, b, c, r, seed, step, out_x, out_y);
     if (!fused) {
         const int rc = rb_update(rb, batch_x, batch_y, b, c, seed, step);
         if (rc != RB_OK) return rc;

@@ -1,0 +1,519 @@
+// rb_update_sample in ONE launch for every shape that rb_step_small_kernel does not serve: any candidate and
+// representative count, any selection and replacement strategy, any storage form, up to ONE_CLASSES classes.
+// Included by rb.hip only, after rb_kernels_small.h (whose wavefront selection it uses).
+#pragma once
+
+#include "rb_device.h"
+#include "rb_kernels_small.h"
+
+namespace {
+
+constexpr int ONE_TPB = 512;                        // threads of a workgroup: one workgroup per compute unit
+constexpr int ONE_NWAVE = ONE_TPB / WAVE;
+constexpr int ONE_PER = RB_MAX_BATCH / ONE_TPB;     // mini-batch positions, candidates and representatives per thread at most
+constexpr int ONE_CLASSES = 10240;                  // most classes: their fill counts are kept in LDS
+constexpr int ONE_FILL_PER = (ONE_CLASSES / 4 + ONE_TPB - 1) / ONE_TPB;    // vectors of four fill counts per thread
+constexpr int ONE_PACE = 64;                        // stores of a tile go out in one burst (paced ones measured 0.4 us slower)
+constexpr int ONE_PLANNED = 64;                     // rows a workgroup plans at a time
+constexpr int ONE_LIST = 4 * WAVE;                  // the candidate list and the draws are read this many at a time
+constexpr int ONE_POS_BITS = 12;                    // candidate list: class << ONE_POS_BITS | mini-batch position
+constexpr uint32_t ONE_NO_CLASS = 0xFFFFFFFFu;      // ... of a candidate whose label is outside [0, K), and behind the list's end
+static_assert(RB_MAX_BATCH <= 1 << ONE_POS_BITS && ONE_CLASSES < 1 << (31 - ONE_POS_BITS), "class and position in one word");
+constexpr int ONE_WORDS = RB_MAX_BATCH / 32;        // words of a bitmap over the mini-batch's positions
+
+struct OneArgs {
+    UpdateArgs u;                       // (u.tpr, u.tile_vec, u.tile_rem: tiles of the candidates' rows)
+    vec16* out_x;
+    int64_t* out_y;
+    int32_t r;
+    int32_t tpr, tile_vec, tile_rem;    // tiles of the representatives' rows
+    int32_t share, cshare;              // work items (row, tile) per workgroup; cshare: of the candidates, 0: as many as make the shares equal
+    int32_t nwg;                        // workgroups of the launch
+    int32_t first_cand;                 // workgroups 0 ... first_cand - 1 move representatives (and keep the books), the others candidates
+};
+
+// LDS words in front of the arrays whose size depends on the shape (see rb_step_one_kernel)
+constexpr size_t ONE_MATE_WORDS = ONE_NWAVE * (WAVE / 2 + ONE_WORDS + ONE_WORDS / 2);
+__host__ __device__ inline int one_padded(int n) { return (n + ONE_LIST - 1) / ONE_LIST * ONE_LIST; }
+inline size_t one_lds_bytes(int b, int cap, int r, int nchunks)
+{
+    return 4 * ((size_t)nchunks * CH + ONE_TPB + ONE_MATE_WORDS + 2 * (size_t)((b + 3) & ~3) + one_padded(cap) + one_padded(cap > r ? cap : r)) +
+           ((size_t)cap * 2 + 3) / 4 * 4;
+}
+
+// The candidates of one class in a step, as one wavefront collects them from the workgroup's candidate list.
+struct Mates {
+    uint64_t hit;         // bit i: candidate i * WAVE + lane is one of them
+    int mine, before;     // how many of them the lane holds, and the lanes before it
+    int total;
+    int rank;             // ... of them earlier in the mini-batch than position p
+};
+
+__device__ __forceinline__ Mates one_mates(const uint32_t* s_kx, int m, int32_t k, int p)
+{
+    const int lane = threadIdx.x & (WAVE - 1);
+    Mates t;
+    t.hit = 0;
+    int earlier = 0;
+    const uint32_t lo = (uint32_t)k << ONE_POS_BITS, mid = lo | (uint32_t)p, hi = lo | (RB_MAX_BATCH - 1);
+    for (int m0 = 0; m0 < m; m0 += ONE_LIST) {
+        uint32_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = s_kx[m0 + u * WAVE + lane];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            t.hit |= (uint64_t)(v[u] >= lo && v[u] <= hi) << (m0 / WAVE + u);
+            earlier += v[u] >= lo && v[u] < mid;
+        }
+    }
+    t.mine = __popcll(t.hit);
+    const int incl = wave_scan_incl(t.mine | (earlier << 16));      // both sums are <= 4096
+    t.before = (incl & 0xFFFF) - t.mine;
+    t.total = lane_read(incl, WAVE - 1) & 0xFFFF;
+    t.rank = lane_read(incl, WAVE - 1) >> 16;
+    return t;
+}
+
+// Up to WAVE class-mates, one lane each: position (-1: lane has none) and rank.
+__device__ __forceinline__ void one_mate_lanes(const Mates& t, const uint32_t* s_kx, uint16_t* pend, int& x, int& rank)
+{
+    const int lane = threadIdx.x & (WAVE - 1);
+    int at = t.before;
+    for (uint64_t h = t.hit; h != 0; h &= h - 1) pend[at++] = (uint16_t)(s_kx[__builtin_ctzll(h) * WAVE + lane] & (RB_MAX_BATCH - 1));
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // (lanes of one wavefront read what other lanes of it wrote)
+    x = lane < t.total ? pend[lane] : -1;
+    rank = 0;
+    for (int j = 0; j < t.total; ++j) rank += lane_read(x, j) < x;
+}
+
+// More than WAVE class-mates: bitmap of their positions and how many are set before each of its words.
+__device__ __forceinline__ void one_mate_map(const Mates& t, const uint32_t* s_kx, uint32_t* cm, uint16_t* cmpre)
+{
+    const int lane = threadIdx.x & (WAVE - 1);
+    static_assert(ONE_WORDS == 2 * WAVE, "two bitmap words per lane");
+    cm[2 * lane] = 0u;
+    cm[2 * lane + 1] = 0u;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    for (uint64_t h = t.hit; h != 0; h &= h - 1) {
+        const int x = (int)(s_kx[__builtin_ctzll(h) * WAVE + lane] & (RB_MAX_BATCH - 1));
+        atomicOr(&cm[x >> 5], 1u << (x & 31));
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    const int p0 = __popc(cm[2 * lane]), p1 = __popc(cm[2 * lane + 1]);
+    const int before = wave_scan_incl(p0 + p1) - (p0 + p1);
+    cmpre[2 * lane] = (uint16_t)before;
+    cmpre[2 * lane + 1] = (uint16_t)(before + p0);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
+
+// The last position of class k's candidates that go to `slot` and lie behind position p; -1: there is none.  All lanes
+// call it; cm / cmpre as one_mate_map left them.
+__device__ __forceinline__ int one_last_writer(const UpdateArgs& a, const uint32_t* cm, const uint16_t* cmpre, int p, int slot,
+                                               int64_t fill0, int64_t aux0)
+{
+    const int lane = threadIdx.x & (WAVE - 1);
+    int last = -1;
+    // two bitmap words per lane, one class-mate of each lane per round
+    uint64_t bits = (uint64_t)cm[2 * lane] | ((uint64_t)cm[2 * lane + 1] << 32);
+    int rank = cmpre[2 * lane];
+    while (__ballot(bits != 0) != 0) {
+        if (bits != 0) {
+            const int x = 64 * lane + __builtin_ctzll(bits);
+            if (x > p && mate_slot(a, x, rank, fill0, aux0) == slot) last = x;
+            bits &= bits - 1;
+            ++rank;
+        }
+    }
+    const uint64_t found = __ballot(last >= 0);
+    return found == 0 ? -1 : lane_read(last, 63 - __builtin_clzll(found));     // positions grow with the lane
+}
+
+// Where the candidate at position p of class k (>= 0) is stored: its slot, or -1 if it is not stored (not kept, or a later
+// class-mate takes the slot).
+__device__ __forceinline__ int one_place(const UpdateArgs& a, const uint32_t* s_kx, int m, int32_t k, int p,
+                                         int64_t fill0, int64_t aux0, uint16_t* pend, uint32_t* cm, uint16_t* cmpre)
+{
+    const Mates t = one_mates(s_kx, m, k, p);
+    if (fill0 + t.total <= a.S) return (int)(fill0 + t.rank);                   // all of them append: distinct slots
+    if (a.eviction == RB_EVICT_FIFO) {
+        // it is itself overwritten in this step if a class-mate comes a whole round of S later
+        return fill0 + t.rank + a.S < fill0 + t.total ? -1 : mate_slot(a, p, t.rank, fill0, aux0);
+    }
+    if (t.total <= WAVE) {
+        int x, rank;
+        one_mate_lanes(t, s_kx, pend, x, rank);
+        const int slot = x >= p ? mate_slot(a, x, rank, fill0, aux0) : -1;       // this candidate and the later ones
+        const int own = lane_read(slot, __builtin_ctzll(__ballot(x == p) | (1ull << 63)));
+        return own < 0 || __ballot(x > p && slot == own) != 0 ? -1 : own;
+    }
+    const int own = mate_slot(a, p, t.rank, fill0, aux0);
+    if (own < 0) return -1;
+    one_mate_map(t, s_kx, cm, cmpre);
+    return one_last_writer(a, cm, cmpre, p, own, fill0, aux0) >= 0 ? -1 : own;
+}
+
+// Mini-batch position whose row slot `slot` of class k holds after the step if the step writes it, else -1.
+__device__ __forceinline__ int one_writer(const UpdateArgs& a, const uint32_t* s_kx, int m, int32_t k, int slot,
+                                          int64_t filled, uint16_t* pend, uint32_t* cm, uint16_t* cmpre)
+{
+    const Mates t = one_mates(s_kx, m, k, 0);
+    if (t.total == 0) return -1;
+    const int64_t fill0 = filled - t.total;                                     // filled: count before the step plus candidates
+    if (slot < fill0 && filled <= a.S) return -1;                               // held before the step, and nothing is overwritten
+    const int64_t aux0 = a.eviction != RB_EVICT_UNIFORM ? a.aux_old[k] : 0;
+    if (t.total <= WAVE) {
+        int x, rank;
+        one_mate_lanes(t, s_kx, pend, x, rank);
+        int at = x >= 0 && mate_slot(a, x, rank, fill0, aux0) == slot ? x : -1;
+        for (uint64_t w = __ballot(at >= 0); w != 0; w &= w - 1) {              // the one latest in the mini-batch
+            const int xw = lane_read(at, __builtin_ctzll(w));
+            at = xw > at ? xw : at;
+        }
+        return lane_read(at, 0);
+    }
+    one_mate_map(t, s_kx, cm, cmpre);
+    return one_last_writer(a, cm, cmpre, -1, slot, fill0, aux0);
+}
+
+// ---------------------------------------------------------------------------
+// Update and sampling of one step.
+//
+// Every workgroup first works out, in LDS, the candidate list (class and position) and, if it moves representatives,
+// the fill counts after the update and all sampling draws.  It takes a contiguous share of its side's work items (row, tile
+// of at most WAVE * U vectors): its wavefronts plan the share's rows, one row each - with ballots over the candidate list,
+// where a candidate goes, resp. which stored sample a representative is and whether this very step writes that slot (then
+// the mini-batch row stored there is copied: no workgroup reads a row another one writes) - and then move the tiles.
+//
+// What bounds it: the chain arguments -> labels -> candidate list -> fill counts -> draws -> rows, about 0.5 to 2 us a link
+// with the counts, on every compute unit at once; the rows themselves take a third of the time or less.  Hence one
+// workgroup of 512 threads per compute unit (1024 threads: equal at 1024 + 1024 rows, 0.3 to 0.5 us slower at small
+// counts; 256: 2 to 3 us slower; two workgroups per unit: 0.1 to 0.4 us faster for few rows, 6 us slower for 1024 + 1024),
+// a row planned once per workgroup and not by every wavefront, and one list word per candidate.  Measured on MI355X against
+// the two general launches this replaces: 1024 + 1024 rows of 8 KB of 10000 classes 16.3 : 17.0 us; Bernoulli selection with
+// reservoir replacement, 90 + 75 rows of 49 KB kept as bfloat16, 9.3 : 10.9; 6 + 5 rows of 393 KB in 8 bits, Bernoulli,
+// 8.2 : 14.5; 185 + 121 rows of 13 KB in 8 bits of 5654 classes 11.4 : 17.8; 4 + 5 rows of 5 KB of 3179 classes 7.4 : 8.0.
+//
+// LDS (dynamic): s_fill[nchunks * CH] i32, s_before[ONE_TPB] i32, per wavefront pend u16[WAVE], cm u32[ONE_WORDS],
+// cmpre u16[ONE_WORDS]; s_lab[b] u32, s_first[b] u32, s_kx[cap] u32, s_t[max(cap, r)] u32 (both
+// rounded up to ONE_LIST), s_x[cap] u16.
+// ---------------------------------------------------------------------------
+template <int U, bool NT, int ST>
+__global__ void __launch_bounds__(ONE_TPB) rb_step_one_kernel(const OneArgs sa)
+{
+    fetch_args<sizeof(OneArgs)>();
+    const UpdateArgs& a = sa.u;
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
+    const int b = a.b, c = a.c, r = sa.r, nfill = a.nchunks * CH;
+    extern __shared__ __align__(16) uint32_t lds[];
+    int32_t* s_fill = reinterpret_cast<int32_t*>(lds);
+    int32_t* s_before = s_fill + nfill;
+    uint32_t* cm = lds + nfill + ONE_TPB + wave * ONE_WORDS;
+    uint16_t* cmpre = reinterpret_cast<uint16_t*>(lds + nfill + ONE_TPB + ONE_NWAVE * ONE_WORDS) + wave * ONE_WORDS;
+    uint16_t* pend = reinterpret_cast<uint16_t*>(lds + nfill + ONE_TPB + ONE_NWAVE * (ONE_WORDS + ONE_WORDS / 2)) + wave * WAVE;
+    const int bp = (b + 3) & ~3;
+    uint32_t* s_lab = lds + nfill + ONE_TPB + ONE_MATE_WORDS;
+    uint32_t* s_first = s_lab + bp;
+    uint32_t* s_kx = s_first + bp;
+    uint32_t* s_t = s_kx + one_padded(a.cap);
+    uint16_t* s_x = reinterpret_cast<uint16_t*>(s_t + one_padded(a.cap > r ? a.cap : r));
+    __shared__ int s_seg[WAVE];                 // Bernoulli: heads per stretch of WAVE positions
+    __shared__ int s_wave[ONE_NWAVE];
+    __shared__ int s_bad;
+    __shared__ int s_slot[ONE_PLANNED], s_class[ONE_PLANNED], s_fwd[ONE_PLANNED];    // the rows planned last: slot (-1: not moved), class, writer
+
+    const bool gather = (int)blockIdx.x < sa.first_cand;
+    const bool bernoulli = a.selection == RB_SELECT_BERNOULLI;
+
+    // labels of the whole mini-batch and, for the representatives, all fill counts: requested now
+    int64_t yv[ONE_PER];
+#pragma unroll
+    for (int u = 0; u < ONE_PER; ++u) {                     // (threads past the end read the last one again)
+        yv[u] = 0;
+        if (u * ONE_TPB < b) yv[u] = a.batch_y[min(tid + u * ONE_TPB, b - 1)];
+    }
+    int4 fo[ONE_FILL_PER];
+    if (gather) {
+#pragma unroll
+        for (int u = 0; u < ONE_FILL_PER; ++u) {
+            fo[u] = make_int4(0, 0, 0, 0);
+            if (u * 4 * ONE_TPB < nfill) fo[u] = *reinterpret_cast<const int4*>(a.fill_old + min(4 * (tid + u * ONE_TPB), nfill - 4));
+        }
+    }
+    if (tid == 0) s_bad = 0;
+
+    // ---- candidates: positions ----
+    int m = c;                                  // number of candidates
+    int at[ONE_PER];                            // Bernoulli: list index of position tid + u * ONE_TPB, -1: not selected
+    uint64_t bits[ONE_PER];                     // random bits of sampling draw tid + u * ONE_TPB
+    if (bernoulli) {
+        uint64_t heads[ONE_PER];
+#pragma unroll
+        for (int u = 0; u < ONE_PER; ++u) {
+            const int q = tid + u * ONE_TPB;
+            heads[u] = 0;
+            if (u * ONE_TPB < b) heads[u] = __ballot(q < b && (int64_t)below(a.sd, PURPOSE_COIN, (uint32_t)q, (uint64_t)b) < c);
+            if (lane == 0) s_seg[u * ONE_NWAVE + wave] = __popcll(heads[u]);
+        }
+        lds_barrier();
+        const int incl = wave_scan_incl(s_seg[lane]);
+        m = lane_read(incl, WAVE - 1);
+        static_assert(ONE_PER * ONE_NWAVE == WAVE, "one lane per stretch of positions");
+#pragma unroll
+        for (int u = 0; u < ONE_PER; ++u) {
+            const int seg = u * ONE_NWAVE + wave;
+            const bool mine = (heads[u] >> lane) & 1;
+            at[u] = mine ? lane_read(incl, seg) - __popcll(heads[u] >> lane) : -1;       // (this one and the heads behind it)
+            if (mine) s_x[at[u]] = (uint16_t)(tid + u * ONE_TPB);
+        }
+    } else if (c <= WAVE) {
+        if (wave == 0) {
+            bool active;
+            const int x = wave_select(a.sd, b, c, s_first, active);
+            if (active) s_x[lane] = (uint16_t)x;
+        }
+    } else {
+        // Floyd's c-subset, all draws at once (see rb_update_kernel)
+        const int base = b - c;
+        for (int i = 4 * tid; i < b; i += 4 * ONE_TPB) *reinterpret_cast<uint4*>(s_first + i) = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
+        for (int i = tid; i < c; i += ONE_TPB) s_t[i] = (uint32_t)below(a.sd, PURPOSE_SELECT, (uint32_t)i, (uint64_t)(base + i + 1));
+        lds_barrier();
+        for (int i = tid; i < c; i += ONE_TPB) atomicMin(&s_first[s_t[i]], (uint32_t)i);
+        lds_barrier();
+        // a draw is replaced iff an earlier one had the same value, or it is base + q for an earlier q that was replaced
+        for (int i = tid; i < c; i += ONE_TPB) {
+            const int own = (int)s_t[i];
+            int t = own, cur = i;
+            bool taken = false;
+            for (;;) {
+                if (s_first[t] != (uint32_t)cur) { taken = true; break; }
+                const int q = t - base;
+                if (q < 0 || q >= cur) break;
+                cur = q;
+                t = (int)s_t[cur];
+            }
+            s_x[i] = (uint16_t)(taken ? base + i : own);
+        }
+    }
+    if (gather) {
+#pragma unroll
+        for (int u = 0; u < ONE_PER; ++u)
+            bits[u] = u * ONE_TPB < r ? draw64(a.sd, PURPOSE_SAMPLE, (uint32_t)(tid + u * ONE_TPB)) : 0;
+    }
+    lds_barrier();
+
+    // classes of the candidates; ends with a barrier after which the list is complete
+    const auto listed = [&](int x, int64_t y) { return (y >= 0 && y < a.K) ? ((uint32_t)y << ONE_POS_BITS) | (uint32_t)x : ONE_NO_CLASS; };
+    const auto classes = [&]() {
+        for (int q = m + tid; q < one_padded(m); q += ONE_TPB) s_kx[q] = ONE_NO_CLASS;
+        if (bernoulli) {
+#pragma unroll
+            for (int u = 0; u < ONE_PER; ++u) {
+                if (u * ONE_TPB >= b) break;
+                int64_t y = yv[u];
+                asm volatile("" : "+v"(y));     // keeps the range test, and so the wait for the label, from moving up
+                if (at[u] >= 0) s_kx[at[u]] = listed(tid + u * ONE_TPB, y);
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < ONE_PER; ++u) {
+                if (u * ONE_TPB >= b) break;
+                const int q = min(tid + u * ONE_TPB, b - 1);        // (threads past the end hold the last one, too)
+                int64_t y = yv[u];
+                asm volatile("" : "+v"(y));
+                s_lab[q] = listed(q, y);
+            }
+            lds_barrier();
+            for (int q = tid; q < c; q += ONE_TPB) s_kx[q] = s_lab[s_x[q]];
+        }
+        lds_barrier();
+    };
+    constexpr int WIDE = stored_wide(ST);       // vectors of a mini-batch / output row per vector of a stored row
+    int64_t v_lo, v_hi;
+
+    if (!gather) {
+        // ---- candidate movers ----
+        const int items = m * a.tpr, nwg = sa.nwg - sa.first_cand;
+        const int share = sa.cshare != 0 ? sa.cshare : (items + nwg - 1) / nwg;
+        const int lo = ((int)blockIdx.x - sa.first_cand) * share, hi = min(lo + share, items);
+        if (lo >= hi) return;
+        // A row is requested as soon as its position is known, before the labels have arrived (by every wavefront: a load
+        // that only some issue would make the wait for the labels a wait for the rows).
+        int it = min(lo + wave, hi - 1);
+        Tile<U, NT, WAVE, ONE_PACE, stored_cv(ST, CV_NARROW), true> t;
+        {
+            const int i = it / a.tpr;
+            tile_bounds(it - i * a.tpr, a.tile_vec, a.tile_rem, a.row_vec, v_lo, v_hi);
+            t.load(a.batch_x + (int64_t)__builtin_amdgcn_readfirstlane(s_x[i]) * a.row_vec * WIDE, v_lo, v_hi);
+        }
+        classes();
+        it = lo + wave;
+        bool loaded = true;
+        for (int row = lo / a.tpr; row * a.tpr < hi; row += ONE_PLANNED) {
+            const int end = min((hi + a.tpr - 1) / a.tpr, row + ONE_PLANNED);
+            for (int i = row + wave; i < end; i += ONE_NWAVE) {
+                const uint32_t kx = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_kx[i]);
+                int slot = -1;
+                if (kx != ONE_NO_CLASS) {       // else a label outside [0, K): dropped (the representatives' workgroups flag it)
+                    const int32_t ki = (int32_t)(kx >> ONE_POS_BITS);
+                    const int64_t fill0 = a.fill_old[ki];
+                    const int64_t aux0 = a.eviction != RB_EVICT_UNIFORM ? a.aux_old[ki] : 0;
+                    slot = one_place(a, s_kx, m, ki, (int)(kx & (RB_MAX_BATCH - 1)), fill0, aux0, pend, cm, cmpre);
+                }
+                if (lane == 0) s_slot[i - row] = slot;
+            }
+            lds_barrier();
+            for (; it < min(hi, end * a.tpr); it += ONE_NWAVE) {
+                const int i = it / a.tpr, tile = it - i * a.tpr;
+                const int slot = __builtin_amdgcn_readfirstlane(s_slot[i - row]);
+                if (slot >= 0) {
+                    const uint32_t kx = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_kx[i]);
+                    const int64_t dst_row = (int64_t)(kx >> ONE_POS_BITS) * a.S + slot;
+                    if (!loaded) {
+                        tile_bounds(tile, a.tile_vec, a.tile_rem, a.row_vec, v_lo, v_hi);
+                        t.load(a.batch_x + (int64_t)(kx & (RB_MAX_BATCH - 1)) * a.row_vec * WIDE, v_lo, v_hi);
+                    }
+                    t.store(a.buf_x + dst_row * a.row_vec, v_lo, v_hi);
+                    if (tile == 0 && lane == 0) { a.buf_y[dst_row] = (int64_t)(kx >> ONE_POS_BITS); count_moved(a.state); }
+                }
+                loaded = false;
+            }
+            if (end * a.tpr < hi) lds_barrier();
+        }
+        return;
+    }
+
+#pragma unroll
+    for (int u = 0; u < ONE_FILL_PER; ++u) {
+        if (u * 4 * ONE_TPB >= nfill) break;
+        *reinterpret_cast<int4*>(s_fill + min(4 * (tid + u * ONE_TPB), nfill - 4)) = fo[u];
+    }
+    classes();
+
+    // ---- fill counts after the update (not yet cut off at the capacity) ----
+    for (int q = tid; q < m; q += ONE_TPB) {
+        const uint32_t kx = s_kx[q];
+        if (kx != ONE_NO_CLASS) atomicAdd(&s_fill[kx >> ONE_POS_BITS], 1);
+        else s_bad = 1;
+    }
+    lds_barrier();
+    const int32_t cap = (int32_t)(a.S < INT32_MAX ? a.S : INT32_MAX);
+    // stored samples before every thread's stretch of `per` classes (a multiple of four)
+    const int per = (nfill / 4 + ONE_TPB - 1) / ONE_TPB * 4;
+    int local = 0;
+    for (int k = tid * per; k < min(tid * per + per, nfill); k += 4) {
+        const int4 f = *reinterpret_cast<const int4*>(s_fill + k);
+        local += min(f.x, cap) + min(f.y, cap) + min(f.z, cap) + min(f.w, cap);
+    }
+    const int incl = wave_scan_incl(local);
+    if (lane == WAVE - 1) s_wave[wave] = incl;
+    lds_barrier();
+    const int wincl = wave_scan_incl(lane < ONE_NWAVE ? s_wave[lane] : 0);
+    const int F = lane_read(wincl, ONE_NWAVE - 1);
+    s_before[tid] = (wave > 0 ? lane_read(wincl, wave - 1) : 0) + incl - local;
+    const int n = r < F ? r : F;
+    const int base = F - n;
+#pragma unroll
+    for (int u = 0; u < ONE_PER; ++u) {
+        if (u * ONE_TPB >= n) break;
+        const int q = tid + u * ONE_TPB;
+        if (q < n) s_t[q] = reduce32(bits[u], (uint32_t)(base + q + 1));
+    }
+    if (blockIdx.x == 0 && tid == 0) {
+        a.state->last_n = n;
+        if (s_bad) atomicOr(&a.state->flags, RB_FLAG_BAD_LABEL);
+    }
+    lds_barrier();
+
+    // ---- representative movers ----
+    const int lo = (int)blockIdx.x * sa.share, hi = min(lo + sa.share, r * sa.tpr);
+    int it = lo + wave;
+    for (int row = lo / sa.tpr; row * sa.tpr < hi; row += ONE_PLANNED) {
+        const int end = min((hi + sa.tpr - 1) / sa.tpr, row + ONE_PLANNED);
+        for (int j = row + wave; j < end; j += ONE_NWAVE) {
+            if (j >= n) {                      // fewer stored samples than asked for
+                if (lane == 0) s_slot[j - row] = -1;
+                continue;
+            }
+            // draw j is replaced by base + j iff an earlier draw had the same value, or it equals
+            // base + q for an earlier q whose own draw was replaced
+            int cur = j;
+            bool taken = false;
+            for (;;) {
+                const uint32_t tc = s_t[cur];
+                bool same = false;
+                for (int q0 = 0; q0 < cur; q0 += ONE_LIST) {
+                    uint32_t v[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) v[u] = s_t[q0 + u * WAVE + lane];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) same |= q0 + u * WAVE + lane < cur && v[u] == tc;
+                }
+                if (__ballot(same) != 0) { taken = true; break; }
+                const int q = __builtin_amdgcn_readfirstlane((int)tc) - base;
+                if (q < 0 || q >= cur) break;
+                cur = q;
+            }
+            const int g = taken ? base + j : __builtin_amdgcn_readfirstlane((int)s_t[j]);     // class-major number of the sample
+            // the stretch of classes that holds it (the last one that starts at or before it), then the class
+            constexpr int STEP = ONE_TPB / WAVE;
+            const int big = __popcll(__ballot(s_before[STEP * lane] <= g)) - 1;
+            const int owner = STEP * big + __popcll(__ballot(lane < STEP && s_before[STEP * big + (lane & (STEP - 1))] <= g)) - 1;
+            const int gl = g - __builtin_amdgcn_readfirstlane(s_before[owner]);
+            const int kl = owner * per + lane;
+            const int held = lane < per && kl < nfill ? min(s_fill[kl], cap) : 0;
+            const int hincl = wave_scan_incl(held);
+            const int u = __popcll(__ballot(lane < per && hincl <= gl));
+            const int pk = owner * per + u, ps = gl - (lane_read(hincl, u) - lane_read(held, u));
+            const int fwd = one_writer(a, s_kx, m, pk, ps, s_fill[pk], pend, cm, cmpre);
+            if (lane == 0) {
+                s_slot[j - row] = ps;
+                s_class[j - row] = pk;
+                s_fwd[j - row] = fwd;
+            }
+        }
+        lds_barrier();
+        for (; it < min(hi, end * sa.tpr); it += ONE_NWAVE) {
+            const int j = it / sa.tpr, tile = it - j * sa.tpr;
+            const int ps = __builtin_amdgcn_readfirstlane(s_slot[j - row]);
+            if (ps < 0) {
+                if (tile == 0 && lane == 0) sa.out_y[j] = -1;
+                continue;
+            }
+            const int pk = __builtin_amdgcn_readfirstlane(s_class[j - row]), fwd = __builtin_amdgcn_readfirstlane(s_fwd[j - row]);
+            tile_bounds(tile, sa.tile_vec, sa.tile_rem, a.row_vec, v_lo, v_hi);
+            vec16* dst = sa.out_x + (int64_t)j * a.row_vec * WIDE;
+            if (ST != RB_STORE_SAME && fwd >= 0) {
+                // from the mini-batch: what the slot will hold is the row in its stored form
+                Tile<U, NT, WAVE, ONE_PACE, stored_cv(ST, CV_BOTH)> o;
+                o.load(a.batch_x + (int64_t)fwd * a.row_vec * WIDE, v_lo, v_hi);
+                o.store(dst, v_lo, v_hi);
+            } else {
+                const vec16* src = fwd >= 0 ? a.batch_x + (int64_t)fwd * a.row_vec : a.buf_x + ((int64_t)pk * a.S + ps) * a.row_vec;
+                Tile<U, NT, WAVE, ONE_PACE, stored_cv(ST, CV_WIDEN)> o;
+                o.load(src, v_lo, v_hi);
+                o.store(dst, v_lo, v_hi);
+            }
+            if (tile == 0 && lane == 0) { sa.out_y[j] = pk; count_moved(a.state); }
+        }
+        if (end * sa.tpr < hi) lds_barrier();
+    }
+
+    // ---- books: new fill counts, their sums per chunk, the strategy's state (a chunk per wavefront, dealt over the workgroups) ----
+    for (int ch = wave * sa.first_cand + blockIdx.x; ch < a.nchunks; ch += sa.first_cand * ONE_NWAVE) {
+        const int k0 = ch * CH + 4 * lane;
+        const int4 v = *reinterpret_cast<const int4*>(s_fill + k0);
+        const int4 f = make_int4(min(v.x, cap), min(v.y, cap), min(v.z, cap), min(v.w, cap));
+        *reinterpret_cast<int4*>(a.fill_new + k0) = f;
+        const int sum = lane_read(wave_scan_incl(f.x + f.y + f.z + f.w), WAVE - 1);
+        if (lane == 0) a.chunk_new[ch] = sum;
+        if (a.eviction != RB_EVICT_UNIFORM) {
+            const int4 old4 = *reinterpret_cast<const int4*>(a.fill_old + k0);
+            const int4 aux4 = *reinterpret_cast<const int4*>(a.aux_old + k0);
+            const int4 next = make_int4(next_aux(a, old4.x, aux4.x, v.x - old4.x), next_aux(a, old4.y, aux4.y, v.y - old4.y),
+                                        next_aux(a, old4.z, aux4.z, v.z - old4.z), next_aux(a, old4.w, aux4.w, v.w - old4.w));
+            *reinterpret_cast<int4*>(a.aux_new + k0) = next;
+        }
+    }
+}
+
+}  // namespace
