@@ -120,12 +120,13 @@ struct Shape {
 // Split `rows` rows of `row_vec` vectors into tiles of at most width * unroll vectors, where `width`
 // is the number of threads that share a tile: TPB in the small-count kernels (a workgroup per tile),
 // WAVE in the general ones (a wavefront per tile).
-// (With 8-bit storage a vector stands for four accesses of a thread: one is enough in flight.  Measured on MI355X, update and
-// sampling in one launch: 8 + 8 rows of 602 KB stored in 8 bits 7.06 us with one vector per thread, 7.33 with two, 9.5 with
-// four; 32 + 32 rows of 49 KB 6.65, 7.42, 9.5; 64 + 64 rows of 602 KB 25.6, 24.5, 27.7.)
+// (With 8-bit storage a vector stands for four accesses of a thread, so one may be enough in flight: `few` is the number of
+// tiles below which two become one.  Measured on MI355X, one vector per thread against two: update and sampling in one launch,
+// 8 + 8 rows of 602 KB (592 and 304 tiles) 6.9 : 6.4 us, 32 + 32 rows of 49 KB (192 and 128 tiles) 6.0 : 6.4; in two launches
+// 32 + 32 rows of 602 KB (1184 and 608 tiles each) 14.7 : 15.7, 64 + 64 26.5 : 23.3.)
 // most: the most vectors per thread the caller's kernel can hold (the converting movers hold several accesses per
 // vector); preferred: what the caller's kernel does best with, taken when the option leaves the choice open.
-Shape plan_shape(const rb_buffer* rb, int64_t rows, int width, int most = 8, int preferred = 0)
+Shape plan_shape(const rb_buffer* rb, int64_t rows, int width, int most = 8, int preferred = 0, int64_t few = 1024)
 {
     Shape s;
     const int64_t row_vec = rb->row_vec;
@@ -135,8 +136,8 @@ Shape plan_shape(const rb_buffer* rb, int64_t rows, int width, int most = 8, int
         // the small-count kernels, four wavefronts in the general ones); never below two vectors in
         // flight per thread (one was slower at every size measured) unless the row is shorter.
         u = 8;
-        const int least = rb->storage == RB_STORE_U8 ? 1 : 2;
-        while (u > least && rows * ((row_vec + (int64_t)width * u - 1) / ((int64_t)width * u)) < 1024) u >>= 1;
+        while (u > 2 && rows * ((row_vec + (int64_t)width * u - 1) / ((int64_t)width * u)) < 1024) u >>= 1;
+        if (u == 2 && rb->storage == RB_STORE_U8 && rows * ((row_vec + 2 * width - 1) / (2 * width)) < few) u = 1;
         while (u > 1 && (int64_t)width * (u / 2) >= row_vec) u >>= 1;
     }
     if (u > most) u = most;
@@ -279,7 +280,8 @@ hipError_t launch_step_s(const StepArgs& a, int unroll, dim3 grid, size_t lds, h
     default:
         if constexpr (ST == RB_STORE_U8) return hipErrorInvalidValue;
         else if (unroll == 4) rb_step_small_kernel<4, NT, ST, AUX><<<grid, TPB, lds, st>>>(a);
-        else rb_step_small_kernel<8, NT, ST, AUX><<<grid, TPB, lds, st>>>(a);
+        else if constexpr (ST == RB_STORE_SAME) rb_step_small_kernel<8, NT, ST, AUX><<<grid, TPB, lds, st>>>(a);
+        else return hipErrorInvalidValue;
         break;
     }
     return hipGetLastError();
@@ -329,9 +331,12 @@ hipError_t launch_planned_s(const MoveArgs& m, const PlanArgs& next, int unroll,
     switch (unroll) {
     case 1: rb_step_planned_kernel<1, NT, ST><<<grid, TPB, lds, st>>>(m, next); break;
     case 2: rb_step_planned_kernel<2, NT, ST><<<grid, TPB, lds, st>>>(m, next); break;
-    case 4: rb_step_planned_kernel<4, NT, ST><<<grid, TPB, lds, st>>>(m, next); break;
+    case 4:
+        if constexpr (ST == RB_STORE_U8) return hipErrorInvalidValue;    // (at most two vectors per lane: step_planned)
+        else rb_step_planned_kernel<4, NT, ST><<<grid, TPB, lds, st>>>(m, next);
+        break;
     default:
-        if constexpr (ST == RB_STORE_U8) return hipErrorInvalidValue;    // (at most four vectors per lane: step_planned)
+        if constexpr (ST != RB_STORE_SAME) return hipErrorInvalidValue;  // (bfloat16 rows: at most four)
         else rb_step_planned_kernel<8, NT, ST><<<grid, TPB, lds, st>>>(m, next);
         break;
     }
@@ -437,8 +442,9 @@ int step_planned(rb_buffer* rb, const void* batch_x, const int64_t* batch_y, int
         if (hipGetLastError() != hipSuccess) return RB_EHIP;
         plan_enqueued(rb, batch_y, b, c, r, seed, step);
     }
-    // (with 8-bit storage a lane holds four accesses per vector: at most four vectors)
-    const Shape sh = plan_shape(rb, c + r, TPB, rb->storage == RB_STORE_U8 ? 4 : 8);
+    // (rows that are converted do better with fewer vectors per thread: 64 + 64 rows of 602 KB in 8 bits 25.6 us with four,
+    // 21.0 with two; as bfloat16 25.9 with eight, 23.1 with four)
+    const Shape sh = plan_shape(rb, c + r, TPB, rb->storage == RB_STORE_U8 ? 2 : rb->storage == RB_STORE_BF16 ? 4 : 8);
     MoveArgs m;
     m.batch_x = static_cast<const vec16*>(batch_x);
     m.buf_x = static_cast<vec16*>(rb->buf_x);
@@ -1422,7 +1428,8 @@ int rb_update_sample(rb_buffer* rb, const void* batch_x, const int64_t* batch_y,
         if (rc != RB_OK) return rc;
         return rb_sample_augment(rb, r, seed, step, out_x, out_y);
     }
-    const Shape sh = plan_shape(rb, c + r, TPB, rb->storage == RB_STORE_U8 ? 2 : 8);
+    // (bfloat16 rows: 64 + 64 rows of 602 KB 28.8 us with eight vectors per thread, 25.3 with four)
+    const Shape sh = plan_shape(rb, c + r, TPB, rb->storage == RB_STORE_U8 ? 2 : rb->storage == RB_STORE_BF16 ? 4 : 8, 0, 256);
     StepArgs sa;
     UpdateArgs& a = sa.u;
     a.batch_x = static_cast<const vec16*>(batch_x);

@@ -356,6 +356,17 @@ struct Tile {
     }
 };
 
+// Pacing of the one-step kernels' tiles.  Rows that are converted on the way do better with burst stores (a thread has two or
+// four narrow accesses per vector, and a wait after each costs more than it spares): update and sampling in one launch,
+// 8 + 8 rows of 602 KB in 8 bits 7.1 -> 6.4 us, 32 + 32 11.6 -> 10.6, 16 + 16 rows of 12 KB 6.2 -> 5.6; as bfloat16
+// 8 + 8 7.2 -> 6.7, 64 + 64 rows of 49 KB 7.1 -> 6.6; two launches 9.3 -> 8.3.  With four bfloat16 vectors per thread and
+// more, where a launch is about one round of workgroups, paced ones stay (32 + 32 rows of 602 KB 12.3 against 13.2), as for
+// rows moved as they are (64 + 64 rows of 301 KB 15.4 against 17.2).
+constexpr int step_pace(int storage, int unroll)
+{
+    return storage == RB_STORE_U8 || (storage == RB_STORE_BF16 && unroll <= 2) ? 64 : 1;
+}
+
 // Vector range [lo, hi) of tile `tile` of a row of row_vec vectors.  The row is cut into units of
 // TILE_UNIT vectors (1 KiB: what one wavefront moves per instruction, so that a wavefront's access
 // does not straddle two such blocks of a 1 KiB-aligned row) and the units are dealt evenly: the

@@ -350,10 +350,13 @@ __global__ void __launch_bounds__(TPB) rb_step_planned_kernel(const MoveArgs m, 
         if (h.flags != 0) atomicOr(&m.state->flags, h.flags);
     }
     constexpr int WIDE = stored_wide(ST);         // vectors of a mini-batch / output row per vector of a stored row
+    // burst stores for 8-bit rows (8 + 8 rows of 602 KB 6.3 -> 6.1 us, 32 + 32 13.0 -> 12.2); bfloat16 rows are paced here
+    // (16 + 16 rows 7.1 against 7.6 us)
+    constexpr int PACE = ST == RB_STORE_U8 ? 64 : 1;
     if (e < m.c) {
         if (en.row < 0) return;                 // label outside [0, K), or a later class-mate takes the slot
         if (first) { m.buf_y[en.row] = en.label; count_moved(m.state); }
-        Tile<U, NT, TPB, true, stored_cv(ST, CV_NARROW)> t;
+        Tile<U, NT, TPB, PACE, stored_cv(ST, CV_NARROW)> t;
         t.load(m.batch_x + (int64_t)en.pos * m.row_vec * WIDE, v_lo, v_hi);
         t.store(m.buf_x + en.row * m.row_vec, v_lo, v_hi);
         return;
@@ -365,12 +368,12 @@ __global__ void __launch_bounds__(TPB) rb_step_planned_kernel(const MoveArgs m, 
     vec16* dst = m.out_x + (int64_t)j * m.row_vec * WIDE;
     if (ST != RB_STORE_SAME && en.pos >= 0) {
         // forwarded from the mini-batch: what the slot will hold is the row in its stored form
-        Tile<U, NT, TPB, true, stored_cv(ST, CV_BOTH)> t;
+        Tile<U, NT, TPB, PACE, stored_cv(ST, CV_BOTH)> t;
         t.load(m.batch_x + (int64_t)en.pos * m.row_vec * WIDE, v_lo, v_hi);
         t.store(dst, v_lo, v_hi);
     } else {
         const vec16* src = en.pos >= 0 ? m.batch_x + (int64_t)en.pos * m.row_vec : m.buf_x + en.row * m.row_vec;
-        Tile<U, NT, TPB, true, stored_cv(ST, CV_WIDEN)> t;
+        Tile<U, NT, TPB, PACE, stored_cv(ST, CV_WIDEN)> t;
         t.load(src, v_lo, v_hi);
         t.store(dst, v_lo, v_hi);
     }

@@ -223,7 +223,7 @@ __global__ void __launch_bounds__(TPB) rb_update_small_kernel(const UpdateArgs a
         const int p = s_p[0];
         // The row is requested as soon as its position is known: before the labels have
         // arrived, and long before wavefront 0 has worked out where it goes.
-        Tile<U, NT, TPB, 1, stored_cv(ST, CV_NARROW), true> t;
+        Tile<U, NT, TPB, step_pace(ST, U), stored_cv(ST, CV_NARROW), true> t;
         t.load(a.batch_x + (int64_t)p * a.row_vec * stored_wide(ST), v_lo, v_hi);
         park_labels(yv, a.batch_y, b, a.K, s_y);
         __syncthreads();
@@ -250,7 +250,7 @@ __global__ void __launch_bounds__(TPB) rb_update_small_kernel(const UpdateArgs a
         }
         __syncthreads();
         const int p = s_p[par];
-        Tile<U, NT, TPB, 1, stored_cv(ST, CV_NARROW), true> t;
+        Tile<U, NT, TPB, step_pace(ST, U), stored_cv(ST, CV_NARROW), true> t;
         t.load(a.batch_x + (int64_t)p * a.row_vec * stored_wide(ST), v_lo, v_hi);
         if (w0) {
             const int32_t ki = lane_read(k, i);
@@ -377,7 +377,7 @@ __global__ void __launch_bounds__(TPB) rb_sample_small_kernel(const SampleArgs a
             continue;
         }
         const int pk = s_pick[par][0], ps = s_pick[par][1];
-        Tile<U, NT, TPB, 1, stored_cv(ST, CV_WIDEN)> t2;
+        Tile<U, NT, TPB, step_pace(ST, U), stored_cv(ST, CV_WIDEN)> t2;
         t2.load(a.buf_x + ((int64_t)pk * a.S + ps) * a.row_vec, v_lo, v_hi);
         t2.store(a.out_x + (int64_t)j * a.row_vec * stored_wide(ST), v_lo, v_hi);
         if (tile == 0 && tid == 0) { a.out_y[j] = pk; count_moved(a.state); }
@@ -494,7 +494,7 @@ __global__ void __launch_bounds__(TPB) rb_step_small_kernel(const StepArgs sa)
         __syncthreads();
         const int p = s_p;
         // requested as soon as the position is known, before the labels have arrived
-        Tile<U, NT, TPB, 1, stored_cv(ST, CV_NARROW), true> t;
+        Tile<U, NT, TPB, step_pace(ST, U), stored_cv(ST, CV_NARROW), true> t;
         t.load(a.batch_x + (int64_t)p * a.row_vec * stored_wide(ST), v_lo, v_hi);
         park_labels(yv, a.batch_y, b, a.K, s_y);
         __syncthreads();
@@ -602,13 +602,13 @@ __global__ void __launch_bounds__(TPB) rb_step_small_kernel(const StepArgs sa)
     vec16* dst = sa.out_x + (int64_t)j * a.row_vec * stored_wide(ST);
     if (ST != RB_STORE_SAME && fwd >= 0) {
         // from the mini-batch: what the slot will hold is the row in its stored form
-        Tile<U, NT, TPB, 1, stored_cv(ST, CV_BOTH)> t;
+        Tile<U, NT, TPB, step_pace(ST, U), stored_cv(ST, CV_BOTH)> t;
         t.load(a.batch_x + (int64_t)fwd * a.row_vec * stored_wide(ST), v_lo, v_hi);
         t.store(dst, v_lo, v_hi);
     } else {
         const vec16* src = fwd >= 0 ? a.batch_x + (int64_t)fwd * a.row_vec
                                     : a.buf_x + ((int64_t)pk * a.S + ps) * a.row_vec;
-        Tile<U, NT, TPB, 1, stored_cv(ST, CV_WIDEN)> t;
+        Tile<U, NT, TPB, step_pace(ST, U), stored_cv(ST, CV_WIDEN)> t;
         t.load(src, v_lo, v_hi);
         t.store(dst, v_lo, v_hi);
     }
