@@ -220,19 +220,15 @@ hipError_t launch_sample_small(const SampleArgs& a, int storage, int unroll, dim
 template <bool NT>
 hipError_t launch_update(const UpdateArgs& a, int narrow, int unroll, dim3 grid, size_t lds, hipStream_t st)
 {
-    if (narrow == 2) {                  // 8 bits per element: a lane holds four accesses per vector of the tile (at most four vectors)
+    if (narrow == 2) {                  // 8 bits per element: a lane holds four accesses per vector of the tile (at most two vectors)
         if (unroll == 1) rb_update_kernel<1, NT, 2><<<grid, TPB, lds, st>>>(a);
-        else if (unroll == 2) rb_update_kernel<2, NT, 2><<<grid, TPB, lds, st>>>(a);
-        else rb_update_kernel<4, NT, 2><<<grid, TPB, lds, st>>>(a);
+        else rb_update_kernel<2, NT, 2><<<grid, TPB, lds, st>>>(a);
         return hipGetLastError();
     }
-    if (narrow == 1) {
-        switch (unroll) {
-        case 1: rb_update_kernel<1, NT, 1><<<grid, TPB, lds, st>>>(a); break;
-        case 2: rb_update_kernel<2, NT, 1><<<grid, TPB, lds, st>>>(a); break;
-        case 4: rb_update_kernel<4, NT, 1><<<grid, TPB, lds, st>>>(a); break;
-        default: rb_update_kernel<8, NT, 1><<<grid, TPB, lds, st>>>(a); break;
-        }
+    if (narrow == 1) {                  // bfloat16: at most four
+        if (unroll == 1) rb_update_kernel<1, NT, 1><<<grid, TPB, lds, st>>>(a);
+        else if (unroll == 2) rb_update_kernel<2, NT, 1><<<grid, TPB, lds, st>>>(a);
+        else rb_update_kernel<4, NT, 1><<<grid, TPB, lds, st>>>(a);
         return hipGetLastError();
     }
     switch (unroll) {
@@ -249,17 +245,13 @@ hipError_t launch_sample(const SampleArgs& a, int widen, int unroll, dim3 grid, 
 {
     if (widen == 2) {
         if (unroll == 1) rb_sample_kernel<1, NT, 2><<<grid, TPB, lds, st>>>(a);
-        else if (unroll == 2) rb_sample_kernel<2, NT, 2><<<grid, TPB, lds, st>>>(a);
-        else rb_sample_kernel<4, NT, 2><<<grid, TPB, lds, st>>>(a);
+        else rb_sample_kernel<2, NT, 2><<<grid, TPB, lds, st>>>(a);
         return hipGetLastError();
     }
     if (widen == 1) {
-        switch (unroll) {
-        case 1: rb_sample_kernel<1, NT, 1><<<grid, TPB, lds, st>>>(a); break;
-        case 2: rb_sample_kernel<2, NT, 1><<<grid, TPB, lds, st>>>(a); break;
-        case 4: rb_sample_kernel<4, NT, 1><<<grid, TPB, lds, st>>>(a); break;
-        default: rb_sample_kernel<8, NT, 1><<<grid, TPB, lds, st>>>(a); break;
-        }
+        if (unroll == 1) rb_sample_kernel<1, NT, 1><<<grid, TPB, lds, st>>>(a);
+        else if (unroll == 2) rb_sample_kernel<2, NT, 1><<<grid, TPB, lds, st>>>(a);
+        else rb_sample_kernel<4, NT, 1><<<grid, TPB, lds, st>>>(a);
         return hipGetLastError();
     }
     switch (unroll) {
@@ -1328,7 +1320,7 @@ int rb_update(rb_buffer* rb, const void* batch_x, const int64_t* batch_y,
         while (slack * slack < 36 * c) ++slack;          // about six standard deviations
         rows = c + slack < b ? c + slack : b;
     }
-    const Shape sh = plan_shape(rb, rows, small ? TPB : WAVE, narrow == 2 ? (small ? 2 : 4) : 8);   // (see plan_shape)
+    const Shape sh = plan_shape(rb, rows, small ? TPB : WAVE, narrow == 2 ? 2 : narrow == 1 && !small ? 4 : 8);   // (general kernel: 100 + 90 bfloat16 rows of 602 KB 40.0 us with eight, 38.1 with four)
     UpdateArgs a;
     a.batch_x = static_cast<const vec16*>(batch_x);
     a.batch_y = batch_y;
@@ -1370,7 +1362,7 @@ int rb_sample_augment(rb_buffer* rb, int64_t r, uint64_t seed, uint64_t step, vo
 
     const int widen = rb->storage == RB_STORE_BF16 ? 1 : rb->storage == RB_STORE_U8 ? 2 : 0;
     const bool small = r <= WAVE && rb->nchunks <= WAVE;
-    const Shape sh = plan_shape(rb, r, small ? TPB : WAVE, widen == 2 ? (small ? 2 : 4) : 8);
+    const Shape sh = plan_shape(rb, r, small ? TPB : WAVE, widen == 2 ? 2 : widen == 1 && !small ? 4 : 8);
     SampleArgs a;
     a.buf_x = static_cast<const vec16*>(rb->buf_x);
     a.out_x = static_cast<vec16*>(out_x);
