@@ -123,7 +123,7 @@ int rb_set_storage(rb_buffer *rb, int32_t storage);
  * offered to a full class replaces a uniformly drawn slot with probability
  * slots_per_class / n and is dropped otherwise (exact while a class has been
  * offered fewer than 2^31 - 1 samples).
- * rb_update_sample serves every variant in one launch (up to 10240 classes).
+ * Every variant is served by rb_update_sample.
  * The plan-ahead forms of the single launch (rb_announce_next) serve every variant (the Bernoulli selection for b <= 1024), and so do the
  * several-steps launches of rb_update_sample_many (the form for small counts
  * with the exact selection only; the form for large counts takes over for the
@@ -202,8 +202,9 @@ int rb_sample_augment(rb_buffer *rb, int64_t r, uint64_t seed, uint64_t step,
  * representatives): rb_update(rb, batch_x, batch_y, b, c, seed, step) followed
  * by rb_sample_augment(rb, r, seed, step, out_x, out_y), as one call with the
  * same arguments, meaning, errors and, bit for bit, the same results.  With
- * c >= 1, r >= 1 and up to 10240 classes both halves run as ONE kernel launch (a
- * representative whose slot is being written in this very step is copied from
+ * 1 <= c, r <= 64, up to 1024 classes and the exact selection, and with c, r >= 1
+ * and up to 10240 classes when the rows are not too many bytes, both halves run
+ * as ONE kernel launch (a representative whose slot is being written in this very step is copied from
  * the mini-batch row stored there); otherwise the two kernels are enqueued one
  * after the other.  out_x must not overlap batch_x.
  */

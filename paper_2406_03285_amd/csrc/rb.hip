@@ -1002,8 +1002,8 @@ int many_form(const rb_buffer* rb, int64_t b, int64_t c, int64_t r, int64_t& ste
 template <int U, bool NT, int ST>
 hipError_t launch_one_u(const OneArgs& a, dim3 grid, size_t lds, hipStream_t st)
 {
-    if constexpr (ST == RB_STORE_U8 && U > 4) {
-        return hipErrorInvalidValue;           // (a lane holds four accesses per vector: step_one)
+    if constexpr ((ST == RB_STORE_U8 && U > 1) || (ST == RB_STORE_BF16 && U > 2)) {
+        return hipErrorInvalidValue;           // (converted rows: step_one)
     } else {
         constexpr int most = 4 * (ONE_CLASSES + ONE_TPB + (int)ONE_MATE_WORDS + 4 * RB_MAX_BATCH) + 2 * RB_MAX_BATCH;      // one_lds_bytes at its largest
         static_assert(most <= 156 * 1024, "a compute unit has 160 KB of LDS");
@@ -1088,7 +1088,9 @@ int step_one(rb_buffer* rb, const void* batch_x, const int64_t* batch_y, int64_t
     }
     constexpr int64_t CUS = 256;                // one workgroup per compute unit, dealt to the two sides by their rows
     const int64_t most_r = std::min<int64_t>(CUS - 1, std::max<int64_t>(1, (CUS * r + (rows + r) / 2) / (rows + r)));
-    int limit = rb->storage == RB_STORE_U8 ? 4 : 8;
+    // (rows that are converted: small tiles.  612 + 625 rows of 11.5 KB in 8 bits 15.6 us with one vector per lane, 17.8 with two,
+    // 20.5 with four; as bfloat16 13.9, 12.9 with two, 14.2)
+    int limit = rb->storage == RB_STORE_U8 ? 1 : rb->storage == RB_STORE_BF16 ? 2 : 8;
     if (rb->opt_unroll != 0) limit = std::min(limit, rb->opt_unroll);
     const int uc = one_tiles(rb, rows, (CUS - most_r) * ONE_NWAVE, limit, a.tpr, a.tile_vec, a.tile_rem);
     const int ur = one_tiles(rb, r, most_r * ONE_NWAVE, limit, oa.tpr, oa.tile_vec, oa.tile_rem);
@@ -1411,8 +1413,16 @@ int rb_update_sample(rb_buffer* rb, const void* batch_x, const int64_t* batch_y,
         return step_planned(rb, batch_x, batch_y, b, c, r, seed, step, out_x, out_y, next_y);
     if (big && (rb->plan_valid || next_y))
         return step_big(rb, batch_x, batch_y, b, c, r, seed, step, out_x, out_y, next_y);
-    // every other shape in one launch as well, as long as the fill counts fit LDS and work items are counted in 32 bits
-    if (!fused && c >= 1 && r >= 1 && rb->K <= ONE_CLASSES && rb->opt_fuse &&
+    // Other shapes in one launch as well, as long as the fill counts fit LDS, work items are counted in 32 bits and the rows are
+    // moved soon enough: with one workgroup of planners and movers per compute unit long rows move slower than in the general
+    // kernels, rows that are converted most of all.  Measured on MI355X, one launch against two (in brackets the time the rows
+    // take at 5.5 TB/s): as they are, 300 + 300 rows of 12 KB [2.7 us] 10.2 : 11.7, 200 + 200 of 49 KB [7.2] 14.3 : 15.8,
+    // 100 + 100 of 192 KB [14.0] 21.5 : 22.1, 40 + 66 of 602 KB [23] 30.9 : 27.7; as bfloat16 200 + 200 of 49 KB [5.4] 13.3 : 13.9,
+    // 66 + 200 of 80 KB [5.8] 13.7 : 13.4, 200 + 200 of 192 KB [21] 31.0 : 29.0; in 8 bits 70 + 70 of 49 KB [1.6] 9.6 : 10.3,
+    // 300 + 300 of 12 KB [1.7] 11.6 : 11.6, 200 + 200 of 49 KB [4.5] 16.2 : 14.0.
+    const double one_us = (double)(c + r) * (double)(rb->row_bytes + rb->sample_bytes) / 5.5e6;
+    const double one_most = rb->storage == RB_STORE_U8 ? 2.0 : rb->storage == RB_STORE_BF16 ? 5.5 : 14.0;
+    if (!fused && one_us < one_most && c >= 1 && r >= 1 && rb->K <= ONE_CLASSES && rb->opt_fuse &&
         (rb->row_vec + TILE_UNIT - 1) / TILE_UNIT <= INT32_MAX / 2 / RB_MAX_BATCH)
         return step_one(rb, batch_x, batch_y, b, c, r, seed, step, out_x, out_y);
     if (!fused) {

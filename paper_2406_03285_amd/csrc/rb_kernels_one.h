@@ -1,5 +1,5 @@
-// rb_update_sample in ONE launch for every shape that rb_step_small_kernel does not serve: any candidate and
-// representative count, any selection and replacement strategy, any storage form, up to ONE_CLASSES classes.
+// rb_update_sample in ONE launch for shapes that rb_step_small_kernel does not serve: any candidate and representative
+// count, any selection and replacement strategy, any storage form, up to ONE_CLASSES classes, rows that are moved soon.
 // Included by rb.hip only, after rb_kernels_small.h (whose wavefront selection it uses).
 #pragma once
 
@@ -192,6 +192,7 @@ __device__ __forceinline__ int one_writer(const UpdateArgs& a, const uint32_t* s
 // the two general launches this replaces: 1024 + 1024 rows of 8 KB of 10000 classes 16.3 : 17.0 us; Bernoulli selection with
 // reservoir replacement, 90 + 75 rows of 49 KB kept as bfloat16, 9.3 : 10.9; 6 + 5 rows of 393 KB in 8 bits, Bernoulli,
 // 8.2 : 14.5; 185 + 121 rows of 13 KB in 8 bits of 5654 classes 11.4 : 17.8; 4 + 5 rows of 5 KB of 3179 classes 7.4 : 8.0.
+// (Rows of more bytes stay with the two launches: rb_update_sample.)
 //
 // LDS (dynamic): s_fill[nchunks * CH] i32, s_before[ONE_TPB] i32, per wavefront pend u16[WAVE], cm u32[ONE_WORDS],
 // cmpre u16[ONE_WORDS]; s_lab[b] u32, s_first[b] u32, s_kx[cap] u32, s_t[max(cap, r)] u32 (both
