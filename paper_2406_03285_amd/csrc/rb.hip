@@ -220,15 +220,19 @@ hipError_t launch_sample_small(const SampleArgs& a, int storage, int unroll, dim
 template <bool NT>
 hipError_t launch_update(const UpdateArgs& a, int narrow, int unroll, dim3 grid, size_t lds, hipStream_t st)
 {
-    if (narrow == 2) {                  // 8 bits per element: a lane holds four accesses per vector of the tile (at most two vectors)
+    if (narrow == 2) {                  // 8 bits per element: a lane holds four accesses per vector of the tile (at most four vectors)
         if (unroll == 1) rb_update_kernel<1, NT, 2><<<grid, TPB, lds, st>>>(a);
-        else rb_update_kernel<2, NT, 2><<<grid, TPB, lds, st>>>(a);
+        else if (unroll == 2) rb_update_kernel<2, NT, 2><<<grid, TPB, lds, st>>>(a);
+        else rb_update_kernel<4, NT, 2><<<grid, TPB, lds, st>>>(a);
         return hipGetLastError();
     }
-    if (narrow == 1) {                  // bfloat16: at most four
-        if (unroll == 1) rb_update_kernel<1, NT, 1><<<grid, TPB, lds, st>>>(a);
-        else if (unroll == 2) rb_update_kernel<2, NT, 1><<<grid, TPB, lds, st>>>(a);
-        else rb_update_kernel<4, NT, 1><<<grid, TPB, lds, st>>>(a);
+    if (narrow == 1) {
+        switch (unroll) {
+        case 1: rb_update_kernel<1, NT, 1><<<grid, TPB, lds, st>>>(a); break;
+        case 2: rb_update_kernel<2, NT, 1><<<grid, TPB, lds, st>>>(a); break;
+        case 4: rb_update_kernel<4, NT, 1><<<grid, TPB, lds, st>>>(a); break;
+        default: rb_update_kernel<8, NT, 1><<<grid, TPB, lds, st>>>(a); break;
+        }
         return hipGetLastError();
     }
     switch (unroll) {
@@ -1322,7 +1326,10 @@ int rb_update(rb_buffer* rb, const void* batch_x, const int64_t* batch_y,
         while (slack * slack < 36 * c) ++slack;          // about six standard deviations
         rows = c + slack < b ? c + slack : b;
     }
-    const Shape sh = plan_shape(rb, rows, small ? TPB : WAVE, narrow == 2 ? 2 : narrow == 1 && !small ? 4 : 8);   // (general kernel: 100 + 90 bfloat16 rows of 602 KB 40.0 us with eight, 38.1 with four)
+    // (converted rows, general kernel: 100 + 90 bfloat16 rows of 602 KB 40.0 us with eight vectors per lane, 38.1 with four; with
+    // thousands of candidates every tile's share of the plan counts more: large tiles)
+    const bool many = !small && c > BIG_MAX;
+    const Shape sh = plan_shape(rb, rows, small ? TPB : WAVE, narrow == 2 ? (many ? 4 : 2) : narrow == 1 && !small && !many ? 4 : 8);
     UpdateArgs a;
     a.batch_x = static_cast<const vec16*>(batch_x);
     a.batch_y = batch_y;
@@ -1422,7 +1429,11 @@ int rb_update_sample(rb_buffer* rb, const void* batch_x, const int64_t* batch_y,
     // 300 + 300 of 12 KB [1.7] 11.6 : 11.6, 200 + 200 of 49 KB [4.5] 16.2 : 14.0.
     const double one_us = (double)(c + r) * (double)(rb->row_bytes + rb->sample_bytes) / 5.5e6;
     const double one_most = rb->storage == RB_STORE_U8 ? 2.0 : rb->storage == RB_STORE_BF16 ? 5.5 : 14.0;
-    if (!fused && one_us < one_most && c >= 1 && r >= 1 && rb->K <= ONE_CLASSES && rb->opt_fuse &&
+    // (every representative's workgroup reads all fill counts: with many classes and few plain rows that is what two launches
+    // cost.  7832 classes, 109 + 29 rows of 3 KB 9.1 : 8.6 us; 3179 classes, 4 + 5 rows 7.4 : 8.0; 10000 classes, 1024 + 1024 rows
+    // of 8 KB 16.3 : 17.1)
+    const bool many_classes = rb->K > 6144 && c + r <= 512 && rb->selection == RB_SELECT_EXACT && rb->storage == RB_STORE_SAME;
+    if (!fused && one_us < one_most && !many_classes && c >= 1 && r >= 1 && rb->K <= ONE_CLASSES && rb->opt_fuse &&
         (rb->row_vec + TILE_UNIT - 1) / TILE_UNIT <= INT32_MAX / 2 / RB_MAX_BATCH)
         return step_one(rb, batch_x, batch_y, b, c, r, seed, step, out_x, out_y);
     if (!fused) {
