@@ -308,6 +308,15 @@ int rb_announce_next_many(rb_buffer *rb, int64_t n, const int64_t *const *next_b
 int rb_query_steps_per_launch(const rb_buffer *rb, int64_t b, int64_t c, int64_t r, int64_t *steps);
 
 /*
+ * How many kernel launches rb_update_sample enqueues for a step of this shape
+ * that was not announced, with the handle's present policy, storage and
+ * options: 1 (both halves in one kernel), 2 (one after the other), or fewer
+ * when c or r is 0.  Host only.
+ * RB_EINVAL: null pointers, b, c or r out of range (as in rb_update_sample).
+ */
+int rb_query_launches(const rb_buffer *rb, int64_t b, int64_t c, int64_t r, int64_t *launches);
+
+/*
  * The asynchronous form of that primitive (Sec. IV-D, Fig. 4, Listing 1): the
  * training loop calls it once per iteration with the iteration's mini-batch;
  * the call (1) makes `train_stream` wait until the representatives that the

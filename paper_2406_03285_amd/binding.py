@@ -25,7 +25,7 @@ RB_EVICT_UNIFORM, RB_EVICT_FIFO, RB_EVICT_RESERVOIR = 0, 1, 2
 
 EXPORTS = (
     "rb_create", "rb_query_sizes", "rb_set_storage", "rb_bind", "rb_bind_static", "rb_set_policy", "rb_set_stream", "rb_update", "rb_sample_augment", "rb_update_sample",
-    "rb_announce_next", "rb_announce_next_many", "rb_query_steps_per_launch", "rb_update_sample_many", "rb_pipeline_create", "rb_pipeline_step", "rb_pipeline_step_many", "rb_pipeline_drain", "rb_pipeline_destroy",
+    "rb_announce_next", "rb_announce_next_many", "rb_query_steps_per_launch", "rb_query_launches", "rb_update_sample_many", "rb_pipeline_create", "rb_pipeline_step", "rb_pipeline_step_many", "rb_pipeline_drain", "rb_pipeline_destroy",
     "rb_read_state", "rb_read_moved_rows", "rb_set_option", "rb_destroy", "rb_strerror", "rb_standin_compute", "rb_copy_bytes",
 )
 
@@ -56,6 +56,7 @@ def _load():
     L.rb_announce_next.argtypes = [vp, vp]
     L.rb_announce_next_many.argtypes = [vp, i64, C.POINTER(vp)]
     L.rb_query_steps_per_launch.argtypes = [vp, i64, i64, i64, C.POINTER(i64)]
+    L.rb_query_launches.argtypes = [vp, i64, i64, i64, C.POINTER(i64)]
     L.rb_update_sample_many.argtypes = [vp, i64, C.POINTER(vp), C.POINTER(vp), i64, i64, i64, u64, u64, C.POINTER(vp), C.POINTER(vp)]
     L.rb_pipeline_create.argtypes = [C.POINTER(vp), vp]
     L.rb_pipeline_step.argtypes = [vp, vp, vp, i64, i64, i64, u64, u64, vp, vp, vp, C.POINTER(i64)]
@@ -161,6 +162,12 @@ def rb_query_steps_per_launch(rb, b, c, r):
     steps = C.c_int64(0)
     rc = _L.rb_query_steps_per_launch(rb, int(b), int(c), int(r), C.byref(steps))
     return rc, steps.value
+
+
+def rb_query_launches(rb, b, c, r):
+    launches = C.c_int64(0)
+    rc = _L.rb_query_launches(rb, int(b), int(c), int(r), C.byref(launches))
+    return rc, launches.value
 
 
 def pointer_array(items):

@@ -1055,6 +1055,37 @@ int one_tiles(const rb_buffer* rb, int64_t rows, int64_t waves, int most, int32_
     return (int)((units + n - 1) / n);
 }
 
+// Shapes whose whole plan one wavefront can make: rb_step_small_kernel, and the plan-ahead step of rb_kernels_planned.h.
+bool small_counts(const rb_buffer* rb, int64_t c, int64_t r)
+{
+    return c >= 1 && c <= WAVE && r >= 1 && r <= WAVE && rb->nchunks <= DIRECT_CHUNKS && rb->opt_fuse && rb->selection == RB_SELECT_EXACT;
+}
+
+// How rb_update_sample carries out a step that is not planned ahead: STEP_SMALL (rb_step_small_kernel), STEP_ONE
+// (rb_step_one_kernel) or STEP_TWO (the two kernels of rb_update and rb_sample_augment).
+// STEP_ONE as long as the fill counts fit LDS, work items are counted in 32 bits and the rows are
+// moved soon enough: with one workgroup of planners and movers per compute unit long rows move slower than in the general
+// kernels, rows that are converted most of all.  Measured on MI355X, one launch against two (in brackets the time the rows
+// take at 5.5 TB/s): as they are, 300 + 300 rows of 12 KB [2.7 us] 10.2 : 11.7, 200 + 200 of 49 KB [7.2] 14.3 : 15.8,
+// 100 + 100 of 192 KB [14.0] 21.5 : 22.1, 40 + 66 of 602 KB [23] 30.9 : 27.7; as bfloat16 200 + 200 of 49 KB [5.4] 13.3 : 13.9,
+// 66 + 200 of 80 KB [5.8] 13.7 : 13.4, 200 + 200 of 192 KB [21] 31.0 : 29.0; in 8 bits 70 + 70 of 49 KB [1.6] 9.6 : 10.3,
+// 300 + 300 of 12 KB [1.7] 11.6 : 11.6, 200 + 200 of 49 KB [4.5] 16.2 : 14.0.
+enum { STEP_TWO = 0, STEP_SMALL = 1, STEP_ONE = 2 };
+int step_form(const rb_buffer* rb, int64_t c, int64_t r)
+{
+    if (small_counts(rb, c, r)) return STEP_SMALL;
+    const double one_us = (double)(c + r) * (double)(rb->row_bytes + rb->sample_bytes) / 5.5e6;
+    const double one_most = rb->storage == RB_STORE_U8 ? 2.0 : rb->storage == RB_STORE_BF16 ? 5.5 : 14.0;
+    // (every representative's workgroup reads all fill counts: with many classes and few plain rows that is what two launches
+    // cost.  7832 classes, 109 + 29 rows of 3 KB 9.1 : 8.6 us; 3179 classes, 4 + 5 rows 7.4 : 8.0; 10000 classes, 1024 + 1024 rows
+    // of 8 KB 16.3 : 17.1)
+    const bool many_classes = rb->K > 6144 && c + r <= 512 && rb->selection == RB_SELECT_EXACT && rb->storage == RB_STORE_SAME;
+    if (one_us < one_most && !many_classes && c >= 1 && r >= 1 && rb->K <= ONE_CLASSES && rb->opt_fuse &&
+        (rb->row_vec + TILE_UNIT - 1) / TILE_UNIT <= INT32_MAX / 2 / RB_MAX_BATCH)
+        return STEP_ONE;
+    return STEP_TWO;
+}
+
 // Update and sampling of one step in one launch without a plan (rb_kernels_one.h).
 int step_one(rb_buffer* rb, const void* batch_x, const int64_t* batch_y, int64_t b, int64_t c, int64_t r,
              uint64_t seed, uint64_t step, void* out_x, int64_t* out_y)
@@ -1402,10 +1433,7 @@ int rb_update_sample(rb_buffer* rb, const void* batch_x, const int64_t* batch_y,
     discard_window_plan(rb);                     // a single step is not what a planned window was made for
     rb->ann_n = 0;
 
-    // the plan-ahead form covers both storage forms; the kernel that plans and moves in one launch only the plain one
-    const bool plannable = c >= 1 && c <= WAVE && r >= 1 && r <= WAVE && rb->nchunks <= DIRECT_CHUNKS && rb->opt_fuse &&
-                           rb->selection == RB_SELECT_EXACT;
-    const bool fused = plannable;
+    const bool plannable = small_counts(rb, c, r);
     // larger counts have a plan-ahead form of their own
     // (with the Bernoulli selection, whose number of candidates is only bounded by b, for mini-batches of at most BIG_MAX)
     const bool big = !plannable && c >= 1 && c <= BIG_MAX && r >= 1 && r <= BIG_MAX && b <= BIG_BATCH &&
@@ -1420,23 +1448,9 @@ int rb_update_sample(rb_buffer* rb, const void* batch_x, const int64_t* batch_y,
         return step_planned(rb, batch_x, batch_y, b, c, r, seed, step, out_x, out_y, next_y);
     if (big && (rb->plan_valid || next_y))
         return step_big(rb, batch_x, batch_y, b, c, r, seed, step, out_x, out_y, next_y);
-    // Other shapes in one launch as well, as long as the fill counts fit LDS, work items are counted in 32 bits and the rows are
-    // moved soon enough: with one workgroup of planners and movers per compute unit long rows move slower than in the general
-    // kernels, rows that are converted most of all.  Measured on MI355X, one launch against two (in brackets the time the rows
-    // take at 5.5 TB/s): as they are, 300 + 300 rows of 12 KB [2.7 us] 10.2 : 11.7, 200 + 200 of 49 KB [7.2] 14.3 : 15.8,
-    // 100 + 100 of 192 KB [14.0] 21.5 : 22.1, 40 + 66 of 602 KB [23] 30.9 : 27.7; as bfloat16 200 + 200 of 49 KB [5.4] 13.3 : 13.9,
-    // 66 + 200 of 80 KB [5.8] 13.7 : 13.4, 200 + 200 of 192 KB [21] 31.0 : 29.0; in 8 bits 70 + 70 of 49 KB [1.6] 9.6 : 10.3,
-    // 300 + 300 of 12 KB [1.7] 11.6 : 11.6, 200 + 200 of 49 KB [4.5] 16.2 : 14.0.
-    const double one_us = (double)(c + r) * (double)(rb->row_bytes + rb->sample_bytes) / 5.5e6;
-    const double one_most = rb->storage == RB_STORE_U8 ? 2.0 : rb->storage == RB_STORE_BF16 ? 5.5 : 14.0;
-    // (every representative's workgroup reads all fill counts: with many classes and few plain rows that is what two launches
-    // cost.  7832 classes, 109 + 29 rows of 3 KB 9.1 : 8.6 us; 3179 classes, 4 + 5 rows 7.4 : 8.0; 10000 classes, 1024 + 1024 rows
-    // of 8 KB 16.3 : 17.1)
-    const bool many_classes = rb->K > 6144 && c + r <= 512 && rb->selection == RB_SELECT_EXACT && rb->storage == RB_STORE_SAME;
-    if (!fused && one_us < one_most && !many_classes && c >= 1 && r >= 1 && rb->K <= ONE_CLASSES && rb->opt_fuse &&
-        (rb->row_vec + TILE_UNIT - 1) / TILE_UNIT <= INT32_MAX / 2 / RB_MAX_BATCH)
-        return step_one(rb, batch_x, batch_y, b, c, r, seed, step, out_x, out_y);
-    if (!fused) {
+    const int form = step_form(rb, c, r);
+    if (form == STEP_ONE) return step_one(rb, batch_x, batch_y, b, c, r, seed, step, out_x, out_y);
+    if (form == STEP_TWO) {
         const int rc = rb_update(rb, batch_x, batch_y, b, c, seed, step);
         if (rc != RB_OK) return rc;
         return rb_sample_augment(rb, r, seed, step, out_x, out_y);
@@ -1489,6 +1503,14 @@ int rb_query_steps_per_launch(const rb_buffer* rb, int64_t b, int64_t c, int64_t
     if (!rb || !steps) return RB_EINVAL;
     if (b < 1 || b > RB_MAX_BATCH || c < 0 || c > b || r < 0 || r > RB_MAX_BATCH) return RB_EINVAL;
     (void)many_form(rb, b, c, r, *steps);
+    return RB_OK;
+}
+
+int rb_query_launches(const rb_buffer* rb, int64_t b, int64_t c, int64_t r, int64_t* launches)
+{
+    if (!rb || !launches) return RB_EINVAL;
+    if (b < 1 || b > RB_MAX_BATCH || c < 0 || c > b || r < 0 || r > RB_MAX_BATCH) return RB_EINVAL;
+    *launches = step_form(rb, c, r) != STEP_TWO ? 1 : (c > 0) + (r > 0);
     return RB_OK;
 }
 

@@ -139,3 +139,16 @@ def test_variant_setters_validate_on_the_host():
     assert rb.rb_set_option(h, rb.RB_OPT_PLANNERS, 2) == rb.RB_OK and rb.rb_query_steps_per_launch(h, 64, 8, 8) == (rb.RB_OK, 16)
     assert rb.rb_set_option(h, rb.RB_OPT_PLANNERS, 1) == rb.RB_OK and rb.rb_query_steps_per_launch(h, 64, 4, 4) == (rb.RB_OK, 32)
     rb.rb_destroy(h)
+
+
+def test_launches_of_a_step_validate_on_the_host():
+    import paper_2406_03285_amd as rb
+    rc, h = rb.rb_create(100, 20, (3072,), rb.RB_F32)
+    assert rb.rb_query_launches(None, 8, 2, 2)[0] == rb.RB_EINVAL
+    assert rb.rb_query_launches(h, 0, 0, 0)[0] == rb.RB_EINVAL and rb.rb_query_launches(h, 8, 9, 2)[0] == rb.RB_EINVAL
+    assert rb.rb_query_launches(h, 8, 2, rb.RB_MAX_BATCH + 1)[0] == rb.RB_EINVAL
+    assert rb.rb_query_launches(h, 128, 16, 16) == (rb.RB_OK, 1) and rb.rb_query_launches(h, 256, 100, 90) == (rb.RB_OK, 1)
+    assert rb.rb_query_launches(h, 128, 0, 16) == (rb.RB_OK, 1) and rb.rb_query_launches(h, 128, 0, 0) == (rb.RB_OK, 0)
+    assert rb.rb_set_option(h, rb.RB_OPT_FUSE, 0) == rb.RB_OK
+    assert rb.rb_query_launches(h, 128, 16, 16) == (rb.RB_OK, 2) and rb.rb_query_launches(h, 256, 100, 90) == (rb.RB_OK, 2)
+    rb.rb_destroy(h)
