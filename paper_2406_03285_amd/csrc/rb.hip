@@ -1063,8 +1063,8 @@ bool small_counts(const rb_buffer* rb, int64_t c, int64_t r)
 
 // How rb_update_sample carries out a step that is not planned ahead: STEP_SMALL (rb_step_small_kernel), STEP_ONE
 // (rb_step_one_kernel) or STEP_TWO (the two kernels of rb_update and rb_sample_augment).
-// STEP_ONE as long as the fill counts fit LDS, work items are counted in 32 bits and the rows are
-// moved soon enough: with one workgroup of planners and movers per compute unit long rows move slower than in the general
+// STEP_ONE as long as the fill counts fit LDS, work items and a class's count with a step's candidates on top (not yet cut
+// off at the capacity) are counted in 32 bits, and the rows are moved soon enough: with one workgroup of planners and movers per compute unit long rows move slower than in the general
 // kernels, rows that are converted most of all.  Measured on MI355X, one launch against two (in brackets the time the rows
 // take at 5.5 TB/s): as they are, 300 + 300 rows of 12 KB [2.7 us] 10.2 : 11.7, 200 + 200 of 49 KB [7.2] 14.3 : 15.8,
 // 100 + 100 of 192 KB [14.0] 21.5 : 22.1, 40 + 66 of 602 KB [23] 30.9 : 27.7; as bfloat16 200 + 200 of 49 KB [5.4] 13.3 : 13.9,
@@ -1081,7 +1081,7 @@ int step_form(const rb_buffer* rb, int64_t c, int64_t r)
     // of 8 KB 16.3 : 17.1)
     const bool many_classes = rb->K > 6144 && c + r <= 512 && rb->selection == RB_SELECT_EXACT && rb->storage == RB_STORE_SAME;
     if (one_us < one_most && !many_classes && c >= 1 && r >= 1 && rb->K <= ONE_CLASSES && rb->opt_fuse &&
-        (rb->row_vec + TILE_UNIT - 1) / TILE_UNIT <= INT32_MAX / 2 / RB_MAX_BATCH)
+        rb->S <= INT32_MAX - RB_MAX_BATCH && (rb->row_vec + TILE_UNIT - 1) / TILE_UNIT <= INT32_MAX / 2 / RB_MAX_BATCH)
         return STEP_ONE;
     return STEP_TWO;
 }

@@ -390,7 +390,7 @@ __global__ void __launch_bounds__(ONE_TPB) rb_step_one_kernel(const OneArgs sa)
     }
     classes();
 
-    // ---- fill counts after the update (not yet cut off at the capacity) ----
+    // ---- fill counts after the update (not yet cut off at the capacity: step_form keeps S + RB_MAX_BATCH within 32 bits) ----
     for (int q = tid; q < m; q += ONE_TPB) {
         const uint32_t kx = s_kx[q];
         if (kx != ONE_NO_CLASS) atomicAdd(&s_fill[kx >> ONE_POS_BITS], 1);

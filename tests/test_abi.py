@@ -152,3 +152,20 @@ def test_launches_of_a_step_validate_on_the_host():
     assert rb.rb_set_option(h, rb.RB_OPT_FUSE, 0) == rb.RB_OK
     assert rb.rb_query_launches(h, 128, 16, 16) == (rb.RB_OK, 2) and rb.rb_query_launches(h, 256, 100, 90) == (rb.RB_OK, 2)
     rb.rb_destroy(h)
+
+
+# The single launch for any counts adds a step's candidates to the fill counts in 32 bits: a class may hold up to
+# slots_per_class samples, and a step offers it up to RB_MAX_BATCH more.
+@pytest.mark.parametrize("storage,elems", [(0, 4), (1, 8), (2, 16)], ids=["same", "bf16", "u8"])
+@pytest.mark.parametrize("selection", [0, 1])
+@pytest.mark.parametrize("eviction", [0, 1, 2])
+def test_single_launch_leaves_room_for_a_step_above_the_slots(storage, elems, selection, eviction):
+    import paper_2406_03285_amd as rb
+    most = 2**31 - 1 - rb.RB_MAX_BATCH
+    for classes, slots, launches in ((1, most, 1), (1, most + 1, 2), (1, 2**31 - 1, 2), (2, 2**30 - 1, 1)):
+        rc, h = rb.rb_create(classes, slots, (elems,), rb.RB_F32)
+        assert rc == rb.RB_OK and rb.rb_set_storage(h, storage) == rb.RB_OK
+        assert rb.rb_set_policy(h, selection, eviction) == rb.RB_OK
+        for b, c, r in ((4096, 4096, 10), (100, 65, 10), (66, 65, 1)):
+            assert rb.rb_query_launches(h, b, c, r) == (rb.RB_OK, launches), (classes, slots, b, c, r)
+        rb.rb_destroy(h)
