@@ -1076,6 +1076,16 @@ int step_form(const rb_buffer* rb, int64_t c, int64_t r)
     if (small_counts(rb, c, r)) return STEP_SMALL;
     const double one_us = (double)(c + r) * (double)(rb->row_bytes + rb->sample_bytes) / 5.5e6;
     const double one_most = rb->storage == RB_STORE_U8 ? 2.0 : rb->storage == RB_STORE_BF16 ? 5.5 : 14.0;
+    // A representative of a class that overwrites slots in this step searches the step's candidates of that class, in the two
+    // launches nobody does.  With few classes, i.e. many candidates of each (labels that occur equally often assumed), that
+    // costs more than a launch, sooner with FIFO and reservoir replacement, where the two launches' candidates need no search
+    // or mostly none.  One launch against two, rows of 2 KB: uniform replacement, 10 classes 4096 + 4096 [410 candidates per
+    // class] 64 : 114 us, 4 classes 2000 + 2000 [500] 32.1 : 30.2, 2 classes 2000 + 2000 [1000] 40 : 33; reservoir, 1 class
+    // 150 + 150 9.1 : 9.0 and 600 + 600 14.9 : 11.2, as bfloat16 2 classes 150 + 150 [75] 9.9 : 9.0 and 4 classes 600 + 600
+    // [150] 13.2 : 11.9, 10 classes 1000 + 1000 [100] 13.1 : 15.6 and 4096 + 4096 [410] 54.6 : 50.1, 50 classes 4096 + 4096
+    // [82] 44.5 : 60.9; FIFO, 1 class 600 + 600 11.8 : 10.6.
+    const int64_t mates = rb->eviction == RB_EVICT_UNIFORM ? 448 : std::max<int64_t>(WAVE, 8 * rb->K + 32);
+    if (c > mates * rb->K) return STEP_TWO;
     // (every representative's workgroup reads all fill counts: with many classes and few plain rows that is what two launches
     // cost.  7832 classes, 109 + 29 rows of 3 KB 9.1 : 8.6 us; 3179 classes, 4 + 5 rows 7.4 : 8.0; 10000 classes, 1024 + 1024 rows
     // of 8 KB 16.3 : 17.1)

@@ -166,6 +166,21 @@ def test_single_launch_leaves_room_for_a_step_above_the_slots(storage, elems, se
         rc, h = rb.rb_create(classes, slots, (elems,), rb.RB_F32)
         assert rc == rb.RB_OK and rb.rb_set_storage(h, storage) == rb.RB_OK
         assert rb.rb_set_policy(h, selection, eviction) == rb.RB_OK
-        for b, c, r in ((4096, 4096, 10), (100, 65, 10), (66, 65, 1)):
+        for b, c, r in ((4096, 64, 4096), (100, 64, 65), (1, 1, 65)):
             assert rb.rb_query_launches(h, b, c, r) == (rb.RB_OK, launches), (classes, slots, b, c, r)
         rb.rb_destroy(h)
+
+
+# Few classes: beyond so many candidates of each class per step, what a representative's search among them costs exceeds a launch.
+@pytest.mark.parametrize("eviction,classes,most", [(0, 1, 448), (0, 2, 896), (0, 9, 4032), (0, 10, 4096),
+                                                   (1, 1, 64), (1, 4, 256), (1, 10, 1120), (1, 20, 3840), (1, 21, 4096),
+                                                   (2, 1, 64), (2, 4, 256), (2, 10, 1120), (2, 20, 3840), (2, 21, 4096)])
+@pytest.mark.parametrize("selection", [0, 1])
+def test_single_launch_with_few_classes(eviction, classes, most, selection):
+    import paper_2406_03285_amd as rb
+    rc, h = rb.rb_create(classes, 40, (256,), rb.RB_F32)
+    assert rb.rb_set_policy(h, selection, eviction) == rb.RB_OK
+    for c in (most - 1, most, most + 1, 4096):
+        if c <= 4096:
+            assert rb.rb_query_launches(h, 4096, c, 100) == (rb.RB_OK, 1 if c <= most else 2), c
+    rb.rb_destroy(h)

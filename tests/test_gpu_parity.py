@@ -136,6 +136,23 @@ def test_single_call_without_a_plan(K, S, vecs, b, c, r, store, labels, policy):
                store_bf16=store == "bf16", store_u8=store == "u8")
 
 
+# ... with more candidates of a class than a wavefront has lanes: as many as the single launch takes with few classes, and skewed labels.
+@pytest.mark.parametrize("policy", ["exact-uniform"] + sorted(POLICIES))
+@pytest.mark.parametrize("K,S,vecs,b,c,r,store,labels", [
+    (20, 30, 4, 4096, 3800, 900, "same", "uniform"),        # ~190 class-mates, several per slot: full at once, whole rounds of FIFO
+    (20, 300, 8, 4096, 3000, 600, "bf16", "uniform"),       # ~150: fill up in the second step, appended and overwritten slots mixed
+    (60, 50, 2, 3001, 2900, 700, "u8", "zipf"),             # the head class has ~700, most classes few
+    (1, 3000, 1, 300, 64, 3000, "same", "uniform"),         # one class of all candidates, nothing is overwritten
+])
+def test_single_call_without_a_plan_and_many_class_mates(K, S, vecs, b, c, r, store, labels, policy):
+    rb = _rb()
+    shape = (vecs * {"same": 4, "bf16": 8, "u8": 16}[store],)
+    w = wl.Workload(f"mates-K{K}-b{b}-c{c}-r{r}-{store}", 9, K, S, shape, "f32", b, c, r, 5, "uniform", labels)
+    buf, _ = run_parity(w, check_state_every=2, single_call=True, policy=POLICIES.get(policy),
+                        store_bf16=store == "bf16", store_u8=store == "u8")
+    assert rb.rb_query_launches(buf.handle, b, c, r) == (rb.RB_OK, 1)
+
+
 def test_single_call_without_a_plan_drops_and_flags_bad_labels():
     rb = _rb()
     K, S, b, c, r = 1500, 3, 300, 200, 70
