@@ -1367,9 +1367,12 @@ int rb_update(rb_buffer* rb, const void* batch_x, const int64_t* batch_y,
         while (slack * slack < 36 * c) ++slack;          // about six standard deviations
         rows = c + slack < b ? c + slack : b;
     }
-    // (converted rows, general kernel: 100 + 90 bfloat16 rows of 602 KB 40.0 us with eight vectors per lane, 38.1 with four; with
-    // thousands of candidates every tile's share of the plan counts more: large tiles)
-    const bool many = !small && c > BIG_MAX;
+    // (converted rows, general kernel: 100 + 90 bfloat16 rows of 602 KB 40.0 us with eight vectors per lane, 38.1 with four.  Every
+    // tile repeats the plan's pass over the candidate list, so from about 770 candidates on rows that have several large tiles
+    // keep those.  Both calls, r = 64, large against small tiles: bfloat16 rows of 49 KB 600 candidates 18.5 : 18.5 us,
+    // 800 23.1 : 22.9, 900 24.7 : 26.1, 1000 25.4 : 28.1; of 192 KB 600 44.7 : 43.9, 800 55.8 : 57.6, 1000 66.5 : 71.8; 8 bits,
+    // 49 KB, 700 21.0 : 20.4, 900 22.9 : 25.1; rows of 12 KB, one large tile, 1024 as bfloat16 15.4 : 14.5, 8 bits 16.5 : 15.2)
+    const bool many = !small && (c > BIG_MAX || (rows > 768 && rb->row_vec > WAVE * (narrow == 2 ? 4 : 8)));
     const Shape sh = plan_shape(rb, rows, small ? TPB : WAVE, narrow == 2 ? (many ? 4 : 2) : narrow == 1 && !small && !many ? 4 : 8);
     UpdateArgs a;
     a.batch_x = static_cast<const vec16*>(batch_x);

@@ -220,6 +220,14 @@ def test_float32_samples_stored_as_bfloat16(w, steps):
     assert buf.buf_x.dtype == torch.bfloat16 and buf.row_bytes == w.row_bytes // 2
 
 
+# The tiles of converted rows change with the number of candidates: both sides of the line, ragged rows of one and of several tiles.
+@pytest.mark.parametrize("store,vecs", [("bf16", 513), ("bf16", 512), ("u8", 257), ("u8", 256)])
+@pytest.mark.parametrize("c", [768, 769, 1025])
+def test_converted_rows_with_many_candidates(store, vecs, c):
+    w = wl.Workload(f"tiles-{store}-{vecs}-{c}", 9, 70, 9, (vecs * (8 if store == "bf16" else 16),), "f32", 1100, c, 30, 2, "uniform", "uniform")
+    run_parity(w, store_bf16=store == "bf16", store_u8=store == "u8")
+
+
 def test_bfloat16_storage_rounds_every_special_value_like_the_oracle(monkeypatch):
     w = wl.variant(wl.C2, name="C2-bf16-special", S=3, c=64, r=64)
     monkeypatch.setattr(wl, "make_batch", lambda ww, step, dev="cpu": _special_values_batch(ww, step, dev))
