@@ -1086,10 +1086,21 @@ int step_form(const rb_buffer* rb, int64_t c, int64_t r)
     // [82] 44.5 : 60.9; FIFO, 1 class 600 + 600 11.8 : 10.6.
     const int64_t mates = rb->eviction == RB_EVICT_UNIFORM ? 448 : std::max<int64_t>(WAVE, 8 * rb->K + 32);
     if (c > mates * rb->K) return STEP_TWO;
-    // (every representative's workgroup reads all fill counts: with many classes and few plain rows that is what two launches
-    // cost.  7832 classes, 109 + 29 rows of 3 KB 9.1 : 8.6 us; 3179 classes, 4 + 5 rows 7.4 : 8.0; 10000 classes, 1024 + 1024 rows
-    // of 8 KB 16.3 : 17.1)
-    const bool many_classes = rb->K > 6144 && c + r <= 512 && rb->selection == RB_SELECT_EXACT && rb->storage == RB_STORE_SAME;
+    // Every representative's workgroup copies and sums all fill counts: 0.21 us per 1000 classes, which the second launch does
+    // not cost.  What that one costs instead, measured at 2000 classes, where the counts are nearly free, grows with the rows; two
+    // launches of the small-count kernels cost least.  One launch against two, rows of 3 KB, at 6000 / 8000 / 10000 classes:
+    // as they are 5 + 5 rows 7.5 : 7.3 at 6000; 30 + 30 7.9 : 8.0 at 6000; 109 + 29 8.2 : 8.5, 9.1 : 8.6 (7832 classes); 200 + 200
+    // 8.7 : 9.4 at 6000; 400 + 400 9.7 : 10.7, 10.1 : 10.7, 10.5 : 10.8; 1000 + 1000 13.6 : 16.2 at 10000.  As bfloat16 5 + 5
+    // 7.6 : 7.6 at 4000, 8.9 : 7.6 at 10000; 30 + 30 8.3 : 8.4, 8.6 : 8.2; 200 + 200 9.0 : 9.8, 9.5 : 9.9, 9.9 : 9.9.  In 8 bits 5 + 5
+    // 8.5 : 8.3 at 4000, 10.1 : 8.3 at 10000; 200 + 200 10.1 : 10.2, 10.5 : 10.1; 1000 + 1000 15.1 : 15.1 at 10000.  Bernoulli
+    // selection, as they are, 5 + 5 7.9 : 7.9, 8.4 : 7.9; 109 + 29 8.2 : 8.6, 8.6 : 8.7, 9.0 : 8.9; 200 + 200 9.5 : 10.0 at 10000; in
+    // 8 bits 30 + 30 9.3 : 9.5, 9.8 : 9.7, 10.2 : 9.5.
+    const bool u8 = rb->storage == RB_STORE_U8;
+    const double rows = (double)(c + r);
+    const double second_us = rb->selection == RB_SELECT_BERNOULLI ? (u8 ? 0.72 : 0.82) + 0.004 * rows
+                           : c <= WAVE && r <= WAVE ? (rb->storage == RB_STORE_SAME ? 0.5 + 0.0085 * rows : 0.3 + 0.007 * rows)
+                           : u8 ? 0.63 + 0.0005 * rows : 0.85 + 0.0019 * rows;
+    const bool many_classes = 0.21e-3 * (double)(rb->K - 2000) > second_us;
     if (one_us < one_most && !many_classes && c >= 1 && r >= 1 && rb->K <= ONE_CLASSES && rb->opt_fuse &&
         rb->S <= INT32_MAX - RB_MAX_BATCH && (rb->row_vec + TILE_UNIT - 1) / TILE_UNIT <= INT32_MAX / 2 / RB_MAX_BATCH)
         return STEP_ONE;

@@ -184,3 +184,24 @@ def test_single_launch_with_few_classes(eviction, classes, most, selection):
         if c <= 4096:
             assert rb.rb_query_launches(h, 4096, c, 100) == (rb.RB_OK, 1 if c <= most else 2), c
     rb.rb_destroy(h)
+
+
+# Many classes: the single launch reads all fill counts in many workgroups.  Shapes next to the crossing that was measured, on
+# both sides of it (what lies far from it on either side is in the same list).
+@pytest.mark.parametrize("storage,selection,classes,c,r,launches", [
+    (0, 0, 2000, 5, 5, 1), (0, 0, 4000, 5, 5, 1), (0, 0, 6000, 5, 5, 2), (0, 0, 6000, 30, 30, 1), (0, 0, 8000, 30, 30, 2),
+    (0, 0, 6000, 109, 29, 1), (0, 0, 7832, 109, 29, 2), (0, 0, 8000, 200, 200, 1), (0, 0, 10000, 200, 200, 2), (0, 0, 10240, 400, 400, 1),
+    (0, 1, 6000, 5, 5, 1), (0, 1, 8000, 5, 5, 2), (0, 1, 8000, 109, 29, 1), (0, 1, 10000, 109, 29, 2), (0, 1, 10240, 200, 200, 1),
+    (1, 0, 2000, 5, 5, 1), (1, 0, 6000, 5, 5, 2), (1, 0, 8000, 30, 30, 2), (1, 0, 8000, 200, 200, 1), (1, 0, 10240, 400, 400, 1),
+    (1, 1, 6000, 5, 5, 1), (1, 1, 10000, 109, 29, 2),
+    (2, 0, 2000, 5, 5, 1), (2, 0, 6000, 5, 5, 2), (2, 0, 6000, 30, 30, 2), (2, 0, 6000, 200, 200, 2), (2, 0, 8000, 400, 400, 2),
+    (2, 0, 4000, 200, 200, 1), (2, 0, 4000, 400, 400, 1), (2, 0, 9700, 1000, 1000, 1),
+    (2, 1, 8000, 5, 5, 2), (2, 1, 6000, 30, 30, 1), (2, 1, 10000, 30, 30, 2), (2, 1, 10240, 400, 400, 1),
+    (0, 0, 10241, 1000, 1000, 2), (0, 1, 10241, 1000, 1000, 2),
+])
+def test_single_launch_with_many_classes(storage, selection, classes, c, r, launches):
+    import paper_2406_03285_amd as rb
+    rc, h = rb.rb_create(classes, 10, (784,), rb.RB_F32)
+    assert rb.rb_set_storage(h, storage) == rb.RB_OK and rb.rb_set_policy(h, selection, 0) == rb.RB_OK
+    assert rb.rb_query_launches(h, 4096, c, r) == (rb.RB_OK, launches)
+    rb.rb_destroy(h)
