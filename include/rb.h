@@ -206,7 +206,8 @@ int rb_sample_augment(rb_buffer *rb, int64_t r, uint64_t seed, uint64_t step,
  * and up to 10240 classes when the rows are not too many bytes, both halves run
  * as ONE kernel launch (a representative whose slot is being written in this very step is copied from
  * the mini-batch row stored there); otherwise the two kernels are enqueued one
- * after the other.  out_x must not overlap batch_x.
+ * after the other, as they are when out_y lies over batch_y (the labels are
+ * read before they are replaced).  out_x must not overlap batch_x.
  */
 int rb_update_sample(rb_buffer *rb, const void *batch_x, const int64_t *batch_y, int64_t b, int64_t c,
                      int64_t r, uint64_t seed, uint64_t step, void *out_x, int64_t *out_y);

@@ -106,6 +106,11 @@ void* scratch_ptr[MAX_DEVICES] = {};          // device address of `scratch` on 
 rb_buffer* scratch_holder[MAX_DEVICES] = {};  // the handle that is bound to it
 
 inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
+inline bool overlap(const void* p, int64_t p_bytes, const void* q, int64_t q_bytes)
+{
+    const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
+    return a < b + (uintptr_t)q_bytes && b < a + (uintptr_t)p_bytes;
+}
 inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // How rb_update_sample_many carries out a call: step by step, or several steps per launch planned by one workgroup per
@@ -1472,7 +1477,11 @@ int rb_update_sample(rb_buffer* rb, const void* batch_x, const int64_t* batch_y,
         return step_planned(rb, batch_x, batch_y, b, c, r, seed, step, out_x, out_y, next_y);
     if (big && (rb->plan_valid || next_y))
         return step_big(rb, batch_x, batch_y, b, c, r, seed, step, out_x, out_y, next_y);
-    const int form = step_form(rb, c, r);
+    // (results that lie over the mini-batch: a single launch would write them while it still reads it)
+    const int64_t bx = b * rb->sample_bytes, by = b * (int64_t)sizeof(int64_t), ox = r * rb->sample_bytes, oy = r * (int64_t)sizeof(int64_t);
+    const bool apart = !overlap(out_y, oy, batch_y, by) && !overlap(out_x, ox, batch_x, bx) && !overlap(out_y, oy, batch_x, bx) &&
+                       !overlap(out_x, ox, batch_y, by);
+    const int form = apart ? step_form(rb, c, r) : STEP_TWO;
     if (form == STEP_ONE) return step_one(rb, batch_x, batch_y, b, c, r, seed, step, out_x, out_y);
     if (form == STEP_TWO) {
         const int rc = rb_update(rb, batch_x, batch_y, b, c, seed, step);

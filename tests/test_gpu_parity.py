@@ -174,6 +174,32 @@ def test_single_call_without_a_plan_drops_and_flags_bad_labels():
     compare_buffers(buf, orc, "bad labels, single call")
 
 
+@pytest.mark.parametrize("policy", ["exact-uniform", "exact-fifo", "bernoulli-reservoir"])
+@pytest.mark.parametrize("c,r", [(200, 70), (40, 64)])          # shapes of the single launches when the results lie elsewhere
+def test_single_call_may_replace_the_labels_of_the_mini_batch(c, r, policy):
+    rb = _rb()
+    K, S, b = 90, 3, 300
+    buf = rb.RehearsalBuffer(K, S, (64,), torch.float32)
+    orc = rbo.Buffer(K, S, 256)
+    if policy in POLICIES:
+        buf.set_policy(*POLICIES[policy])
+        orc.set_policy(*POLICIES[policy])
+    assert rb.rb_query_launches(buf.handle, b, c, r) == (rb.RB_OK, 1)
+    x = torch.randn((b, 64), device="cuda:0")
+    out_x = torch.zeros((r, 64), device="cuda:0")
+    for step in range(6):
+        y = torch.randint(0, K, (b,), device="cuda:0")
+        hy = y.cpu().numpy()
+        buf.update_sample(x, y, c, r, 5, step, out_x, y[7:7 + r])
+        hx = x.cpu().numpy().view(np.uint8).reshape(b, 256)
+        orc.update(hx, hy, c, 5, step)
+        n, want_x, want_y = orc.sample_augment(r, 5, step, out_x=np.zeros((r, 256), dtype=np.uint8))
+        got = y.cpu().numpy()
+        assert np.array_equal(got[7:7 + r], want_y) and np.array_equal(got[:7], hy[:7]) and np.array_equal(got[7 + r:], hy[7 + r:])
+        assert np.array_equal(out_x.cpu().numpy().view(np.uint8).reshape(r, 256)[:n], want_x[:n])
+    compare_buffers(buf, orc, "labels replaced")
+
+
 def test_policy_cannot_change_after_an_update():
     rb = _rb()
     w = wl.C1
