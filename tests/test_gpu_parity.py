@@ -54,7 +54,7 @@ def test_full_size_workloads(w):
 def test_c5_with_one_fixed_set_of_active_classes():
     """C5's shape with the same 50 active classes in every step: they are full after about 50 steps, then every
     step overwrites about 20 slots of each and several candidates share a slot (the configured C5, whose active
-    classes change every step, never fills a class).  The two general kernels, all 500 steps."""
+    classes change every step, never fills a class).  The two calls, all 500 steps."""
     buf, orc = run_parity(wl.C5F, steps=wl.C5F.steps, progress=100)
     assert int((orc.fill == wl.C5F.S).sum()) == 50
 
@@ -74,7 +74,7 @@ def test_c3_on_a_side_stream():
     (wl.variant(wl.C1, name="C1-one-class", K=1, S=7, c=16, r=16), 40),        # every representative competes with this step's writes
     (wl.variant(wl.C1, name="C1-r-large", S=3, c=16, r=64, b=64), 40),         # r above what is stored for a while, then r = F
     (wl.variant(wl.C2, name="C2-odd-b", b=77, c=33, r=21, S=2), 60),           # odd b: LDS table alignment
-    (wl.variant(wl.C5, name="C5-fallback", K=2000, S=4, shape=(64,), b=256, c=100, r=30), 20),   # not eligible: two launches
+    (wl.variant(wl.C5, name="C5-any-counts", K=2000, S=4, shape=(64,), b=256, c=100, r=30), 20),   # counts beyond a wavefront, more classes: one launch too
 ])
 def test_single_call_primitive(w, steps):
     run_parity(w, steps=steps, check_state_every=max(1, steps // 4), single_call=True)
@@ -116,24 +116,33 @@ def test_policy_variant_through_the_single_call_and_at_full_size():
 
 
 # The single call without a plan: small counts (one launch, any strategy and storage form) and the shapes beyond them.
+# launches: what the call has to take, (exact, Bernoulli selection) where they differ.
 @pytest.mark.parametrize("policy", ["exact-uniform"] + sorted(POLICIES))
-@pytest.mark.parametrize("K,S,vecs,b,c,r,store,labels", [
-    (10, 3, 64, 40, 9, 12, "bf16", "uniform"),              # both counts within a wavefront, classes fill at once
-    (300, 4, 133, 200, 64, 64, "u8", "zipf"),               # the last counts one wavefront selects; ragged rows
-    (300, 4, 133, 200, 65, 63, "same", "zipf"),             # ... and the first ones the workgroup does
-    (2, 700, 1, 4096, 4096, 4096, "same", "uniform"),       # every count at its limit, ~2048 class-mates, one vector per row
-    (1, 37, 4, 1100, 1024, 1025, "bf16", "uniform"),        # one class: thousands of rivals, r above what is stored
-    (1024, 9, 192, 1025, 500, 128, "u8", "active50"),       # ~10 class-mates, more positions than threads
-    (10240, 2, 64, 300, 90, 200, "same", "uniform"),        # most classes this launch serves
-    (10241, 2, 64, 300, 90, 200, "same", "uniform"),        # one more: two launches
-    (1025, 6, 9408, 64, 8, 8, "same", "uniform"),           # long rows: several tiles per row
-    (50, 5, 1176, 1000, 700, 900, "bf16", "zipf"),          # more tiles than wavefronts: they take several each
+@pytest.mark.parametrize("K,S,vecs,b,c,r,store,labels,launches", [
+    (10, 3, 64, 40, 9, 12, "bf16", "uniform", 1),           # both counts within a wavefront, classes fill at once
+    (300, 4, 133, 200, 64, 64, "u8", "zipf", 1),            # the last counts one wavefront selects; ragged rows
+    (300, 4, 133, 200, 65, 63, "same", "zipf", 1),          # ... and the first ones the workgroup does
+    (2, 700, 1, 4096, 4096, 4096, "same", "uniform", 2),    # every count at its limit, ~2048 class-mates: two launches
+    (21, 70, 1, 4096, 4096, 4096, "same", "uniform", 1),    # ... ~195 class-mates, one vector per row: one
+    (1, 37, 4, 1100, 1024, 1025, "bf16", "uniform", 2),     # one class: thousands of rivals, r above what is stored
+    (1024, 9, 192, 1025, 500, 128, "u8", "active50", 1),    # ~10 class-mates, more positions than threads
+    (10240, 2, 64, 300, 90, 200, "same", "uniform", (2, 1)),    # most classes the one launch serves, where it pays
+    (10240, 2, 64, 700, 400, 450, "same", "uniform", 1),    # ... and with rows enough for either selection
+    (10241, 2, 64, 700, 400, 450, "same", "uniform", 2),    # one more
+    (1025, 6, 9408, 64, 8, 8, "same", "uniform", 1),        # long rows: several tiles per row
+    (300, 5, 300, 1000, 700, 900, "bf16", "zipf", 1),       # more tiles than wavefronts, three per row: reloaded, converted late
+    (50, 40, 130, 1000, 500, 500, "u8", "uniform", 1),      # ... in 8 bits
+    (200, 30, 500, 3000, 1500, 1500, "same", "uniform", 1), # ... rows of one tile of eight vectors per lane
+    (50, 5, 1176, 1000, 700, 900, "bf16", "zipf", 2),       # rows that take too long to move for one launch
 ])
-def test_single_call_without_a_plan(K, S, vecs, b, c, r, store, labels, policy):
+def test_single_call_without_a_plan(K, S, vecs, b, c, r, store, labels, launches, policy):
+    rb = _rb()
     shape = (vecs * {"same": 4, "bf16": 8, "u8": 16}[store],)       # vecs: 16-byte vectors of a stored row
     w = wl.Workload(f"one-K{K}-b{b}-c{c}-r{r}-{store}", 9, K, S, shape, "f32", b, c, r, 4, "uniform", labels)
-    run_parity(w, check_state_every=2, single_call=True, policy=POLICIES.get(policy),
-               store_bf16=store == "bf16", store_u8=store == "u8")
+    buf, _ = run_parity(w, check_state_every=2, single_call=True, policy=POLICIES.get(policy),
+                        store_bf16=store == "bf16", store_u8=store == "u8")
+    want = launches if isinstance(launches, int) else launches[policy.startswith("bernoulli")]
+    assert rb.rb_query_launches(buf.handle, b, c, r) == (rb.RB_OK, want)
 
 
 # ... with more candidates of a class than a wavefront has lanes: as many as the single launch takes with few classes, and skewed labels.
@@ -378,8 +387,7 @@ def test_8_bit_storage_decides_every_value_like_the_oracle_with_large_counts(mon
 
 @pytest.mark.parametrize("style", ["single", "ahead", "many", "many-announced", "fifo-bernoulli"])
 def test_8_bit_storage_through_every_call_form(style):
-    """The 8-bit form is served by the general kernels, the plan-ahead steps and the several-steps launches; the bytes are
-    the oracle's in every call form."""
+    """The 8-bit form is served by every launch form; the bytes are the oracle's in every call form."""
     w = wl.variant(wl.C4, name=f"C4-u8-{style}", S=8, shape=(3, 32, 32), dtype="f32", b=128, c=40, r=40)
     if style == "single":
         run_parity(w, steps=40, store_u8=True, single_call=True)
@@ -928,7 +936,7 @@ def test_many_steps_drop_and_flag_bad_labels(planners):
 
 @pytest.mark.parametrize("w,steps", [
     (wl.variant(wl.C2, name="C2-pipeline", S=6), 60),                                      # fused single launch
-    (wl.variant(wl.C5, name="C5-pipeline", K=300, S=12, shape=(256,), b=512, c=200, r=150), 25),   # two general kernels
+    (wl.variant(wl.C5, name="C5-pipeline", K=300, S=12, shape=(256,), b=512, c=200, r=150), 25),   # counts beyond a wavefront, also one launch
 ], ids=["small", "general"])
 def test_pipelined_primitive_returns_the_previous_iterations_representatives(w, steps):
     """Iteration t trains on the representatives that iteration t-1 started to collect, while the
@@ -1162,7 +1170,7 @@ def test_rows_in_pinned_host_memory(single):
 # ------------------------------------------------------ random configurations ---
 
 def _random_workload(rng, i):
-    big = rng.random() < 0.3                                  # sometimes large counts (general kernels)
+    big = rng.random() < 0.3                                  # sometimes large counts
     b = int(rng.integers(1, 4097 if big else 200))
     c = int(rng.integers(0, b + 1)) if rng.random() < 0.7 else int(min(b, rng.integers(0, 65)))
     r = int(rng.integers(0, 4097 if big else 130))
