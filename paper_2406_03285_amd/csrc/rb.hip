@@ -1148,11 +1148,7 @@ int step_one(rb_buffer* rb, const void* batch_x, const int64_t* batch_y, int64_t
         rows = std::min(b, c + slack);
     }
     constexpr int64_t CUS = 256;                // one workgroup per compute unit, dealt to the two sides by their rows
-    // (a representatives' workgroup plans its whole share at once: at most ONE_PLANNED - 2 whole rows and two parts of one.  Dealt by
-    // their rows alone no workgroup of 4096 + 4096 rows has more than 33)
-    const int64_t least_r = (r + ONE_PLANNED - 3) / (ONE_PLANNED - 2);
-    const int64_t most_r = std::min<int64_t>(CUS - 1, std::max<int64_t>(least_r, (CUS * r + (rows + r) / 2) / (rows + r)));
-    static_assert((RB_MAX_BATCH + ONE_PLANNED - 3) / (ONE_PLANNED - 2) < CUS, "room for the candidates' workgroups");
+    const int64_t most_r = std::min<int64_t>(CUS - 1, std::max<int64_t>(1, (CUS * r + (rows + r) / 2) / (rows + r)));
     // (rows that are converted: small tiles.  612 + 625 rows of 11.5 KB in 8 bits 15.6 us with one vector per lane, 17.8 with two,
     // 20.5 with four; as bfloat16 13.9, 12.9 with two, 14.2)
     int limit = rb->storage == RB_STORE_U8 ? 1 : rb->storage == RB_STORE_BF16 ? 2 : 8;

@@ -14,7 +14,7 @@ constexpr int ONE_PER = RB_MAX_BATCH / ONE_TPB;     // mini-batch positions, can
 constexpr int ONE_CLASSES = 10240;                  // most classes: their fill counts are kept in LDS
 constexpr int ONE_FILL_PER = (ONE_CLASSES / 4 + ONE_TPB - 1) / ONE_TPB;    // vectors of four fill counts per thread
 constexpr int ONE_PACE = 64;                        // stores of a tile go out in one burst (paced ones measured 0.4 us slower)
-constexpr int ONE_PLANNED = 64;                     // rows a workgroup plans at a time (a share of representatives has fewer)
+constexpr int ONE_PLANNED = 64;                     // rows a workgroup plans at a time
 constexpr int ONE_LIST = 4 * WAVE;                  // the candidate list and the draws are read this many at a time
 constexpr int ONE_POS_BITS = 12;                    // candidate list: class << ONE_POS_BITS | mini-batch position
 constexpr uint32_t ONE_NO_CLASS = 0xFFFFFFFFu;      // ... of a candidate whose label is outside [0, K), and behind the list's end
@@ -375,7 +375,6 @@ __global__ void __launch_bounds__(ONE_TPB) rb_step_one_kernel(const OneArgs sa)
         classes();
         it = lo + wave;
         bool loaded = true;
-        // (one round, unless the coins of the Bernoulli selection gave many more candidates than the grid was sized for)
         for (int row = lo / a.tpr; row * a.tpr < hi; row += ONE_PLANNED) {
             const int end = min((hi + a.tpr - 1) / a.tpr, row + ONE_PLANNED);
             for (int i = row + wave; i < end; i += ONE_NWAVE) {
@@ -455,72 +454,75 @@ __global__ void __launch_bounds__(ONE_TPB) rb_step_one_kernel(const OneArgs sa)
     // ---- representative movers ----
     const int lo = (int)blockIdx.x * sa.share, hi = min(lo + sa.share, r * sa.tpr);
     int it = lo + wave;
-    const int row = lo / sa.tpr, end = (hi + sa.tpr - 1) / sa.tpr;      // at most ONE_PLANNED rows: step_one
-    for (int j = row + wave; j < end; j += ONE_NWAVE) {
-        if (j >= n) {                      // fewer stored samples than asked for
-            if (lane == 0) s_slot[j - row] = -1;
-            continue;
-        }
-        // draw j is replaced by base + j iff an earlier draw had the same value, or it equals
-        // base + q for an earlier q whose own draw was replaced
-        int cur = j;
-        bool taken = false;
-        for (;;) {
-            const uint32_t tc = s_t[cur];
-            bool same = false;
-            for (int q0 = 0; q0 < cur; q0 += ONE_LIST) {
-                uint32_t v[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) v[u] = s_t[q0 + u * WAVE + lane];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) same |= q0 + u * WAVE + lane < cur && v[u] == tc;
+    for (int row = lo / sa.tpr; row * sa.tpr < hi; row += ONE_PLANNED) {
+        const int end = min((hi + sa.tpr - 1) / sa.tpr, row + ONE_PLANNED);
+        for (int j = row + wave; j < end; j += ONE_NWAVE) {
+            if (j >= n) {                      // fewer stored samples than asked for
+                if (lane == 0) s_slot[j - row] = -1;
+                continue;
             }
-            if (__ballot(same) != 0) { taken = true; break; }
-            const int q = __builtin_amdgcn_readfirstlane((int)tc) - base;
-            if (q < 0 || q >= cur) break;
-            cur = q;
+            // draw j is replaced by base + j iff an earlier draw had the same value, or it equals
+            // base + q for an earlier q whose own draw was replaced
+            int cur = j;
+            bool taken = false;
+            for (;;) {
+                const uint32_t tc = s_t[cur];
+                bool same = false;
+                for (int q0 = 0; q0 < cur; q0 += ONE_LIST) {
+                    uint32_t v[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) v[u] = s_t[q0 + u * WAVE + lane];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) same |= q0 + u * WAVE + lane < cur && v[u] == tc;
+                }
+                if (__ballot(same) != 0) { taken = true; break; }
+                const int q = __builtin_amdgcn_readfirstlane((int)tc) - base;
+                if (q < 0 || q >= cur) break;
+                cur = q;
+            }
+            const int g = taken ? base + j : __builtin_amdgcn_readfirstlane((int)s_t[j]);     // class-major number of the sample
+            // the stretch of classes that holds it (the last one that starts at or before it), then the class
+            constexpr int STEP = ONE_TPB / WAVE;
+            const int big = __popcll(__ballot(s_before[STEP * lane] <= g)) - 1;
+            const int owner = STEP * big + __popcll(__ballot(lane < STEP && s_before[STEP * big + (lane & (STEP - 1))] <= g)) - 1;
+            const int gl = g - __builtin_amdgcn_readfirstlane(s_before[owner]);
+            const int kl = owner * per + lane;
+            const int held = lane < per && kl < nfill ? min(s_fill[kl], cap) : 0;
+            const int hincl = wave_scan_incl(held);
+            const int u = __popcll(__ballot(lane < per && hincl <= gl));
+            const int pk = owner * per + u, ps = gl - (lane_read(hincl, u) - lane_read(held, u));
+            const int fwd = one_writer(a, s_kx, m, pk, ps, s_fill[pk], pend, cm, cmpre);
+            if (lane == 0) {
+                s_slot[j - row] = ps;
+                s_class[j - row] = pk;
+                s_fwd[j - row] = fwd;
+            }
         }
-        const int g = taken ? base + j : __builtin_amdgcn_readfirstlane((int)s_t[j]);     // class-major number of the sample
-        // the stretch of classes that holds it (the last one that starts at or before it), then the class
-        constexpr int STEP = ONE_TPB / WAVE;
-        const int big = __popcll(__ballot(s_before[STEP * lane] <= g)) - 1;
-        const int owner = STEP * big + __popcll(__ballot(lane < STEP && s_before[STEP * big + (lane & (STEP - 1))] <= g)) - 1;
-        const int gl = g - __builtin_amdgcn_readfirstlane(s_before[owner]);
-        const int kl = owner * per + lane;
-        const int held = lane < per && kl < nfill ? min(s_fill[kl], cap) : 0;
-        const int hincl = wave_scan_incl(held);
-        const int u = __popcll(__ballot(lane < per && hincl <= gl));
-        const int pk = owner * per + u, ps = gl - (lane_read(hincl, u) - lane_read(held, u));
-        const int fwd = one_writer(a, s_kx, m, pk, ps, s_fill[pk], pend, cm, cmpre);
-        if (lane == 0) {
-            s_slot[j - row] = ps;
-            s_class[j - row] = pk;
-            s_fwd[j - row] = fwd;
+        lds_barrier();
+        for (; it < min(hi, end * sa.tpr); it += ONE_NWAVE) {
+            const int j = it / sa.tpr, tile = it - j * sa.tpr;
+            const int ps = __builtin_amdgcn_readfirstlane(s_slot[j - row]);
+            if (ps < 0) {
+                if (tile == 0 && lane == 0) sa.out_y[j] = -1;
+                continue;
+            }
+            const int pk = __builtin_amdgcn_readfirstlane(s_class[j - row]), fwd = __builtin_amdgcn_readfirstlane(s_fwd[j - row]);
+            tile_bounds(tile, sa.tile_vec, sa.tile_rem, a.row_vec, v_lo, v_hi);
+            vec16* dst = sa.out_x + (int64_t)j * a.row_vec * WIDE;
+            if (ST != RB_STORE_SAME && fwd >= 0) {
+                // from the mini-batch: what the slot will hold is the row in its stored form
+                Tile<U, NT, WAVE, ONE_PACE, stored_cv(ST, CV_BOTH)> o;
+                o.load(a.batch_x + (int64_t)fwd * a.row_vec * WIDE, v_lo, v_hi);
+                o.store(dst, v_lo, v_hi);
+            } else {
+                const vec16* src = fwd >= 0 ? a.batch_x + (int64_t)fwd * a.row_vec : a.buf_x + ((int64_t)pk * a.S + ps) * a.row_vec;
+                Tile<U, NT, WAVE, ONE_PACE, stored_cv(ST, CV_WIDEN)> o;
+                o.load(src, v_lo, v_hi);
+                o.store(dst, v_lo, v_hi);
+            }
+            if (tile == 0 && lane == 0) { sa.out_y[j] = pk; count_moved(a.state); }
         }
-    }
-    lds_barrier();
-    for (; it < hi; it += ONE_NWAVE) {
-        const int j = it / sa.tpr, tile = it - j * sa.tpr;
-        const int ps = __builtin_amdgcn_readfirstlane(s_slot[j - row]);
-        if (ps < 0) {
-            if (tile == 0 && lane == 0) sa.out_y[j] = -1;
-            continue;
-        }
-        const int pk = __builtin_amdgcn_readfirstlane(s_class[j - row]), fwd = __builtin_amdgcn_readfirstlane(s_fwd[j - row]);
-        tile_bounds(tile, sa.tile_vec, sa.tile_rem, a.row_vec, v_lo, v_hi);
-        vec16* dst = sa.out_x + (int64_t)j * a.row_vec * WIDE;
-        if (ST != RB_STORE_SAME && fwd >= 0) {
-            // from the mini-batch: what the slot will hold is the row in its stored form
-            Tile<U, NT, WAVE, ONE_PACE, stored_cv(ST, CV_BOTH)> o;
-            o.load(a.batch_x + (int64_t)fwd * a.row_vec * WIDE, v_lo, v_hi);
-            o.store(dst, v_lo, v_hi);
-        } else {
-            const vec16* src = fwd >= 0 ? a.batch_x + (int64_t)fwd * a.row_vec : a.buf_x + ((int64_t)pk * a.S + ps) * a.row_vec;
-            Tile<U, NT, WAVE, ONE_PACE, stored_cv(ST, CV_WIDEN)> o;
-            o.load(src, v_lo, v_hi);
-            o.store(dst, v_lo, v_hi);
-        }
-        if (tile == 0 && lane == 0) { sa.out_y[j] = pk; count_moved(a.state); }
+        if (end * sa.tpr < hi) lds_barrier();
     }
 
     // ---- books: new fill counts, their sums per chunk, the strategy's state (a chunk per wavefront, dealt over the workgroups) ----
