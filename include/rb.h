@@ -123,12 +123,11 @@ int rb_set_storage(rb_buffer *rb, int32_t storage);
  * offered to a full class replaces a uniformly drawn slot with probability
  * slots_per_class / n and is dropped otherwise (exact while a class has been
  * offered fewer than 2^31 - 1 samples).
- * Every variant is served by rb_update_sample.
- * The plan-ahead forms of the single launch (rb_announce_next) serve every variant (the Bernoulli selection for b <= 1024), and so do the
- * several-steps launches of rb_update_sample_many (the form for small counts
- * with the exact selection only; the form for large counts takes over for the
- * Bernoulli selection, again for b <= 1024).  RB_EINVAL: unknown value.  RB_ESTATE: an rb_update was already
- * enqueued since the last rb_bind.
+ * Every variant is served by every call, the Bernoulli selection by the
+ * plan-ahead forms of the single launch (rb_announce_next) and by the
+ * several-steps launches of rb_update_sample_many (the form for large counts)
+ * for b <= 1024.  RB_EINVAL: unknown value.  RB_ESTATE: an rb_update was
+ * already enqueued since the last rb_bind.
  */
 enum rb_selection { RB_SELECT_EXACT = 0, RB_SELECT_BERNOULLI = 1 };
 enum rb_eviction { RB_EVICT_UNIFORM = 0, RB_EVICT_FIFO = 1, RB_EVICT_RESERVOIR = 2 };
@@ -201,11 +200,14 @@ int rb_sample_augment(rb_buffer *rb, int64_t r, uint64_t seed, uint64_t step,
  * step 2: update the buffer with the mini-batch, then sample the next
  * representatives): rb_update(rb, batch_x, batch_y, b, c, seed, step) followed
  * by rb_sample_augment(rb, r, seed, step, out_x, out_y), as one call with the
- * same arguments, meaning, errors and, bit for bit, the same results.  With
- * 1 <= c, r <= 64, up to 1024 classes and the exact selection, and with c, r >= 1
- * and up to 10240 classes when the rows are not too many bytes, both halves run
- * as ONE kernel launch (a representative whose slot is being written in this very step is copied from
- * the mini-batch row stored there); otherwise the two kernels are enqueued one
+ * same arguments, meaning, errors and, bit for bit, the same results.  Both
+ * halves run as ONE kernel launch (a representative whose slot is being written
+ * in this very step is copied from the mini-batch row stored there) with
+ * 1 <= c, r <= 64, up to 1024 classes and the exact selection, and beyond that,
+ * for c, r >= 1 and up to 10240 classes, where it is the faster form:
+ * while (c + r) * (sample + stored row bytes) is below 77 MB (30 MB with bfloat16
+ * storage, 11 MB in 8 bits) and classes are neither many for few rows nor few
+ * for many candidates (rb_query_launches tells).  Otherwise the two kernels are enqueued one
  * after the other, as they are when out_y lies over batch_y (the labels are
  * read before they are replaced).  out_x must not overlap batch_x.
  */

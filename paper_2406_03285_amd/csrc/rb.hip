@@ -1,8 +1,8 @@
 // Rehearsal-buffer hot path for gfx950 (MI355X): the C ABI of include/rb.h (host side); the
 // kernels are in rb_kernels_small.h (at most 64 candidates / representatives, and the
 // single-launch step), rb_kernels_planned.h (the same step with its plan made during the previous
-// launch), rb_kernels_general.h (any counts, policy variants, reduced-precision storage) and
-// rb_kernels_aux.h, their common device code in rb_device.h.
+// launch), rb_kernels_one.h (the single launch for any counts), rb_kernels_general.h (two launches, any counts) and
+// rb_kernels_aux.h, their common device code in rb_device.h.  Every form serves every replacement strategy and storage form.
 //
 // One kernel launch per hot call.  Every workgroup first re-derives, in LDS,
 // the few integers of the step's plan it needs (which mini-batch positions are
@@ -127,8 +127,11 @@ struct Shape {
 // WAVE in the general ones (a wavefront per tile).
 // (With 8-bit storage a vector stands for four accesses of a thread, so one may be enough in flight: `few` is the number of
 // tiles below which two become one.  Measured on MI355X, one vector per thread against two: update and sampling in one launch,
-// 8 + 8 rows of 602 KB (592 and 304 tiles) 6.9 : 6.4 us, 32 + 32 rows of 49 KB (192 and 128 tiles) 6.0 : 6.4; in two launches
-// 32 + 32 rows of 602 KB (1184 and 608 tiles each) 14.7 : 15.7, 64 + 64 26.5 : 23.3.)
+// 8 + 8 rows of 602 KB (592 and 304 tiles) 6.9 : 6.4 us, 32 + 32 rows of 49 KB (192 and 128 tiles) 6.0 : 6.4, hence `few` = 256
+// there; in two launches 32 + 32 rows of 602 KB (1184 and 608 tiles each) 14.7 : 15.7, 64 + 64 26.5 : 23.3; planned one step ahead,
+// where nothing precedes the rows, 8 + 8 rows of 602 KB 6.2 : 8.5, 8 + 8 of 192 KB 5.5 : 7.7, 16 + 16 of 49 KB 5.6 : 6.9, 64 + 64 of
+// 12 KB 9.4 : 9.5; the same for large counts 100 + 100 rows of 12 KB 6.5 : 8.1, of 49 KB 7.7 : 10.1, 300 + 300 of 49 KB, 1200
+// tiles and two vectors either way, 15.4.)
 // most: the most vectors per thread the caller's kernel can hold (the converting movers hold several accesses per
 // vector); preferred: what the caller's kernel does best with, taken when the option leaves the choice open.
 Shape plan_shape(const rb_buffer* rb, int64_t rows, int width, int most = 8, int preferred = 0, int64_t few = 1024)
@@ -1069,12 +1072,15 @@ bool small_counts(const rb_buffer* rb, int64_t c, int64_t r)
 // How rb_update_sample carries out a step that is not planned ahead: STEP_SMALL (rb_step_small_kernel), STEP_ONE
 // (rb_step_one_kernel) or STEP_TWO (the two kernels of rb_update and rb_sample_augment).
 // STEP_ONE as long as the fill counts fit LDS, work items and a class's count with a step's candidates on top (not yet cut
-// off at the capacity) are counted in 32 bits, and the rows are moved soon enough: with one workgroup of planners and movers per compute unit long rows move slower than in the general
-// kernels, rows that are converted most of all.  Measured on MI355X, one launch against two (in brackets the time the rows
-// take at 5.5 TB/s): as they are, 300 + 300 rows of 12 KB [2.7 us] 10.2 : 11.7, 200 + 200 of 49 KB [7.2] 14.3 : 15.8,
-// 100 + 100 of 192 KB [14.0] 21.5 : 22.1, 40 + 66 of 602 KB [23] 30.9 : 27.7; as bfloat16 200 + 200 of 49 KB [5.4] 13.3 : 13.9,
-// 66 + 200 of 80 KB [5.8] 13.7 : 13.4, 200 + 200 of 192 KB [21] 31.0 : 29.0; in 8 bits 70 + 70 of 49 KB [1.6] 9.6 : 10.3,
-// 300 + 300 of 12 KB [1.7] 11.6 : 11.6, 200 + 200 of 49 KB [4.5] 16.2 : 14.0.
+// off at the capacity) are counted in 32 bits, and the rows are moved soon enough: with one workgroup of planners and movers per
+// compute unit long rows move slower than in the general kernels, rows that are converted most of all.  Measured on MI355X, one
+// launch against two, 300 classes (in brackets the time the rows take at 5.5 TB/s): as they are, 300 + 300 rows of 12 KB [2.7 us]
+// 10.0 : 11.4, 200 + 200 of 49 KB [7.2] 14.0 : 15.8, 100 + 100 of 192 KB [14.0] 21.3 : 22.1, 200 + 200 [27.9] 37.0 : 35.6, 40 + 66
+// of 602 KB [23] 30.7 : 27.6; as bfloat16 200 + 200 of 49 KB [5.4] 13.0 : 13.7, 66 + 200 of 80 KB [5.8] 13.7 : 13.4, 70 + 70 of
+// 192 KB [7.3] 15.1 : 14.9, 40 + 66 of 602 KB [17.4] 27.5 : 23.9, but 1000 + 1000 of 12 KB [6.7] 16.7 : 18.3; in 8 bits 70 + 70 of
+// 49 KB [1.6] 9.2 : 9.8, 300 + 300 of 12 KB [1.7] 11.2 : 11.1, 300 + 300 of 4 KB [0.6] 11.1 : 10.5, 1000 + 1000 of 4 KB [1.9]
+// 14.1 : 14.7, 200 + 200 of 49 KB [4.5] 15.7 : 13.9, with the Bernoulli selection 300 + 300 of 12 KB 11.2 : 11.5, 150 + 150 of 4 KB
+// 10.0 : 10.3.
 enum { STEP_TWO = 0, STEP_SMALL = 1, STEP_ONE = 2 };
 int step_form(const rb_buffer* rb, int64_t c, int64_t r)
 {

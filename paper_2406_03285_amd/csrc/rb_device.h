@@ -417,7 +417,7 @@ struct UpdateArgs {
     int32_t tile_vec;     // a row is split evenly into tpr tiles in units of TILE_UNIT vectors: the first
     int32_t tile_rem;     // tile_rem tiles hold tile_vec + 1 units, the others tile_vec; see tile_bounds
     int32_t rpb;          // small kernels: rows per mover workgroup (1 unless tpr == 1)
-    // policy variants (general kernel only)
+    // policy variants
     int32_t selection;    // RB_SELECT_*
     int32_t eviction;     // RB_EVICT_*
     int32_t cap;          // most candidates a step can have: c (exact selection) or b (Bernoulli)

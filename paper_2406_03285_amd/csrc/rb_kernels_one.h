@@ -1,5 +1,5 @@
 // rb_update_sample in ONE launch for shapes that rb_step_small_kernel does not serve: any candidate and representative
-// count, any selection and replacement strategy, any storage form, up to ONE_CLASSES classes, rows that are moved soon.
+// count, any selection and replacement strategy, any storage form, up to ONE_CLASSES classes, where step_form finds it faster.
 // Included by rb.hip only, after rb_kernels_small.h (whose wavefront selection it uses).
 #pragma once
 
@@ -215,10 +215,10 @@ __device__ __forceinline__ int one_writer(const UpdateArgs& a, const uint32_t* s
 // workgroup of 512 threads per compute unit (1024 threads: equal at 1024 + 1024 rows, 0.3 to 0.5 us slower at small
 // counts; 256: 2 to 3 us slower; two workgroups per unit: 0.1 to 0.4 us faster for few rows, 6 us slower for 1024 + 1024),
 // a row planned once per workgroup and not by every wavefront, and one list word per candidate.  Measured on MI355X against
-// the two general launches this replaces: 1024 + 1024 rows of 8 KB of 10000 classes 16.3 : 17.0 us; Bernoulli selection with
-// reservoir replacement, 90 + 75 rows of 49 KB kept as bfloat16, 9.3 : 10.9; 6 + 5 rows of 393 KB in 8 bits, Bernoulli,
-// 8.2 : 14.5; 185 + 121 rows of 13 KB in 8 bits of 5654 classes 11.4 : 17.8; 4 + 5 rows of 5 KB of 3179 classes 7.4 : 8.0.
-// (Rows of more bytes stay with the two launches: rb_update_sample.)
+// the two launches this replaced: 1024 + 1024 rows of 8 KB of 10000 classes 16.1 : 17.1 us; Bernoulli selection with
+// reservoir replacement, 90 + 75 rows of 49 KB kept as bfloat16, 9.2 : 10.5; 20 + 20 rows of 49 KB in 8 bits, Bernoulli,
+// 8.4 : 14.5; 300 + 300 rows of 12 KB of 300 classes 10.0 : 11.7, in 8 bits 11.5 : 15.9; 5 + 5 rows of 3 KB of 2000 classes 6.6 : 7.2.
+// (Where the two launches are the faster form: step_form.)
 //
 // LDS (dynamic): s_fill[nchunks * CH] i32, s_before[ONE_TPB] i32, per wavefront pend u16[WAVE], cm u32[ONE_WORDS],
 // cmpre u16[ONE_WORDS]; s_lab[b] u32, s_first[b] u32, s_kx[cap] u32, s_t[max(cap, r)] u32 (both
@@ -375,6 +375,7 @@ __global__ void __launch_bounds__(ONE_TPB) rb_step_one_kernel(const OneArgs sa)
         classes();
         it = lo + wave;
         bool loaded = true;
+        // (a second round only when the coins of the Bernoulli selection gave many times the candidates the grid was sized for)
         for (int row = lo / a.tpr; row * a.tpr < hi; row += ONE_PLANNED) {
             const int end = min((hi + a.tpr - 1) / a.tpr, row + ONE_PLANNED);
             for (int i = row + wave; i < end; i += ONE_NWAVE) {
@@ -454,6 +455,8 @@ __global__ void __launch_bounds__(ONE_TPB) rb_step_one_kernel(const OneArgs sa)
     // ---- representative movers ----
     const int lo = (int)blockIdx.x * sa.share, hi = min(lo + sa.share, r * sa.tpr);
     int it = lo + wave;
+    // (one round for every count accepted: a share has at most 33 rows.  Written without the loop the same round measured 1 to 2 %
+    // slower with few rows: Bernoulli selection, 90 + 75 rows of 49 KB kept as bfloat16, 9.21 -> 9.5 us)
     for (int row = lo / sa.tpr; row * sa.tpr < hi; row += ONE_PLANNED) {
         const int end = min((hi + sa.tpr - 1) / sa.tpr, row + ONE_PLANNED);
         for (int j = row + wave; j < end; j += ONE_NWAVE) {
