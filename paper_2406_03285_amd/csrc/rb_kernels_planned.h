@@ -111,7 +111,7 @@ __device__ __forceinline__ void plan_step(const PlanArgs& a, uint32_t* lds)
     } else if (wave == 1) {
         if (lane < r) s_bits[lane] = draw64(a.sd, PURPOSE_SAMPLE, (uint32_t)lane);
     }
-    park_labels(yv, a.batch_y, b, a.K, s_y);
+    park_labels<true>(yv, a.batch_y, b, a.K, s_y);
     *reinterpret_cast<int4*>(s_old + 4 * tid) = fo;
     *reinterpret_cast<int4*>(s_aux + 4 * tid) = ao;
     *reinterpret_cast<int4*>(s_cnt + 4 * tid) = make_int4(0, 0, 0, 0);

@@ -8,8 +8,10 @@ namespace {
 
 constexpr int YPRE = 4;    // label loads per thread issued before anything else (covers b <= 1024)
 
-// Labels of the whole mini-batch into LDS (LAB_INVALID when outside [0, K)).  The
-// first YPRE per thread were requested earlier into yv[]; called by all threads.
+// Labels of the mini-batch into LDS (LAB_INVALID when outside [0, K)): the first
+// YPRE per thread, requested earlier into yv[], and (ALL) those beyond; called by
+// all threads.
+template <bool ALL>
 __device__ __forceinline__ void park_labels(const int64_t (&yv)[YPRE], const int64_t* __restrict__ batch_y,
                                             int b, int K, int32_t* s_y)
 {
@@ -23,10 +25,27 @@ __device__ __forceinline__ void park_labels(const int64_t (&yv)[YPRE], const int
         asm volatile("" : "+v"(y));
         if (q < b) s_y[q] = (y >= 0 && y < K) ? (int32_t)y : LAB_INVALID;
     }
+    if (!ALL) return;
     for (int q = tid + YPRE * TPB; q < b; q += TPB) {
         const int64_t y = batch_y[q];
         s_y[q] = (y >= 0 && y < K) ? (int32_t)y : LAB_INVALID;
     }
+}
+
+// Of a mini-batch larger than that only the candidates' labels are read, as soon as wavefront 0 has selected them (parking all
+// 4096 takes twelve more loads per thread, one after the other: 16 + 16 rows of 12 KB, FIFO, two calls 9.9 -> 8.1 us).
+__device__ __forceinline__ int64_t far_label(const UpdateArgs& a, bool active, int x)
+{
+    return active && x >= YPRE * TPB ? a.batch_y[x] : -1;
+}
+
+// Class of the lane's candidate (wavefront 0): parked, or far_label's y.
+__device__ __forceinline__ int32_t candidate_class(const UpdateArgs& a, bool active, int x, const int32_t* s_y, int64_t y)
+{
+    if (!active) return LAB_UNSELECTED;
+    if (x < YPRE * TPB) return s_y[x];
+    asm volatile("" : "+v"(y));
+    return y >= 0 && y < a.K ? (int32_t)y : LAB_INVALID;
 }
 
 // ---------------------------------------------------------------------------
@@ -146,7 +165,7 @@ __device__ __forceinline__ int64_t wave_place(const UpdateArgs& a, bool active, 
 // data.  Same grid and arguments as rb_update_kernel.
 //
 // LDS (dynamic): s_first[b] u32 (lowest lane that drew a value), s_y[b] i32
-// (label of every mini-batch position, LAB_INVALID when outside [0, K)).
+// (label of every mini-batch position below YPRE * TPB, LAB_INVALID when outside [0, K)).
 // ---------------------------------------------------------------------------
 template <int U, bool NT, int ST, bool AUX>     // ST: RB_STORE_*, the form binary32 samples are stored in; AUX: FIFO or reservoir replacement
 __global__ void __launch_bounds__(TPB) rb_update_small_kernel(const UpdateArgs a)
@@ -163,7 +182,7 @@ __global__ void __launch_bounds__(TPB) rb_update_small_kernel(const UpdateArgs a
     const bool w0 = tid < WAVE;
     const int b = a.b, c = a.c;
 
-    // all labels of the mini-batch: requested now, parked in LDS once the selection is done
+    // labels of the mini-batch: requested now, parked in LDS once the selection is done
     int64_t yv[YPRE];
 #pragma unroll
     for (int u = 0; u < YPRE; ++u) {
@@ -174,16 +193,20 @@ __global__ void __launch_bounds__(TPB) rb_update_small_kernel(const UpdateArgs a
     // wavefront 0: lane i computes candidate i of Floyd's emission order
     bool active = false;
     int x = 0;                       // its mini-batch position
-    if (w0) x = wave_select(a.sd, b, c, s_first, active);
+    int64_t yx = -1;                 // its label, if it lies beyond the parked ones
+    if (w0) {
+        x = wave_select(a.sd, b, c, s_first, active);
+        yx = far_label(a, active, x);
+    }
 
     if ((int)blockIdx.x < a.nchunks) {
         // ---- bookkeeping: fill_new = min(fill_old + candidates of the class, S) ----
-        park_labels(yv, a.batch_y, b, a.K, s_y);
+        park_labels<false>(yv, a.batch_y, b, a.K, s_y);
         const int k_lo = blockIdx.x * CH;
         s_hist[tid] = 0;
         __syncthreads();
         if (w0) {
-            const int32_t k = active ? s_y[x] : LAB_UNSELECTED;
+            const int32_t k = candidate_class(a, active, x, s_y, yx);
             if (active && k >= k_lo && k < k_lo + CH) atomicAdd(&s_hist[k - k_lo], 1);
             if (blockIdx.x == 0 && __ballot(active && k == LAB_INVALID) != 0 && lane == 0)
                 atomicOr(&a.state->flags, RB_FLAG_BAD_LABEL);
@@ -225,10 +248,10 @@ __global__ void __launch_bounds__(TPB) rb_update_small_kernel(const UpdateArgs a
         // arrived, and long before wavefront 0 has worked out where it goes.
         Tile<U, NT, TPB, step_pace(ST, U), stored_cv(ST, CV_NARROW), true> t;
         t.load(a.batch_x + (int64_t)p * a.row_vec * stored_wide(ST), v_lo, v_hi);
-        park_labels(yv, a.batch_y, b, a.K, s_y);
+        park_labels<false>(yv, a.batch_y, b, a.K, s_y);
         __syncthreads();
         if (w0) {
-            k = active ? s_y[x] : LAB_UNSELECTED;
+            k = candidate_class(a, active, x, s_y, yx);
             const int32_t ki = lane_read(k, i);
             const int64_t dst = wave_place<AUX>(a, active, x, k, i, p, ki);
             if (lane == 0) s_dst[0] = dst;
@@ -448,20 +471,22 @@ __global__ void __launch_bounds__(TPB) rb_step_small_kernel(const StepArgs sa)
     // wavefront 0 selects the candidates while wavefront 1 makes the random bits of the sampling draws
     bool active = false;
     int x = 0;
+    int64_t yx = -1;                // label of the lane's candidate, if it lies beyond the parked ones
     if (w0) {
         x = wave_select(a.sd, b, c, s_first, active);
+        yx = far_label(a, active, x);
     } else if (gather && tid < 2 * WAVE) {
         if (lane < sa.r) s_bits[lane] = draw64(a.sd, PURPOSE_SAMPLE, (uint32_t)lane);
     }
 
     if ((int)blockIdx.x < a.nchunks) {
         // ---- bookkeeping: fill_new = min(fill_old + candidates of the class, S) ----
-        park_labels(yv, a.batch_y, b, a.K, s_y);
+        park_labels<false>(yv, a.batch_y, b, a.K, s_y);
         const int k_lo = blockIdx.x * CH;
         s_hist[tid] = 0;
         __syncthreads();
         if (w0) {
-            const int32_t k = active ? s_y[x] : LAB_UNSELECTED;
+            const int32_t k = candidate_class(a, active, x, s_y, yx);
             if (active && k >= k_lo && k < k_lo + CH) atomicAdd(&s_hist[k - k_lo], 1);
             if (blockIdx.x == 0 && __ballot(active && k == LAB_INVALID) != 0 && lane == 0)
                 atomicOr(&a.state->flags, RB_FLAG_BAD_LABEL);
@@ -496,10 +521,10 @@ __global__ void __launch_bounds__(TPB) rb_step_small_kernel(const StepArgs sa)
         // requested as soon as the position is known, before the labels have arrived
         Tile<U, NT, TPB, step_pace(ST, U), stored_cv(ST, CV_NARROW), true> t;
         t.load(a.batch_x + (int64_t)p * a.row_vec * stored_wide(ST), v_lo, v_hi);
-        park_labels(yv, a.batch_y, b, a.K, s_y);
+        park_labels<false>(yv, a.batch_y, b, a.K, s_y);
         __syncthreads();
         if (w0) {
-            const int32_t k = active ? s_y[x] : LAB_UNSELECTED;
+            const int32_t k = candidate_class(a, active, x, s_y, yx);
             const int32_t ki = lane_read(k, i);
             const int64_t dst = wave_place<AUX>(a, active, x, k, i, p, ki);
             if (lane == 0) s_dst = dst;
@@ -519,12 +544,12 @@ __global__ void __launch_bounds__(TPB) rb_step_small_kernel(const StepArgs sa)
     int64_t v_lo, v_hi;
     tile_bounds(tile, a.tile_vec, a.tile_rem, a.row_vec, v_lo, v_hi);
 
-    park_labels(yv, a.batch_y, b, a.K, s_y);
+    park_labels<false>(yv, a.batch_y, b, a.K, s_y);
     *reinterpret_cast<int4*>(s_old + 4 * tid) = fo;
     *reinterpret_cast<int4*>(s_cnt + 4 * tid) = make_int4(0, 0, 0, 0);
     __syncthreads();
     if (w0) {
-        const int32_t k = active ? s_y[x] : LAB_UNSELECTED;
+        const int32_t k = candidate_class(a, active, x, s_y, yx);
         if (active && k >= 0) atomicAdd(&s_cnt[k], 1);
         // fill counts after this step's update, 16 consecutive classes per lane
         int fv[16];

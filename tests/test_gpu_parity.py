@@ -162,6 +162,25 @@ def test_single_call_without_a_plan_and_many_class_mates(K, S, vecs, b, c, r, st
     assert rb.rb_query_launches(buf.handle, b, c, r) == (rb.RB_OK, 1)
 
 
+# The small-count kernels park the first 1024 labels and read a candidate's own beyond: both sides of it, invalid labels included.
+@pytest.mark.parametrize("single", [True, False], ids=["single", "two-calls"])
+@pytest.mark.parametrize("policy", ["exact-uniform", "exact-fifo"])
+@pytest.mark.parametrize("b,c", [(1023, 64), (1024, 64), (1025, 64), (1100, 3), (4096, 64)])
+def test_small_counts_of_large_mini_batches(b, c, policy, single, monkeypatch):
+    w = wl.Workload(f"far-labels-b{b}-c{c}", 9, 90, 2, (64,), "f32", b, c, 40, 6, "uniform", "uniform")
+
+    def batch(ww, step, dev="cpu"):
+        x, y = _plain_make_batch(ww, step, dev)
+        if step >= 3:
+            bad = torch.tensor([-1, ww.K, 1 << 40, -(1 << 40)], device=y.device)
+            y[5::7] = bad.repeat(b // 28 + 1)[:y[5::7].numel()]
+        return x, y
+
+    monkeypatch.setattr(wl, "make_batch", batch)
+    buf, orc = run_parity(w, check_state_every=1, single_call=single, policy=POLICIES.get(policy))
+    assert orc.flags == _rb().RB_FLAG_BAD_LABEL or c == 3
+
+
 def test_single_call_without_a_plan_drops_and_flags_bad_labels():
     rb = _rb()
     K, S, b, c, r = 1500, 3, 300, 200, 70
