@@ -1085,8 +1085,12 @@ enum { STEP_TWO = 0, STEP_SMALL = 1, STEP_ONE = 2 };
 int step_form(const rb_buffer* rb, int64_t c, int64_t r)
 {
     if (small_counts(rb, c, r)) return STEP_SMALL;
+    // (up to 64 rows on either side, with the exact selection, the two launches are those of the small-count kernels, a workgroup per
+    // tile: plain rows, 1378 classes, 30 + 30 rows of 371 KB [8.1 us] 14.5 : 14.2, 64 + 64 of 192 KB [8.9] 15.6 : 15.1, 60 + 10 of
+    // 371 KB [9.4] 15.9 : 14.5, 30 + 30 of 602 KB [13.1] 20.1 : 18.1, but 56 + 21 of 192 KB [5.4] 10.8 : 11.6)
+    const bool small_two = rb->selection == RB_SELECT_EXACT && c <= WAVE && r <= WAVE;
     const double one_us = (double)(c + r) * (double)(rb->row_bytes + rb->sample_bytes) / 5.5e6;
-    const double one_most = rb->storage == RB_STORE_U8 ? 2.0 : rb->storage == RB_STORE_BF16 ? 5.5 : 14.0;
+    const double one_most = rb->storage == RB_STORE_U8 ? 2.0 : rb->storage == RB_STORE_BF16 ? 5.5 : small_two ? 8.0 : 14.0;
     // A representative of a class that overwrites slots in this step searches the step's candidates of that class, in the two
     // launches nobody does.  With few classes, i.e. many candidates of each (labels that occur equally often assumed), that
     // costs more than a launch, sooner with FIFO and reservoir replacement, where the two launches' candidates need no search
@@ -1100,7 +1104,7 @@ int step_form(const rb_buffer* rb, int64_t c, int64_t r)
     // Every representative's workgroup copies and sums all fill counts: 0.21 us per 1000 classes, which the second launch does
     // not cost.  What that one costs instead, measured at 2000 classes, where the counts are nearly free, grows with the rows; two
     // launches of the small-count kernels cost least.  One launch against two, rows of 3 KB, at 6000 / 8000 / 10000 classes:
-    // as they are 5 + 5 rows 7.5 : 7.3 at 6000; 30 + 30 7.9 : 8.0 at 6000; 109 + 29 8.2 : 8.5, 9.1 : 8.6 (7832 classes); 200 + 200
+    // as they are 5 + 5 rows 7.5 : 7.3 at 6000; 17 + 7, FIFO, 8.3 : 8.1 at 5076; 30 + 30 7.9 : 8.0 at 6000; 109 + 29 8.2 : 8.5, 9.1 : 8.6 (7832 classes); 200 + 200
     // 8.7 : 9.4 at 6000; 400 + 400 9.7 : 10.7, 10.1 : 10.7, 10.5 : 10.8; 1000 + 1000 13.6 : 16.2 at 10000.  As bfloat16 5 + 5
     // 7.6 : 7.6 at 4000, 8.9 : 7.6 at 10000; 30 + 30 8.3 : 8.4, 8.6 : 8.2; 200 + 200 9.0 : 9.8, 9.5 : 9.9, 9.9 : 9.9.  In 8 bits 5 + 5
     // 8.5 : 8.3 at 4000, 10.1 : 8.3 at 10000; 200 + 200 10.1 : 10.2, 10.5 : 10.1; 1000 + 1000 15.1 : 15.1 at 10000.  Bernoulli
@@ -1109,7 +1113,7 @@ int step_form(const rb_buffer* rb, int64_t c, int64_t r)
     const bool u8 = rb->storage == RB_STORE_U8;
     const double rows = (double)(c + r);
     const double second_us = rb->selection == RB_SELECT_BERNOULLI ? (u8 ? 0.72 : 0.82) + 0.004 * rows
-                           : c <= WAVE && r <= WAVE ? (rb->storage == RB_STORE_SAME ? 0.5 + 0.0085 * rows : 0.3 + 0.007 * rows)
+                           : small_two ? (rb->storage == RB_STORE_SAME ? 0.4 + 0.0085 * rows : 0.3 + 0.007 * rows)
                            : u8 ? 0.63 + 0.0005 * rows : 0.85 + 0.0019 * rows;
     const bool many_classes = 0.21e-3 * (double)(rb->K - 2000) > second_us;
     if (one_us < one_most && !many_classes && c >= 1 && r >= 1 && rb->K <= ONE_CLASSES && rb->opt_fuse &&

@@ -189,7 +189,7 @@ def test_single_launch_with_few_classes(eviction, classes, most, selection):
 # Many classes: the single launch reads all fill counts in many workgroups.  Shapes next to the crossing that was measured, on
 # both sides of it (what lies far from it on either side is in the same list).
 @pytest.mark.parametrize("storage,selection,classes,c,r,launches", [
-    (0, 0, 2000, 5, 5, 1), (0, 0, 4000, 5, 5, 1), (0, 0, 6000, 5, 5, 2), (0, 0, 6000, 30, 30, 1), (0, 0, 8000, 30, 30, 2),
+    (0, 0, 2000, 5, 5, 1), (0, 0, 4000, 5, 5, 1), (0, 0, 5076, 17, 7, 2), (0, 0, 6000, 5, 5, 2), (0, 0, 6000, 30, 30, 1), (0, 0, 8000, 30, 30, 2),
     (0, 0, 6000, 109, 29, 1), (0, 0, 7832, 109, 29, 2), (0, 0, 8000, 200, 200, 1), (0, 0, 10000, 200, 200, 2), (0, 0, 10240, 400, 400, 1),
     (0, 1, 6000, 5, 5, 1), (0, 1, 8000, 5, 5, 2), (0, 1, 8000, 109, 29, 1), (0, 1, 10000, 109, 29, 2), (0, 1, 10240, 200, 200, 1),
     (1, 0, 2000, 5, 5, 1), (1, 0, 6000, 5, 5, 2), (1, 0, 8000, 30, 30, 2), (1, 0, 8000, 200, 200, 1), (1, 0, 10240, 400, 400, 1),
@@ -204,4 +204,19 @@ def test_single_launch_with_many_classes(storage, selection, classes, c, r, laun
     rc, h = rb.rb_create(classes, 10, (784,), rb.RB_F32)
     assert rb.rb_set_storage(h, storage) == rb.RB_OK and rb.rb_set_policy(h, selection, 0) == rb.RB_OK
     assert rb.rb_query_launches(h, 4096, c, r) == (rb.RB_OK, launches)
+    rb.rb_destroy(h)
+
+
+# Rows that take too long to move for a launch of one workgroup per compute unit; two launches of the small-count kernels move
+# long rows better than those of the general kernels.
+@pytest.mark.parametrize("storage,selection,c,r,elems,launches", [
+    (0, 0, 56, 21, 48000, 1), (0, 0, 30, 30, 92768, 2), (0, 0, 64, 64, 48000, 2), (0, 0, 60, 10, 92768, 2), (0, 0, 21, 56, 92768, 2),
+    (0, 0, 70, 60, 48000, 1), (0, 0, 100, 90, 48000, 1), (0, 0, 120, 100, 48000, 2), (0, 1, 30, 30, 92768, 1), (0, 1, 64, 64, 48000, 1),
+    (1, 0, 30, 30, 48000, 1), (1, 0, 64, 64, 48000, 2), (2, 0, 60, 10, 20000, 1), (2, 0, 64, 64, 48000, 2),
+])
+def test_single_launch_with_long_rows(storage, selection, c, r, elems, launches):
+    import paper_2406_03285_amd as rb
+    rc, h = rb.rb_create(1378, 4, (elems,), rb.RB_F32)
+    assert rb.rb_set_storage(h, storage) == rb.RB_OK and rb.rb_set_policy(h, selection, 0) == rb.RB_OK
+    assert rb.rb_query_launches(h, 400, c, r) == (rb.RB_OK, launches)
     rb.rb_destroy(h)
