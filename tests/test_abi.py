@@ -178,7 +178,7 @@ def test_single_launch_leaves_room_for_a_step_above_the_slots(storage, elems, se
 @pytest.mark.parametrize("selection", [0, 1])
 def test_single_launch_with_few_classes(eviction, classes, most, selection):
     import paper_2406_03285_amd as rb
-    rc, h = rb.rb_create(classes, 40, (256,), rb.RB_F32)
+    rc, h = rb.rb_create(classes, 200, (256,), rb.RB_F32)
     assert rb.rb_set_policy(h, selection, eviction) == rb.RB_OK
     for c in (most - 1, most, most + 1, 4096):
         if c <= 4096:
@@ -219,4 +219,17 @@ def test_single_launch_with_long_rows(storage, selection, c, r, elems, launches)
     rc, h = rb.rb_create(1378, 4, (elems,), rb.RB_F32)
     assert rb.rb_set_storage(h, storage) == rb.RB_OK and rb.rb_set_policy(h, selection, 0) == rb.RB_OK
     assert rb.rb_query_launches(h, 400, c, r) == (rb.RB_OK, launches)
+    rb.rb_destroy(h)
+
+
+def test_single_launch_with_more_representatives_than_slots():
+    import paper_2406_03285_amd as rb
+    for selection in (0, 1):
+        rc, h = rb.rb_create(9, 40, (32,), rb.RB_F32)
+        assert rb.rb_set_policy(h, selection, 0) == rb.RB_OK
+        for r, launches in ((65, 1), (360, 1), (361, 2), (4096, 2)):
+            assert rb.rb_query_launches(h, 100, 9, r) == (rb.RB_OK, launches)
+        rb.rb_destroy(h)
+    rc, h = rb.rb_create(2, 3, (32,), rb.RB_F32)
+    assert rb.rb_query_launches(h, 100, 9, 64) == (rb.RB_OK, 1)             # small counts: one launch in any case
     rb.rb_destroy(h)

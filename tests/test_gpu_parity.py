@@ -123,7 +123,7 @@ def test_policy_variant_through_the_single_call_and_at_full_size():
     (300, 4, 133, 200, 64, 64, "u8", "zipf", 1),            # the last counts one wavefront selects; ragged rows
     (300, 4, 133, 200, 65, 63, "same", "zipf", 1),          # ... and the first ones the workgroup does
     (2, 700, 1, 4096, 4096, 4096, "same", "uniform", 2),    # every count at its limit, ~2048 class-mates: two launches
-    (21, 70, 1, 4096, 4096, 4096, "same", "uniform", 1),    # ... ~195 class-mates, one vector per row: one
+    (21, 196, 1, 4096, 4096, 4096, "same", "uniform", 1),   # ... ~195 class-mates, one vector per row: one
     (1, 37, 4, 1100, 1024, 1025, "bf16", "uniform", 2),     # one class: thousands of rivals, r above what is stored
     (1024, 9, 192, 1025, 500, 128, "u8", "active50", 1),    # ~10 class-mates, more positions than threads
     (10240, 2, 64, 300, 90, 200, "same", "uniform", (2, 1)),    # most classes the one launch serves, where it pays
@@ -148,7 +148,7 @@ def test_single_call_without_a_plan(K, S, vecs, b, c, r, store, labels, launches
 # ... with more candidates of a class than a wavefront has lanes: as many as the single launch takes with few classes, and skewed labels.
 @pytest.mark.parametrize("policy", ["exact-uniform"] + sorted(POLICIES))
 @pytest.mark.parametrize("K,S,vecs,b,c,r,store,labels", [
-    (20, 30, 4, 4096, 3800, 900, "same", "uniform"),        # ~190 class-mates, several per slot: full at once, whole rounds of FIFO
+    (20, 30, 4, 4096, 3800, 600, "same", "uniform"),        # ~190 class-mates, several per slot: full at once, whole rounds of FIFO
     (20, 300, 8, 4096, 3000, 600, "bf16", "uniform"),       # ~150: fill up in the second step, appended and overwritten slots mixed
     (60, 50, 2, 3001, 2900, 700, "u8", "zipf"),             # the head class has ~700, most classes few
     (1, 3000, 1, 300, 64, 3000, "same", "uniform"),         # one class of all candidates, nothing is overwritten
