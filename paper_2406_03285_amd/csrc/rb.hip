@@ -550,7 +550,12 @@ hipError_t launch_big(const MoveArgs& m, const PlanArgs& next, const uint32_t* f
 Shape big_shape(const rb_buffer* rb, int64_t rows, int planners)
 {
     // (with 8-bit storage a lane holds four accesses per vector, and these workgroups have 128 registers per lane: two vectors)
-    if (rb->storage == RB_STORE_U8) return plan_shape(rb, rows, BIG_GROUP, 2);
+    // - or one, as long as the tiles of one vector keep the launch within one round (100 + 100 rows of 49 KB 7.7 us with one, 10.1
+    // with two; 302 + 85 rows of 51 KB, 387 and 194 workgroups, 12.1 : 10.8)
+    if (rb->storage == RB_STORE_U8) {
+        const int64_t tiles = rows * ((rb->row_vec + BIG_GROUP - 1) / BIG_GROUP);
+        return plan_shape(rb, rows, BIG_GROUP, 2, 0, tiles <= (256 - planners) * (int64_t)BIG_GROUPS ? 1024 : 0);
+    }
     Shape s = plan_shape(rb, rows, BIG_GROUP);
     if (rb->opt_unroll != 0) return s;
     constexpr int64_t CUS = 256;
