@@ -1407,7 +1407,13 @@ int rb_update(rb_buffer* rb, const void* batch_x, const int64_t* batch_y,
     // keep those.  Both calls, r = 64, large against small tiles: bfloat16 rows of 49 KB 600 candidates 18.5 : 18.5 us,
     // 800 23.1 : 22.9, 900 24.7 : 26.1, 1000 25.4 : 28.1; of 192 KB 600 44.7 : 43.9, 800 55.8 : 57.6, 1000 66.5 : 71.8; 8 bits,
     // 49 KB, 700 21.0 : 20.4, 900 22.9 : 25.1; rows of 12 KB, one large tile, 1024 as bfloat16 15.4 : 14.5, 8 bits 16.5 : 15.2)
-    const bool many = !small && (c > BIG_MAX || (rows > 768 && rb->row_vec > WAVE * (narrow == 2 ? 4 : 8)));
+    // (Bernoulli selection: a coin per position of the mini-batch in every workgroup, and 12 bytes of LDS for it, so the size of the
+    // mini-batch counts as well: large against small tiles, bfloat16 rows of 602 KB, r = 8, mini-batch of 512 / 1024 / 2048 / 4096,
+    // c = 10 [537 workgroups of small tiles] 12.7 : 11.6, 13.2 : 12.0, 14.1 : 13.2, 16.5 : 19.1, c = 60 [1980] 20.2 : 19.8, 21.0 : 21.3,
+    // 23.2 : 25.2, 31.1 : 43.4; of 192 KB, c = 60 [642] 12.7 : 12.1, 13.1 : 12.8, 14.1 : 14.2, 16.6 : 23.0; in 8 bits alike)
+    const int64_t small_tiles = (rb->row_vec + WAVE * (narrow == 2 ? 2 : 4) - 1) / (WAVE * (narrow == 2 ? 2 : 4));
+    const bool coins = rb->selection == RB_SELECT_BERNOULLI && (b >= 3072 || (b >= 1024 && rows * small_tiles > 1024 * NWAVE));
+    const bool many = !small && (c > BIG_MAX || coins || (rows > 768 && rb->row_vec > WAVE * (narrow == 2 ? 4 : 8)));
     const Shape sh = plan_shape(rb, rows, small ? TPB : WAVE, narrow == 2 ? (many ? 4 : 2) : narrow == 1 && !small && !many ? 4 : 8);
     UpdateArgs a;
     a.batch_x = static_cast<const vec16*>(batch_x);

@@ -282,6 +282,14 @@ def test_converted_rows_with_many_candidates(store, vecs, c):
     run_parity(w, store_bf16=store == "bf16", store_u8=store == "u8")
 
 
+# ... and with the size of the mini-batch under the Bernoulli selection.
+@pytest.mark.parametrize("store,vecs", [("bf16", 4097), ("u8", 2049)])
+@pytest.mark.parametrize("b", [1023, 1024, 3072])
+def test_converted_rows_of_large_mini_batches_with_coins(store, vecs, b):
+    w = wl.Workload(f"coins-{store}-{vecs}-{b}", 9, 30, 4, (vecs * (8 if store == "bf16" else 16),), "f32", b, 150, 20, 2, "uniform", "uniform")
+    run_parity(w, store_bf16=store == "bf16", store_u8=store == "u8", policy=POLICIES["bernoulli-fifo"])
+
+
 def test_bfloat16_storage_rounds_every_special_value_like_the_oracle(monkeypatch):
     w = wl.variant(wl.C2, name="C2-bf16-special", S=3, c=64, r=64)
     monkeypatch.setattr(wl, "make_batch", lambda ww, step, dev="cpu": _special_values_batch(ww, step, dev))
