@@ -137,8 +137,12 @@ __device__ __forceinline__ int64_t wave_place(const UpdateArgs& a, bool active, 
     const int total = __popcll(__ballot(same));
     const int rank = __popcll(__ballot(same && x < p));
     if (fill0 + total <= S) return (int64_t)ki * S + fill0 + rank;     // all append: distinct slots
+    if (AUX && a.eviction == RB_EVICT_FIFO) {
+        // it is itself overwritten in this step if a class-mate comes a whole round of S later
+        return rank + S < total ? -1 : (int64_t)ki * S + mate_slot(a, p, rank, fill0, a.aux_old[ki]);
+    }
     if (AUX) {
-        // a later class-mate may take the slot, or (reservoir) it may not be kept
+        // a later class-mate may take the slot, or it may not be kept
         const int slot = same ? mate_slot(a, x, rank_among(__ballot(same), x), fill0, a.aux_old[ki]) : -1;
         const int own = lane_read(slot, i);
         return own < 0 || __ballot(same && x > p && slot == own) != 0 ? -1 : (int64_t)ki * S + own;
