@@ -1096,6 +1096,10 @@ int step_form(const rb_buffer* rb, int64_t c, int64_t r)
     const bool small_two = rb->selection == RB_SELECT_EXACT && c <= WAVE && r <= WAVE;
     const double one_us = (double)(c + r) * (double)(rb->row_bytes + rb->sample_bytes) / 5.5e6;
     const double one_most = rb->storage == RB_STORE_U8 ? 2.0 : rb->storage == RB_STORE_BF16 ? 5.5 : small_two ? 8.0 : 14.0;
+    // (bfloat16 rows that are mostly representatives': 27 + 107 rows of 127 KB, Bernoulli [4.7 us, 3.7 of them representatives] 13.8 : 13.0,
+    // 3 + 40 of 371 KB [4.4, 4.1] 11.9 : 11.5, 10 + 60 of 192 KB [3.7, 3.1] 10.5 : 10.5)
+    const double reps_most = rb->storage == RB_STORE_BF16 ? 3.3 : one_most;
+    if (one_us * (double)r / (double)(c + r) >= reps_most) return STEP_TWO;
     // Representatives that cannot exist leave the workgroups they are dealt to idle, and the others, planned by eight wavefronts
     // each, take longer than one wavefront per row of the two launches: 9 + 3754 rows of 128 bytes, 360 slots, 11.9 : 8.6 us;
     // 15 + 2593 of 1.5 KB, 120 slots, 10.6 : 8.2; 9 + 552 of 36 KB, 120 slots, 10.9 : 9.9; 17 + 185 in 8 bits, 160 slots, 10.0 : 9.3.

@@ -212,7 +212,7 @@ def test_single_launch_with_many_classes(storage, selection, classes, c, r, laun
 @pytest.mark.parametrize("storage,selection,c,r,elems,launches", [
     (0, 0, 56, 21, 48000, 1), (0, 0, 30, 30, 92768, 2), (0, 0, 64, 64, 48000, 2), (0, 0, 60, 10, 92768, 2), (0, 0, 21, 56, 92768, 2),
     (0, 0, 70, 60, 48000, 1), (0, 0, 100, 90, 48000, 1), (0, 0, 120, 100, 48000, 2), (0, 1, 30, 30, 92768, 1), (0, 1, 64, 64, 48000, 1),
-    (1, 0, 30, 30, 48000, 1), (1, 0, 64, 64, 48000, 2), (2, 0, 60, 10, 20000, 1), (2, 0, 64, 64, 48000, 2),
+    (1, 0, 30, 30, 48000, 1), (1, 0, 64, 64, 48000, 2), (1, 1, 3, 40, 92768, 2), (1, 1, 40, 3, 92768, 1), (1, 0, 10, 60, 48000, 1), (2, 0, 60, 10, 20000, 1), (2, 0, 64, 64, 48000, 2),
 ])
 def test_single_launch_with_long_rows(storage, selection, c, r, elems, launches):
     import paper_2406_03285_amd as rb
