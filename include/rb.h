@@ -206,8 +206,9 @@ int rb_sample_augment(rb_buffer *rb, int64_t r, uint64_t seed, uint64_t step,
  * 1 <= c, r <= 64, up to 1024 classes and the exact selection, and beyond that,
  * for c, r >= 1 and up to 10240 classes, where it is the faster form:
  * while (c + r) * (sample + stored row bytes) is below 77 MB (30 MB with bfloat16
- * storage, 11 MB in 8 bits) and classes are neither many for few rows nor few
- * for many candidates (rb_query_launches tells).  Otherwise the two kernels are enqueued one
+ * storage, 11 MB in 8 bits, less for some shapes), classes are neither many for
+ * few rows nor few for many candidates, and r is not above the number of slots
+ * (rb_query_launches tells).  Otherwise the two kernels are enqueued one
  * after the other, as they are when out_y lies over batch_y (the labels are
  * read before they are replaced).  out_x must not overlap batch_x.
  */
