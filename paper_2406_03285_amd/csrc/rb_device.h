@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "rb.h"
 
@@ -226,6 +227,36 @@ constexpr int stored_wide(int storage)
 // ---------------------------------------------------------------------------
 // Row mover: one tile of one row, U vectors per thread in flight.
 // ---------------------------------------------------------------------------
+// Units [lo, hi) of 16, 8 or 4 bytes of a row (row, lo and hi the same in all lanes of the wavefront), of which lane l of the W
+// lanes that share a tile takes units lo + l, lo + W + l, lo + 2 W + l ...  NT: streaming accesses.
+// Accesses go through a buffer descriptor that ends where the span ends.
+template <typename T, bool NT, int W>
+struct TileSpan {
+    static constexpr int POLICY = NT ? 2 : 0;                // cache policy bits of the buffer instructions: nt
+    __amdgpu_buffer_rsrc_t desc;
+
+    __device__ __forceinline__ TileSpan(const void* row, int64_t lo, int64_t hi)
+    {
+        const uint64_t a = reinterpret_cast<uint64_t>(row) + (uint64_t)lo * sizeof(T);
+        const uint64_t a0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a), a1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(a >> 32));
+        const int bytes = __builtin_amdgcn_readfirstlane((int)(hi - lo) * (int)sizeof(T));
+        desc = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(a1 << 32 | a0), 0, bytes, 0x00027000);
+    }
+    __device__ __forceinline__ int at(int u) const { return (u * W + ((int)threadIdx.x & (W - 1))) * (int)sizeof(T); }
+    __device__ __forceinline__ T load(int u) const
+    {
+        if constexpr (sizeof(T) == 16) return __builtin_amdgcn_raw_buffer_load_b128(desc, at(u), 0, POLICY);
+        else if constexpr (sizeof(T) == 8) return __builtin_amdgcn_raw_buffer_load_b64(desc, at(u), 0, POLICY);
+        else return __builtin_amdgcn_raw_buffer_load_b32(desc, at(u), 0, POLICY);
+    }
+    __device__ __forceinline__ void store(int u, T a) const
+    {
+        if constexpr (sizeof(T) == 16) __builtin_amdgcn_raw_buffer_store_b128(a, desc, at(u), 0, POLICY);
+        else if constexpr (sizeof(T) == 8) __builtin_amdgcn_raw_buffer_store_b64(a, desc, at(u), 0, POLICY);
+        else __builtin_amdgcn_raw_buffer_store_b32(a, desc, at(u), 0, POLICY);
+    }
+};
+
 // W: threads that share the tile (a workgroup or one wavefront).  CV: CV_NARROW - the source row is
 // binary32 (two vectors per vector of the tile), converted to bfloat16 while it is loaded; CV_WIDEN -
 // the destination row is binary32, converted from the tile's bfloat16 while it is stored; CV_BOTH -
@@ -233,124 +264,100 @@ constexpr int stored_wide(int storage)
 // vectors of the narrow (stored) row.
 // LATE (CV_NARROW only): the binary32 vectors are kept as they come and converted when they are stored, so that load()
 // does not wait for them.
-template <int U, bool NT, int W = TPB, int PACED = 1, int CV = CV_NONE, bool LATE = false>
+// DESC: the accesses go through a buffer descriptor that ends where the tile ends: what a lane has past the end is dropped by the
+// memory unit (a load gives zeros).  Without it a lane past the end moves the tile's last vector again (same bytes, same place),
+// and lanes that store to one place wait for each other: 64 rows of 301 KB, four vectors per thread, bare mover, 9.0 us without
+// and 7.3 with descriptors; 175 rows of 24 KB 3.6 and 3.2; 10 + 20 slots of 12 KB, two calls, 7.8 -> 7.3.  Without remains where
+// rows are whole multiples of a wavefront's accesses and many rounds of workgroups follow each other (the several-steps launch for
+// large counts, plain rows: 16 steps of 1024 + 1024 rows of 8 KB 91.2 us without, 93.5 with).
+// Either way no lane is masked off, so the number of loads in flight is known at compile time - a wait for an earlier load then does
+// not have to drain these - and the compiler cannot move a load down into a guarded store.
+template <int U, bool NT, int W = TPB, int PACED = 1, int CV = CV_NONE, bool LATE = false, bool DESC = true>
 struct Tile {
     static constexpr bool RAW = LATE && CV != CV_NONE;       // load() moves vectors of the binary32 row
     static constexpr int PARTS = CV & CV_Q8 ? 4 : CV ? 2 : 1;
+    static constexpr int N = PARTS * U;                      // accesses per lane
     // Without conversion a lane holds U vectors.  With one, it holds 2 U half vectors (four bfloat16 each):
     // a lane then touches 8 bytes of the narrow row and 16 bytes of the binary32 row per access, so every
     // instruction of a wavefront covers one contiguous run of bytes on either side.
-    vec16 v[RAW ? PARTS * U : CV ? 1 : U];
-    vec8 h[CV && !(CV & CV_Q8) && !RAW ? 2 * U : 1];
+    vec16 v[RAW || !CV ? N : 1];
+    vec8 h[CV && !(CV & CV_Q8) && !RAW ? N : 1];
     // 8-bit storage: 4 U quarter vectors (four bytes of the stored row against 16 bytes of the binary32 row per access)
-    uint32_t q[CV & CV_Q8 && !RAW ? 4 * U : 1];
+    uint32_t q[CV & CV_Q8 && !RAW ? N : 1];
 
-    // Requires lo < hi.  No lane is ever masked off: a lane whose index falls past the end of
-    // the tile moves the tile's last vector again (same source, same destination, same bytes as
-    // the lane that owns it), so the copy stays correct and branch-free.  That keeps the number
-    // of loads in flight known at compile time - a wait for an earlier load then does not have
-    // to drain these - and keeps the compiler from moving loads down into a guarded store.
+    static_assert(DESC || !CV, "converted rows are moved through descriptors");
+    static __device__ __forceinline__ int64_t clamped(int u, int64_t lo, int64_t hi)
+    {
+        const int64_t i = lo + (int64_t)u * W + (threadIdx.x & (W - 1));
+        return i < hi ? i : hi - 1;
+    }
+
+    // Requires lo < hi, and src / dst, lo and hi the same in all lanes of a wavefront.
     __device__ __forceinline__ void load(const vec16* __restrict__ src, int64_t lo, int64_t hi)
     {
-        if constexpr (RAW) {
+        if constexpr (!DESC) {
 #pragma unroll
-            for (int u = 0; u < PARTS * U; ++u) {
-                int64_t j = PARTS * lo + (int64_t)u * W + (threadIdx.x & (W - 1));
-                j = j < PARTS * hi ? j : PARTS * hi - 1;
-                v[u] = NT ? __builtin_nontemporal_load(src + j) : src[j];
+            for (int u = 0; u < U; ++u) {
+                const int64_t i = clamped(u, lo, hi);
+                v[u] = NT ? __builtin_nontemporal_load(src + i) : src[i];
             }
             return;
         }
-        if (CV & CV_Q8) {
+        if constexpr (RAW || !CV || (CV & CV_NARROW)) {
+            const TileSpan<vec16, NT, W> span(src, PARTS * lo, PARTS * hi);
 #pragma unroll
-            for (int u = 0; u < 4 * U; ++u) {
-                int64_t j = 4 * lo + (int64_t)u * W + (threadIdx.x & (W - 1));
-                j = j < 4 * hi ? j : 4 * hi - 1;
-                if (CV & CV_NARROW) {
-                    q[u] = pack4_u8(NT ? __builtin_nontemporal_load(src + j) : src[j]);
-                } else {
-                    const uint32_t* quarter = reinterpret_cast<const uint32_t*>(src);
-                    q[u] = NT ? __builtin_nontemporal_load(quarter + j) : quarter[j];
-                }
+            for (int u = 0; u < N; ++u) {
+                const vec16 a = span.load(u);
+                if constexpr (RAW || !CV) v[u] = a;
+                else if constexpr (CV & CV_Q8) q[u] = pack4_u8(a);
+                else h[u] = narrow4(a);
             }
-            return;
-        }
-        if (CV) {
+        } else if constexpr (CV & CV_Q8) {
+            const TileSpan<uint32_t, NT, W> span(src, PARTS * lo, PARTS * hi);
 #pragma unroll
-            for (int u = 0; u < 2 * U; ++u) {
-                int64_t j = 2 * lo + (int64_t)u * W + (threadIdx.x & (W - 1));
-                j = j < 2 * hi ? j : 2 * hi - 1;
-                if (CV & CV_NARROW) {
-                    h[u] = narrow4(NT ? __builtin_nontemporal_load(src + j) : src[j]);
-                } else {
-                    const vec8* half = reinterpret_cast<const vec8*>(src);
-                    h[u] = NT ? __builtin_nontemporal_load(half + j) : half[j];
-                }
-            }
-            return;
-        }
+            for (int u = 0; u < N; ++u) q[u] = span.load(u);
+        } else {
+            const TileSpan<vec8, NT, W> span(src, PARTS * lo, PARTS * hi);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            int64_t i = lo + (int64_t)u * W + (threadIdx.x & (W - 1));
-            i = i < hi ? i : hi - 1;
-            v[u] = NT ? __builtin_nontemporal_load(src + i) : src[i];
+            for (int u = 0; u < N; ++u) h[u] = span.load(u);
         }
     }
     // PACED = 1: all loads are waited for first and every store is waited for before the next one
-    // is issued.  Measured on MI355X with a bare mover of the same shape (64 rows of 301 056 bytes,
-    // U = 4): 7.6 us against 8.6 us when each store is issued as soon as its load has arrived
-    // and 8.9 us with the guarded form; a launch of about one workgroup wave does better with few
-    // writes in flight.  PACED = n > 1: a wait after every n-th store; n > U: the stores go out in
+    // is issued: a launch of about one workgroup wave with large tiles does better with few writes in flight
+    // (bare mover on MI355X, 64 rows of 301 056 bytes, U = 4: 7.3 us against 8.5 in one burst; guarded loads and
+    // stores 8.9).  PACED = n > 1: a wait after every n-th store; n > U: the stores go out in
     // one burst once the loads have arrived, which is what launches of many workgroup waves do
     // best with (1024 rows of 301 056 bytes in 19 456 tiles: 105.6 us against 107.1 us paced;
     // 256 rows of 602 112 bytes: 52.1 against 54.1).  PACED = 0: no waits of its own.
     __device__ __forceinline__ void store(vec16* __restrict__ dst, int64_t lo, int64_t hi) const
     {
         if (PACED) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (CV & CV_Q8) {
+        if constexpr (!DESC) {
 #pragma unroll
-            for (int u = 0; u < 4 * U; ++u) {
-                int64_t j = 4 * lo + (int64_t)u * W + (threadIdx.x & (W - 1));
-                j = j < 4 * hi ? j : 4 * hi - 1;
-                if (CV & CV_WIDEN) {
-                    const vec16 a = unpack4_u8(q[RAW ? 0 : u]);
-                    if (NT) __builtin_nontemporal_store(a, dst + j);
-                    else dst[j] = a;
-                } else {
-                    uint32_t* quarter = reinterpret_cast<uint32_t*>(dst);
-                    const uint32_t a = RAW ? pack4_u8(v[RAW ? u : 0]) : q[RAW ? 0 : u];
-                    if (NT) __builtin_nontemporal_store(a, quarter + j);
-                    else quarter[j] = a;
-                }
+            for (int u = 0; u < U; ++u) {
+                const int64_t i = clamped(u, lo, hi);
+                if (NT) __builtin_nontemporal_store(v[u], dst + i);
+                else dst[i] = v[u];
                 if (PACED && (u + 1) % PACED == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             }
             return;
         }
-        if (CV) {
+        constexpr bool WIDE = !CV || (CV & CV_WIDEN) != 0;   // the destination's accesses are whole vectors
+        using Unit = std::conditional_t<WIDE, vec16, std::conditional_t<(CV & CV_Q8) != 0, uint32_t, vec8>>;
+        const TileSpan<Unit, NT, W> span(dst, PARTS * lo, PARTS * hi);
 #pragma unroll
-            for (int u = 0; u < 2 * U; ++u) {
-                int64_t j = 2 * lo + (int64_t)u * W + (threadIdx.x & (W - 1));
-                j = j < 2 * hi ? j : 2 * hi - 1;
-                if (CV & CV_WIDEN) {
-                    const vec16 a = widen4(h[RAW ? 0 : u]);
-                    if (NT) __builtin_nontemporal_store(a, dst + j);
-                    else dst[j] = a;
-                } else {
-                    vec8* half = reinterpret_cast<vec8*>(dst);
-                    const vec8 a = RAW ? narrow4(v[RAW ? u : 0]) : h[RAW ? 0 : u];
-                    if (NT) __builtin_nontemporal_store(a, half + j);
-                    else half[j] = a;
-                }
-                if (PACED && (u + 1) % PACED == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        for (int u = 0; u < N; ++u) {
+            if constexpr (!CV) span.store(u, v[u]);
+            else if constexpr (WIDE) {
+                if constexpr (CV & CV_Q8) span.store(u, unpack4_u8(q[u]));
+                else span.store(u, widen4(h[u]));
+            } else if constexpr (CV & CV_Q8) {
+                if constexpr (RAW) span.store(u, pack4_u8(v[u]));
+                else span.store(u, q[u]);
+            } else {
+                if constexpr (RAW) span.store(u, narrow4(v[u]));
+                else span.store(u, h[u]);
             }
-            return;
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            int64_t i = lo + (int64_t)u * W + (threadIdx.x & (W - 1));
-            i = i < hi ? i : hi - 1;
-            if (NT) __builtin_nontemporal_store(v[u], dst + i);
-            else dst[i] = v[u];
             if (PACED && (u + 1) % PACED == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         }
     }
@@ -359,12 +366,13 @@ struct Tile {
 // Pacing of the one-step kernels' tiles.  Rows that are converted on the way do better with burst stores (a thread has two or
 // four narrow accesses per vector, and a wait after each costs more than it spares): update and sampling in one launch,
 // 8 + 8 rows of 602 KB in 8 bits 7.1 -> 6.4 us, 32 + 32 11.6 -> 10.6, 16 + 16 rows of 12 KB 6.2 -> 5.6; as bfloat16
-// 8 + 8 7.2 -> 6.7, 64 + 64 rows of 49 KB 7.1 -> 6.6; two launches 9.3 -> 8.3.  With four bfloat16 vectors per thread and
-// more, where a launch is about one round of workgroups, paced ones stay (32 + 32 rows of 602 KB 12.3 against 13.2), as for
-// rows moved as they are (64 + 64 rows of 301 KB 15.4 against 17.2).
+// 8 + 8 7.2 -> 6.7, 64 + 64 rows of 49 KB 7.1 -> 6.6; two launches 9.3 -> 8.3.  So do tiles of one or two vectors per thread, where a
+// store's way to memory is a large part of a short launch: 16 + 16 rows of 12 KB 5.4 -> 5.2, 14 + 7 of 602 KB 8.0 -> 7.85, 4 + 4 of
+// 12 KB in two calls 7.7 -> 7.3.  With four vectors per thread and more, where a launch is about one round of workgroups, paced ones
+// stay (bfloat16, 32 + 32 rows of 602 KB 12.3 against 13.2; plain, 64 + 64 rows of 301 KB 15.6 against 17.0, 64 in a call 8.9 against 9.1).
 constexpr int step_pace(int storage, int unroll)
 {
-    return storage == RB_STORE_U8 || (storage == RB_STORE_BF16 && unroll <= 2) ? 64 : 1;
+    return storage == RB_STORE_U8 || unroll <= 2 ? 64 : 1;
 }
 
 // Vector range [lo, hi) of tile `tile` of a row of row_vec vectors.  The row is cut into units of

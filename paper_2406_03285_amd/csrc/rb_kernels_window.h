@@ -560,9 +560,7 @@ __global__ void __launch_bounds__(TPB) rb_window_kernel(const WinMoveArgs m, con
             old.store(m.out_x[qs] + (int64_t)qj * m.row_vec * WIDE, v_lo, v_hi);
             q = rq.chain;
         }
-        // Lanes past the end of a tile move its last vector again, so a vector may be read by one
-        // wavefront and overwritten by another: everybody has read before anybody overwrites.
-        if (en.chain >= 0) __syncthreads();
+        // (the lane that has read a vector of the old content is the one that overwrites it: no barrier in between)
         if (first) { m.buf_y[en.row] = en.label; count_moved(m.state); }
         Tile<U, NT, TPB, WIN_PACE, stored_cv(ST, CV_NARROW)> t;
         t.load(m.batch_x[s] + (int64_t)en.src * m.row_vec * WIDE, v_lo, v_hi);
