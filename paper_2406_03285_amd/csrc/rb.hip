@@ -169,18 +169,28 @@ Shape plan_shape(const rb_buffer* rb, int64_t rows, int width, int most = 8, int
     return s;
 }
 
+// LDS of rb_update_small_kernel and rb_step_small_kernel
+size_t small_lds_bytes(int64_t b, int nchunks)
+{
+    return round_up((size_t)b * 8, 16) + (nchunks <= DIRECT_CHUNKS ? (size_t)DIRECT_CHUNKS * CH * 4 : 0);
+}
+
 // The small-count kernels: vectors per thread (8-bit storage: at most two, a thread holds four accesses per vector),
 // storage form and whether the replacement strategy keeps per-class state are template parameters.
 template <bool NT, int ST, bool AUX>
 hipError_t launch_update_small_s(const UpdateArgs& a, int unroll, dim3 grid, size_t lds, hipStream_t st)
 {
+    const auto go = [&](auto kernel) {
+        kernel<<<grid, TPB, lds, st>>>(a.batch_y, a.fill_old, a.sd.seed_lo, a.sd.seed_hi, a.sd.step_lo, a.sd.step_hi,
+                                       (uint32_t)(a.b | a.c << 16), a.nchunks, a);
+    };
     switch (unroll) {
-    case 1: rb_update_small_kernel<1, NT, ST, AUX><<<grid, TPB, lds, st>>>(a); break;
-    case 2: rb_update_small_kernel<2, NT, ST, AUX><<<grid, TPB, lds, st>>>(a); break;
+    case 1: go(rb_update_small_kernel<1, NT, ST, AUX>); break;
+    case 2: go(rb_update_small_kernel<2, NT, ST, AUX>); break;
     default:
         if constexpr (ST == RB_STORE_U8) return hipErrorInvalidValue;
-        else if (unroll == 4) rb_update_small_kernel<4, NT, ST, AUX><<<grid, TPB, lds, st>>>(a);
-        else rb_update_small_kernel<8, NT, ST, AUX><<<grid, TPB, lds, st>>>(a);
+        else if (unroll == 4) go(rb_update_small_kernel<4, NT, ST, AUX>);
+        else go(rb_update_small_kernel<8, NT, ST, AUX>);
         break;
     }
     return hipGetLastError();
@@ -203,13 +213,16 @@ hipError_t launch_update_small(const UpdateArgs& a, int storage, int unroll, dim
 template <bool NT, int ST>
 hipError_t launch_sample_small_s(const SampleArgs& a, int unroll, dim3 grid, hipStream_t st)
 {
+    const auto go = [&](auto kernel) {
+        kernel<<<grid, TPB, 0, st>>>(a.fill, a.chunk, a.sd.seed_lo, a.sd.seed_hi, a.sd.step_lo, a.sd.step_hi, a.r, a.nchunks, a);
+    };
     switch (unroll) {
-    case 1: rb_sample_small_kernel<1, NT, ST><<<grid, TPB, 0, st>>>(a); break;
-    case 2: rb_sample_small_kernel<2, NT, ST><<<grid, TPB, 0, st>>>(a); break;
+    case 1: go(rb_sample_small_kernel<1, NT, ST>); break;
+    case 2: go(rb_sample_small_kernel<2, NT, ST>); break;
     default:
         if constexpr (ST == RB_STORE_U8) return hipErrorInvalidValue;
-        else if (unroll == 4) rb_sample_small_kernel<4, NT, ST><<<grid, TPB, 0, st>>>(a);
-        else rb_sample_small_kernel<8, NT, ST><<<grid, TPB, 0, st>>>(a);
+        else if (unroll == 4) go(rb_sample_small_kernel<4, NT, ST>);
+        else go(rb_sample_small_kernel<8, NT, ST>);
         break;
     }
     return hipGetLastError();
@@ -276,15 +289,20 @@ hipError_t launch_sample(const SampleArgs& a, int widen, int unroll, dim3 grid, 
 }
 
 template <bool NT, int ST, bool AUX>
-hipError_t launch_step_s(const StepArgs& a, int unroll, dim3 grid, size_t lds, hipStream_t st)
+hipError_t launch_step_s(const StepArgs& sa, int unroll, dim3 grid, size_t lds, hipStream_t st)
 {
+    const UpdateArgs& a = sa.u;
+    const auto go = [&](auto kernel) {
+        kernel<<<grid, TPB, lds, st>>>(a.batch_y, a.fill_old, a.sd.seed_lo, a.sd.seed_hi, a.sd.step_lo, a.sd.step_hi,
+                                       (uint32_t)(a.b | a.c << 16), (uint32_t)(sa.r | a.nchunks << 16), a.tpr, a.nchunks + a.c * a.tpr, sa);
+    };
     switch (unroll) {
-    case 1: rb_step_small_kernel<1, NT, ST, AUX><<<grid, TPB, lds, st>>>(a); break;
-    case 2: rb_step_small_kernel<2, NT, ST, AUX><<<grid, TPB, lds, st>>>(a); break;
+    case 1: go(rb_step_small_kernel<1, NT, ST, AUX>); break;
+    case 2: go(rb_step_small_kernel<2, NT, ST, AUX>); break;
     default:
         if constexpr (ST == RB_STORE_U8) return hipErrorInvalidValue;
-        else if (unroll == 4) rb_step_small_kernel<4, NT, ST, AUX><<<grid, TPB, lds, st>>>(a);
-        else if constexpr (ST == RB_STORE_SAME) rb_step_small_kernel<8, NT, ST, AUX><<<grid, TPB, lds, st>>>(a);
+        else if (unroll == 4) go(rb_step_small_kernel<4, NT, ST, AUX>);
+        else if constexpr (ST == RB_STORE_SAME) go(rb_step_small_kernel<8, NT, ST, AUX>);
         else return hipErrorInvalidValue;
         break;
     }
@@ -1439,7 +1457,7 @@ int rb_update(rb_buffer* rb, const void* batch_x, const int64_t* batch_y,
     a.aux_old = reinterpret_cast<const int32_t*>(rb->ws + rb->off_aux[rb->cur]);
     a.aux_new = reinterpret_cast<int32_t*>(rb->ws + rb->off_aux[rb->cur ^ 1]);
     const dim3 grid((unsigned)(rb->nchunks + (small ? sh.groups * sh.tpr : (rows * sh.tpr + NWAVE - 1) / NWAVE)));
-    const size_t lds = small ? (size_t)b * 8 : (size_t)b * 4 + (size_t)a.cap * 8;
+    const size_t lds = small ? small_lds_bytes(b, rb->nchunks) : (size_t)b * 4 + (size_t)a.cap * 8;
     const hipError_t e = small ? (rb->opt_nt ? launch_update_small<true>(a, rb->storage, sh.unroll, grid, lds, rb->stream)
                                              : launch_update_small<false>(a, rb->storage, sh.unroll, grid, lds, rb->stream))
                                : (rb->opt_nt ? launch_update<true>(a, narrow, sh.unroll, grid, lds, rb->stream)
@@ -1541,9 +1559,8 @@ int rb_update_sample(rb_buffer* rb, const void* batch_x, const int64_t* batch_y,
     sa.out_x = static_cast<vec16*>(out_x);
     sa.out_y = out_y;
     sa.r = (int32_t)r;
-    sa.first_gather = (int32_t)(rb->nchunks + c * sh.tpr);
     const dim3 grid((unsigned)(rb->nchunks + (c + r) * sh.tpr));
-    const size_t lds = (((size_t)b * 2 + 3) & ~(size_t)3) * 4 + (size_t)DIRECT_CHUNKS * CH * 8;
+    const size_t lds = small_lds_bytes(b, rb->nchunks);
     const hipError_t e = rb->opt_nt ? launch_step<true>(sa, rb->storage, sh.unroll, grid, lds, rb->stream)
                                     : launch_step<false>(sa, rb->storage, sh.unroll, grid, lds, rb->stream);
     if (e != hipSuccess) return RB_EHIP;

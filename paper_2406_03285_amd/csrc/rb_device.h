@@ -456,7 +456,6 @@ struct StepArgs {
     vec16* out_x;
     int64_t* out_y;
     int32_t r;
-    int32_t first_gather;   // index of the first representative mover (the candidate movers come before)
 };
 
 }  // namespace

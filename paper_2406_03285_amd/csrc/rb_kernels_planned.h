@@ -93,11 +93,7 @@ __device__ __forceinline__ void plan_step(const PlanArgs& a, uint32_t* lds)
     PlanEntry* entry = reinterpret_cast<PlanEntry*>(a.table + sizeof(PlanHeader));
 
     int64_t yv[YPRE];
-#pragma unroll
-    for (int u = 0; u < YPRE; ++u) {
-        const int q = tid + u * TPB;
-        yv[u] = q < b ? a.batch_y[q] : -1;
-    }
+    request_labels(yv, a.batch_y, b);
     int4 fo = make_int4(0, 0, 0, 0), ao = make_int4(0, 0, 0, 0);
     if (4 * tid < a.nchunks * CH) {
         fo = *reinterpret_cast<const int4*>(a.fill_old + 4 * tid);

@@ -181,6 +181,15 @@ def test_small_counts_of_large_mini_batches(b, c, policy, single, monkeypatch):
     assert orc.flags == _rb().RB_FLAG_BAD_LABEL or c == 3
 
 
+@pytest.mark.parametrize("single", [True, False], ids=["single", "two-calls"])
+@pytest.mark.parametrize("K,vecs", [(1, 1), (255, 63), (256, 64), (257, 65), (512, 511), (513, 513), (769, 1025), (1024, 2049), (1025, 255),
+                                    (16384, 3), (16385, 3)])
+def test_small_counts_at_the_edges_of_class_chunks_and_tiles(K, vecs, single):
+    """A wavefront holds a chunk of 256 classes, up to four chunks; tiles end with a full, a partly filled or one lane."""
+    w = wl.variant(wl.C1, name=f"chunks-{K}-{vecs}", K=K, S=3, shape=(4 * vecs,), b=130, c=64, r=64)
+    run_parity(w, steps=12, check_state_every=4, single_call=single)
+
+
 def test_single_call_without_a_plan_drops_and_flags_bad_labels():
     rb = _rb()
     K, S, b, c, r = 1500, 3, 300, 200, 70
