@@ -1034,40 +1034,51 @@ int many_form(const rb_buffer* rb, int64_t b, int64_t c, int64_t r, int64_t& ste
     return form;
 }
 
-template <int U, bool NT, int ST>
+template <int U, bool NT, int ST, bool BERNOULLI>
 hipError_t launch_one_u(const OneArgs& a, dim3 grid, size_t lds, hipStream_t st)
 {
     if constexpr ((ST == RB_STORE_U8 && U > 1) || (ST == RB_STORE_BF16 && U > 2)) {
         return hipErrorInvalidValue;           // (converted rows: step_one)
     } else {
-        constexpr int most = 4 * (ONE_CLASSES + ONE_TPB + (int)ONE_MATE_WORDS + 4 * RB_MAX_BATCH) + 2 * RB_MAX_BATCH;      // one_lds_bytes at its largest
+        constexpr int most = 4 * (ONE_CLASSES + ONE_CLASSES / 32 + ONE_CHUNKS + (int)ONE_MATE_WORDS + 4 * RB_MAX_BATCH) + 2 * RB_MAX_BATCH;      // one_lds_bytes at its largest
         static_assert(most <= 156 * 1024, "a compute unit has 160 KB of LDS");
-        const hipError_t e = allow_big_lds<&rb_step_one_kernel<U, NT, ST>, most>();
+        constexpr auto kernel = &rb_step_one_kernel<U, NT, ST, BERNOULLI>;
+        const hipError_t e = allow_big_lds<kernel, most>();
         if (e != hipSuccess) return e;
-        rb_step_one_kernel<U, NT, ST><<<grid, ONE_TPB, lds, st>>>(a);
+        const UpdateArgs& u = a.u;
+        kernel<<<grid, ONE_TPB, lds, st>>>(u.batch_y, u.fill_old, a.chunk_old, u.sd.seed_lo, u.sd.seed_hi, u.sd.step_lo, u.sd.step_hi,
+                                           (uint32_t)(u.b | u.c << 16), (uint32_t)(a.r | u.nchunks << 16), a.first_cand, a);
         return hipGetLastError();
     }
 }
 
-template <bool NT, int ST>
+template <bool NT, int ST, bool BERNOULLI>
 hipError_t launch_one_s(const OneArgs& a, int unroll, dim3 grid, size_t lds, hipStream_t st)
 {
-    switch (unroll) {
-    case 1: return launch_one_u<1, NT, ST>(a, grid, lds, st);
-    case 2: return launch_one_u<2, NT, ST>(a, grid, lds, st);
-    case 4: return launch_one_u<4, NT, ST>(a, grid, lds, st);
-    default: return launch_one_u<8, NT, ST>(a, grid, lds, st);
+    // (without streaming accesses: one kernel per storage form, the one with the most vectors per lane)
+    if constexpr (!NT) return launch_one_u<ST == RB_STORE_U8 ? 1 : ST == RB_STORE_BF16 ? 2 : 8, NT, ST, BERNOULLI>(a, grid, lds, st);
+    else switch (unroll) {
+    case 1: return launch_one_u<1, NT, ST, BERNOULLI>(a, grid, lds, st);
+    case 2: return launch_one_u<2, NT, ST, BERNOULLI>(a, grid, lds, st);
+    case 4: return launch_one_u<4, NT, ST, BERNOULLI>(a, grid, lds, st);
+    default: return launch_one_u<8, NT, ST, BERNOULLI>(a, grid, lds, st);
+    }
+}
+
+template <bool NT, bool BERNOULLI>
+hipError_t launch_one_f(const OneArgs& a, int storage, int unroll, dim3 grid, size_t lds, hipStream_t st)
+{
+    switch (storage) {
+    case RB_STORE_BF16: return launch_one_s<NT, RB_STORE_BF16, BERNOULLI>(a, unroll, grid, lds, st);
+    case RB_STORE_U8: return launch_one_s<NT, RB_STORE_U8, BERNOULLI>(a, unroll, grid, lds, st);
+    default: return launch_one_s<NT, RB_STORE_SAME, BERNOULLI>(a, unroll, grid, lds, st);
     }
 }
 
 template <bool NT>
 hipError_t launch_one(const OneArgs& a, int storage, int unroll, dim3 grid, size_t lds, hipStream_t st)
 {
-    switch (storage) {
-    case RB_STORE_BF16: return launch_one_s<NT, RB_STORE_BF16>(a, unroll, grid, lds, st);
-    case RB_STORE_U8: return launch_one_s<NT, RB_STORE_U8>(a, unroll, grid, lds, st);
-    default: return launch_one_s<NT, RB_STORE_SAME>(a, unroll, grid, lds, st);
-    }
+    return a.u.selection == RB_SELECT_BERNOULLI ? launch_one_f<NT, true>(a, storage, unroll, grid, lds, st) : launch_one_f<NT, false>(a, storage, unroll, grid, lds, st);
 }
 
 // Tiles of `rows` rows for `waves` wavefronts that take one tile after the other: as many tiles per row as make the
@@ -1180,6 +1191,7 @@ int step_one(rb_buffer* rb, const void* batch_x, const int64_t* batch_y, int64_t
     oa.out_x = static_cast<vec16*>(out_x);
     oa.out_y = out_y;
     oa.r = (int32_t)r;
+    oa.chunk_old = reinterpret_cast<const int32_t*>(rb->ws + rb->off_chunk[rb->cur]);
     // rows the grid is sized for (Bernoulli selection: the mean and about one standard deviation; the movers loop, and a grid
     // sized for more leaves that many more wavefronts without work)
     int64_t rows = c;

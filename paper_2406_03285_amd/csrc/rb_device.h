@@ -55,19 +55,36 @@ struct Seed {
     uint32_t seed_lo, seed_hi, step_lo, step_hi;
 };
 
-// Requests every 64-byte line of the kernel's arguments at once and waits for them together.  A launch's arguments are in
-// no cache, and the compiler reads them in batches as it comes to need them: each batch that starts a new line is one more
-// trip to memory (measured on MI355X: about 0.5 us) before the wavefront goes on.
+// The 64-byte lines of a kernel's arguments behind the first one, requested without waiting for them.  A launch's arguments are in no
+// cache: what is read of a new line is one more trip to memory (measured on MI355X: about 0.5 us) before the wavefront goes on.
+// arrived() is called where enough else has been done meanwhile.
 template <size_t BYTES>
-__device__ __forceinline__ void fetch_args()
-{
-    constexpr int LINES = (int)((BYTES + 63) / 64);
-    const __attribute__((address_space(4))) uint32_t* args = (const __attribute__((address_space(4))) uint32_t*)__builtin_amdgcn_kernarg_segment_ptr();
+struct ArgLines {
+    static constexpr int LINES = (int)((BYTES + 63) / 64);
     uint32_t v[LINES];
+
+    __device__ __forceinline__ ArgLines()
+    {
+        const __attribute__((address_space(4))) uint32_t* args = (const __attribute__((address_space(4))) uint32_t*)__builtin_amdgcn_kernarg_segment_ptr();
 #pragma unroll
-    for (int i = 0; i < LINES; ++i) v[i] = args[16 * i];
+        for (int i = 1; i < LINES; ++i) v[i] = args[16 * i];
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    __device__ __forceinline__ void arrived() const
+    {
 #pragma unroll
-    for (int i = 0; i < LINES; ++i) asm volatile("" : : "s"(v[i]));
+        for (int i = 1; i < LINES; ++i) asm volatile("" : : "s"(v[i]));
+    }
+};
+
+// The structure at `offset` bytes of a kernel's arguments, read where its members are used.  Used as an ordinary argument it would be
+// read as a whole when the kernel starts, and what does not fit the scalar registers moved to vector lanes and back (the single launch
+// for any counts: 172 such moves in front of and between the waits, 418 back).
+template <typename T>
+__device__ __forceinline__ const T& kernel_argument(size_t offset)
+{
+    const __attribute__((address_space(4))) char* args = (const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr();
+    return *(const T*)(const __attribute__((address_space(4))) T*)(args + offset);
 }
 
 // ---------------------------------------------------------------------------

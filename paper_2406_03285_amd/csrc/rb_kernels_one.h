@@ -16,10 +16,14 @@ constexpr int ONE_FILL_PER = (ONE_CLASSES / 4 + ONE_TPB - 1) / ONE_TPB;    // ve
 constexpr int ONE_PACE = 64;                        // stores of a tile go out in one burst (paced ones measured 0.4 us slower)
 constexpr int ONE_PLANNED = 64;                     // rows a workgroup plans at a time
 constexpr int ONE_LIST = 4 * WAVE;                  // the candidate list and the draws are read this many at a time
+constexpr int ONE_PARKED = 2 * ONE_TPB;             // mini-batches up to this size have all their labels read into LDS
 constexpr int ONE_POS_BITS = 12;                    // candidate list: class << ONE_POS_BITS | mini-batch position
 constexpr uint32_t ONE_NO_CLASS = 0xFFFFFFFFu;      // ... of a candidate whose label is outside [0, K), and behind the list's end
 static_assert(RB_MAX_BATCH <= 1 << ONE_POS_BITS && ONE_CLASSES < 1 << (31 - ONE_POS_BITS), "class and position in one word");
 constexpr int ONE_WORDS = RB_MAX_BATCH / 32;        // words of a bitmap over the mini-batch's positions
+
+// Lanes of one wavefront read what other lanes of it have written to LDS.
+__device__ __forceinline__ void wave_lds_wait() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 struct OneArgs {
     UpdateArgs u;                       // (u.tpr, u.tile_vec, u.tile_rem: tiles of the candidates' rows)
@@ -29,21 +33,39 @@ struct OneArgs {
     int32_t tpr, tile_vec, tile_rem;    // tiles of the representatives' rows
     int32_t share, cshare;              // work items (row, tile) per workgroup; cshare: of the candidates, 0: as many as make the shares equal
     int32_t nwg;                        // workgroups of the launch
+    const int32_t* chunk_old;           // samples per chunk of classes before the step
     int32_t first_cand;                 // workgroups 0 ... first_cand - 1 move representatives (and keep the books), the others candidates
 };
 
+// The arguments of rb_step_one_kernel as they lie in memory
+struct OneKernelArgs {
+    const int64_t* batch_y;
+    const int32_t* fill_old;
+    const int32_t* chunk_old;
+    Seed sd;
+    uint32_t b_c, r_nchunks;
+    int32_t first_cand;
+    OneArgs rest;
+};
+
 // LDS words in front of the arrays whose size depends on the shape (see rb_step_one_kernel)
+constexpr int ONE_CHUNKS = WAVE;                    // chunk sums: one per lane
+static_assert(ONE_CLASSES <= ONE_CHUNKS * CH, "a wavefront holds all chunk sums");
 constexpr size_t ONE_MATE_WORDS = ONE_NWAVE * (WAVE / 2 + ONE_WORDS + ONE_WORDS / 2);
 __host__ __device__ inline int one_padded(int n) { return (n + ONE_LIST - 1) / ONE_LIST * ONE_LIST; }
 inline size_t one_lds_bytes(int b, int cap, int r, int nchunks)
 {
-    return 4 * ((size_t)nchunks * CH + ONE_TPB + ONE_MATE_WORDS + 2 * (size_t)((b + 3) & ~3) + one_padded(cap) + one_padded(cap > r ? cap : r)) +
+    return 4 * ((size_t)nchunks * (CH + CH / 32) + ONE_CHUNKS + ONE_MATE_WORDS + 2 * (size_t)((b + 3) & ~3) + one_padded(cap) + one_padded(cap > r ? cap : r)) +
            ((size_t)cap * 2 + 3) / 4 * 4;
 }
 
+// Lane `lane` looks at four consecutive words of every ONE_LIST of the candidate list or the draws (one LDS access): number `bit` of
+// its words is this one of the list.
+__device__ __forceinline__ int one_entry(int bit, int lane) { return (bit >> 2) * ONE_LIST + 4 * lane + (bit & 3); }
+
 // The candidates of one class in a step, as one wavefront collects them from the workgroup's candidate list.
 struct Mates {
-    uint64_t hit;         // bit i: candidate i * WAVE + lane is one of them
+    uint64_t hit;         // bit i: candidate one_entry(i, lane) is one of them
     int mine, before;     // how many of them the lane holds, and the lanes before it
     int total;
     int rank;             // ... of them earlier in the mini-batch than position p
@@ -56,15 +78,12 @@ __device__ __forceinline__ Mates one_mates(const uint32_t* s_kx, int m, int32_t 
     t.hit = 0;
     int earlier = 0;
     const uint32_t lo = (uint32_t)k << ONE_POS_BITS, mid = lo | (uint32_t)p, hi = lo | (RB_MAX_BATCH - 1);
+#pragma unroll 4
     for (int m0 = 0; m0 < m; m0 += ONE_LIST) {
-        uint32_t v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = s_kx[m0 + u * WAVE + lane];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            t.hit |= (uint64_t)(v[u] >= lo && v[u] <= hi) << (m0 / WAVE + u);
-            earlier += v[u] >= lo && v[u] < mid;
-        }
+        const uint4 v = *reinterpret_cast<const uint4*>(s_kx + m0 + 4 * lane);
+        const uint32_t mate = (v.x >= lo && v.x <= hi ? 1u : 0u) | (v.y >= lo && v.y <= hi ? 2u : 0u) | (v.z >= lo && v.z <= hi ? 4u : 0u) | (v.w >= lo && v.w <= hi ? 8u : 0u);
+        t.hit |= (uint64_t)mate << (m0 / WAVE);
+        earlier += (v.x >= lo && v.x < mid) + (v.y >= lo && v.y < mid) + (v.z >= lo && v.z < mid) + (v.w >= lo && v.w < mid);
     }
     t.mine = __popcll(t.hit);
     const int incl = wave_scan_incl(t.mine | (earlier << 16));      // both sums are <= 4096
@@ -79,8 +98,8 @@ __device__ __forceinline__ void one_mate_lanes(const Mates& t, const uint32_t* s
 {
     const int lane = threadIdx.x & (WAVE - 1);
     int at = t.before;
-    for (uint64_t h = t.hit; h != 0; h &= h - 1) pend[at++] = (uint16_t)(s_kx[__builtin_ctzll(h) * WAVE + lane] & (RB_MAX_BATCH - 1));
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // (lanes of one wavefront read what other lanes of it wrote)
+    for (uint64_t h = t.hit; h != 0; h &= h - 1) pend[at++] = (uint16_t)(s_kx[one_entry(__builtin_ctzll(h), lane)] & (RB_MAX_BATCH - 1));
+    wave_lds_wait();
     x = lane < t.total ? pend[lane] : -1;
     rank = 0;
     for (int j = 0; j < t.total; ++j) rank += lane_read(x, j) < x;
@@ -93,17 +112,17 @@ __device__ __forceinline__ void one_mate_map(const Mates& t, const uint32_t* s_k
     static_assert(ONE_WORDS == 2 * WAVE, "two bitmap words per lane");
     cm[2 * lane] = 0u;
     cm[2 * lane + 1] = 0u;
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    wave_lds_wait();
     for (uint64_t h = t.hit; h != 0; h &= h - 1) {
-        const int x = (int)(s_kx[__builtin_ctzll(h) * WAVE + lane] & (RB_MAX_BATCH - 1));
+        const int x = (int)(s_kx[one_entry(__builtin_ctzll(h), lane)] & (RB_MAX_BATCH - 1));
         atomicOr(&cm[x >> 5], 1u << (x & 31));
     }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    wave_lds_wait();
     const int p0 = __popc(cm[2 * lane]), p1 = __popc(cm[2 * lane + 1]);
     const int before = wave_scan_incl(p0 + p1) - (p0 + p1);
     cmpre[2 * lane] = (uint16_t)before;
     cmpre[2 * lane + 1] = (uint16_t)(before + p0);
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    wave_lds_wait();
 }
 
 // The last position of class k's candidates that go to `slot` and lie behind position p (ANY: some number >= 0 if there is
@@ -117,7 +136,7 @@ __device__ __forceinline__ int one_last_writer(const UpdateArgs& a, const Mates&
     const int lane = threadIdx.x & (WAVE - 1);
     int last = -1;
     for (uint64_t h = t.hit; __ballot(h != 0) != 0; h &= h - 1) {
-        const int x = h != 0 ? (int)(s_kx[__builtin_ctzll(h) * WAVE + lane] & (RB_MAX_BATCH - 1)) : -1;
+        const int x = h != 0 ? (int)(s_kx[one_entry(__builtin_ctzll(h), lane)] & (RB_MAX_BATCH - 1)) : -1;
         if (x > p && x > last) {
             const int rank = cmpre[x >> 5] + __popc(cm[x >> 5] & ((1u << (x & 31)) - 1u));
             if (mate_slot(a, x, rank, fill0, aux0) == slot) last = x;
@@ -210,129 +229,162 @@ __device__ __forceinline__ int one_writer(const UpdateArgs& a, const uint32_t* s
 // where a candidate goes, resp. which stored sample a representative is and whether this very step writes that slot (then
 // the mini-batch row stored there is copied: no workgroup reads a row another one writes) - and then move the tiles.
 //
-// What bounds it: the chain arguments -> labels -> candidate list -> fill counts -> draws -> rows, about 0.5 to 2 us a link
+// What bounds it: the chain selection -> labels -> candidate list -> fill counts -> draws -> rows, 0.3 to 1 us a link
 // with the counts, on every compute unit at once; the rows themselves take a third of the time or less.  Hence one
 // workgroup of 512 threads per compute unit (1024 threads: equal at 1024 + 1024 rows, 0.3 to 0.5 us slower at small
 // counts; 256: 2 to 3 us slower; two workgroups per unit: 0.1 to 0.4 us faster for few rows, 6 us slower for 1024 + 1024),
-// a row planned once per workgroup and not by every wavefront, and one list word per candidate.  Measured on MI355X against
-// the two launches this replaced: 1024 + 1024 rows of 8 KB of 10000 classes 16.1 : 17.1 us; Bernoulli selection with
-// reservoir replacement, 90 + 75 rows of 49 KB kept as bfloat16, 9.2 : 10.5; 20 + 20 rows of 49 KB in 8 bits, Bernoulli,
-// 8.4 : 14.5; 300 + 300 rows of 12 KB of 300 classes 10.0 : 11.7, in 8 bits 11.5 : 15.9; 5 + 5 rows of 3 KB of 2000 classes 6.6 : 7.2.
-// (Where the two launches are the faster form: step_form.)
+// a row planned once per workgroup and not by every wavefront, one list word per candidate, four words of it per lane and LDS access,
+// the samples before a class from the old sums per chunk and the candidates that add to them (summing 10240 counts took 1.4 us),
+// the candidates' labels alone of a large mini-batch (2 us), a kernel per kind of selection and arguments read where they are used
+// (0.7 to 1 us: what did not fit the scalar registers went to vector lanes and back).  Measured on MI355X, us, before these and now:
+// 1024 + 1024 rows of 8 KB of 10000 classes 16.5 -> 14.2; Bernoulli selection with reservoir replacement, 90 + 75 rows of 49 KB kept as
+// bfloat16, 9.4 -> 8.6; Bernoulli, 9 + 20 rows of 59 KB kept as bfloat16 7.5 -> 6.4; FIFO, 563 + 150 rows of 1 KB of 2017 classes
+// 9.3 -> 8.6; 9 + 7 rows of 99 KB in 8 bits of 1160 classes 7.4 -> 6.6.  (Where the two launches are the faster form: step_form.)
 //
-// LDS (dynamic): s_fill[nchunks * CH] i32, s_before[ONE_TPB] i32, per wavefront pend u16[WAVE], cm u32[ONE_WORDS],
-// cmpre u16[ONE_WORDS]; s_lab[b] u32, s_first[b] u32, s_kx[cap] u32, s_t[max(cap, r)] u32 (both
-// rounded up to ONE_LIST), s_x[cap] u16.
+// LDS (dynamic): s_fill[nchunks * CH] i32, s_hit[nchunks * CH / 32] u32 (bitmap of the classes with candidates), s_chunk[ONE_CHUNKS] i32,
+// per wavefront pend u16[WAVE], cm u32[ONE_WORDS], cmpre u16[ONE_WORDS]; s_lab[b] u32, s_first[b] u32, s_kx[cap] u32,
+// s_t[max(cap, r)] u32 (both rounded up to ONE_LIST), s_x[cap] u16.
 // ---------------------------------------------------------------------------
-template <int U, bool NT, int ST>
-__global__ void __launch_bounds__(ONE_TPB) rb_step_one_kernel(const OneArgs sa)
+template <int U, bool NT, int ST, bool BERNOULLI>
+__global__ void __launch_bounds__(ONE_TPB) rb_step_one_kernel(const int64_t* batch_y, const int32_t* fill_old, const int32_t* chunk_old,
+                                                              uint32_t seed_lo, uint32_t seed_hi, uint32_t step_lo, uint32_t step_hi,
+                                                              uint32_t b_c, uint32_t r_nchunks, int32_t first_cand, const OneArgs)
 {
-    fetch_args<sizeof(OneArgs)>();
+    const OneArgs& sa = kernel_argument<OneArgs>(offsetof(OneKernelArgs, rest));
     const UpdateArgs& a = sa.u;
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
-    const int b = a.b, c = a.c, r = sa.r, nfill = a.nchunks * CH;
-    extern __shared__ __align__(16) uint32_t lds[];
-    int32_t* s_fill = reinterpret_cast<int32_t*>(lds);
-    int32_t* s_before = s_fill + nfill;
-    uint32_t* cm = lds + nfill + ONE_TPB + wave * ONE_WORDS;
-    uint16_t* cmpre = reinterpret_cast<uint16_t*>(lds + nfill + ONE_TPB + ONE_NWAVE * ONE_WORDS) + wave * ONE_WORDS;
-    uint16_t* pend = reinterpret_cast<uint16_t*>(lds + nfill + ONE_TPB + ONE_NWAVE * (ONE_WORDS + ONE_WORDS / 2)) + wave * WAVE;
-    const int bp = (b + 3) & ~3;
-    uint32_t* s_lab = lds + nfill + ONE_TPB + ONE_MATE_WORDS;
-    uint32_t* s_first = s_lab + bp;
-    uint32_t* s_kx = s_first + bp;
-    uint32_t* s_t = s_kx + one_padded(a.cap);
-    uint16_t* s_x = reinterpret_cast<uint16_t*>(s_t + one_padded(a.cap > r ? a.cap : r));
-    __shared__ int s_seg[WAVE];                 // Bernoulli: heads per stretch of WAVE positions
-    __shared__ int s_wave[ONE_NWAVE];
-    __shared__ int s_bad;
-    __shared__ int s_slot[ONE_PLANNED], s_class[ONE_PLANNED], s_fwd[ONE_PLANNED];    // the rows planned last: slot (-1: not moved), class, writer
+    const int b = (int)(b_c & 0xFFFFu), c = (int)(b_c >> 16);
+    const int r = (int)(r_nchunks & 0xFFFFu), nchunks = (int)(r_nchunks >> 16), nfill = nchunks * CH;
+    const Seed sd = {seed_lo, seed_hi, step_lo, step_hi};
+    const bool gather = (int)blockIdx.x < first_cand;
 
-    const bool gather = (int)blockIdx.x < sa.first_cand;
-    const bool bernoulli = a.selection == RB_SELECT_BERNOULLI;
-
-    // labels of the whole mini-batch and, for the representatives, all fill counts: requested now
-    int64_t yv[ONE_PER];
+    // labels of the whole mini-batch and, for the representatives, all fill counts and their sums per chunk: requested now.
+    // Of a large mini-batch under the exact selection only the candidates' labels are read, once their positions are known; a load
+    // per 64 bytes brings them near until then.  (All 4096 read and parked in LDS cost 2 us more.)
+    constexpr int HELD = BERNOULLI ? ONE_PER : ONE_PARKED / ONE_TPB;
+    const bool parked = BERNOULLI || b <= ONE_PARKED;
+    int64_t yv[HELD], near_label = 0;
 #pragma unroll
-    for (int u = 0; u < ONE_PER; ++u) {                     // (threads past the end read the last one again)
+    for (int u = 0; u < HELD; ++u) {                        // (threads past the end read the last one again)
         yv[u] = 0;
-        if (u * ONE_TPB < b) yv[u] = a.batch_y[min(tid + u * ONE_TPB, b - 1)];
+        if (u * ONE_TPB < b && parked) yv[u] = batch_y[min(tid + u * ONE_TPB, b - 1)];
+    }
+    if (!BERNOULLI) {
+        static_assert(RB_MAX_BATCH * sizeof(int64_t) / 64 <= ONE_TPB, "one load per thread");
+        near_label = batch_y[min(8 * tid, b - 1)];
     }
     int4 fo[ONE_FILL_PER];
+    int chunk_sum = 0;
     if (gather) {
 #pragma unroll
         for (int u = 0; u < ONE_FILL_PER; ++u) {
             fo[u] = make_int4(0, 0, 0, 0);
-            if (u * 4 * ONE_TPB < nfill) fo[u] = *reinterpret_cast<const int4*>(a.fill_old + min(4 * (tid + u * ONE_TPB), nfill - 4));
+            if (u * 4 * ONE_TPB < nfill) fo[u] = *reinterpret_cast<const int4*>(fill_old + min(4 * (tid + u * ONE_TPB), nfill - 4));
         }
+        if (wave == 0 && lane < nchunks) chunk_sum = chunk_old[lane];
     }
+
+    const ArgLines<sizeof(OneKernelArgs)> lines;
+
+    extern __shared__ __align__(16) uint32_t lds[];
+    int32_t* s_fill = reinterpret_cast<int32_t*>(lds);
+    uint32_t* s_hit = lds + nfill;
+    int32_t* s_chunk = reinterpret_cast<int32_t*>(s_hit + nfill / 32);
+    uint32_t* mates = reinterpret_cast<uint32_t*>(s_chunk + ONE_CHUNKS);
+    uint32_t* cm = mates + wave * ONE_WORDS;
+    uint16_t* cmpre = reinterpret_cast<uint16_t*>(mates + ONE_NWAVE * ONE_WORDS) + wave * ONE_WORDS;
+    uint16_t* pend = reinterpret_cast<uint16_t*>(mates + ONE_NWAVE * (ONE_WORDS + ONE_WORDS / 2)) + wave * WAVE;
+    const int bp = (b + 3) & ~3;
+    const int cand_cap = BERNOULLI ? b : c;
+    uint32_t* s_lab = mates + ONE_MATE_WORDS;
+    uint32_t* s_first = s_lab + bp;
+    uint32_t* s_kx = s_first + bp;
+    uint32_t* s_t = s_kx + one_padded(cand_cap);
+    uint16_t* s_x = reinterpret_cast<uint16_t*>(s_t + one_padded(cand_cap > r ? cand_cap : r));
+    __shared__ int s_seg[WAVE];                 // Bernoulli: heads per stretch of WAVE positions
+    __shared__ int s_bad;
+    __shared__ int s_slot[ONE_PLANNED], s_class[ONE_PLANNED], s_fwd[ONE_PLANNED];    // the rows planned last: slot (-1: not moved), class, writer
     if (tid == 0) s_bad = 0;
 
     // ---- candidates: positions ----
     int m = c;                                  // number of candidates
     int at[ONE_PER];                            // Bernoulli: list index of position tid + u * ONE_TPB, -1: not selected
     uint64_t bits[ONE_PER];                     // random bits of sampling draw tid + u * ONE_TPB
-    if (bernoulli) {
-        uint64_t heads[ONE_PER];
+    if (gather) {
 #pragma unroll
-        for (int u = 0; u < ONE_PER; ++u) {
+        for (int u = 0; u < ONE_PER; u += 2) {              // (two at a time: one draw is a chain of twenty dependent multiplications)
+            if (u * ONE_TPB >= r) break;
+            bits[u] = draw64(sd, PURPOSE_SAMPLE, (uint32_t)(tid + u * ONE_TPB));
+            bits[u + 1] = draw64(sd, PURPOSE_SAMPLE, (uint32_t)(tid + (u + 1) * ONE_TPB));
+        }
+    }
+    if constexpr (BERNOULLI) {
+        uint32_t heads = 0;                     // bit u: the coin of position tid + u * ONE_TPB
+#pragma unroll 1
+        for (int u = 0; u * ONE_TPB < b; ++u) {
             const int q = tid + u * ONE_TPB;
-            heads[u] = 0;
-            if (u * ONE_TPB < b) heads[u] = __ballot(q < b && (int64_t)below(a.sd, PURPOSE_COIN, (uint32_t)q, (uint64_t)b) < c);
-            if (lane == 0) s_seg[u * ONE_NWAVE + wave] = __popcll(heads[u]);
+            const bool head = q < b && (int)below(sd, PURPOSE_COIN, (uint32_t)q, (uint64_t)b) < c;
+            heads |= (uint32_t)head << u;
+            const int in_seg = __popcll(__ballot(head));
+            if (lane == 0) s_seg[u * ONE_NWAVE + wave] = in_seg;
         }
         lds_barrier();
-        const int incl = wave_scan_incl(s_seg[lane]);
-        m = lane_read(incl, WAVE - 1);
         static_assert(ONE_PER * ONE_NWAVE == WAVE, "one lane per stretch of positions");
+        const int segs = (b + ONE_TPB - 1) / ONE_TPB * ONE_NWAVE;
+        const int incl = wave_scan_incl(lane < segs ? s_seg[lane] : 0);
+        m = lane_read(incl, WAVE - 1);
 #pragma unroll
         for (int u = 0; u < ONE_PER; ++u) {
-            const int seg = u * ONE_NWAVE + wave;
-            const bool mine = (heads[u] >> lane) & 1;
-            at[u] = mine ? lane_read(incl, seg) - __popcll(heads[u] >> lane) : -1;       // (this one and the heads behind it)
+            if (u * ONE_TPB >= b) break;
+            const bool mine = (heads >> u) & 1;
+            const uint64_t seg_heads = __ballot(mine);
+            at[u] = mine ? lane_read(incl, u * ONE_NWAVE + wave) - __popcll(seg_heads >> lane) : -1;       // (this one and the heads behind it)
             if (mine) s_x[at[u]] = (uint16_t)(tid + u * ONE_TPB);
         }
     } else if (c <= WAVE) {
         if (wave == 0) {
             bool active;
-            const int x = wave_select(a.sd, b, c, s_first, active);
+            const int x = wave_select(sd, b, c, s_first, active);
             if (active) s_x[lane] = (uint16_t)x;
         }
     } else {
         // Floyd's c-subset, all draws at once (see rb_update_kernel)
         const int base = b - c;
-        for (int i = 4 * tid; i < b; i += 4 * ONE_TPB) *reinterpret_cast<uint4*>(s_first + i) = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
-        for (int i = tid; i < c; i += ONE_TPB) s_t[i] = (uint32_t)below(a.sd, PURPOSE_SELECT, (uint32_t)i, (uint64_t)(base + i + 1));
+#pragma unroll 1
+        for (int i0 = tid; i0 < c; i0 += 2 * ONE_TPB) {
+            const int i1 = i0 + ONE_TPB;
+            const uint64_t d0 = draw64(sd, PURPOSE_SELECT, (uint32_t)i0), d1 = draw64(sd, PURPOSE_SELECT, (uint32_t)i1);
+            const uint32_t t0 = reduce32(d0, (uint32_t)(base + i0 + 1)), t1 = reduce32(d1, (uint32_t)(base + i1 + 1));
+            s_t[i0] = t0;
+            s_first[t0] = 0xFFFFFFFFu;
+            if (i1 < c) { s_t[i1] = t1; s_first[t1] = 0xFFFFFFFFu; }
+        }
         lds_barrier();
         for (int i = tid; i < c; i += ONE_TPB) atomicMin(&s_first[s_t[i]], (uint32_t)i);
         lds_barrier();
         // a draw is replaced iff an earlier one had the same value, or it is base + q for an earlier q that was replaced
+#pragma unroll 2
         for (int i = tid; i < c; i += ONE_TPB) {
             const int own = (int)s_t[i];
-            int t = own, cur = i;
-            bool taken = false;
-            for (;;) {
-                if (s_first[t] != (uint32_t)cur) { taken = true; break; }
-                const int q = t - base;
-                if (q < 0 || q >= cur) break;
+            bool taken = s_first[own] != (uint32_t)i;
+            int cur = i, q = own - base;
+            while (!taken && q >= 0 && q < cur) {
                 cur = q;
-                t = (int)s_t[cur];
+                const int d = (int)s_t[cur];
+                taken = s_first[d] != (uint32_t)cur;
+                q = d - base;
             }
             s_x[i] = (uint16_t)(taken ? base + i : own);
         }
     }
-    if (gather) {
-#pragma unroll
-        for (int u = 0; u < ONE_PER; ++u)
-            bits[u] = u * ONE_TPB < r ? draw64(a.sd, PURPOSE_SAMPLE, (uint32_t)(tid + u * ONE_TPB)) : 0;
-    }
+    lines.arrived();
     lds_barrier();
 
     // classes of the candidates; ends with a barrier after which the list is complete
-    const auto listed = [&](int x, int64_t y) { return (y >= 0 && y < a.K) ? ((uint32_t)y << ONE_POS_BITS) | (uint32_t)x : ONE_NO_CLASS; };
+    const auto listed = [&](int x, int64_t y) { return (uint64_t)y < (uint64_t)a.K ? ((uint32_t)y << ONE_POS_BITS) | (uint32_t)x : ONE_NO_CLASS; };
     const auto classes = [&]() {
         for (int q = m + tid; q < one_padded(m); q += ONE_TPB) s_kx[q] = ONE_NO_CLASS;
-        if (bernoulli) {
+        if constexpr (BERNOULLI) {
 #pragma unroll
             for (int u = 0; u < ONE_PER; ++u) {
                 if (u * ONE_TPB >= b) break;
@@ -340,17 +392,26 @@ __global__ void __launch_bounds__(ONE_TPB) rb_step_one_kernel(const OneArgs sa)
                 asm volatile("" : "+v"(y));     // keeps the range test, and so the wait for the label, from moving up
                 if (at[u] >= 0) s_kx[at[u]] = listed(tid + u * ONE_TPB, y);
             }
-        } else {
+        } else if (parked) {
 #pragma unroll
-            for (int u = 0; u < ONE_PER; ++u) {
+            for (int u = 0; u < ONE_PARKED / ONE_TPB; ++u) {
                 if (u * ONE_TPB >= b) break;
-                const int q = min(tid + u * ONE_TPB, b - 1);        // (threads past the end hold the last one, too)
+                const int q = tid + u * ONE_TPB;
                 int64_t y = yv[u];
                 asm volatile("" : "+v"(y));
-                s_lab[q] = listed(q, y);
+                if (q < b) s_lab[q] = listed(q, y);
             }
             lds_barrier();
             for (int q = tid; q < c; q += ONE_TPB) s_kx[q] = s_lab[s_x[q]];
+        } else {
+            asm volatile("" : : "v"(near_label));
+            for (int i0 = tid; i0 < c; i0 += 2 * ONE_TPB) {
+                const int i1 = i0 + ONE_TPB;
+                const int x0 = s_x[i0], x1 = s_x[min(i1, c - 1)];
+                const int64_t y0 = batch_y[x0], y1 = batch_y[x1];
+                s_kx[i0] = listed(x0, y0);
+                if (i1 < c) s_kx[i1] = listed(x1, y1);
+            }
         }
         lds_barrier();
     };
@@ -359,9 +420,9 @@ __global__ void __launch_bounds__(ONE_TPB) rb_step_one_kernel(const OneArgs sa)
 
     if (!gather) {
         // ---- candidate movers ----
-        const int items = m * a.tpr, nwg = sa.nwg - sa.first_cand;
+        const int items = m * a.tpr, nwg = sa.nwg - first_cand;
         const int share = sa.cshare != 0 ? sa.cshare : (items + nwg - 1) / nwg;
-        const int lo = ((int)blockIdx.x - sa.first_cand) * share, hi = min(lo + share, items);
+        const int lo = ((int)blockIdx.x - first_cand) * share, hi = min(lo + share, items);
         if (lo >= hi) return;
         // A row is requested as soon as its position is known, before the labels have arrived (by every wavefront: a load
         // that only some issue would make the wait for the labels a wait for the rows).
@@ -389,7 +450,8 @@ __global__ void __launch_bounds__(ONE_TPB) rb_step_one_kernel(const OneArgs sa)
                 }
                 if (lane == 0) s_slot[i - row] = slot;
             }
-            lds_barrier();
+            if (a.tpr == 1) wave_lds_wait();        // (the rows a wavefront moves are the ones it planned)
+            else lds_barrier();
             for (; it < min(hi, end * a.tpr); it += ONE_NWAVE) {
                 const int i = it / a.tpr, tile = it - i * a.tpr;
                 const int slot = __builtin_amdgcn_readfirstlane(s_slot[i - row]);
@@ -405,39 +467,42 @@ __global__ void __launch_bounds__(ONE_TPB) rb_step_one_kernel(const OneArgs sa)
                 }
                 loaded = false;
             }
-            if (end * a.tpr < hi) lds_barrier();
+            if (a.tpr != 1 && end * a.tpr < hi) lds_barrier();
         }
         return;
     }
 
+    // ---- fill counts after the update (not yet cut off at the capacity: step_form keeps S + RB_MAX_BATCH within 32 bits) ----
+    for (int i = tid; i < nfill / 32; i += ONE_TPB) s_hit[i] = 0u;
+    if (wave == 0) s_chunk[lane] = chunk_sum;
 #pragma unroll
     for (int u = 0; u < ONE_FILL_PER; ++u) {
         if (u * 4 * ONE_TPB >= nfill) break;
-        *reinterpret_cast<int4*>(s_fill + min(4 * (tid + u * ONE_TPB), nfill - 4)) = fo[u];
+        if (4 * (tid + u * ONE_TPB) < nfill) *reinterpret_cast<int4*>(s_fill + 4 * (tid + u * ONE_TPB)) = fo[u];
     }
     classes();
-
-    // ---- fill counts after the update (not yet cut off at the capacity: step_form keeps S + RB_MAX_BATCH within 32 bits) ----
-    for (int q = tid; q < m; q += ONE_TPB) {
-        const uint32_t kx = s_kx[q];
-        if (kx != ONE_NO_CLASS) atomicAdd(&s_fill[kx >> ONE_POS_BITS], 1);
-        else s_bad = 1;
+    const int32_t cap = (int32_t)a.S;
+    for (int q = tid; q < m; q += 2 * ONE_TPB) {
+        const uint32_t kx[2] = {s_kx[q], q + ONE_TPB < m ? s_kx[q + ONE_TPB] : ONE_NO_CLASS};
+        int held[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            if (kx[u] != ONE_NO_CLASS) held[u] = atomicAdd(&s_fill[kx[u] >> ONE_POS_BITS], 1);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const uint32_t k = kx[u] >> ONE_POS_BITS;
+            if (kx[u] == ONE_NO_CLASS) {
+                if (q + u * ONE_TPB < m) s_bad = 1;
+                continue;
+            }
+            atomicOr(&s_hit[k >> 5], 1u << (k & 31));
+            if (held[u] < cap) atomicAdd(&s_chunk[k / CH], 1);      // one more sample of the class
+        }
     }
     lds_barrier();
-    const int32_t cap = (int32_t)(a.S < INT32_MAX ? a.S : INT32_MAX);
-    // stored samples before every thread's stretch of `per` classes (a multiple of four)
-    const int per = (nfill / 4 + ONE_TPB - 1) / ONE_TPB * 4;
-    int local = 0;
-    for (int k = tid * per; k < min(tid * per + per, nfill); k += 4) {
-        const int4 f = *reinterpret_cast<const int4*>(s_fill + k);
-        local += min(f.x, cap) + min(f.y, cap) + min(f.z, cap) + min(f.w, cap);
-    }
-    const int incl = wave_scan_incl(local);
-    if (lane == WAVE - 1) s_wave[wave] = incl;
-    lds_barrier();
-    const int wincl = wave_scan_incl(lane < ONE_NWAVE ? s_wave[lane] : 0);
-    const int F = lane_read(wincl, ONE_NWAVE - 1);
-    s_before[tid] = (wave > 0 ? lane_read(wincl, wave - 1) : 0) + incl - local;
+    // stored samples up to and including chunk `lane`
+    const int in_chunk = s_chunk[lane], upto = wave_scan_incl(in_chunk);
+    const int F = lane_read(upto, WAVE - 1);
     const int n = r < F ? r : F;
     const int base = F - n;
 #pragma unroll
@@ -466,42 +531,41 @@ __global__ void __launch_bounds__(ONE_TPB) rb_step_one_kernel(const OneArgs sa)
             }
             // draw j is replaced by base + j iff an earlier draw had the same value, or it equals
             // base + q for an earlier q whose own draw was replaced
-            int cur = j;
+            const int own = __builtin_amdgcn_readfirstlane((int)s_t[j]);
+            int cur = j, tc = own;
             bool taken = false;
             for (;;) {
-                const uint32_t tc = s_t[cur];
                 bool same = false;
+#pragma unroll 4
                 for (int q0 = 0; q0 < cur; q0 += ONE_LIST) {
-                    uint32_t v[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) v[u] = s_t[q0 + u * WAVE + lane];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) same |= q0 + u * WAVE + lane < cur && v[u] == tc;
+                    const uint4 v = *reinterpret_cast<const uint4*>(s_t + q0 + 4 * lane);
+                    const int left = cur - q0 - 4 * lane;           // of the lane's words, those before draw `cur`
+                    same |= (v.x == (uint32_t)tc && left > 0) | (v.y == (uint32_t)tc && left > 1) | (v.z == (uint32_t)tc && left > 2) | (v.w == (uint32_t)tc && left > 3);
                 }
                 if (__ballot(same) != 0) { taken = true; break; }
-                const int q = __builtin_amdgcn_readfirstlane((int)tc) - base;
+                const int q = tc - base;
                 if (q < 0 || q >= cur) break;
                 cur = q;
+                tc = __builtin_amdgcn_readfirstlane((int)s_t[cur]);
             }
-            const int g = taken ? base + j : __builtin_amdgcn_readfirstlane((int)s_t[j]);     // class-major number of the sample
-            // the stretch of classes that holds it (the last one that starts at or before it), then the class
-            constexpr int STEP = ONE_TPB / WAVE;
-            const int big = __popcll(__ballot(s_before[STEP * lane] <= g)) - 1;
-            const int owner = STEP * big + __popcll(__ballot(lane < STEP && s_before[STEP * big + (lane & (STEP - 1))] <= g)) - 1;
-            const int gl = g - __builtin_amdgcn_readfirstlane(s_before[owner]);
-            const int kl = owner * per + lane;
-            const int held = lane < per && kl < nfill ? min(s_fill[kl], cap) : 0;
-            const int hincl = wave_scan_incl(held);
-            const int u = __popcll(__ballot(lane < per && hincl <= gl));
-            const int pk = owner * per + u, ps = gl - (lane_read(hincl, u) - lane_read(held, u));
-            const int fwd = one_writer(a, s_kx, m, pk, ps, s_fill[pk], pend, cm, cmpre);
+            const int g = taken ? base + j : own;          // class-major number of the sample
+            // the chunk of classes that holds it (the number of chunks that end at or before it), then the class
+            const int ch = __popcll(__ballot(upto <= g));
+            const int4 f = *reinterpret_cast<const int4*>(s_fill + ch * CH + 4 * lane);
+            int owner, sub, ps;
+            WaveFill(make_int4(min(f.x, cap), min(f.y, cap), min(f.z, cap), min(f.w, cap)))
+                .locate(g - (lane_read(upto, ch) - lane_read(in_chunk, ch)), owner, sub, ps);
+            const int pk = ch * CH + 4 * owner + sub;
+            int fwd = -1;
+            if ((__builtin_amdgcn_readfirstlane((int)s_hit[pk >> 5]) >> (pk & 31)) & 1) fwd = one_writer(a, s_kx, m, pk, ps, s_fill[pk], pend, cm, cmpre);
             if (lane == 0) {
                 s_slot[j - row] = ps;
                 s_class[j - row] = pk;
                 s_fwd[j - row] = fwd;
             }
         }
-        lds_barrier();
+        if (sa.tpr == 1) wave_lds_wait();           // (the rows a wavefront moves are the ones it planned)
+        else lds_barrier();
         for (; it < min(hi, end * sa.tpr); it += ONE_NWAVE) {
             const int j = it / sa.tpr, tile = it - j * sa.tpr;
             const int ps = __builtin_amdgcn_readfirstlane(s_slot[j - row]);
@@ -525,17 +589,16 @@ __global__ void __launch_bounds__(ONE_TPB) rb_step_one_kernel(const OneArgs sa)
             }
             if (tile == 0 && lane == 0) { sa.out_y[j] = pk; count_moved(a.state); }
         }
-        if (end * sa.tpr < hi) lds_barrier();
+        if (sa.tpr != 1 && end * sa.tpr < hi) lds_barrier();
     }
 
     // ---- books: new fill counts, their sums per chunk, the strategy's state (a chunk per wavefront, dealt over the workgroups) ----
-    for (int ch = wave * sa.first_cand + blockIdx.x; ch < a.nchunks; ch += sa.first_cand * ONE_NWAVE) {
+    for (int ch = wave * first_cand + blockIdx.x; ch < nchunks; ch += first_cand * ONE_NWAVE) {
         const int k0 = ch * CH + 4 * lane;
         const int4 v = *reinterpret_cast<const int4*>(s_fill + k0);
         const int4 f = make_int4(min(v.x, cap), min(v.y, cap), min(v.z, cap), min(v.w, cap));
         *reinterpret_cast<int4*>(a.fill_new + k0) = f;
-        const int sum = lane_read(wave_scan_incl(f.x + f.y + f.z + f.w), WAVE - 1);
-        if (lane == 0) a.chunk_new[ch] = sum;
+        if (lane == 0) a.chunk_new[ch] = s_chunk[ch];
         if (a.eviction != RB_EVICT_UNIFORM) {
             const int4 old4 = *reinterpret_cast<const int4*>(a.fill_old + k0);
             const int4 aux4 = *reinterpret_cast<const int4*>(a.aux_old + k0);

@@ -96,7 +96,8 @@ __device__ __forceinline__ int mate_slot(const UpdateArgs& a, int x, int rank, i
 {
     const int64_t at = fill0 + rank;
     if (at < a.S) return (int)at;
-    if (a.eviction == RB_EVICT_FIFO) return (int)((aux0 + at - a.S) % a.S);
+    // (aux0 < S and at - S < RB_MAX_BATCH: 32 unsigned bits; a 64-bit remainder is some hundred instructions)
+    if (a.eviction == RB_EVICT_FIFO) return (int)((uint32_t)(aux0 + at - a.S) % (uint32_t)a.S);
     const bool reservoir = a.eviction == RB_EVICT_RESERVOIR;
     const int64_t offers = aux0 + rank < INT32_MAX ? aux0 + rank : INT32_MAX;      // to the class, before this one
     const int64_t draw = (int64_t)below(a.sd, PURPOSE_EVICT, (uint32_t)x, reservoir ? (uint64_t)offers + 1 : (uint64_t)a.S);
@@ -108,7 +109,7 @@ __device__ __forceinline__ int32_t next_aux(const UpdateArgs& a, int64_t old, in
 {
     if (a.eviction == RB_EVICT_FIFO) {
         const int64_t over = old + count > a.S ? old + count - a.S : 0;            // the oldest sample moves on by the overwrites
-        return (int32_t)((aux + over) % a.S);
+        return (int32_t)((uint32_t)(aux + over) % (uint32_t)a.S);
     }
     const int64_t seen = aux + count;
     return (int32_t)(seen < INT32_MAX ? seen : INT32_MAX);
