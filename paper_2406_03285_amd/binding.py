@@ -1,4 +1,4 @@
-"""Thin ctypes binding of the C ABI in include/rb.h (argument marshalling only).
+"""Thin binding of the C ABI in include/rb.h (argument marshalling only): ctypes, and a native one for the calls of every step.
 
 Every function has the name and argument order of its C counterpart; tensors
 are passed as device pointers.  PyTorch is used for device memory and streams
@@ -8,6 +8,8 @@ import ctypes as C
 import os
 
 import torch  # first: the library must bind to the HIP runtime PyTorch has loaded
+
+from ._calls import Call
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.environ.get("RB_LIBRARY") or os.path.join(HERE, "librb.so")   # RB_LIBRARY: another build of the same library
@@ -156,6 +158,17 @@ def rb_announce_next_many(rb, n, next_batch_y):
     """next_batch_y: sequence of n label tensors / addresses, or an array made by pointer_array."""
     arr = next_batch_y if next_batch_y is None or isinstance(next_batch_y, (C.Array, C._Pointer)) else pointer_array(next_batch_y)
     return _L.rb_announce_next_many(rb, int(n), arr)
+
+
+def _native(general, layout):
+    """The same function with its usual arguments (integers, None, tensors) marshalled natively; everything else goes to `general`."""
+    return Call(C.cast(getattr(_L, general.__name__), C.c_void_p).value, layout, general)
+
+
+rb_update = _native(rb_update, "hppiiii")
+rb_sample_augment = _native(rb_sample_augment, "hiiipp")
+rb_update_sample = _native(rb_update_sample, "hppiiiiipp")
+rb_announce_next = _native(rb_announce_next, "hp")
 
 
 def rb_query_steps_per_launch(rb, b, c, r):

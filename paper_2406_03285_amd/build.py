@@ -1,6 +1,7 @@
 """Compile the HIP library (csrc/rb.hip and the headers it includes -> librb.so, gfx950 only) in-tree with hipcc."""
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -18,6 +19,10 @@ HIPCC_FLAGS = [
 ]
 
 
+# The calls of a training loop without ctypes in between (a CPython extension, given the library's functions by the binding)
+CALLS_SRC = os.path.join(HERE, "csrc", "rb_calls.c")
+CALLS = os.path.join(HERE, "_calls.so")
+
 # A caller that is not Python: a plain C program against include/rb.h and the HIP runtime API (used by a GPU test).
 CLIENT_SRC = os.path.join(ROOT, "tests", "c_client", "rb_client.c")
 CLIENT = os.path.join(ROOT, "tests", "c_client", "rb_client")
@@ -27,6 +32,10 @@ ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", os.path.join(ROCM, "bin", "hipcc"))
     cmd = [hipcc, *HIPCC_FLAGS, "-I", INCLUDE, SRC, "-o", LIB]
+    if verbose:
+        print(" ".join(cmd))
+    subprocess.run(cmd, check=True)
+    cmd = ["gcc", "-std=c11", "-O2", "-Wall", "-Werror", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"], CALLS_SRC, "-o", CALLS]
     if verbose:
         print(" ".join(cmd))
     subprocess.run(cmd, check=True)

@@ -30,6 +30,43 @@ def test_binding_has_the_same_names():
         assert callable(getattr(rb, name))
 
 
+@pytest.mark.parametrize("layout", ["hp", "hiiipp", "hppiiii", "hppiiiiipp"])
+def test_native_marshalling_passes_what_ctypes_passes(layout):
+    """Integers of any size, None, tensors, bools, floats, numpy numbers, keywords, wrong counts and types."""
+    import numpy as np
+    import torch
+    from paper_2406_03285_amd import binding
+    ctype = {"h": C.c_void_p, "p": C.c_void_p, "i": C.c_int64}
+    seen = []
+    entry = C.CFUNCTYPE(C.c_int, *[C.c_uint64] * len(layout))(lambda *a: seen.append(a) or len(a) - 5)
+    through_ctypes = C.cast(entry, C.CFUNCTYPE(C.c_int, *[ctype[k] for k in layout]))
+    names = [f"a{i}" for i in range(len(layout))]
+
+    def general(*args, **kw):
+        args = args + tuple(kw[n] for n in names[len(args):])
+        return through_ctypes(*[binding._ptr(v) if k == "p" else int(v) if k == "i" else v for v, k in zip(args, layout, strict=True)])
+
+    native = binding.Call(C.cast(entry, C.c_void_p).value, layout, general)
+    t = torch.zeros(4)
+    usual = {"h": 2 ** 47 + 8, "p": 2 ** 46 + 16, "i": 5}
+    odd = {"h": [None, 0, 7, C.c_void_p(9), 3.5], "p": [None, 0, t, True, 3.5, object()],
+           "i": [0, -1, 2 ** 63, 2 ** 64 - 1, 2 ** 64 + 3, -2 ** 70, True, 2.75, np.int64(-4), np.float32(2.0), torch.tensor(6), "8", None, []]}
+    cases = [(tuple(usual[k] for k in layout), {})]
+    for i, k in enumerate(layout):
+        cases += [(tuple(v if j == i else usual[q] for j, q in enumerate(layout)), {}) for v in odd[k]]
+    cases += [(cases[0][0][:-1], {}), (cases[0][0] + (1,), {}), (cases[0][0][:1], dict(zip(names[1:], cases[0][0][1:])))]
+    for args, kw in cases:
+        got = []
+        for f in (native, general):
+            seen.clear()
+            try:
+                got.append((f(*args, **kw), list(seen)))
+            except Exception as e:      # noqa: BLE001  (the same refusal from both)
+                got.append((type(e), list(seen)))
+        assert got[0] == got[1], (args, kw)
+    assert native.__wrapped__ is general and native.__name__ == "general"
+
+
 def test_create_validation_and_sizes():
     import paper_2406_03285_amd as rb
     rc, h = rb.rb_create(1000, 130, (3, 224, 224), rb.RB_F32)
