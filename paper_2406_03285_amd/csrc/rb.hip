@@ -350,16 +350,20 @@ Seed make_seed(uint64_t seed, uint64_t step)
 template <bool NT, int ST>
 hipError_t launch_planned_s(const MoveArgs& m, const PlanArgs& next, int unroll, dim3 grid, size_t lds, hipStream_t st)
 {
+    const auto go = [&](auto kernel) {
+        kernel<<<grid, TPB, lds, st>>>(m.table, m.batch_x, m.buf_x, m.out_x, m.row_vec, (uint32_t)(m.c | m.r << 16),
+                                       (uint32_t)m.tpr | (uint32_t)m.plan_next << 31, m.tile_vec, m.tile_rem, m, next);
+    };
     switch (unroll) {
-    case 1: rb_step_planned_kernel<1, NT, ST><<<grid, TPB, lds, st>>>(m, next); break;
-    case 2: rb_step_planned_kernel<2, NT, ST><<<grid, TPB, lds, st>>>(m, next); break;
+    case 1: go(rb_step_planned_kernel<1, NT, ST>); break;
+    case 2: go(rb_step_planned_kernel<2, NT, ST>); break;
     case 4:
         if constexpr (ST == RB_STORE_U8) return hipErrorInvalidValue;    // (at most two vectors per lane: step_planned)
-        else rb_step_planned_kernel<4, NT, ST><<<grid, TPB, lds, st>>>(m, next);
+        else go(rb_step_planned_kernel<4, NT, ST>);
         break;
     default:
         if constexpr (ST != RB_STORE_SAME) return hipErrorInvalidValue;  // (bfloat16 rows: at most four)
-        else rb_step_planned_kernel<8, NT, ST><<<grid, TPB, lds, st>>>(m, next);
+        else go(rb_step_planned_kernel<8, NT, ST>);
         break;
     }
     return hipGetLastError();
@@ -521,7 +525,9 @@ hipError_t launch_big_u(const MoveArgs& m, const PlanArgs& next, const uint32_t*
             const hipError_t e = allow_big_lds<&rb_step_big_kernel<U, NT, ST>>();
             if (e != hipSuccess) return e;
         }
-        rb_step_big_kernel<U, NT, ST><<<grid, BIG_TPB, lds, st>>>(m, next, fwd, fwd_next);
+        rb_step_big_kernel<U, NT, ST><<<grid, BIG_TPB, lds, st>>>(m.table, m.batch_x, m.buf_x, m.out_x, m.row_vec, (uint32_t)(m.cgrid | m.r << 16),
+                                                                  (uint32_t)m.tpr | (uint32_t)m.plan_next << 31,
+                                                                  m.tile_vec, m.tile_rem, m, next, fwd, fwd_next);
         return hipGetLastError();
     }
 }

@@ -450,26 +450,40 @@ __global__ void __launch_bounds__(BIG_TPB) rb_big_plan_kernel(const PlanArgs a, 
 // row (candidates first, then representatives); with plan_next the first
 // workgroup of the grid plans the next step instead.
 // ---------------------------------------------------------------------------
+struct BigKernelArgs {
+    MoveLead lead;
+    MoveArgs m;
+    PlanArgs next;
+    const uint32_t* fwd;
+    uint32_t* fwd_next;
+};
+
 template <int U, bool NT, int ST>           // ST: RB_STORE_*, the form binary32 samples are stored in (row_vec counts stored vectors)
-__global__ void __launch_bounds__(BIG_TPB) rb_step_big_kernel(const MoveArgs m, const PlanArgs next, const uint32_t* fwd, uint32_t* fwd_next)
+__global__ void __launch_bounds__(BIG_TPB) rb_step_big_kernel(const char* table, const vec16* batch_x, vec16* buf_x, vec16* out_x, int64_t row_vec,
+                                                              uint32_t cgrid_r, uint32_t tpr_plan, int32_t tile_vec, int32_t tile_rem,
+                                                              const MoveArgs, const PlanArgs, const uint32_t*, uint32_t*)
 {
     extern __shared__ uint32_t lds[];
-    const int planners = m.plan_next != 0 ? 2 : 0;
+    const BigKernelArgs& all = kernel_argument<BigKernelArgs>(0);
+    const MoveArgs& m = all.m;
+    const uint32_t* fwd = all.fwd;
+    const int cgrid = (int)(cgrid_r & 0xFFFFu), r = (int)(cgrid_r >> 16);
+    const int tpr = (int)(tpr_plan & 0x7FFFFFFFu), planners = tpr_plan >> 31 != 0 ? 2 : 0;
     if ((int)blockIdx.x < planners) {          // dispatched first: they have the longest way to go
         __builtin_amdgcn_s_setprio(3);
-        if (blockIdx.x == 0) plan_big_update(next, lds, fwd_next);
-        else plan_big_sample(next, lds);
+        if (blockIdx.x == 0) plan_big_update(all.next, lds, all.fwd_next);
+        else plan_big_sample(all.next, lds);
         return;
     }
     const int64_t item = (int64_t)((int)blockIdx.x - planners) * BIG_GROUPS + threadIdx.x / BIG_GROUP;
-    const int64_t items = (int64_t)(m.cgrid + m.r) * m.tpr;
+    const int64_t items = (int64_t)(cgrid + r) * tpr;
     if (item >= items) return;
     int e, tile;
-    split_item(item, m.tpr, e, tile);
-    const PlanHeader* head = reinterpret_cast<const PlanHeader*>(m.table);
-    const PlanEntry* entry = reinterpret_cast<const PlanEntry*>(m.table + sizeof(PlanHeader));
+    split_item(item, tpr, e, tile);
+    const PlanHeader* head = reinterpret_cast<const PlanHeader*>(table);
+    const PlanEntry* entry = reinterpret_cast<const PlanEntry*>(table + sizeof(PlanHeader));
     int64_t v_lo, v_hi;
-    tile_bounds(tile, m.tile_vec, m.tile_rem, m.row_vec, v_lo, v_hi);
+    tile_bounds(tile, tile_vec, tile_rem, row_vec, v_lo, v_hi);
     const bool first = tile == 0 && (threadIdx.x & (BIG_GROUP - 1)) == 0;
     if (item == 0 && first) {
         const PlanHeader hh = *head;
@@ -477,35 +491,35 @@ __global__ void __launch_bounds__(BIG_TPB) rb_step_big_kernel(const MoveArgs m, 
         if (hh.flags != 0) atomicOr(&m.state->flags, hh.flags);
     }
     constexpr int WIDE = stored_wide(ST);         // vectors of a mini-batch / output row per vector of a stored row
-    if (e < m.cgrid) {
+    if (e < cgrid) {
         // the grid covers cgrid candidate rows; when the plan has more (Bernoulli selection: their number is random),
         // a group goes on to the entry cgrid further on
         const int count = (int)fwd[2 * BIG_HASH];
-        for (int ee = e; ee < count; ee += m.cgrid) {
+        for (int ee = e; ee < count; ee += cgrid) {
             const PlanEntry en = entry[ee];
             if (en.row < 0) continue;           // label outside [0, K), or a later class-mate takes the slot
             if (first) { m.buf_y[en.row] = en.label; count_moved(m.state); }
             Tile<U, NT, BIG_GROUP, true, stored_cv(ST, CV_NARROW)> t;
-            t.load(m.batch_x + (int64_t)en.pos * m.row_vec * WIDE, v_lo, v_hi);
-            t.store(m.buf_x + en.row * m.row_vec, v_lo, v_hi);
+            t.load(batch_x + (int64_t)en.pos * row_vec * WIDE, v_lo, v_hi);
+            t.store(buf_x + en.row * row_vec, v_lo, v_hi);
         }
         return;
     }
-    const int j = e - m.cgrid;
+    const int j = e - cgrid;
     const PlanEntry en = entry[m.c + j];
     if (first) m.out_y[j] = en.label;           // -1 when fewer samples are stored than asked for
     if (en.label < 0) return;
     if (first) count_moved(m.state);
     // written in this very step?  Then the stored candidate's mini-batch row is what the slot will hold.
     const int pos = en.pos == BIG_LOOK_UP ? big_forwarded(fwd, (uint32_t)en.row) : -1;
-    vec16* dst = m.out_x + (int64_t)j * m.row_vec * WIDE;
+    vec16* dst = out_x + (int64_t)j * row_vec * WIDE;
     if (ST != RB_STORE_SAME && pos >= 0) {
         // forwarded from the mini-batch: what the slot will hold is the row in its stored form
         Tile<U, NT, BIG_GROUP, true, stored_cv(ST, CV_BOTH)> t;
-        t.load(m.batch_x + (int64_t)pos * m.row_vec * WIDE, v_lo, v_hi);
+        t.load(batch_x + (int64_t)pos * row_vec * WIDE, v_lo, v_hi);
         t.store(dst, v_lo, v_hi);
     } else {
-        const vec16* src = pos >= 0 ? m.batch_x + (int64_t)pos * m.row_vec : m.buf_x + en.row * m.row_vec;
+        const vec16* src = pos >= 0 ? batch_x + (int64_t)pos * row_vec : buf_x + en.row * row_vec;
         Tile<U, NT, BIG_GROUP, true, stored_cv(ST, CV_WIDEN)> t;
         t.load(src, v_lo, v_hi);
         t.store(dst, v_lo, v_hi);

@@ -307,18 +307,45 @@ __global__ void __launch_bounds__(TPB) rb_plan_kernel(const PlanArgs a)
     plan_step(a, lds);
 }
 
+// What a mover needs to request its row comes as arguments of its own in front of the structures (the hardware puts them into scalar
+// registers when it starts a wavefront), the structures are read where they are used: a mover starts with the trip for its table entry
+// instead of one for the arguments in front of it.  A step with the next one announced, us, before and after: 64 + 64 rows of 301 KB
+// 14.7 -> 14.3, 10 + 6 of 250 KB in 8 bits 5.0 -> 4.5, 21 + 18 of 474 KB as bfloat16 7.1 -> 6.75; the large-count launch, 31 + 45 rows
+// of 146 KB as bfloat16, Bernoulli, 7.1 -> 6.8.
+struct MoveLead {
+    const char* table;
+    const vec16* batch_x;
+    vec16* buf_x;
+    vec16* out_x;
+    int64_t row_vec;
+    uint32_t c_r;             // candidate rows the grid covers | representatives << 16
+    uint32_t tpr_plan;        // tiles per row | planners in front of the movers << 31
+    int32_t tile_vec, tile_rem;
+};
+struct PlannedKernelArgs {
+    MoveLead lead;
+    MoveArgs m;
+    PlanArgs next;
+};
+static_assert(sizeof(MoveLead) == 14 * sizeof(uint32_t), "what fits the scalar registers");
+
 // ---------------------------------------------------------------------------
 // One step by its table: workgroup (e, tile) moves one tile of row e (candidates
 // first, then representatives); with plan_next the first workgroup of the grid
 // plans the next step instead.
 // ---------------------------------------------------------------------------
 template <int U, bool NT, int ST>           // ST: RB_STORE_*, the form binary32 samples are stored in (row_vec counts stored vectors)
-__global__ void __launch_bounds__(TPB) rb_step_planned_kernel(const MoveArgs m, const PlanArgs next)
+__global__ void __launch_bounds__(TPB) rb_step_planned_kernel(const char* table, const vec16* batch_x, vec16* buf_x, vec16* out_x, int64_t row_vec,
+                                                              uint32_t c_r, uint32_t tpr_plan, int32_t tile_vec, int32_t tile_rem,
+                                                              const MoveArgs, const PlanArgs)
 {
     extern __shared__ uint32_t lds[];
-    const bool plan_next = m.plan_next != 0;
+    const MoveArgs& m = kernel_argument<MoveArgs>(offsetof(PlannedKernelArgs, m));
+    const int c = (int)(c_r & 0xFFFFu), rows = c + (int)(c_r >> 16);
+    const int tpr = (int)(tpr_plan & 0x7FFFFFFFu);
+    const bool plan_next = tpr_plan >> 31 != 0;
     if (plan_next && blockIdx.x == 0) {        // dispatched first: it has the longest way to go
-        plan_step(next, lds);
+        plan_step(kernel_argument<PlanArgs>(offsetof(PlannedKernelArgs, next)), lds);
         return;
     }
     const int mover = blockIdx.x - (plan_next ? 1 : 0);
@@ -326,19 +353,19 @@ __global__ void __launch_bounds__(TPB) rb_step_planned_kernel(const MoveArgs m, 
     // addresses for itself: all tiles of a row are given to workgroups of one die (rows are dealt
     // to the dies in turn), so that a die touches an eighth of the rows' pages instead of all.
     int e, tile;
-    const int rows = m.c + m.r, dealt = rows / XCDS * XCDS;
-    if (mover < dealt * m.tpr) {
+    const int dealt = rows / XCDS * XCDS;
+    if (mover < dealt * tpr) {
         const int die = mover % XCDS, i = mover / XCDS;
-        e = i / m.tpr * XCDS + die;
-        tile = i % m.tpr;
+        e = i / tpr * XCDS + die;
+        tile = i % tpr;
     } else {
-        e = mover / m.tpr;
-        tile = mover % m.tpr;
+        e = mover / tpr;
+        tile = mover % tpr;
     }
-    const PlanHeader* head = reinterpret_cast<const PlanHeader*>(m.table);
-    const PlanEntry en = reinterpret_cast<const PlanEntry*>(m.table + sizeof(PlanHeader))[e];
+    const PlanHeader* head = reinterpret_cast<const PlanHeader*>(table);
+    const PlanEntry en = reinterpret_cast<const PlanEntry*>(table + sizeof(PlanHeader))[e];
     int64_t v_lo, v_hi;
-    tile_bounds(tile, m.tile_vec, m.tile_rem, m.row_vec, v_lo, v_hi);
+    tile_bounds(tile, tile_vec, tile_rem, row_vec, v_lo, v_hi);
     const bool first = tile == 0 && threadIdx.x == 0;
     if (mover == 0 && threadIdx.x == 0) {
         const PlanHeader h = *head;
@@ -349,26 +376,26 @@ __global__ void __launch_bounds__(TPB) rb_step_planned_kernel(const MoveArgs m, 
     // burst stores for 8-bit rows (8 + 8 rows of 602 KB 6.3 -> 6.1 us, 32 + 32 13.0 -> 12.2); bfloat16 rows are paced here
     // (16 + 16 rows 7.1 against 7.6 us)
     constexpr int PACE = ST == RB_STORE_U8 ? 64 : 1;
-    if (e < m.c) {
+    if (e < c) {
         if (en.row < 0) return;                 // label outside [0, K), or a later class-mate takes the slot
         if (first) { m.buf_y[en.row] = en.label; count_moved(m.state); }
         Tile<U, NT, TPB, PACE, stored_cv(ST, CV_NARROW)> t;
-        t.load(m.batch_x + (int64_t)en.pos * m.row_vec * WIDE, v_lo, v_hi);
-        t.store(m.buf_x + en.row * m.row_vec, v_lo, v_hi);
+        t.load(batch_x + (int64_t)en.pos * row_vec * WIDE, v_lo, v_hi);
+        t.store(buf_x + en.row * row_vec, v_lo, v_hi);
         return;
     }
-    const int j = e - m.c;
+    const int j = e - c;
     if (first) m.out_y[j] = en.label;           // -1 when fewer samples are stored than asked for
     if (en.label < 0) return;
     if (first) count_moved(m.state);
-    vec16* dst = m.out_x + (int64_t)j * m.row_vec * WIDE;
+    vec16* dst = out_x + (int64_t)j * row_vec * WIDE;
     if (ST != RB_STORE_SAME && en.pos >= 0) {
         // forwarded from the mini-batch: what the slot will hold is the row in its stored form
         Tile<U, NT, TPB, PACE, stored_cv(ST, CV_BOTH)> t;
-        t.load(m.batch_x + (int64_t)en.pos * m.row_vec * WIDE, v_lo, v_hi);
+        t.load(batch_x + (int64_t)en.pos * row_vec * WIDE, v_lo, v_hi);
         t.store(dst, v_lo, v_hi);
     } else {
-        const vec16* src = en.pos >= 0 ? m.batch_x + (int64_t)en.pos * m.row_vec : m.buf_x + en.row * m.row_vec;
+        const vec16* src = en.pos >= 0 ? batch_x + (int64_t)en.pos * row_vec : buf_x + en.row * row_vec;
         Tile<U, NT, TPB, PACE, stored_cv(ST, CV_WIDEN)> t;
         t.load(src, v_lo, v_hi);
         t.store(dst, v_lo, v_hi);
