@@ -286,7 +286,8 @@ struct TileSpan {
 // and lanes that store to one place wait for each other: 64 rows of 301 KB, four vectors per thread, bare mover, 9.0 us without
 // and 7.3 with descriptors; 175 rows of 24 KB 3.6 and 3.2; 10 + 20 slots of 12 KB, two calls, 7.8 -> 7.3.  Without remains where
 // rows are whole multiples of a wavefront's accesses and many rounds of workgroups follow each other (the several-steps launch for
-// large counts, plain rows: 16 steps of 1024 + 1024 rows of 8 KB 91.2 us without, 93.5 with).
+// large counts, plain rows: 16 steps of 1024 + 1024 rows of 8 KB 91.2 us without, 93.5 with; there also rows kept as bfloat16 with
+// eight vectors per lane, which just fit the registers without: 304 + 127 rows of 12 KB, 13 steps, 42.0 us without, 43.1 with).
 // Either way no lane is masked off, so the number of loads in flight is known at compile time - a wait for an earlier load then does
 // not have to drain these - and the compiler cannot move a load down into a guarded store.
 template <int U, bool NT, int W = TPB, int PACED = 1, int CV = CV_NONE, bool LATE = false, bool DESC = true>
@@ -302,7 +303,15 @@ struct Tile {
     // 8-bit storage: 4 U quarter vectors (four bytes of the stored row against 16 bytes of the binary32 row per access)
     uint32_t q[CV & CV_Q8 && !RAW ? N : 1];
 
-    static_assert(DESC || !CV, "converted rows are moved through descriptors");
+    static_assert(DESC || !RAW, "late conversion goes through descriptors");
+    template <typename T>
+    static __device__ __forceinline__ T flat_load(const T* p) { return NT ? __builtin_nontemporal_load(p) : *p; }
+    template <typename T>
+    static __device__ __forceinline__ void flat_store(T a, T* p)
+    {
+        if (NT) __builtin_nontemporal_store(a, p);
+        else *p = a;
+    }
     static __device__ __forceinline__ int64_t clamped(int u, int64_t lo, int64_t hi)
     {
         const int64_t i = lo + (int64_t)u * W + (threadIdx.x & (W - 1));
@@ -314,9 +323,13 @@ struct Tile {
     {
         if constexpr (!DESC) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int64_t i = clamped(u, lo, hi);
-                v[u] = NT ? __builtin_nontemporal_load(src + i) : src[i];
+            for (int u = 0; u < N; ++u) {
+                const int64_t i = clamped(u, PARTS * lo, PARTS * hi);
+                if constexpr (!CV) v[u] = flat_load(src + i);
+                else if constexpr ((CV & CV_NARROW) && (CV & CV_Q8)) q[u] = pack4_u8(flat_load(src + i));
+                else if constexpr (CV & CV_NARROW) h[u] = narrow4(flat_load(src + i));
+                else if constexpr (CV & CV_Q8) q[u] = flat_load(reinterpret_cast<const uint32_t*>(src) + i);
+                else h[u] = flat_load(reinterpret_cast<const vec8*>(src) + i);
             }
             return;
         }
@@ -351,10 +364,13 @@ struct Tile {
         if (PACED) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         if constexpr (!DESC) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int64_t i = clamped(u, lo, hi);
-                if (NT) __builtin_nontemporal_store(v[u], dst + i);
-                else dst[i] = v[u];
+            for (int u = 0; u < N; ++u) {
+                const int64_t i = clamped(u, PARTS * lo, PARTS * hi);
+                if constexpr (!CV) flat_store(v[u], dst + i);
+                else if constexpr ((CV & CV_WIDEN) && (CV & CV_Q8)) flat_store(unpack4_u8(q[u]), dst + i);
+                else if constexpr (CV & CV_WIDEN) flat_store(widen4(h[u]), dst + i);
+                else if constexpr (CV & CV_Q8) flat_store(q[u], reinterpret_cast<uint32_t*>(dst) + i);
+                else flat_store(h[u], reinterpret_cast<vec8*>(dst) + i);
                 if (PACED && (u + 1) % PACED == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             }
             return;
