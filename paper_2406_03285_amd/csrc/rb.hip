@@ -169,6 +169,16 @@ Shape plan_shape(const rb_buffer* rb, int64_t rows, int width, int most = 8, int
     return s;
 }
 
+// Whether a one-step launch that moves `rows` plain rows in tiles of eight vectors per thread (33 MB and more, about one round of
+// workgroups) does better with ordinary stores behind its streaming loads: what a workgroup writes waits in the die's L2 while
+// others read.  rb_step_small_kernel always does: one launch, us, streaming and ordinary: 64 + 64 rows of 301 KB [38.5 MB] 15.2 : 14.6, 64 + 8 of
+// 602 KB [43 MB] 17.1 : 16.1, 48 + 48 [58] 23.2 : 20.3, 64 + 64 [77] 31.7 : 28.7, of 1 MB [128] 50.7 : 45.2.  Launches whose rows all move at
+// the same time do from about 45 MB on.  Planned one step ahead: 64 + 64 of 301 KB [38.5] 13.8 : 14.2, 48 + 48 of 400 KB [38.4] 13.8 : 14.3,
+// 64 + 64 of 400 KB [51] 20.4 : 19.8, of 602 KB [77] 29.1 : 26.8, of 1 MB 47.5 : 42.7; two calls: 64 + 64 of 602 KB [38.5 each] 29.3 : 30.0,
+// of 800 KB [51] 41.3 : 38.2, of 1 MB [64] 51.2 : 46.6.  Smaller tiles and launches of many rounds lose (14 + 7 rows of 602 KB 8.0 : 8.4,
+// 64 rows of 301 KB with four vectors 8.9 : 9.4, 20 steps of 64 + 64 rows of 301 KB at once 225 : 253).
+bool plain_stores(int64_t rows, int64_t row_vec) { return rows * row_vec >= INT64_C(45000000) / 16; }
+
 // LDS of rb_update_small_kernel and rb_step_small_kernel
 size_t small_lds_bytes(int64_t b, int nchunks)
 {
@@ -190,6 +200,7 @@ hipError_t launch_update_small_s(const UpdateArgs& a, int unroll, dim3 grid, siz
     default:
         if constexpr (ST == RB_STORE_U8) return hipErrorInvalidValue;
         else if (unroll == 4) go(rb_update_small_kernel<4, NT, ST, AUX>);
+        else if (ST == RB_STORE_SAME && plain_stores(a.c, a.row_vec)) go(rb_update_small_kernel<8, NT, ST, AUX, NT && ST != RB_STORE_SAME>);
         else go(rb_update_small_kernel<8, NT, ST, AUX>);
         break;
     }
@@ -222,6 +233,7 @@ hipError_t launch_sample_small_s(const SampleArgs& a, int unroll, dim3 grid, hip
     default:
         if constexpr (ST == RB_STORE_U8) return hipErrorInvalidValue;
         else if (unroll == 4) go(rb_sample_small_kernel<4, NT, ST>);
+        else if (ST == RB_STORE_SAME && plain_stores(a.r, a.row_vec)) go(rb_sample_small_kernel<8, NT, ST, NT && ST != RB_STORE_SAME>);
         else go(rb_sample_small_kernel<8, NT, ST>);
         break;
     }
@@ -363,6 +375,7 @@ hipError_t launch_planned_s(const MoveArgs& m, const PlanArgs& next, int unroll,
         break;
     default:
         if constexpr (ST != RB_STORE_SAME) return hipErrorInvalidValue;  // (bfloat16 rows: at most four)
+        else if (plain_stores(m.c + m.r, m.row_vec)) go(rb_step_planned_kernel<8, NT, ST, false>);
         else go(rb_step_planned_kernel<8, NT, ST>);
         break;
     }

@@ -288,9 +288,10 @@ struct TileSpan {
 // rows are whole multiples of a wavefront's accesses and many rounds of workgroups follow each other (the several-steps launch for
 // large counts, plain rows: 16 steps of 1024 + 1024 rows of 8 KB 91.2 us without, 93.5 with; there also rows kept as bfloat16 with
 // eight vectors per lane, which just fit the registers without: 304 + 127 rows of 12 KB, 13 steps, 42.0 us without, 43.1 with).
+// STREAM: the stores are streaming as well (plain_stores in rb.hip).
 // Either way no lane is masked off, so the number of loads in flight is known at compile time - a wait for an earlier load then does
 // not have to drain these - and the compiler cannot move a load down into a guarded store.
-template <int U, bool NT, int W = TPB, int PACED = 1, int CV = CV_NONE, bool LATE = false, bool DESC = true>
+template <int U, bool NT, int W = TPB, int PACED = 1, int CV = CV_NONE, bool LATE = false, bool DESC = true, bool STREAM = NT>
 struct Tile {
     static constexpr bool RAW = LATE && CV != CV_NONE;       // load() moves vectors of the binary32 row
     static constexpr int PARTS = CV & CV_Q8 ? 4 : CV ? 2 : 1;
@@ -377,7 +378,7 @@ struct Tile {
         }
         constexpr bool WIDE = !CV || (CV & CV_WIDEN) != 0;   // the destination's accesses are whole vectors
         using Unit = std::conditional_t<WIDE, vec16, std::conditional_t<(CV & CV_Q8) != 0, uint32_t, vec8>>;
-        const TileSpan<Unit, NT, W> span(dst, PARTS * lo, PARTS * hi);
+        const TileSpan<Unit, STREAM, W> span(dst, PARTS * lo, PARTS * hi);
 #pragma unroll
         for (int u = 0; u < N; ++u) {
             if constexpr (!CV) span.store(u, v[u]);

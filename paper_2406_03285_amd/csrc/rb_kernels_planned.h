@@ -334,7 +334,7 @@ static_assert(sizeof(MoveLead) == 14 * sizeof(uint32_t), "what fits the scalar r
 // first, then representatives); with plan_next the first workgroup of the grid
 // plans the next step instead.
 // ---------------------------------------------------------------------------
-template <int U, bool NT, int ST>           // ST: RB_STORE_*, the form binary32 samples are stored in (row_vec counts stored vectors)
+template <int U, bool NT, int ST, bool STREAM = NT>           // ST: RB_STORE_*, the form binary32 samples are stored in (row_vec counts stored vectors); STREAM: streaming stores
 __global__ void __launch_bounds__(TPB) rb_step_planned_kernel(const char* table, const vec16* batch_x, vec16* buf_x, vec16* out_x, int64_t row_vec,
                                                               uint32_t c_r, uint32_t tpr_plan, int32_t tile_vec, int32_t tile_rem,
                                                               const MoveArgs, const PlanArgs)
@@ -379,7 +379,7 @@ __global__ void __launch_bounds__(TPB) rb_step_planned_kernel(const char* table,
     if (e < c) {
         if (en.row < 0) return;                 // label outside [0, K), or a later class-mate takes the slot
         if (first) { m.buf_y[en.row] = en.label; count_moved(m.state); }
-        Tile<U, NT, TPB, PACE, stored_cv(ST, CV_NARROW)> t;
+        Tile<U, NT, TPB, PACE, stored_cv(ST, CV_NARROW), false, true, STREAM> t;
         t.load(batch_x + (int64_t)en.pos * row_vec * WIDE, v_lo, v_hi);
         t.store(buf_x + en.row * row_vec, v_lo, v_hi);
         return;
@@ -396,7 +396,7 @@ __global__ void __launch_bounds__(TPB) rb_step_planned_kernel(const char* table,
         t.store(dst, v_lo, v_hi);
     } else {
         const vec16* src = en.pos >= 0 ? batch_x + (int64_t)en.pos * row_vec : buf_x + en.row * row_vec;
-        Tile<U, NT, TPB, PACE, stored_cv(ST, CV_WIDEN)> t;
+        Tile<U, NT, TPB, PACE, stored_cv(ST, CV_WIDEN), false, true, STREAM> t;
         t.load(src, v_lo, v_hi);
         t.store(dst, v_lo, v_hi);
     }

@@ -238,7 +238,7 @@ __device__ __forceinline__ int4 request_fill(const int32_t* fill, int nchunks)
 // (label of every mini-batch position below YPRE * TPB, LAB_INVALID when outside [0, K)),
 // s_old[DIRECT_CHUNKS * CH] i32 (fill counts before the step, if there are no more classes).
 // ---------------------------------------------------------------------------
-template <int U, bool NT, int ST, bool AUX>     // ST: RB_STORE_*, the form binary32 samples are stored in; AUX: FIFO or reservoir replacement
+template <int U, bool NT, int ST, bool AUX, bool STREAM = NT>     // ST: RB_STORE_*, the form binary32 samples are stored in; AUX: FIFO or reservoir replacement; STREAM: streaming stores
 __global__ void __launch_bounds__(TPB) rb_update_small_kernel(const int64_t* batch_y, const int32_t* fill_old, uint32_t seed_lo, uint32_t seed_hi, uint32_t step_lo, uint32_t step_hi,
                                                               uint32_t b_c, int32_t nchunks, const UpdateArgs a)
 {
@@ -325,7 +325,7 @@ __global__ void __launch_bounds__(TPB) rb_update_small_kernel(const int64_t* bat
         const int p = s_p[0];
         // The row is requested as soon as its position is known: before the labels have
         // arrived, and long before wavefront 0 has worked out where it goes.
-        Tile<U, NT, TPB, step_pace(ST, U), stored_cv(ST, CV_NARROW), true> t;
+        Tile<U, NT, TPB, step_pace(ST, U), stored_cv(ST, CV_NARROW), true, true, STREAM> t;
         t.load(a.batch_x + (int64_t)p * a.row_vec * stored_wide(ST), v_lo, v_hi);
         if (!AUX && w0) draw = (int)below(sd, PURPOSE_EVICT, (uint32_t)x, (uint64_t)a.S);
         park_labels<false>(yv, batch_y, b, a.K, s_y);
@@ -353,7 +353,7 @@ __global__ void __launch_bounds__(TPB) rb_update_small_kernel(const int64_t* bat
         }
         __syncthreads();
         const int p = s_p[par];
-        Tile<U, NT, TPB, step_pace(ST, U), stored_cv(ST, CV_NARROW), true> t;
+        Tile<U, NT, TPB, step_pace(ST, U), stored_cv(ST, CV_NARROW), true, true, STREAM> t;
         t.load(a.batch_x + (int64_t)p * a.row_vec * stored_wide(ST), v_lo, v_hi);
         if (w0) {
             const int64_t dst = place(i, p);
@@ -377,7 +377,7 @@ __global__ void __launch_bounds__(TPB) rb_update_small_kernel(const int64_t* bat
 // and three comparisons; one wavefront with sixteen consecutive classes per lane took 1 us longer.  With rb_update_small_kernel,
 // both calls, us before and after: 4 + 4 rows of 12 KB 7.29 -> 6.49, 64 + 64 of 301 KB 17.75 -> 16.85, 31 + 22 of 370 KB 13.2 -> 11.8.)
 // ---------------------------------------------------------------------------
-template <int U, bool NT, int ST>
+template <int U, bool NT, int ST, bool STREAM = NT>
 __global__ void __launch_bounds__(TPB) rb_sample_small_kernel(const int32_t* fill, const int32_t* chunk, uint32_t seed_lo, uint32_t seed_hi, uint32_t step_lo, uint32_t step_hi,
                                                               int32_t r, int32_t nchunks, const SampleArgs a)
 {
@@ -443,7 +443,7 @@ __global__ void __launch_bounds__(TPB) rb_sample_small_kernel(const int32_t* fil
             continue;
         }
         const int pk = s_pick[par][0], ps = s_pick[par][1];
-        Tile<U, NT, TPB, step_pace(ST, U), stored_cv(ST, CV_WIDEN)> t2;
+        Tile<U, NT, TPB, step_pace(ST, U), stored_cv(ST, CV_WIDEN), false, true, STREAM> t2;
         t2.load(a.buf_x + ((int64_t)pk * a.S + ps) * a.row_vec, v_lo, v_hi);
         t2.store(a.out_x + (int64_t)j * a.row_vec * stored_wide(ST), v_lo, v_hi);
         if (tile == 0 && tid == 0) { a.out_y[j] = pk; count_moved(a.state); }
@@ -483,6 +483,7 @@ template <int U, bool NT, int ST, bool AUX>
 __global__ void __launch_bounds__(TPB) rb_step_small_kernel(const int64_t* batch_y, const int32_t* fill_old, uint32_t seed_lo, uint32_t seed_hi, uint32_t step_lo, uint32_t step_hi, uint32_t b_c,
                                                             uint32_t r_nchunks, int32_t tpr, int32_t first_gather, const StepArgs sa)
 {
+    constexpr bool STREAM = NT && !(U == 8 && ST == RB_STORE_SAME);        // (see plain_stores)
     const UpdateArgs& a = sa.u;
     const int b = (int)(b_c & 0xFFFFu), c = (int)(b_c >> 16), r = (int)(r_nchunks & 0xFFFFu), nchunks = (int)(r_nchunks >> 16);
     const Seed sd = {seed_lo, seed_hi, step_lo, step_hi};
@@ -559,7 +560,7 @@ __global__ void __launch_bounds__(TPB) rb_step_small_kernel(const int64_t* batch
         lds_barrier();
         const int p = s_p;
         // requested as soon as the position is known, before the labels have arrived
-        Tile<U, NT, TPB, step_pace(ST, U), stored_cv(ST, CV_NARROW), true> t;
+        Tile<U, NT, TPB, step_pace(ST, U), stored_cv(ST, CV_NARROW), true, true, STREAM> t;
         t.load(a.batch_x + (int64_t)p * a.row_vec * stored_wide(ST), v_lo, v_hi);
         int draw = -1;                                         // (uniform replacement) the slot the lane's candidate overwrites if its class is full
         if (!AUX && wave == 0) draw = (int)below(sd, PURPOSE_EVICT, (uint32_t)x, (uint64_t)a.S);
@@ -652,7 +653,7 @@ __global__ void __launch_bounds__(TPB) rb_step_small_kernel(const int64_t* batch
     } else {
         const vec16* src = fwd >= 0 ? a.batch_x + (int64_t)fwd * a.row_vec
                                     : a.buf_x + ((int64_t)pk * a.S + ps) * a.row_vec;
-        Tile<U, NT, TPB, step_pace(ST, U), stored_cv(ST, CV_WIDEN)> t;
+        Tile<U, NT, TPB, step_pace(ST, U), stored_cv(ST, CV_WIDEN), false, true, STREAM> t;
         t.load(src, v_lo, v_hi);
         t.store(dst, v_lo, v_hi);
     }

@@ -190,6 +190,16 @@ def test_small_counts_at_the_edges_of_class_chunks_and_tiles(K, vecs, single):
     run_parity(w, steps=12, check_state_every=4, single_call=single)
 
 
+@pytest.mark.parametrize("form", ["two-calls", "single", "ahead"])
+@pytest.mark.parametrize("vecs", [58593, 58594])          # 48 rows of 45 MB in all, and one vector per row more: streaming and ordinary stores
+def test_rows_in_large_tiles_on_both_sides_of_the_store_rule(vecs, form):
+    w = wl.variant(wl.C1, name=f"stores-{vecs}", K=6, S=4, shape=(4 * vecs,), b=50, c=48 if form == "two-calls" else 26, r=48 if form == "two-calls" else 22)
+    if form == "ahead":
+        run_ahead_parity(w, 5)
+    else:
+        run_parity(w, steps=5, check_state_every=2, single_call=form == "single")
+
+
 def test_single_call_without_a_plan_drops_and_flags_bad_labels():
     rb = _rb()
     K, S, b, c, r = 1500, 3, 300, 200, 70
