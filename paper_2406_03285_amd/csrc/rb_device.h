@@ -284,10 +284,11 @@ struct TileSpan {
 // DESC: the accesses go through a buffer descriptor that ends where the tile ends: what a lane has past the end is dropped by the
 // memory unit (a load gives zeros).  Without it a lane past the end moves the tile's last vector again (same bytes, same place),
 // and lanes that store to one place wait for each other: 64 rows of 301 KB, four vectors per thread, bare mover, 9.0 us without
-// and 7.3 with descriptors; 175 rows of 24 KB 3.6 and 3.2; 10 + 20 slots of 12 KB, two calls, 7.8 -> 7.3.  Without remains where
-// rows are whole multiples of a wavefront's accesses and many rounds of workgroups follow each other (the several-steps launch for
-// large counts, plain rows: 16 steps of 1024 + 1024 rows of 8 KB 91.2 us without, 93.5 with; there also rows kept as bfloat16 with
-// eight vectors per lane, which just fit the registers without: 304 + 127 rows of 12 KB, 13 steps, 42.0 us without, 43.1 with).
+// and 7.3 with descriptors; 175 rows of 24 KB 3.6 and 3.2; 10 + 20 slots of 12 KB, two calls, 7.8 -> 7.3.  Without remains in
+// the several-steps launch for large counts, where many rounds of workgroups follow each other and the accesses spread out by the
+// index arithmetic between them do better (16 steps of 1024 + 1024 plain rows of 8 KB 91.2 us without, 93.5 with; rows kept as bfloat16, 13 steps of 304 + 127 rows
+// of 12 KB 42.0 : 43.1 (with eight vectors per lane they just fit the registers without), 19 steps of 56 + 116 of 31 KB 91.5 : 93.2; in
+// 8 bits with them, 7 steps of 31 + 35 rows of 27 KB 21.0 : 20.4, 10 of 312 + 115 of 4 KB 32.6 : 32.0).
 // STREAM: the stores are streaming as well (plain_stores in rb.hip).
 // Either way no lane is masked off, so the number of loads in flight is known at compile time - a wait for an earlier load then does
 // not have to drain these - and the compiler cannot move a load down into a guarded store.

@@ -756,7 +756,7 @@ __global__ void __launch_bounds__(BIG_TPB) rb_bigwin_kernel(const BwMoveArgs m, 
             const vec16* fresh = batch_x_of(s) + (int64_t)en.src * m.row_vec * WIDE;
             if (first) { m.buf_y[en.row] = en.label; count_moved(m.state); }
             if (__builtin_expect(heir == BW_NONE, 1)) {
-                Tile<U, NT, W, WIN_PACE, stored_cv(ST, CV_NARROW), false, ST != RB_STORE_SAME && U <= 4> t;
+                Tile<U, NT, W, WIN_PACE, stored_cv(ST, CV_NARROW), false, ST == RB_STORE_U8> t;
                 t.load(fresh, v_lo, v_hi);
                 t.store(slot, v_lo, v_hi);
                 return;
@@ -789,13 +789,13 @@ __global__ void __launch_bounds__(BIG_TPB) rb_bigwin_kernel(const BwMoveArgs m, 
     vec16* dst = out_x_of(s) + (int64_t)j * m.row_vec * WIDE;
     if (ST != RB_STORE_SAME && en.src >= 0) {
         // taken from a mini-batch row of this launch: what the slot will hold is that row in its stored form
-        Tile<U, NT, W, WIN_PACE, stored_cv(ST, CV_BOTH), false, ST != RB_STORE_SAME && U <= 4> t;
+        Tile<U, NT, W, WIN_PACE, stored_cv(ST, CV_BOTH), false, ST == RB_STORE_U8> t;
         t.load(batch_x_of(en.src >> 16) + (int64_t)(en.src & 0xFFFF) * m.row_vec * WIDE, v_lo, v_hi);
         t.store(dst, v_lo, v_hi);
     } else {
         const vec16* src = en.src >= 0 ? batch_x_of(en.src >> 16) + (int64_t)(en.src & 0xFFFF) * m.row_vec
                                        : m.buf_x + en.row * m.row_vec;
-        Tile<U, NT, W, WIN_PACE, stored_cv(ST, CV_WIDEN), false, ST != RB_STORE_SAME && U <= 4> t;
+        Tile<U, NT, W, WIN_PACE, stored_cv(ST, CV_WIDEN), false, ST == RB_STORE_U8> t;
         t.load(src, v_lo, v_hi);
         t.store(dst, v_lo, v_hi);
     }
