@@ -1134,11 +1134,11 @@ bool small_counts(const rb_buffer* rb, int64_t c, int64_t r)
 // 49 KB [1.6] 9.2 : 9.8, 300 + 300 of 12 KB [1.7] 11.2 : 11.1, 300 + 300 of 4 KB [0.6] 11.1 : 10.5, 1000 + 1000 of 4 KB [1.9]
 // 14.1 : 14.7, 200 + 200 of 49 KB [4.5] 15.7 : 13.9, with the Bernoulli selection 300 + 300 of 12 KB 11.2 : 11.5, 150 + 150 of 4 KB
 // 10.0 : 10.3.
-// Both sides have become faster since (1 us for one launch, up to 1.5 us for two launches of the small-count kernels); 1093 random shapes
+// Both sides have become faster since (1 us for one launch, up to 1.5 us for two launches of the small-count kernels); 1089 random shapes
 // measured with the present kernels put the lines of the row time further out (plain rows 22 us, 6 with two launches of the small-count
 // kernels; bfloat16 20 and 5.5; 8 bits 4, 5.5 with the Bernoulli selection, 3) and find no class count up to ONE_CLASSES where two launches
 // are more than 4 % faster.  On this side of the lines drawn here one launch loses more than 3 % in 3 of them (8-bit FIFO, 13 classes,
-// 624 + 360 rows of 512 bytes 13.0 : 11.8); what lies between the two is up to 20 % slower than it could be.  rb_query_launches
+// 624 + 360 rows of 512 bytes 13.0 : 11.8); what lies between the two is up to 28 % slower than it could be.  rb_query_launches
 // tells callers which steps take one launch, and the lines stay where it has reported them.
 enum { STEP_TWO = 0, STEP_SMALL = 1, STEP_ONE = 2 };
 int step_form(const rb_buffer* rb, int64_t c, int64_t r)
