@@ -23,6 +23,8 @@ typedef struct {
     char layout[MAX_ARGS + 1];  /* per argument: h - handle, p - device pointer, i - number (all 64 bits wide) */
     Py_ssize_t count;
     PyObject* general;          /* the Python function that takes everything */
+    PyObject* dict;             /* attributes set on this object */
+    PyObject* weakrefs;
 } Call;
 
 static PyObject* data_ptr_name;
@@ -102,18 +104,21 @@ static int call_init(PyObject* self, PyObject* args, PyObject* kwargs)
 static int call_traverse(PyObject* self, visitproc visit, void* arg)
 {
     Py_VISIT(((Call*)self)->general);
+    Py_VISIT(((Call*)self)->dict);
     return 0;
 }
 
 static int call_clear(PyObject* self)
 {
     Py_CLEAR(((Call*)self)->general);
+    Py_CLEAR(((Call*)self)->dict);
     return 0;
 }
 
 static void call_dealloc(PyObject* self)
 {
     PyObject_GC_UnTrack(self);
+    if (((Call*)self)->weakrefs != NULL) PyObject_ClearWeakRefs(self);
     call_clear(self);
     Py_TYPE(self)->tp_free(self);
 }
@@ -136,7 +141,40 @@ static PyObject* call_wrapped(PyObject* self, void* unused)
     return g;
 }
 
-static PyGetSetDef call_getset[] = {{"__wrapped__", call_wrapped, NULL, NULL, NULL}, {NULL, NULL, NULL, NULL, NULL}};
+/* What a Python function can do besides being called: it is copied and pickled as what its name stands for, ... */
+static PyObject* call_reduce(PyObject* self, PyObject* unused)
+{
+    (void)unused;
+    return PyObject_GetAttrString(self, "__qualname__");
+}
+
+/* ... becomes a method when it is an attribute of a class, ... */
+static PyObject* call_descr_get(PyObject* self, PyObject* instance, PyObject* type)
+{
+    (void)type;
+    if (instance == NULL || instance == Py_None) {
+        Py_INCREF(self);
+        return self;
+    }
+    return PyMethod_New(self, instance);
+}
+
+/* ... and has its own docstring */
+static PyObject* call_doc(PyObject* self, void* unused)
+{
+    (void)unused;
+    PyObject* g = ((Call*)self)->general;
+    if (g == NULL) Py_RETURN_NONE;
+    return PyObject_GetAttrString(g, "__doc__");
+}
+
+static PyMethodDef call_methods[] = {{"__reduce__", call_reduce, METH_NOARGS, NULL}, {NULL, NULL, 0, NULL}};
+static PyGetSetDef call_getset[] = {
+    {"__wrapped__", call_wrapped, NULL, NULL, NULL},
+    {"__doc__", call_doc, NULL, NULL, NULL},
+    {"__dict__", PyObject_GenericGetDict, PyObject_GenericSetDict, NULL, NULL},
+    {NULL, NULL, NULL, NULL, NULL},
+};
 
 static PyTypeObject CallType = {
     PyVarObject_HEAD_INIT(NULL, 0)
@@ -151,6 +189,11 @@ static PyTypeObject CallType = {
     .tp_vectorcall_offset = offsetof(Call, vectorcall),
     .tp_call = PyVectorcall_Call,
     .tp_getattro = call_getattro,
+    .tp_setattro = PyObject_GenericSetAttr,
+    .tp_descr_get = call_descr_get,
+    .tp_dictoffset = offsetof(Call, dict),
+    .tp_weaklistoffset = offsetof(Call, weakrefs),
+    .tp_methods = call_methods,
     .tp_getset = call_getset,
 };
 

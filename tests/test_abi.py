@@ -67,6 +67,34 @@ def test_native_marshalling_passes_what_ctypes_passes(layout):
     assert native.__wrapped__ is general and native.__name__ == "general"
 
 
+@pytest.mark.parametrize("name", ["rb_update", "rb_sample_augment", "rb_update_sample", "rb_announce_next", "rb_bind"])
+def test_calls_are_copied_pickled_referenced_and_bound_like_functions(name):
+    import copy
+    import inspect
+    import pickle
+    import weakref
+    import paper_2406_03285_amd as rb
+    f = getattr(rb, name)
+    for protocol in range(pickle.HIGHEST_PROTOCOL + 1):
+        assert pickle.loads(pickle.dumps(f, protocol)) is f
+    assert copy.copy(f) is f and copy.deepcopy([f]) == [f]
+    assert weakref.ref(f)() is f
+    f.note = [name]
+    try:
+        assert f.note == [name] and f.__dict__["note"] == [name] and vars(f)["note"] == [name]
+    finally:
+        del f.note
+    assert not hasattr(f, "note")
+    assert f.__name__ == name and f.__module__ == "paper_2406_03285_amd.binding" and f.__doc__ is None
+    assert f.__get__(None, object) is f and next(iter(inspect.signature(f).parameters)) == "rb"
+
+    class Handle(int):          # a handle that carries its calls as methods
+        call = f
+
+    missing = [0] * (len(inspect.signature(f).parameters) - 1)
+    assert Handle(0).call(*missing) == f(0, *missing) == rb.RB_EINVAL
+
+
 def test_create_validation_and_sizes():
     import paper_2406_03285_amd as rb
     rc, h = rb.rb_create(1000, 130, (3, 224, 224), rb.RB_F32)
