@@ -137,6 +137,10 @@ static PyObject* call_wrapped(PyObject* self, void* unused)
 {
     (void)unused;
     PyObject* g = ((Call*)self)->general;
+    if (g == NULL) {            /* made without __init__ */
+        PyErr_SetString(PyExc_AttributeError, "__wrapped__");
+        return NULL;
+    }
     Py_INCREF(g);
     return g;
 }

@@ -95,6 +95,30 @@ def test_calls_are_copied_pickled_referenced_and_bound_like_functions(name):
     assert Handle(0).call(*missing) == f(0, *missing) == rb.RB_EINVAL
 
 
+def test_a_call_object_without_a_function_raises():
+    import subprocess
+    import sys
+    code = """
+from paper_2406_03285_amd._calls import Call
+c = Call.__new__(Call)
+def refuses(error, f):
+    try:
+        f()
+    except error:
+        return
+    raise SystemExit(f"{error} expected")
+refuses(AttributeError, lambda: c.__wrapped__)
+refuses(AttributeError, lambda: c.__name__)
+refuses(AttributeError, lambda: c.__reduce__())
+refuses(TypeError, lambda: c(1, 2))
+refuses(ValueError, lambda: c.__init__(0, "hp", len))
+refuses(TypeError, lambda: c(1, 2))
+assert c.__doc__ is None
+"""
+    done = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert done.returncode == 0, (done.returncode, done.stderr[-500:])
+
+
 def test_create_validation_and_sizes():
     import paper_2406_03285_amd as rb
     rc, h = rb.rb_create(1000, 130, (3, 224, 224), rb.RB_F32)
