@@ -29,7 +29,8 @@ typedef struct {
 
 static PyObject* data_ptr_name;
 
-/* 1: *out is set; 0: not one of the forms handled here (no exception pending) */
+/* 1: *out is set; 0: not one of the forms handled here (no exception pending); -1: the tensor's data_ptr() raised (the Python
+   function takes its arguments in the same order and would raise the same; asked again there, an interrupt would be lost) */
 static int plain_argument(PyObject* o, char kind, uint64_t* out)
 {
     if (PyLong_CheckExact(o)) {
@@ -41,12 +42,9 @@ static int plain_argument(PyObject* o, char kind, uint64_t* out)
         *out = 0;
         return 1;
     }
-    if (kind != 'p') return 0;
+    if (kind != 'p' || PyLong_Check(o)) return 0;       /* (bool and other kinds of int are no tensors) */
     PyObject* p = PyObject_CallMethodNoArgs(o, data_ptr_name);
-    if (p == NULL) {
-        PyErr_Clear();
-        return 0;
-    }
+    if (p == NULL) return -1;
     const int ok = PyLong_CheckExact(p);
     if (ok) *out = PyLong_AsUnsignedLongLongMask(p);
     Py_DECREF(p);
@@ -59,8 +57,9 @@ static PyObject* call(PyObject* self, PyObject* const* args, size_t nargsf, PyOb
     const Py_ssize_t n = PyVectorcall_NARGS(nargsf);
     uint64_t a[MAX_ARGS];
     int ok = n == c->count && (kwnames == NULL || PyTuple_GET_SIZE(kwnames) == 0);
-    for (Py_ssize_t i = 0; ok && i < n; ++i) ok = plain_argument(args[i], c->layout[i], &a[i]);
-    if (!ok) return PyObject_Vectorcall(c->general, args, nargsf, kwnames);
+    for (Py_ssize_t i = 0; ok > 0 && i < n; ++i) ok = plain_argument(args[i], c->layout[i], &a[i]);
+    if (ok < 0) return NULL;
+    if (ok == 0) return PyObject_Vectorcall(c->general, args, nargsf, kwnames);
     int status;
     Py_BEGIN_ALLOW_THREADS
     switch (n) {

@@ -95,6 +95,26 @@ def test_calls_are_copied_pickled_referenced_and_bound_like_functions(name):
     assert Handle(0).call(*missing) == f(0, *missing) == rb.RB_EINVAL
 
 
+@pytest.mark.parametrize("error", [KeyboardInterrupt, MemoryError, AttributeError, TypeError, RuntimeError])
+def test_what_data_ptr_raises_ends_the_call(error):
+    """... as it does in the Python function: once asked, nothing called, the very exception handed on."""
+    import paper_2406_03285_amd as rb
+    asked = []
+
+    class Sample:
+        def data_ptr(self):
+            asked.append(error("first" if not asked else "again"))
+            if len(asked) > 1:
+                return 16
+            raise asked[0]
+
+    for f in (rb.rb_announce_next, rb.rb_announce_next.__wrapped__):
+        asked.clear()
+        with pytest.raises(error) as caught:
+            f(0, Sample())
+        assert len(asked) == 1 and caught.value is asked[0]
+
+
 def test_a_call_object_without_a_function_raises():
     import subprocess
     import sys
