@@ -1,6 +1,6 @@
 """Per-GPU rehearsal buffer for MI355X (gfx950): C-ABI HIP library plus a thin binding (ctypes, native for the calls of every step).
 
-Importing this package loads paper_2406_03285_amd/librb.so and _calls.so and fails if they have
+Importing this package loads paper_2406_03285_amd/librb.so and fails if it has
 not been built (`python paper_2406_03285_amd/build.py`); there is no CPU path.
 """
 from .binding import *  # noqa: F401,F403

@@ -2,14 +2,21 @@
 
 Every function has the name and argument order of its C counterpart; tensors
 are passed as device pointers.  PyTorch is used for device memory and streams
-only.  There is no fallback: if librb.so is missing the import fails.
+only.  There is no fallback: if librb.so is missing the import fails.  (The
+native marshalling is built where Python's headers are; without it all calls
+go through ctypes.)
 """
 import ctypes as C
 import os
 
 import torch  # first: the library must bind to the HIP runtime PyTorch has loaded
 
-from ._calls import Call
+try:
+    from ._calls import Call
+except ModuleNotFoundError as missing:
+    if missing.name != __package__ + "._calls":
+        raise
+    Call = None
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.environ.get("RB_LIBRARY") or os.path.join(HERE, "librb.so")   # RB_LIBRARY: another build of the same library
@@ -162,6 +169,8 @@ def rb_announce_next_many(rb, n, next_batch_y):
 
 def _native(general, layout):
     """The same function with its usual arguments (integers, None, tensors) marshalled natively; everything else goes to `general`."""
+    if Call is None:
+        return general
     return Call(C.cast(getattr(_L, general.__name__), C.c_void_p).value, layout, general)
 
 

@@ -19,14 +19,33 @@ HIPCC_FLAGS = [
 ]
 
 
-# The calls of a training loop without ctypes in between (a CPython extension, given the library's functions by the binding)
+# The calls of a training loop without ctypes in between: a CPython extension, given the library's functions by the binding, named for
+# the interpreter it is built for.  Built where that interpreter's headers are; the binding does without.
 CALLS_SRC = os.path.join(HERE, "csrc", "rb_calls.c")
-CALLS = os.path.join(HERE, "_calls.so")
+CALLS = os.path.join(HERE, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
+PYTHON_INCLUDE = sysconfig.get_paths()["include"]
 
 # A caller that is not Python: a plain C program against include/rb.h and the HIP runtime API (used by a GPU test).
 CLIENT_SRC = os.path.join(ROOT, "tests", "c_client", "rb_client.c")
 CLIENT = os.path.join(ROOT, "tests", "c_client", "rb_client")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+
+
+def calls_can_be_built() -> bool:
+    return os.path.exists(os.path.join(PYTHON_INCLUDE, "Python.h"))
+
+
+def build_calls(verbose: bool = False) -> None:
+    for stale in {CALLS, os.path.join(HERE, "_calls.so")}:
+        if os.path.exists(stale):
+            os.remove(stale)
+    if not calls_can_be_built():
+        print(f"no Python.h in {PYTHON_INCLUDE}: calls go through ctypes")
+        return
+    cmd = ["gcc", "-std=c11", "-O2", "-Wall", "-Werror", "-shared", "-fPIC", "-I", PYTHON_INCLUDE, CALLS_SRC, "-o", CALLS]
+    if verbose:
+        print(" ".join(cmd))
+    subprocess.run(cmd, check=True)
 
 
 def build(verbose: bool = False) -> str:
@@ -35,10 +54,7 @@ def build(verbose: bool = False) -> str:
     if verbose:
         print(" ".join(cmd))
     subprocess.run(cmd, check=True)
-    cmd = ["gcc", "-std=c11", "-O2", "-Wall", "-Werror", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"], CALLS_SRC, "-o", CALLS]
-    if verbose:
-        print(" ".join(cmd))
-    subprocess.run(cmd, check=True)
+    build_calls(verbose)
     if os.path.exists(CLIENT_SRC):
         cmd = ["gcc", "-std=c11", "-O2", "-Wall", "-Werror", "-D__HIP_PLATFORM_AMD__", "-I", INCLUDE, "-I", os.path.join(ROCM, "include"),
                CLIENT_SRC, "-o", CLIENT, "-L", HERE, "-lrb", "-L", os.path.join(ROCM, "lib"), "-lamdhip64",

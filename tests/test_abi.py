@@ -139,6 +139,29 @@ assert c.__doc__ is None
     assert done.returncode == 0, (done.returncode, done.stderr[-500:])
 
 
+def test_without_the_native_marshalling_the_calls_go_through_ctypes():
+    """Where Python's headers are missing the extension cannot be built: the package works all the same."""
+    import subprocess
+    import sys
+    code = """
+import sys
+sys.modules["paper_2406_03285_amd._calls"] = None       # an import of it raises ModuleNotFoundError
+import types
+import paper_2406_03285_amd as rb
+for name in ("rb_update", "rb_sample_augment", "rb_update_sample", "rb_announce_next"):
+    assert isinstance(getattr(rb, name), types.FunctionType), name
+assert rb.rb_update(None, None, None, 1, 1, 0, 0) == rb.RB_EINVAL
+"""
+    done = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert done.returncode == 0, (done.returncode, done.stderr[-500:])
+
+
+def test_the_native_marshalling_is_built_here_and_for_this_interpreter():
+    import sysconfig
+    from paper_2406_03285_amd import _calls, build
+    assert _calls.__file__ == build.CALLS and build.CALLS.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+
+
 def test_create_validation_and_sizes():
     import paper_2406_03285_amd as rb
     rc, h = rb.rb_create(1000, 130, (3, 224, 224), rb.RB_F32)
