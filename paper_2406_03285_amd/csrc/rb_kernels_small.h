@@ -395,7 +395,10 @@ __global__ void __launch_bounds__(TPB) rb_sample_small_kernel(const int32_t* fil
     int cs = 0;                     // not direct: samples in chunk `lane`
     if (direct) fo = request_fill(fill, nchunks);
     else if (lane < nchunks) cs = chunk[lane];
-    const uint64_t bits = draw64(sd, PURPOSE_SAMPLE, (uint32_t)lane);
+    uint64_t bits = draw64(sd, PURPOSE_SAMPLE, (uint32_t)lane);
+    // (keeps the compiler from moving the draw down to its only use, behind the wait for the counts, the scan and the barrier:
+    // rb_sample_augment alone, 4 rows of 8 KB 3.1 -> 2.8 us, 16 of 99 KB 3.55 -> 3.3, 7 of 602 KB 4.2 -> 3.9)
+    asm volatile("" : "+v"(bits));
     const WaveFill mine(fo);
     const int cincl = direct ? 0 : wave_scan_incl(cs);
     int F, before = 0;              // stored samples; direct: of the chunks before this wavefront's

@@ -59,3 +59,16 @@ def test_vectors_that_are_converted_at_the_load_are_requested_together(kernels, 
             seen += 1
             assert most_together(code, "buffer_load_dwordx4") >= (4 if storage == U8 else 2) * unroll, (name, args)
     assert seen >= 4
+
+
+def test_sampling_draws_are_made_while_the_counts_travel(kernels):
+    """rb_sample_small_kernel: the ten rounds of the draw (two multiplications each; the scalar part of the first rounds is shared)
+    stand before the scan of the counts; behind it only the reduction to the range and addresses are left."""
+    seen = 0
+    for (name, args), code in kernels.items():
+        if name == "rb_sample_small_kernel":
+            seen += 1
+            scan = next(i for i, c in enumerate(code) if "row_shr:1 " in c)
+            wide = [i for i, c in enumerate(code) if re.match(r"v_mad_u64_u32|v_mul_(hi|lo)_u32", c)]
+            assert sum(i < scan for i in wide) >= 14, (name, args)
+    assert seen >= 10
