@@ -187,6 +187,7 @@ struct WaveFill {
     int4 f;
     int local, incl;      // samples of the lane's classes, and of the lanes up to and including this one
 
+    WaveFill() = default;
     __device__ __forceinline__ explicit WaveFill(int4 counts) : f(counts)
     {
         local = f.x + f.y + f.z + f.w;
@@ -389,31 +390,46 @@ __global__ void __launch_bounds__(TPB) rb_sample_small_kernel(const int32_t* fil
     const bool direct = nchunks <= DIRECT_CHUNKS;
     static_assert(DIRECT_CHUNKS == NWAVE && CH == 4 * WAVE, "a chunk per wavefront, four classes per lane");
 
-    // the fill counts are requested first; the random bits do not depend on them
-    // (only their reduction to [0, F-n+i] does) and are computed while the loads fly
-    int4 fo = make_int4(0, 0, 0, 0);
-    int cs = 0;                     // not direct: samples in chunk `lane`
-    if (direct) fo = request_fill(fill, nchunks);
-    else if (lane < nchunks) cs = chunk[lane];
-    uint64_t bits = draw64(sd, PURPOSE_SAMPLE, (uint32_t)lane);
-    // (keeps the compiler from moving the draw down to its only use, behind the wait for the counts, the scan and the barrier:
-    // rb_sample_augment alone, 4 rows of 8 KB 3.1 -> 2.8 us, 16 of 99 KB 3.55 -> 3.3, 7 of 602 KB 4.2 -> 3.9)
-    asm volatile("" : "+v"(bits));
-    const WaveFill mine(fo);
-    const int cincl = direct ? 0 : wave_scan_incl(cs);
-    int F, before = 0;              // stored samples; direct: of the chunks before this wavefront's
-    if (direct) {
-        if (lane == WAVE - 1) s_tot[wave] = mine.incl;
-        lds_barrier();
-        const int4 tot = *reinterpret_cast<const int4*>(s_tot);
-        before = __builtin_amdgcn_readfirstlane((wave > 0 ? tot.x : 0) + (wave > 1 ? tot.y : 0) + (wave > 2 ? tot.z : 0));
-        F = __builtin_amdgcn_readfirstlane(tot.x + tot.y + tot.z + tot.w);
-    } else {
-        F = lane_read(cincl, WAVE - 1);
+    // The wavefronts that plan: one per chunk of classes, or the first alone (no more than that have anything to add, and with three
+    // and more workgroups on a compute unit they take issue slots from the others' planners: 40 rows of 301 KB in 8 bits, 1025
+    // classes, 5.85 us with four of them and 4.95 with one; 64 of 203 KB, 10 classes, 6.5 and 6.0).
+    const bool plans = wave < (direct ? nchunks : 1);
+    WaveFill mine;
+    uint64_t bits = 0;
+    int cs = 0, cincl = 0;          // not direct: samples in chunk `lane`, and up to it
+    int F = 0, before = 0;          // stored samples; direct: of the chunks before this wavefront's
+    if (plans) {
+        // the fill counts are requested first; the random bits do not depend on them
+        // (only their reduction to [0, F-n+i] does) and are computed while the loads fly
+        int4 fo = make_int4(0, 0, 0, 0);
+        if (direct) fo = request_fill(fill, nchunks);
+        else if (lane < nchunks) cs = chunk[lane];
+        bits = draw64(sd, PURPOSE_SAMPLE, (uint32_t)lane);
+        // (keeps the compiler from moving the draw down to its only use, behind the wait for the counts, the scan and the barrier:
+        // rb_sample_augment alone, 4 rows of 8 KB 3.1 -> 2.8 us, 16 of 99 KB 3.55 -> 3.3, 7 of 602 KB 4.2 -> 3.9)
+        asm volatile("" : "+v"(bits));
+        if (direct) mine = WaveFill(fo);
+        else cincl = wave_scan_incl(cs);
     }
-    const int n = r < F ? r : F, base = F - n;
-    const uint32_t t = lane < n ? reduce32(bits, (uint32_t)base + lane + 1) : 0xFFFFFFFFu;      // Floyd draw `lane`
-    if (blockIdx.x == 0 && tid == 0) a.state->last_n = n;
+    if (direct) {
+        if (lane == WAVE - 1) s_tot[wave] = plans ? mine.incl : 0;
+        lds_barrier();
+    }
+    int n = 0, base = 0;
+    uint32_t t = 0xFFFFFFFFu;       // Floyd draw `lane`
+    if (plans) {
+        if (direct) {
+            const int4 tot = *reinterpret_cast<const int4*>(s_tot);
+            before = __builtin_amdgcn_readfirstlane((wave > 0 ? tot.x : 0) + (wave > 1 ? tot.y : 0) + (wave > 2 ? tot.z : 0));
+            F = __builtin_amdgcn_readfirstlane(tot.x + tot.y + tot.z + tot.w);
+        } else {
+            F = lane_read(cincl, WAVE - 1);
+        }
+        n = r < F ? r : F;
+        base = F - n;
+        if (lane < n) t = reduce32(bits, (uint32_t)base + lane + 1);
+        if (blockIdx.x == 0 && tid == 0) a.state->last_n = n;
+    }
 
     const int group = blockIdx.x / a.tpr, tile = blockIdx.x % a.tpr;
     int64_t v_lo, v_hi;
@@ -423,29 +439,30 @@ __global__ void __launch_bounds__(TPB) rb_sample_small_kernel(const int32_t* fil
         const int j = group * a.rpb + rr;      // output row
         if (j >= r) break;
         const int par = rr & 1;
-        if (j < n) {
+        if (plans && j < n) {
             int owner, sub, ps;
+            const int g = wave_sample_number(t, j, base) - before;
             if (direct) {
-                const int g = wave_sample_number(t, j, base) - before;
                 if (g >= 0 && g < mine.total()) {                     // in this wavefront's chunk
                     mine.locate(g, owner, sub, ps);
                     if (lane == 0) { s_pick[par][0] = wave * CH + 4 * owner + sub; s_pick[par][1] = ps; }
                 }
-            } else if (wave == 0) {
-                const int g = wave_sample_number(t, j, base);
+            } else {
                 // chunk holding it: the number of chunks that end at or before it
                 const int ch = __popcll(__ballot(lane < nchunks && cincl <= g));
                 const WaveFill in(*reinterpret_cast<const int4*>(fill + (int64_t)ch * CH + 4 * lane));
                 in.locate(g - (lane_read(cincl, ch) - lane_read(cs, ch)), owner, sub, ps);
                 if (lane == 0) { s_pick[par][0] = ch * CH + 4 * owner + sub; s_pick[par][1] = ps; }
             }
+        } else if (tid == 0) {
+            s_pick[par][0] = -1;               // fewer stored samples than asked for
         }
         lds_barrier();
-        if (j >= n) {                          // fewer stored samples than asked for
+        const int pk = __builtin_amdgcn_readfirstlane(s_pick[par][0]), ps = s_pick[par][1];
+        if (pk < 0) {
             if (tile == 0 && tid == 0) a.out_y[j] = -1;
             continue;
         }
-        const int pk = s_pick[par][0], ps = s_pick[par][1];
         Tile<U, NT, TPB, step_pace(ST, U), stored_cv(ST, CV_WIDEN), false, true, STREAM> t2;
         t2.load(a.buf_x + ((int64_t)pk * a.S + ps) * a.row_vec, v_lo, v_hi);
         t2.store(a.out_x + (int64_t)j * a.row_vec * stored_wide(ST), v_lo, v_hi);
