@@ -169,6 +169,25 @@ Shape plan_shape(const rb_buffer* rb, int64_t rows, int width, int most = 8, int
     return s;
 }
 
+// Tiles of rb_sample_small_kernel's launch.  Rows that are converted on the way lose a microsecond when a compute unit gets a fourth
+// workgroup: bfloat16, more than 1024 classes, two vectors per thread, 760 workgroups 5.3 us, 832 6.3, 1000 7.2; 8 bits, one
+// vector, 760 4.95, 832 6.0, 1000 6.6.  From there on the next larger tiles are taken.  bfloat16, two vectors and four: 52 rows of 301 KB 7.15 : 6.7,
+// 64 of 250 KB 7.5 : 6.45, 64 of 301 KB 8.05 : 7.15; up to 1024 classes, where a workgroup starts to move later, 64 of 203 KB
+// 6.2 : 6.6, 64 of 250 KB 7.35 : 6.8: there two stay.  8 bits, one and two: 64 of 203 KB 6.0 : 5.3, 64 of 301 KB 7.45 : 6.15, 52 of 400 KB
+// 7.75 : 6.55, but where two vectors make more than three workgroups per compute unit as well 64 of 450 KB 9.35 : 9.8, 52 of 500 KB 9.2 : 9.15.
+// (There, with 1024 workgroups and more, a wait after every second store instead of a burst: 64 of 602 KB, 10 classes, 11.3 : 10.4 us, 1000 classes
+// 11.9 : 10.8, 64 of 500 KB, 1025 classes, 10.9 : 10.1, 64 of 2 MB 33.7 : 33.4; with three workgroups 64 of 301 KB 6.15 : 6.6.)
+constexpr int64_t THREE_EACH = 3 * 256;           // workgroups
+Shape sample_small_shape(const rb_buffer* rb, int64_t r)
+{
+    const bool u8 = rb->storage == RB_STORE_U8;
+    const int most = u8 ? 2 : 8;
+    const Shape s = plan_shape(rb, r, TPB, most);
+    if (u8 && s.unroll == 1 && r * s.tpr > THREE_EACH && r * ((rb->row_vec + 2 * TPB - 1) / (2 * TPB)) <= THREE_EACH) return plan_shape(rb, r, TPB, most, 2);
+    if (rb->storage == RB_STORE_BF16 && rb->nchunks > DIRECT_CHUNKS && s.unroll == 2 && r * s.tpr > THREE_EACH) return plan_shape(rb, r, TPB, most, 4);
+    return s;
+}
+
 // Whether a one-step launch that moves `rows` plain rows in tiles of eight vectors per thread (33 MB and more, about one round of
 // workgroups) does better with ordinary stores behind its streaming loads: what a workgroup writes waits in the die's L2 while
 // others read.  rb_step_small_kernel always does: one launch, us, streaming and ordinary: 64 + 64 rows of 301 KB [38.5 MB] 15.2 : 14.6, 64 + 8 of
@@ -229,7 +248,10 @@ hipError_t launch_sample_small_s(const SampleArgs& a, int unroll, dim3 grid, hip
     };
     switch (unroll) {
     case 1: go(rb_sample_small_kernel<1, NT, ST>); break;
-    case 2: go(rb_sample_small_kernel<2, NT, ST>); break;
+    case 2:
+        if (ST == RB_STORE_U8 && grid.x > THREE_EACH) go(rb_sample_small_kernel<2, NT, ST, NT, ST == RB_STORE_U8 ? 2 : step_pace(ST, 2)>);
+        else go(rb_sample_small_kernel<2, NT, ST>);
+        break;
     default:
         if constexpr (ST == RB_STORE_U8) return hipErrorInvalidValue;
         else if (unroll == 4) go(rb_sample_small_kernel<4, NT, ST>);
@@ -1518,7 +1540,7 @@ int rb_sample_augment(rb_buffer* rb, int64_t r, uint64_t seed, uint64_t step, vo
 
     const int widen = rb->storage == RB_STORE_BF16 ? 1 : rb->storage == RB_STORE_U8 ? 2 : 0;
     const bool small = r <= WAVE && rb->nchunks <= WAVE;
-    const Shape sh = plan_shape(rb, r, small ? TPB : WAVE, widen == 2 ? 2 : widen == 1 && !small ? 4 : 8);
+    const Shape sh = small ? sample_small_shape(rb, r) : plan_shape(rb, r, WAVE, widen == 2 ? 2 : widen == 1 ? 4 : 8);
     SampleArgs a;
     a.buf_x = static_cast<const vec16*>(rb->buf_x);
     a.out_x = static_cast<vec16*>(out_x);

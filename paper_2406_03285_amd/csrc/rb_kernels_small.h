@@ -378,7 +378,7 @@ __global__ void __launch_bounds__(TPB) rb_update_small_kernel(const int64_t* bat
 // and three comparisons; one wavefront with sixteen consecutive classes per lane took 1 us longer.  With rb_update_small_kernel,
 // both calls, us before and after: 4 + 4 rows of 12 KB 7.29 -> 6.49, 64 + 64 of 301 KB 17.75 -> 16.85, 31 + 22 of 370 KB 13.2 -> 11.8.)
 // ---------------------------------------------------------------------------
-template <int U, bool NT, int ST, bool STREAM = NT>
+template <int U, bool NT, int ST, bool STREAM = NT, int PACE = step_pace(ST, U)>
 __global__ void __launch_bounds__(TPB) rb_sample_small_kernel(const int32_t* fill, const int32_t* chunk, uint32_t seed_lo, uint32_t seed_hi, uint32_t step_lo, uint32_t step_hi,
                                                               int32_t r, int32_t nchunks, const SampleArgs a)
 {
@@ -463,7 +463,7 @@ __global__ void __launch_bounds__(TPB) rb_sample_small_kernel(const int32_t* fil
             if (tile == 0 && tid == 0) a.out_y[j] = -1;
             continue;
         }
-        Tile<U, NT, TPB, step_pace(ST, U), stored_cv(ST, CV_WIDEN), false, true, STREAM> t2;
+        Tile<U, NT, TPB, PACE, stored_cv(ST, CV_WIDEN), false, true, STREAM> t2;
         t2.load(a.buf_x + ((int64_t)pk * a.S + ps) * a.row_vec, v_lo, v_hi);
         t2.store(a.out_x + (int64_t)j * a.row_vec * stored_wide(ST), v_lo, v_hi);
         if (tile == 0 && tid == 0) { a.out_y[j] = pk; count_moved(a.state); }

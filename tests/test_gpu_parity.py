@@ -200,6 +200,14 @@ def test_rows_in_large_tiles_on_both_sides_of_the_store_rule(vecs, form):
         run_parity(w, steps=5, check_state_every=2, single_call=form == "single")
 
 
+# 64 rows in 12 or 13 tiles: three workgroups per compute unit and more, where rb_sample_augment takes the next larger tiles
+@pytest.mark.parametrize("store,stored_vecs", [("u8", 3072), ("u8", 3073), ("u8", 6144), ("u8", 6145), ("bf16", 6144), ("bf16", 6145)])
+@pytest.mark.parametrize("K", [1000, 1025])
+def test_converted_rows_on_both_sides_of_three_sampling_workgroups_per_compute_unit(store, stored_vecs, K):
+    w = wl.variant(wl.C1, name=f"three-{store}-{stored_vecs}", K=K, S=2, shape=(4 * stored_vecs * (4 if store == "u8" else 2),), b=66, c=64, r=64)
+    run_parity(w, steps=4, check_state_every=4, store_bf16=store == "bf16", store_u8=store == "u8")
+
+
 def test_single_call_without_a_plan_drops_and_flags_bad_labels():
     rb = _rb()
     K, S, b, c, r = 1500, 3, 300, 200, 70
