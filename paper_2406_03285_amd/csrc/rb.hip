@@ -190,13 +190,21 @@ Shape sample_small_shape(const rb_buffer* rb, int64_t r)
 
 // Whether a one-step launch that moves `rows` plain rows in tiles of eight vectors per thread (33 MB and more, about one round of
 // workgroups) does better with ordinary stores behind its streaming loads: what a workgroup writes waits in the die's L2 while
-// others read.  rb_step_small_kernel always does: one launch, us, streaming and ordinary: 64 + 64 rows of 301 KB [38.5 MB] 15.2 : 14.6, 64 + 8 of
-// 602 KB [43 MB] 17.1 : 16.1, 48 + 48 [58] 23.2 : 20.3, 64 + 64 [77] 31.7 : 28.7, of 1 MB [128] 50.7 : 45.2.  Launches whose rows all move at
+// others read, and what the chip's last cache (256 MB) holds need not reach memory at once.  In megabytes written by the launch, both
+// ends of each kind of launch.  rb_step_small_kernel does from the start, us, streaming and ordinary: 64 + 64 rows of 301 KB [38.5 MB] 15.2 : 14.6,
+// 64 + 8 of 602 KB [43] 17.1 : 16.1, 48 + 48 [58] 23.2 : 20.3, 64 + 64 [77] 31.7 : 28.7, of 1 MB [128] 50.7 : 45.2, of 2.6 MB [336] 119.0 : 112.8,
+// 64 + 16 of 4.2 MB [336] 105.0 : 95.9, but 64 + 64 of 2.9 MB [369] 130.5 : 133.4, of 4.2 MB [537] 184 : 194.  Launches whose rows all move at
 // the same time do from about 45 MB on.  Planned one step ahead: 64 + 64 of 301 KB [38.5] 13.8 : 14.2, 48 + 48 of 400 KB [38.4] 13.8 : 14.3,
-// 64 + 64 of 400 KB [51] 20.4 : 19.8, of 602 KB [77] 29.1 : 26.8, of 1 MB 47.5 : 42.7; two calls: 64 + 64 of 602 KB [38.5 each] 29.3 : 30.0,
-// of 800 KB [51] 41.3 : 38.2, of 1 MB [64] 51.2 : 46.6.  Smaller tiles and launches of many rounds lose (14 + 7 rows of 602 KB 8.0 : 8.4,
+// 64 + 64 of 400 KB [51] 20.4 : 19.8, of 602 KB [77] 29.1 : 26.8, of 1 MB 47.5 : 42.7, of 2.6 MB [336] 113.7 : 108.1, of 2.9 MB [369] 124.9 : 127.9.
+// Two calls: 64 + 64 of 602 KB [38.5 each] 29.3 : 30.0, of 800 KB [51] 41.3 : 38.2, of 1 MB [64] 51.2 : 46.6, of 3.1 MB [201] 145.0 : 141.9,
+// of 3.7 MB [235] 167.6 : 170.6, of 4.2 MB [268] 186.7 : 189.7.  Smaller tiles and launches of many steps lose (14 + 7 rows of 602 KB 8.0 : 8.4,
 // 64 rows of 301 KB with four vectors 8.9 : 9.4, 20 steps of 64 + 64 rows of 301 KB at once 225 : 253).
-bool plain_stores(int64_t rows, int64_t row_vec) { return rows * row_vec >= INT64_C(45000000) / 16; }
+enum { STORES_STEP = 0, STORES_PLANNED = 1, STORES_HALF = 2 };     // update and sample in one launch; by a plan; one of the two calls
+bool ordinary_stores(const rb_buffer* rb, int64_t rows, int kind)
+{
+    const int64_t bytes = rows * rb->row_bytes;
+    return bytes >= (kind == STORES_STEP ? 0 : INT64_C(45000000)) && bytes < (kind == STORES_HALF ? INT64_C(210000000) : INT64_C(345000000));
+}
 
 // LDS of rb_update_small_kernel and rb_step_small_kernel
 size_t small_lds_bytes(int64_t b, int nchunks)
@@ -207,7 +215,7 @@ size_t small_lds_bytes(int64_t b, int nchunks)
 // The small-count kernels: vectors per thread (8-bit storage: at most two, a thread holds four accesses per vector),
 // storage form and whether the replacement strategy keeps per-class state are template parameters.
 template <bool NT, int ST, bool AUX>
-hipError_t launch_update_small_s(const UpdateArgs& a, int unroll, dim3 grid, size_t lds, hipStream_t st)
+hipError_t launch_update_small_s(const UpdateArgs& a, int unroll, dim3 grid, size_t lds, hipStream_t st, bool ordinary)
 {
     const auto go = [&](auto kernel) {
         kernel<<<grid, TPB, lds, st>>>(a.batch_y, a.fill_old, a.sd.seed_lo, a.sd.seed_hi, a.sd.step_lo, a.sd.step_hi,
@@ -219,7 +227,7 @@ hipError_t launch_update_small_s(const UpdateArgs& a, int unroll, dim3 grid, siz
     default:
         if constexpr (ST == RB_STORE_U8) return hipErrorInvalidValue;
         else if (unroll == 4) go(rb_update_small_kernel<4, NT, ST, AUX>);
-        else if (ST == RB_STORE_SAME && plain_stores(a.c, a.row_vec)) go(rb_update_small_kernel<8, NT, ST, AUX, NT && ST != RB_STORE_SAME>);
+        else if (ST == RB_STORE_SAME && ordinary) go(rb_update_small_kernel<8, NT, ST, AUX, NT && ST != RB_STORE_SAME>);
         else go(rb_update_small_kernel<8, NT, ST, AUX>);
         break;
     }
@@ -227,21 +235,21 @@ hipError_t launch_update_small_s(const UpdateArgs& a, int unroll, dim3 grid, siz
 }
 
 template <bool NT>
-hipError_t launch_update_small(const UpdateArgs& a, int storage, int unroll, dim3 grid, size_t lds, hipStream_t st)
+hipError_t launch_update_small(const UpdateArgs& a, int storage, int unroll, dim3 grid, size_t lds, hipStream_t st, bool ordinary)
 {
     const bool aux = a.eviction != RB_EVICT_UNIFORM;
     switch (storage) {
     case RB_STORE_BF16:
-        return aux ? launch_update_small_s<NT, RB_STORE_BF16, true>(a, unroll, grid, lds, st) : launch_update_small_s<NT, RB_STORE_BF16, false>(a, unroll, grid, lds, st);
+        return aux ? launch_update_small_s<NT, RB_STORE_BF16, true>(a, unroll, grid, lds, st, ordinary) : launch_update_small_s<NT, RB_STORE_BF16, false>(a, unroll, grid, lds, st, ordinary);
     case RB_STORE_U8:
-        return aux ? launch_update_small_s<NT, RB_STORE_U8, true>(a, unroll, grid, lds, st) : launch_update_small_s<NT, RB_STORE_U8, false>(a, unroll, grid, lds, st);
+        return aux ? launch_update_small_s<NT, RB_STORE_U8, true>(a, unroll, grid, lds, st, ordinary) : launch_update_small_s<NT, RB_STORE_U8, false>(a, unroll, grid, lds, st, ordinary);
     default:
-        return aux ? launch_update_small_s<NT, RB_STORE_SAME, true>(a, unroll, grid, lds, st) : launch_update_small_s<NT, RB_STORE_SAME, false>(a, unroll, grid, lds, st);
+        return aux ? launch_update_small_s<NT, RB_STORE_SAME, true>(a, unroll, grid, lds, st, ordinary) : launch_update_small_s<NT, RB_STORE_SAME, false>(a, unroll, grid, lds, st, ordinary);
     }
 }
 
 template <bool NT, int ST>
-hipError_t launch_sample_small_s(const SampleArgs& a, int unroll, dim3 grid, hipStream_t st)
+hipError_t launch_sample_small_s(const SampleArgs& a, int unroll, dim3 grid, hipStream_t st, bool ordinary)
 {
     const auto go = [&](auto kernel) {
         kernel<<<grid, TPB, 0, st>>>(a.fill, a.chunk, a.sd.seed_lo, a.sd.seed_hi, a.sd.step_lo, a.sd.step_hi, a.r, a.nchunks, a);
@@ -255,7 +263,7 @@ hipError_t launch_sample_small_s(const SampleArgs& a, int unroll, dim3 grid, hip
     default:
         if constexpr (ST == RB_STORE_U8) return hipErrorInvalidValue;
         else if (unroll == 4) go(rb_sample_small_kernel<4, NT, ST>);
-        else if (ST == RB_STORE_SAME && plain_stores(a.r, a.row_vec)) go(rb_sample_small_kernel<8, NT, ST, NT && ST != RB_STORE_SAME>);
+        else if (ST == RB_STORE_SAME && ordinary) go(rb_sample_small_kernel<8, NT, ST, NT && ST != RB_STORE_SAME>);
         else go(rb_sample_small_kernel<8, NT, ST>);
         break;
     }
@@ -263,12 +271,12 @@ hipError_t launch_sample_small_s(const SampleArgs& a, int unroll, dim3 grid, hip
 }
 
 template <bool NT>
-hipError_t launch_sample_small(const SampleArgs& a, int storage, int unroll, dim3 grid, hipStream_t st)
+hipError_t launch_sample_small(const SampleArgs& a, int storage, int unroll, dim3 grid, hipStream_t st, bool ordinary)
 {
     switch (storage) {
-    case RB_STORE_BF16: return launch_sample_small_s<NT, RB_STORE_BF16>(a, unroll, grid, st);
-    case RB_STORE_U8: return launch_sample_small_s<NT, RB_STORE_U8>(a, unroll, grid, st);
-    default: return launch_sample_small_s<NT, RB_STORE_SAME>(a, unroll, grid, st);
+    case RB_STORE_BF16: return launch_sample_small_s<NT, RB_STORE_BF16>(a, unroll, grid, st, ordinary);
+    case RB_STORE_U8: return launch_sample_small_s<NT, RB_STORE_U8>(a, unroll, grid, st, ordinary);
+    default: return launch_sample_small_s<NT, RB_STORE_SAME>(a, unroll, grid, st, ordinary);
     }
 }
 
@@ -323,7 +331,7 @@ hipError_t launch_sample(const SampleArgs& a, int widen, int unroll, dim3 grid, 
 }
 
 template <bool NT, int ST, bool AUX>
-hipError_t launch_step_s(const StepArgs& sa, int unroll, dim3 grid, size_t lds, hipStream_t st)
+hipError_t launch_step_s(const StepArgs& sa, int unroll, dim3 grid, size_t lds, hipStream_t st, bool ordinary)
 {
     const UpdateArgs& a = sa.u;
     const auto go = [&](auto kernel) {
@@ -336,24 +344,25 @@ hipError_t launch_step_s(const StepArgs& sa, int unroll, dim3 grid, size_t lds, 
     default:
         if constexpr (ST == RB_STORE_U8) return hipErrorInvalidValue;
         else if (unroll == 4) go(rb_step_small_kernel<4, NT, ST, AUX>);
-        else if constexpr (ST == RB_STORE_SAME) go(rb_step_small_kernel<8, NT, ST, AUX>);
-        else return hipErrorInvalidValue;
+        else if constexpr (ST != RB_STORE_SAME) return hipErrorInvalidValue;
+        else if (ordinary) go(rb_step_small_kernel<8, NT, ST, AUX, false>);
+        else go(rb_step_small_kernel<8, NT, ST, AUX>);
         break;
     }
     return hipGetLastError();
 }
 
 template <bool NT>
-hipError_t launch_step(const StepArgs& a, int storage, int unroll, dim3 grid, size_t lds, hipStream_t st)
+hipError_t launch_step(const StepArgs& a, int storage, int unroll, dim3 grid, size_t lds, hipStream_t st, bool ordinary)
 {
     const bool aux = a.u.eviction != RB_EVICT_UNIFORM;
     switch (storage) {
     case RB_STORE_BF16:
-        return aux ? launch_step_s<NT, RB_STORE_BF16, true>(a, unroll, grid, lds, st) : launch_step_s<NT, RB_STORE_BF16, false>(a, unroll, grid, lds, st);
+        return aux ? launch_step_s<NT, RB_STORE_BF16, true>(a, unroll, grid, lds, st, ordinary) : launch_step_s<NT, RB_STORE_BF16, false>(a, unroll, grid, lds, st, ordinary);
     case RB_STORE_U8:
-        return aux ? launch_step_s<NT, RB_STORE_U8, true>(a, unroll, grid, lds, st) : launch_step_s<NT, RB_STORE_U8, false>(a, unroll, grid, lds, st);
+        return aux ? launch_step_s<NT, RB_STORE_U8, true>(a, unroll, grid, lds, st, ordinary) : launch_step_s<NT, RB_STORE_U8, false>(a, unroll, grid, lds, st, ordinary);
     default:
-        return aux ? launch_step_s<NT, RB_STORE_SAME, true>(a, unroll, grid, lds, st) : launch_step_s<NT, RB_STORE_SAME, false>(a, unroll, grid, lds, st);
+        return aux ? launch_step_s<NT, RB_STORE_SAME, true>(a, unroll, grid, lds, st, ordinary) : launch_step_s<NT, RB_STORE_SAME, false>(a, unroll, grid, lds, st, ordinary);
     }
 }
 
@@ -382,7 +391,7 @@ Seed make_seed(uint64_t seed, uint64_t step)
 }
 
 template <bool NT, int ST>
-hipError_t launch_planned_s(const MoveArgs& m, const PlanArgs& next, int unroll, dim3 grid, size_t lds, hipStream_t st)
+hipError_t launch_planned_s(const MoveArgs& m, const PlanArgs& next, int unroll, dim3 grid, size_t lds, hipStream_t st, bool ordinary)
 {
     const auto go = [&](auto kernel) {
         kernel<<<grid, TPB, lds, st>>>(m.table, m.batch_x, m.buf_x, m.out_x, m.row_vec, (uint32_t)(m.c | m.r << 16),
@@ -397,7 +406,7 @@ hipError_t launch_planned_s(const MoveArgs& m, const PlanArgs& next, int unroll,
         break;
     default:
         if constexpr (ST != RB_STORE_SAME) return hipErrorInvalidValue;  // (bfloat16 rows: at most four)
-        else if (plain_stores(m.c + m.r, m.row_vec)) go(rb_step_planned_kernel<8, NT, ST, false>);
+        else if (ordinary) go(rb_step_planned_kernel<8, NT, ST, false>);
         else go(rb_step_planned_kernel<8, NT, ST>);
         break;
     }
@@ -405,12 +414,12 @@ hipError_t launch_planned_s(const MoveArgs& m, const PlanArgs& next, int unroll,
 }
 
 template <bool NT>
-hipError_t launch_planned(const MoveArgs& m, const PlanArgs& next, int storage, int unroll, dim3 grid, size_t lds, hipStream_t st)
+hipError_t launch_planned(const MoveArgs& m, const PlanArgs& next, int storage, int unroll, dim3 grid, size_t lds, hipStream_t st, bool ordinary)
 {
     switch (storage) {
-    case RB_STORE_BF16: return launch_planned_s<NT, RB_STORE_BF16>(m, next, unroll, grid, lds, st);
-    case RB_STORE_U8: return launch_planned_s<NT, RB_STORE_U8>(m, next, unroll, grid, lds, st);
-    default: return launch_planned_s<NT, RB_STORE_SAME>(m, next, unroll, grid, lds, st);
+    case RB_STORE_BF16: return launch_planned_s<NT, RB_STORE_BF16>(m, next, unroll, grid, lds, st, ordinary);
+    case RB_STORE_U8: return launch_planned_s<NT, RB_STORE_U8>(m, next, unroll, grid, lds, st, ordinary);
+    default: return launch_planned_s<NT, RB_STORE_SAME>(m, next, unroll, grid, lds, st, ordinary);
     }
 }
 
@@ -525,8 +534,9 @@ int step_planned(rb_buffer* rb, const void* batch_x, const int64_t* batch_y, int
     if (next_y) next = make_plan(rb, next_y, b, c, r, seed, step + 1);
     const dim3 grid((unsigned)(movers + m.plan_next));
     const size_t lds = next_y ? (size_t)b * 8 : 0;
-    const hipError_t e = rb->opt_nt ? launch_planned<true>(m, next, rb->storage, sh.unroll, grid, lds, rb->stream)
-                                    : launch_planned<false>(m, next, rb->storage, sh.unroll, grid, lds, rb->stream);
+    const bool ordinary = ordinary_stores(rb, c + r, STORES_PLANNED);
+    const hipError_t e = rb->opt_nt ? launch_planned<true>(m, next, rb->storage, sh.unroll, grid, lds, rb->stream, ordinary)
+                                    : launch_planned<false>(m, next, rb->storage, sh.unroll, grid, lds, rb->stream, ordinary);
     if (e == hipSuccess && next_y) plan_enqueued(rb, next_y, b, c, r, seed, step + 1);
     if (e != hipSuccess) return RB_EHIP;
     rb->updates += 1;
@@ -1520,8 +1530,9 @@ int rb_update(rb_buffer* rb, const void* batch_x, const int64_t* batch_y,
     a.aux_new = reinterpret_cast<int32_t*>(rb->ws + rb->off_aux[rb->cur ^ 1]);
     const dim3 grid((unsigned)(rb->nchunks + (small ? sh.groups * sh.tpr : (rows * sh.tpr + NWAVE - 1) / NWAVE)));
     const size_t lds = small ? small_lds_bytes(b, rb->nchunks) : (size_t)b * 4 + (size_t)a.cap * 8;
-    const hipError_t e = small ? (rb->opt_nt ? launch_update_small<true>(a, rb->storage, sh.unroll, grid, lds, rb->stream)
-                                             : launch_update_small<false>(a, rb->storage, sh.unroll, grid, lds, rb->stream))
+    const bool ordinary = ordinary_stores(rb, c, STORES_HALF);
+    const hipError_t e = small ? (rb->opt_nt ? launch_update_small<true>(a, rb->storage, sh.unroll, grid, lds, rb->stream, ordinary)
+                                             : launch_update_small<false>(a, rb->storage, sh.unroll, grid, lds, rb->stream, ordinary))
                                : (rb->opt_nt ? launch_update<true>(a, narrow, sh.unroll, grid, lds, rb->stream)
                                              : launch_update<false>(a, narrow, sh.unroll, grid, lds, rb->stream));
     if (e != hipSuccess) return RB_EHIP;
@@ -1556,8 +1567,9 @@ int rb_sample_augment(rb_buffer* rb, int64_t r, uint64_t seed, uint64_t step, vo
     a.tpr = sh.tpr; a.tile_vec = sh.tile_vec; a.tile_rem = sh.tile_rem; a.rpb = sh.rpb;
     const dim3 grid((unsigned)(small ? sh.groups * sh.tpr : (r * sh.tpr + NWAVE - 1) / NWAVE));
     const size_t lds = small ? 0 : ((size_t)rb->nchunks + (size_t)r) * 4;
-    const hipError_t e = small ? (rb->opt_nt ? launch_sample_small<true>(a, rb->storage, sh.unroll, grid, rb->stream)
-                                             : launch_sample_small<false>(a, rb->storage, sh.unroll, grid, rb->stream))
+    const bool ordinary = ordinary_stores(rb, r, STORES_HALF);
+    const hipError_t e = small ? (rb->opt_nt ? launch_sample_small<true>(a, rb->storage, sh.unroll, grid, rb->stream, ordinary)
+                                             : launch_sample_small<false>(a, rb->storage, sh.unroll, grid, rb->stream, ordinary))
                                : (rb->opt_nt ? launch_sample<true>(a, widen, sh.unroll, grid, lds, rb->stream)
                                              : launch_sample<false>(a, widen, sh.unroll, grid, lds, rb->stream));
     return e == hipSuccess ? RB_OK : RB_EHIP;
@@ -1623,8 +1635,9 @@ int rb_update_sample(rb_buffer* rb, const void* batch_x, const int64_t* batch_y,
     sa.r = (int32_t)r;
     const dim3 grid((unsigned)(rb->nchunks + (c + r) * sh.tpr));
     const size_t lds = small_lds_bytes(b, rb->nchunks);
-    const hipError_t e = rb->opt_nt ? launch_step<true>(sa, rb->storage, sh.unroll, grid, lds, rb->stream)
-                                    : launch_step<false>(sa, rb->storage, sh.unroll, grid, lds, rb->stream);
+    const bool ordinary = ordinary_stores(rb, c + r, STORES_STEP);
+    const hipError_t e = rb->opt_nt ? launch_step<true>(sa, rb->storage, sh.unroll, grid, lds, rb->stream, ordinary)
+                                    : launch_step<false>(sa, rb->storage, sh.unroll, grid, lds, rb->stream, ordinary);
     if (e != hipSuccess) return RB_EHIP;
     rb->cur ^= 1;
     rb->updates += 1;

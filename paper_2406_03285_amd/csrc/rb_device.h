@@ -289,7 +289,7 @@ struct TileSpan {
 // index arithmetic between them do better (16 steps of 1024 + 1024 plain rows of 8 KB 91.2 us without, 93.5 with; rows kept as bfloat16, 13 steps of 304 + 127 rows
 // of 12 KB 42.0 : 43.1 (with eight vectors per lane they just fit the registers without), 19 steps of 56 + 116 of 31 KB 91.5 : 93.2; in
 // 8 bits with them, 7 steps of 31 + 35 rows of 27 KB 21.0 : 20.4, 10 of 312 + 115 of 4 KB 32.6 : 32.0).
-// STREAM: the stores are streaming as well (plain_stores in rb.hip).
+// STREAM: the stores are streaming as well (ordinary_stores in rb.hip).
 // Either way no lane is masked off, so the number of loads in flight is known at compile time - a wait for an earlier load then does
 // not have to drain these - and the compiler cannot move a load down into a guarded store.
 template <int U, bool NT, int W = TPB, int PACED = 1, int CV = CV_NONE, bool LATE = false, bool DESC = true, bool STREAM = NT>

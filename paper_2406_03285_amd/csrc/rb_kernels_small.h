@@ -499,11 +499,10 @@ __global__ void __launch_bounds__(TPB) rb_sample_small_kernel(const int32_t* fil
 // candidate movers: fill counts before the step; representative movers: candidates of each class in this step.
 // ---------------------------------------------------------------------------
 
-template <int U, bool NT, int ST, bool AUX>
+template <int U, bool NT, int ST, bool AUX, bool STREAM = NT>     // STREAM: streaming stores
 __global__ void __launch_bounds__(TPB) rb_step_small_kernel(const int64_t* batch_y, const int32_t* fill_old, uint32_t seed_lo, uint32_t seed_hi, uint32_t step_lo, uint32_t step_hi, uint32_t b_c,
                                                             uint32_t r_nchunks, int32_t tpr, int32_t first_gather, const StepArgs sa)
 {
-    constexpr bool STREAM = NT && !(U == 8 && ST == RB_STORE_SAME);        // (see plain_stores)
     const UpdateArgs& a = sa.u;
     const int b = (int)(b_c & 0xFFFFu), c = (int)(b_c >> 16), r = (int)(r_nchunks & 0xFFFFu), nchunks = (int)(r_nchunks >> 16);
     const Seed sd = {seed_lo, seed_hi, step_lo, step_hi};

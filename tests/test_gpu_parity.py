@@ -190,14 +190,18 @@ def test_small_counts_at_the_edges_of_class_chunks_and_tiles(K, vecs, single):
     run_parity(w, steps=12, check_state_every=4, single_call=single)
 
 
-@pytest.mark.parametrize("form", ["two-calls", "single", "ahead"])
-@pytest.mark.parametrize("vecs", [58593, 58594])          # 48 rows of 45 MB in all, and one vector per row more: streaming and ordinary stores
-def test_rows_in_large_tiles_on_both_sides_of_the_store_rule(vecs, form):
-    w = wl.variant(wl.C1, name=f"stores-{vecs}", K=6, S=4, shape=(4 * vecs,), b=50, c=48 if form == "two-calls" else 26, r=48 if form == "two-calls" else 22)
+# Where streaming stores become ordinary ones and the other way round: in one launch with the eighth vector per thread, in the others at 45 MB
+# a launch, and again at 345 MB (210 MB in each of two calls): the last row length on one side and the first on the other.
+@pytest.mark.parametrize("form,c,r,vecs", [(form, c, r, v + more) for form, c, r, v in [
+    ("two-calls", 48, 48, 58593), ("ahead", 26, 22, 58593), ("single", 26, 22, 43008),
+    ("two-calls", 64, 64, 205078), ("ahead", 64, 64, 168457), ("single", 64, 64, 168457)] for more in (0, 1)])
+def test_rows_in_large_tiles_on_both_sides_of_the_store_rule(form, c, r, vecs):
+    w = wl.variant(wl.C1, name=f"stores-{vecs}", K=6, S=12, shape=(4 * vecs,), b=66 if c == 64 else 50, c=c, r=r)
+    steps = 3 if c == 64 else 5
     if form == "ahead":
-        run_ahead_parity(w, 5)
+        run_ahead_parity(w, steps)
     else:
-        run_parity(w, steps=5, check_state_every=2, single_call=form == "single")
+        run_parity(w, steps=steps, check_state_every=2, single_call=form == "single")
 
 
 # 64 rows in 12 or 13 tiles: three workgroups per compute unit and more, where rb_sample_augment takes the next larger tiles
