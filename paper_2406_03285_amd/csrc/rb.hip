@@ -57,6 +57,7 @@ struct rb_buffer {
     char* ws;
     hipStream_t stream;
     bool bound;
+    bool host_rows;          // buf_x is host memory the device reaches over the link
     int cur;                 // which of the two fill-count copies is current
     // workspace layout (byte offsets)
     size_t off_fill[2], off_chunk[2], ws_bytes;
@@ -110,6 +111,13 @@ inline bool overlap(const void* p, int64_t p_bytes, const void* q, int64_t q_byt
 {
     const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
     return a < b + (uintptr_t)q_bytes && b < a + (uintptr_t)p_bytes;
+}
+inline bool in_host_memory(const void* p)
+{
+    hipPointerAttribute_t at;
+    if (hipPointerGetAttributes(&at, p) == hipSuccess) return at.type == hipMemoryTypeHost;
+    (void)hipGetLastError();                      // memory the runtime does not know: taken for the device's
+    return false;
 }
 inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -198,11 +206,13 @@ Shape sample_small_shape(const rb_buffer* rb, int64_t r)
 // 64 + 64 of 400 KB [51] 20.4 : 19.8, of 602 KB [77] 29.1 : 26.8, of 1 MB 47.5 : 42.7, of 2.6 MB [336] 113.7 : 108.1, of 2.9 MB [369] 124.9 : 127.9.
 // Two calls: 64 + 64 of 602 KB [38.5 each] 29.3 : 30.0, of 800 KB [51] 41.3 : 38.2, of 1 MB [64] 51.2 : 46.6, of 3.1 MB [201] 145.0 : 141.9,
 // of 3.7 MB [235] 167.6 : 170.6, of 4.2 MB [268] 186.7 : 189.7.  Smaller tiles and launches of many steps lose (14 + 7 rows of 602 KB 8.0 : 8.4,
-// 64 rows of 301 KB with four vectors 8.9 : 9.4, 20 steps of 64 + 64 rows of 301 KB at once 225 : 253).
+// 64 rows of 301 KB with four vectors 8.9 : 9.4, 20 steps of 64 + 64 rows of 301 KB at once 225 : 253), and so do rows stored in host
+// memory, which no cache holds back (one launch, 64 + 64 rows of 301 KB 396 : 474, planned, of 602 KB 785 : 800).
 enum { STORES_STEP = 0, STORES_PLANNED = 1, STORES_HALF = 2 };     // update and sample in one launch; by a plan; one of the two calls
 bool ordinary_stores(const rb_buffer* rb, int64_t rows, int kind)
 {
     const int64_t bytes = rows * rb->row_bytes;
+    if (rb->host_rows) return false;
     return bytes >= (kind == STORES_STEP ? 0 : INT64_C(45000000)) && bytes < (kind == STORES_HALF ? INT64_C(210000000) : INT64_C(345000000));
 }
 
@@ -1342,6 +1352,7 @@ int rb_create(rb_buffer** out, int64_t classes, int64_t slots_per_class,
     rb->nchunks = (int32_t)((classes + CH - 1) / CH);
     rb->buf_x = nullptr; rb->buf_y = nullptr; rb->ws = nullptr; rb->stream = nullptr;
     rb->bound = false;
+    rb->host_rows = false;
     rb->static_dev = -1;
     rb->cur = 0;
     size_t off = STATE_BYTES;
@@ -1424,6 +1435,7 @@ int rb_bind(rb_buffer* rb, void* buf_x, int64_t* buf_y, void* workspace, void* h
     rb->plan_valid = false; rb->next_y = nullptr; rb->tbl_next = 0;
     rb->ann_n = 0; rb->wplan_valid = false;
     rb->bw_number = 0; rb->bw_table_number[0] = 0; rb->bw_table_number[1] = 0;     // (the reset clears the planners' flags)
+    rb->host_rows = in_host_memory(buf_x);
     rb->bound = true;
     return RB_OK;
 }

@@ -1225,6 +1225,46 @@ def test_rows_in_pinned_host_memory(single):
     run_parity(w, steps=10, storage="host_pinned", single_call=single)
 
 
+@pytest.mark.parametrize("single", [False, True])
+def test_rows_in_large_tiles_in_pinned_host_memory(single):
+    """Tiles whose stores would be ordinary ones in device memory."""
+    w = wl.variant(wl.C1, name="host-pinned-large", K=6, S=12, shape=(4 * 44000,), b=66, c=64, r=64)          # 704 KB
+    run_parity(w, steps=4, check_state_every=2, storage="host_pinned", single_call=single)
+
+
+@pytest.mark.parametrize("storage", ["hbm", "host_pinned"])
+@pytest.mark.parametrize("static", [False, True])
+def test_binding_while_a_stream_is_being_captured(storage, static):
+    """rb_bind asks where the rows lie and enqueues the reset: neither disturbs a capture, and every replay resets."""
+    rb = _rb()
+    K, S, b, c, r = 9, 4, 40, 20, 10
+    buf = rb.RehearsalBuffer(K, S, (64,), torch.float32, storage=storage, static_workspace=static)
+    x, y = torch.randn((b, 64), device="cuda:0"), torch.randint(0, K, (b,), device="cuda:0")
+    out_x, out_y = torch.zeros((r, 64), device="cuda:0"), torch.zeros(r, dtype=torch.int64, device="cuda:0")
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        stream = torch.cuda.current_stream()
+        if static:
+            assert rb.rb_bind_static(buf.handle, buf.buf_x, buf.buf_y, stream) == rb.RB_OK
+        else:
+            assert rb.rb_bind(buf.handle, buf.buf_x, buf.buf_y, buf.workspace, stream) == rb.RB_OK
+        assert rb.rb_update_sample(buf.handle, x, y, b, c, r, 3, 0, out_x, out_y) == rb.RB_OK
+    orc = rbo.Buffer(K, S, 256)
+    orc.update(x.cpu().numpy().view(np.uint8).reshape(b, 256), y.cpu().numpy(), c, 3, 0)
+    n, want_x, want_y = orc.sample_augment(r, 3, 0, out_x=np.zeros((r, 256), dtype=np.uint8))
+    buf.set_stream(torch.cuda.current_stream())
+    for replay in range(3):
+        out_x.zero_()
+        out_y.fill_(-7)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(out_y.cpu().numpy(), want_y)
+        assert np.array_equal(out_x.cpu().numpy().view(np.uint8).reshape(r, 256)[:n], want_x[:n])
+        compare_buffers(buf, orc, f"bound in a capture, replay {replay}")
+        buf.buf_y.fill_(5)
+
+
 # ------------------------------------------------------ random configurations ---
 
 def _random_workload(rng, i):
