@@ -233,6 +233,41 @@ def test_single_call_without_a_plan_drops_and_flags_bad_labels():
     compare_buffers(buf, orc, "bad labels, single call")
 
 
+@pytest.mark.parametrize("K,c,r,policy", [(6000, 5, 5, "bernoulli-fifo"), (6000, 5, 5, "bernoulli-reservoir"), (6000, 5, 5, "bernoulli-uniform"),
+                                          (2300, 3, 1, "exact-uniform"), (2300, 3, 1, "exact-fifo"), (2049, 70, 2, "exact-reservoir")])
+def test_single_launch_with_more_books_to_keep_than_rows_to_hand_out(K, c, r, policy):
+    """More workgroups than the representatives' rows need: some of them have books alone."""
+    rb = _rb()
+    w = wl.variant(wl.C1, name=f"books-{K}", K=K, S=2, shape=(64,), b=90, c=c, r=r)
+    buf, _ = run_parity(w, steps=40, check_state_every=1, single_call=True, policy=POLICIES.get(policy))
+    assert rb.rb_query_launches(buf.handle, w.b, c, r) == (rb.RB_OK, 1)
+
+
+@pytest.mark.parametrize("b", [1024, 1025, 4096])          # labels of the whole mini-batch read up to 1024, the candidates' alone beyond
+@pytest.mark.parametrize("c", [64, 65, 513])               # selected by one wavefront up to 64, two candidates per thread beyond 512
+def test_single_launch_reads_and_checks_the_labels_of_large_mini_batches(b, c):
+    rb = _rb()
+    K, S, r = 1500, 3, 70
+    buf = rb.RehearsalBuffer(K, S, (64,), torch.float32)
+    orc = rbo.Buffer(K, S, 256)
+    assert rb.rb_query_launches(buf.handle, b, c, r) == (rb.RB_OK, 1)
+    x = torch.randn((b, 64), device="cuda:0")
+    out_x, out_y = torch.zeros((r, 64), device="cuda:0"), torch.full((r,), -7, dtype=torch.int64, device="cuda:0")
+    g = torch.Generator(device="cuda:0").manual_seed(b + c)
+    for step in range(4):
+        y = torch.randint(0, 50 if step % 2 else K, (b,), device="cuda:0", generator=g)
+        if step >= 2:
+            bad = torch.tensor([-1, K, 1 << 40, -(1 << 40)], device="cuda:0")
+            y[::3] = bad[torch.arange((b + 2) // 3, device="cuda:0") % 4]
+        buf.update_sample(x, y, c, r, 5, step, out_x, out_y)
+        orc.update(x.cpu().numpy().view(np.uint8).reshape(b, 256), y.cpu().numpy(), c, 5, step)
+        n, want_x, want_y = orc.sample_augment(r, 5, step, out_x=np.zeros((r, 256), dtype=np.uint8))
+        assert np.array_equal(out_y.cpu().numpy(), want_y)
+        assert np.array_equal(out_x.cpu().numpy().view(np.uint8).reshape(r, 256)[:n], want_x[:n])
+        assert orc.flags == (0 if step < 2 else rb.RB_FLAG_BAD_LABEL)
+        compare_buffers(buf, orc, f"labels of large mini-batches, step {step}")
+
+
 @pytest.mark.parametrize("policy", ["exact-uniform", "exact-fifo", "bernoulli-reservoir"])
 @pytest.mark.parametrize("c,r", [(200, 70), (40, 64)])          # shapes of the single launches when the results lie elsewhere
 def test_single_call_may_replace_the_labels_of_the_mini_batch(c, r, policy):
