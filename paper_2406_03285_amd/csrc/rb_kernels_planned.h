@@ -345,6 +345,9 @@ __global__ void __launch_bounds__(TPB) rb_step_planned_kernel(const char* table,
     const int tpr = (int)(tpr_plan & 0x7FFFFFFFu);
     const bool plan_next = tpr_plan >> 31 != 0;
     if (plan_next && blockIdx.x == 0) {        // dispatched first: it has the longest way to go
+        // (all of its arguments at once: read where they are used, each new line is one more trip in a chain of dependent ones)
+        const ArgLines<sizeof(PlannedKernelArgs)> lines;
+        lines.arrived();
         plan_step(kernel_argument<PlanArgs>(offsetof(PlannedKernelArgs, next)), lds);
         return;
     }
