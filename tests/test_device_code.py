@@ -72,3 +72,13 @@ def test_sampling_draws_are_made_while_the_counts_travel(kernels):
             wide = [i for i, c in enumerate(code) if re.match(r"v_mad_u64_u32|v_mul_(hi|lo)_u32", c)]
             assert sum(i < scan for i in wide) >= 14, (name, args)
     assert seen >= 10
+
+
+def test_candidates_of_converted_rows_are_placed_while_their_row_travels(kernels):
+    """rb_update_small_kernel: the class's count comes from LDS by an LDS access (a flat one waits for every load in flight)."""
+    seen = 0
+    for (name, args), code in kernels.items():
+        if name == "rb_update_small_kernel" and args[2] != SAME:
+            seen += 1
+            assert not any(c.startswith("flat_load") for c in code), (name, args)
+    assert seen >= 12
