@@ -1176,12 +1176,12 @@ bool small_counts(const rb_buffer* rb, int64_t c, int64_t r)
 // 49 KB [1.6] 9.2 : 9.8, 300 + 300 of 12 KB [1.7] 11.2 : 11.1, 300 + 300 of 4 KB [0.6] 11.1 : 10.5, 1000 + 1000 of 4 KB [1.9]
 // 14.1 : 14.7, 200 + 200 of 49 KB [4.5] 15.7 : 13.9, with the Bernoulli selection 300 + 300 of 12 KB 11.2 : 11.5, 150 + 150 of 4 KB
 // 10.0 : 10.3.
-// Both sides have become faster since (1 us for one launch, up to 1.5 us for two launches of the small-count kernels); 1089 random shapes
-// measured with the present kernels put the lines of the row time further out (plain rows 22 us, 6 with two launches of the small-count
-// kernels; bfloat16 20 and 5.5; 8 bits 4, 5.5 with the Bernoulli selection, 3) and find no class count up to ONE_CLASSES where two launches
-// are more than 4 % faster.  On this side of the lines drawn here one launch loses more than 3 % in 3 of them (8-bit FIFO, 13 classes,
-// 624 + 360 rows of 512 bytes 13.0 : 11.8); what lies between the two is up to 28 % slower than it could be.  rb_query_launches
-// tells callers which steps take one launch, and the lines stay where it has reported them.
+// These figures, and those below, are of the kernels the lines were drawn with.  Both sides have become faster since (1 us for one launch,
+// up to 1.5 us for two launches of the small-count kernels), and the lines have not been moved: 1089 random shapes measured with the newer
+// kernels would put those of the row time further out (plain rows 22 us, 6 with two launches of the small-count kernels; bfloat16 20 and
+// 5.5; 8 bits 4, 5.5 with the Bernoulli selection, 3) and find no class count up to ONE_CLASSES where two launches are more than 4 %
+// faster.  On this side of the lines one launch loses more than 3 % in 3 of them (8-bit FIFO, 13 classes, 624 + 360 rows of 512 bytes
+// 13.0 : 11.8); what lies between the two is up to 28 % slower than it could be.
 enum { STEP_TWO = 0, STEP_SMALL = 1, STEP_ONE = 2 };
 int step_form(const rb_buffer* rb, int64_t c, int64_t r)
 {
@@ -1210,8 +1210,8 @@ int step_form(const rb_buffer* rb, int64_t c, int64_t r)
     // [82] 44.5 : 60.9; FIFO, 1 class 600 + 600 11.8 : 10.6.
     const int64_t mates = rb->eviction == RB_EVICT_UNIFORM ? 448 : std::max<int64_t>(WAVE, 8 * rb->K + 32);
     if (c > mates * rb->K) return STEP_TWO;
-    // Every representative's workgroup copies and sums all fill counts: 0.21 us per 1000 classes, which the second launch does
-    // not cost.  What that one costs instead, measured at 2000 classes, where the counts are nearly free, grows with the rows; two
+    // Every representative's workgroup copies all fill counts into LDS, and summed them as well when this was measured: 0.21 us per 1000
+    // classes then, which the second launch does not cost.  What that one costs instead, measured at 2000 classes, where the counts are nearly free, grows with the rows; two
     // launches of the small-count kernels cost least.  One launch against two, rows of 3 KB, at 6000 / 8000 / 10000 classes:
     // as they are 5 + 5 rows 7.5 : 7.3 at 6000; 17 + 7, FIFO, 8.3 : 8.1 at 5076; 30 + 30 7.9 : 8.0 at 6000; 109 + 29 8.2 : 8.5, 9.1 : 8.6 (7832 classes); 200 + 200
     // 8.7 : 9.4 at 6000; 400 + 400 9.7 : 10.7, 10.1 : 10.7, 10.5 : 10.8; 1000 + 1000 13.6 : 16.2 at 10000.  As bfloat16 5 + 5

@@ -405,6 +405,7 @@ __global__ void __launch_bounds__(ONE_TPB) rb_step_one_kernel(const int64_t* bat
             for (int q = tid; q < c; q += ONE_TPB) s_kx[q] = s_lab[s_x[q]];
         } else {
             asm volatile("" : : "v"(near_label));
+            // (a thread's second label is requested once the first is there: the compiler moves it into its branch)
             for (int i0 = tid; i0 < c; i0 += 2 * ONE_TPB) {
                 const int i1 = i0 + ONE_TPB;
                 const int x0 = s_x[i0], x1 = s_x[min(i1, c - 1)];
@@ -425,7 +426,8 @@ __global__ void __launch_bounds__(ONE_TPB) rb_step_one_kernel(const int64_t* bat
         const int lo = ((int)blockIdx.x - first_cand) * share, hi = min(lo + share, items);
         if (lo >= hi) return;
         // A row is requested as soon as its position is known, before the labels have arrived (by every wavefront: a load
-        // that only some issue would make the wait for the labels a wait for the rows).
+        // that only some issue would make the wait for the labels a wait for the rows).  Of a large mini-batch the candidates' labels are
+        // requested behind the rows, and arrive behind them.
         int it = min(lo + wave, hi - 1);
         Tile<U, NT, WAVE, ONE_PACE, stored_cv(ST, CV_NARROW), true> t;
         {

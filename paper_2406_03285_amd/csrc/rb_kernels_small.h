@@ -1,4 +1,5 @@
-// Small-count kernels (at most 64 candidates / representatives): the plan is computed by one wavefront per workgroup; includes the single-launch update + sample kernel.
+// Small-count kernels (at most 64 candidates / representatives): one wavefront of a workgroup selects and places the candidates, one per
+// chunk of classes finds the representative; includes the single-launch update + sample kernel.
 // Included by rb.hip only, after rb_device.h.
 #pragma once
 
@@ -380,8 +381,8 @@ __global__ void __launch_bounds__(TPB) rb_update_small_kernel(const int64_t* bat
 // ---------------------------------------------------------------------------
 // rb_sample_augment for r <= WAVE representatives and at most WAVE chunks of
 // classes.  Up to DIRECT_CHUNKS chunks each of the four wavefronts reads the counts
-// of one chunk (four consecutive classes per lane), the one whose chunk holds the
-// wanted sample finds its class; above, wavefront 0 reads the sums of all chunks and
+// of one chunk (four consecutive classes per lane; as many as there are chunks), the one whose chunk
+// holds the wanted sample finds its class; above, wavefront 0 reads the sums of all chunks and
 // then the CH counts of the one that holds the sample.  (Four classes per lane are one LDS or memory access without bank conflicts
 // and three comparisons; one wavefront with sixteen consecutive classes per lane took 1 us longer.  With rb_update_small_kernel,
 // both calls, us before and after: 4 + 4 rows of 12 KB 7.29 -> 6.49, 64 + 64 of 301 KB 17.75 -> 16.85, 31 + 22 of 370 KB 13.2 -> 11.8.)
