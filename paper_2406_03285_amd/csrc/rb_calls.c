@@ -3,7 +3,7 @@
  * rb_announce_next).  One `Call` object per function: called with integers, None and tensors in the declared positions it goes
  * straight to the library; anything else (keywords, other number types, wrong argument counts) goes to the Python function it was
  * made with, which says what is accepted and what is not.  A call through ctypes converts every argument through objects of its
- * own: 16 + 16 rows of 12 KB in one call take the host 5.1 us that way and 4.0 so, and the GPU 4.1.
+ * own: 16 + 16 rows of 12 KB in one call take the host 4.2 us that way and 3.3 so (on a slower one 5.1 and 4.0), and the GPU 4.1.
  *
  * Built as the extension module paper_2406_03285_amd._calls; it is not linked to librb.so but given the functions' addresses,
  * so that it calls the library that the binding has loaded.
