@@ -167,17 +167,19 @@ def rb_announce_next_many(rb, n, next_batch_y):
     return _L.rb_announce_next_many(rb, int(n), arr)
 
 
-def _native(general, layout):
-    """The same function with its usual arguments (integers, None, tensors) marshalled natively; everything else goes to `general`."""
+def _native(general, layout, rows=False):
+    """The same function with its usual arguments (integers, None, tensors, lists of them) marshalled natively; everything else goes
+    to `general`.  rows: it returns the number its C counterpart sets beside the status."""
     if Call is None:
         return general
-    return Call(C.cast(getattr(_L, general.__name__), C.c_void_p).value, layout, general)
+    return Call(C.cast(getattr(_L, general.__name__), C.c_void_p).value, layout, general, rows)
 
 
 rb_update = _native(rb_update, "hppiiii")
 rb_sample_augment = _native(rb_sample_augment, "hiiipp")
 rb_update_sample = _native(rb_update_sample, "hppiiiiipp")
 rb_announce_next = _native(rb_announce_next, "hp")
+rb_announce_next_many = _native(rb_announce_next_many, "hiv")
 
 
 def rb_query_steps_per_launch(rb, b, c, r):
@@ -204,6 +206,9 @@ def rb_update_sample_many(rb, n, batch_x, batch_y, b, c, r, seed, first_step, ou
                                     arrs[2], arrs[3])
 
 
+rb_update_sample_many = _native(rb_update_sample_many, "hivviiiiivv")
+
+
 def rb_pipeline_create(rb):
     h = C.c_void_p()
     rc = _L.rb_pipeline_create(C.byref(h), rb)
@@ -228,11 +233,17 @@ def rb_pipeline_step_many(p, n, batch_x, batch_y, b, c, r, seed, first_step, nex
     return rc, rows.value
 
 
+rb_pipeline_step_many = _native(rb_pipeline_step_many, "hivviiiiivvs", rows=True)
+
+
 def rb_pipeline_drain(p, train_stream=None):
     """Returns (status, ready_rows)."""
     n = C.c_int64()
     rc = _L.rb_pipeline_drain(p, _stream(train_stream), C.byref(n))
     return rc, n.value
+
+
+rb_pipeline_drain = _native(rb_pipeline_drain, "hs", rows=True)
 
 
 def rb_pipeline_destroy(p):

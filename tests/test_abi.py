@@ -67,6 +67,68 @@ def test_native_marshalling_passes_what_ctypes_passes(layout):
     assert native.__wrapped__ is general and native.__name__ == "general"
 
 
+@pytest.mark.parametrize("name", ["rb_announce_next_many", "rb_update_sample_many", "rb_pipeline_step_many", "rb_pipeline_drain"])
+def test_native_marshalling_of_many_steps_passes_what_ctypes_passes(name, monkeypatch):
+    """Lists and tuples of addresses and tensors of the right and of other lengths, pointer arrays, None, what is neither, streams."""
+    import inspect
+    import torch
+    from paper_2406_03285_amd import binding
+    native = getattr(binding, name)
+    general = native.__wrapped__
+    params = list(inspect.signature(general).parameters)
+    kinds = ["v" if q in ("batch_x", "batch_y", "out_x", "out_y", "next_x", "next_y", "next_batch_y") else "s" if q == "train_stream" else
+             "h" if q in ("rb", "p") else "i" for q in params]
+    rows = name.startswith("rb_pipeline")
+    seen = []
+
+    def entry(*a):
+        n = a[1] if "v" in kinds else 0
+        seen.append([[(C.c_uint64 * n).from_address(v)[:n] if v else None] if k == "v" else v for v, k in zip(a, kinds)])
+        if rows:
+            C.c_int64.from_address(a[len(kinds)]).value = -3
+        return 7
+
+    function = C.CFUNCTYPE(C.c_int, *[C.c_uint64] * (len(kinds) + rows))(entry)
+    ctype = {"h": C.c_void_p, "v": C.POINTER(C.c_void_p), "i": C.c_int64, "s": C.c_void_p}
+    through_ctypes = C.cast(function, C.CFUNCTYPE(C.c_int, *[ctype[k] for k in kinds], *[C.POINTER(C.c_int64)] * rows))
+
+    class Library:
+        pass
+
+    setattr(Library, name, staticmethod(through_ctypes))
+    monkeypatch.setattr(binding, "_L", Library)
+    there = binding.Call(C.cast(function, C.c_void_p).value, "".join(kinds), general, rows)
+
+    class Stream:
+        def __init__(self, v):
+            self.cuda_stream = v
+
+    t = torch.zeros(4)
+    usual = {"h": 2 ** 47 + 8, "i": 3, "v": [2 ** 46 + 16, t, 0], "s": 2 ** 45}
+    odd = {"h": [None, 0, 3.5], "i": [-1, 2 ** 64 + 3, True, 2.75, None], "s": [None, 0, -1, Stream(0), Stream(2 ** 44), Stream(True), 2.5],
+           "v": [None, (1, 2, t), [1, None, True], [2 ** 64 + 5, -1, 1], [1, 2, 3.5], [1, 2, object()], binding.pointer_array([4, 5, t]), 5, "abc",
+                 range(3), [1, 2, 3, 4]]}
+    cases = [(tuple(usual[k] for k in kinds), {})]
+    for i, k in enumerate(kinds):
+        if k == "i" and params[i] == "n":
+            continue                                    # (as many as there are items)
+        cases += [(tuple(v if j == i else usual[q] for j, q in enumerate(kinds)), {}) for v in odd[k]]
+    if "v" in kinds:
+        for n in (0, 1, 64, 65):
+            cases.append((tuple([8 * i for i in range(n)] if k == "v" else n if q == "n" else usual[k] for q, k in zip(params, kinds)), {}))
+    cases += [(cases[0][0][:-1], {}), (cases[0][0] + (1,), {}), (cases[0][0][:1], dict(zip(params[1:], cases[0][0][1:])))]
+    for args, kw in cases:
+        got = []
+        for f in (there, general):
+            seen.clear()
+            try:
+                got.append((f(*args, **kw), list(seen)))
+            except Exception as e:      # noqa: BLE001  (the same refusal from both)
+                got.append((type(e), list(seen)))
+        assert got[0] == got[1], (args, kw)
+    assert native.__name__ == name
+
+
 @pytest.mark.parametrize("name", ["rb_update", "rb_sample_augment", "rb_update_sample", "rb_announce_next", "rb_bind"])
 def test_calls_are_copied_pickled_referenced_and_bound_like_functions(name):
     import copy
