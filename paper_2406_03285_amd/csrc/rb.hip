@@ -497,7 +497,7 @@ PlanArgs make_plan(const rb_buffer* rb, const int64_t* batch_y, int64_t b, int64
     p.aux_old = reinterpret_cast<const int32_t*>(rb->ws + rb->off_aux[rb->cur]);
     p.aux_new = reinterpret_cast<int32_t*>(rb->ws + rb->off_aux[rb->cur ^ 1]);
     p.selection = rb->selection;
-    p.ce = (int32_t)(rb->selection == RB_SELECT_BERNOULLI ? b : c);
+    p.ce = (int32_t)(rb->selection == RB_SELECT_BERNOULLI ? big_coin_entries(b) : c);
     return p;
 }
 
@@ -677,7 +677,7 @@ int step_big(rb_buffer* rb, const void* batch_x, const int64_t* batch_y, int64_t
     // candidate entries of the table, and how many of them the grid covers: all c, or, with the Bernoulli selection
     // (about c of the b positions are selected), c and eight standard deviations (more are served by going round)
     const bool bernoulli = rb->selection == RB_SELECT_BERNOULLI;
-    const int64_t ce = bernoulli ? b : c;
+    const int64_t ce = bernoulli ? big_coin_entries(b) : c;
     int64_t margin = 16;
     while (margin * margin < 64 * c) ++margin;
     const int64_t cgrid = bernoulli ? std::min(b, c + margin) : c;
@@ -1597,9 +1597,9 @@ int rb_update_sample(rb_buffer* rb, const void* batch_x, const int64_t* batch_y,
 
     const bool plannable = small_counts(rb, c, r);
     // larger counts have a plan-ahead form of their own
-    // (with the Bernoulli selection, whose number of candidates is only bounded by b, for mini-batches of at most BIG_MAX)
+    // (with the Bernoulli selection, whose number of candidates is only bounded by b, where big_coins says so)
     const bool big = !plannable && c >= 1 && c <= BIG_MAX && r >= 1 && r <= BIG_MAX && b <= BIG_BATCH &&
-                     rb->K <= BIG_CLASSES && rb->opt_fuse && (rb->selection == RB_SELECT_EXACT || b <= BIG_MAX) &&
+                     rb->K <= BIG_CLASSES && rb->opt_fuse && (rb->selection == RB_SELECT_EXACT || big_coins(b, c)) &&
                      rb->K * rb->S <= INT64_C(0x7FFFFFFF) && rb->S <= INT32_MAX - RB_MAX_BATCH;
     const int64_t* next_y = rb->next_y;
     rb->next_y = nullptr;                        // an announcement serves one call

@@ -1,6 +1,6 @@
 // Plan-ahead kernels for the single-launch step with up to 1024 candidates and representatives and up
 // to 10240 classes (any replacement strategy, any storage form; exact selection, or the Bernoulli
-// selection for mini-batches of at most 1024 samples): as in rb_kernels_planned.h the plan of a step is worked out by
+// selection where big_coins says so): as in rb_kernels_planned.h the plan of a step is worked out by
 // extra workgroups of the previous step's launch and left in a table, and the step's own launch only
 // moves rows by that table - but the planning workgroups (two: update, sampling) have 1024 threads
 // (one per candidate, resp. representative) and find class-mates, shared slots and repeated draws
@@ -20,6 +20,13 @@ constexpr int BIG_PER = 10;                   // classes per thread in the prefi
 constexpr int BIG_CLASSES = BIG_TPB * BIG_PER;   // most classes
 constexpr int BIG_FILL = BIG_CLASSES + WAVE;  // words of the prefix table: one more than classes, rounded up
 constexpr int BIG_BATCH = 4096;               // largest mini-batch (words of the first-occurrence table)
+// Bernoulli selection: a step's candidates, a random number of them, get one thread each.  There are never more than BIG_MAX in a
+// mini-batch of that size; of a larger one c are expected, and with c <= BIG_COINS the chance of more than BIG_MAX is below
+// exp(-1024 ln(1024 / 512) + 1024 - 512) = 1e-86 in a step (Chernoff's bound).  Such a step would leave out
+// the candidates beyond the BIG_MAX-th and raise RB_FLAG_PLAN_TIMEOUT.
+constexpr int BIG_COINS = BIG_MAX / 2;
+__host__ __device__ constexpr bool big_coins(int64_t b, int64_t c) { return b <= BIG_MAX || (b <= BIG_BATCH && c <= BIG_COINS); }
+__host__ __device__ constexpr int64_t big_coin_entries(int64_t b) { return b < BIG_MAX ? b : BIG_MAX; }   // candidates the planners hold at most
 constexpr int BIG_HASH = 2048;                // slots of each hash table (at most BIG_MAX keys)
 constexpr uint32_t BIG_EMPTY = 0xFFFFFFFFu;   // free slot (no class, row or draw has this value)
 constexpr int BIG_GROUP = TPB;                // threads that move one tile together
@@ -125,6 +132,8 @@ __device__ __forceinline__ int big_scan_excl(int v, int& total, int* s_wave)
 struct BigSelected {
     int x;           // mini-batch position of the thread's candidate
     int32_t k;       // its class, LAB_INVALID, or LAB_UNSELECTED for threads without a candidate
+    int count;       // candidates of the step: the threads 0 ... count - 1 have one each
+    bool lost;       // Bernoulli selection: there are more than threads
 };
 
 // Selection and classes; by all threads of either workgroup.  Uses region U (first occurrences), region V (labels)
@@ -147,30 +156,65 @@ __device__ __forceinline__ BigSelected big_select(const PlanArgs& a, int32_t* s_
         const int q = tid + u * BIG_TPB;
         fo[u] = q < K ? a.fill_old[q] : 0;
     }
-    // Bernoulli selection (b <= BIG_MAX): thread i = mini-batch position i, selected by its own coin; the rounds
-    // of Floyd's subset below then run empty
-    const bool bernoulli = a.selection == RB_SELECT_BERNOULLI;
-    const bool heads = bernoulli && tid < b && (int64_t)below(a.sd, PURPOSE_COIN, (uint32_t)tid, (uint64_t)b) < c;
-    const bool active = !bernoulli && tid < c;
-    const int sel_base = b - c;
-    const uint32_t t = active ? (uint32_t)below(a.sd, PURPOSE_SELECT, (uint32_t)tid, (uint64_t)(sel_base + tid + 1)) : 0u;
-    if (active) s_u[t] = 0xFFFFFFFFu;
-    __syncthreads();
-    if (active) atomicMin(&s_u[t], (uint32_t)tid);
-    __syncthreads();
-    if (active) s_draw[tid] = t | ((s_u[t] != (uint32_t)tid) ? 0x80000000u : 0u);     // t < 4096
-    // the loads have had the two rounds above to arrive
+    const auto park = [&]() {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int64_t y = yv[u];
-        s_v[tid + u * BIG_TPB] = (uint32_t)((y >= 0 && y < K) ? (int32_t)y : LAB_INVALID);
-    }
+        for (int u = 0; u < 4; ++u) {
+            const int64_t y = yv[u];
+            s_v[tid + u * BIG_TPB] = (uint32_t)((y >= 0 && y < K) ? (int32_t)y : LAB_INVALID);
+        }
 #pragma unroll
-    for (int u = 0; u < BIG_PER; ++u) s_fill[tid + u * BIG_TPB] = fo[u];
-    __syncthreads();
+        for (int u = 0; u < BIG_PER; ++u) s_fill[tid + u * BIG_TPB] = fo[u];
+    };
     BigSelected sel;
-    sel.x = active ? (big_replaced(s_draw, tid, sel_base) ? sel_base + tid : (int)t) : (heads ? tid : 0);
-    sel.k = active || heads ? (int32_t)s_v[sel.x] : LAB_UNSELECTED;
+    sel.lost = false;
+    if (a.selection == RB_SELECT_BERNOULLI) {
+        // A coin per position of the mini-batch; thread i gets the i-th position that is selected, in mini-batch order, whatever the
+        // size of the mini-batch (one thread per position would limit that to BIG_MAX).
+        const int lane = tid & (WAVE - 1), wave = tid / WAVE;
+        static_assert(4 * BIG_NWAVE == WAVE, "one lane per stretch of WAVE positions");
+        const int segs = (b + BIG_TPB - 1) / BIG_TPB * BIG_NWAVE;
+        uint32_t heads = 0;                     // bit u: the coin of position tid + u * BIG_TPB
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (u * BIG_TPB >= b) break;
+            const int q = tid + u * BIG_TPB;
+            const bool head = q < b && (int64_t)below(a.sd, PURPOSE_COIN, (uint32_t)q, (uint64_t)b) < c;
+            heads |= (uint32_t)head << u;
+            const int in_seg = __popcll(__ballot(head));
+            if (lane == 0) s_u[u * BIG_NWAVE + wave] = (uint32_t)in_seg;
+        }
+        park();
+        __syncthreads();
+        const int incl = wave_scan_incl(lane < segs ? (int)s_u[lane] : 0);
+        const int m = lane_read(incl, WAVE - 1);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (u * BIG_TPB >= b) break;
+            const bool mine = (heads >> u) & 1;
+            const uint64_t seg_heads = __ballot(mine);
+            // (the stretch's sum less this one and the heads behind it)
+            const int at = lane_read(incl, u * BIG_NWAVE + __builtin_amdgcn_readfirstlane(wave)) - __popcll(seg_heads >> lane);
+            if (mine && at < BIG_MAX) s_draw[at] = (uint32_t)(tid + u * BIG_TPB);
+        }
+        __syncthreads();
+        sel.count = m < BIG_MAX ? m : BIG_MAX;
+        sel.lost = m > BIG_MAX;
+        sel.x = tid < sel.count ? (int)s_draw[tid] : 0;
+    } else {
+        const bool active = tid < c;
+        const int sel_base = b - c;
+        const uint32_t t = active ? (uint32_t)below(a.sd, PURPOSE_SELECT, (uint32_t)tid, (uint64_t)(sel_base + tid + 1)) : 0u;
+        if (active) s_u[t] = 0xFFFFFFFFu;
+        __syncthreads();
+        if (active) atomicMin(&s_u[t], (uint32_t)tid);
+        __syncthreads();
+        if (active) s_draw[tid] = t | ((s_u[t] != (uint32_t)tid) ? 0x80000000u : 0u);     // t < 4096
+        park();                                 // the loads have had the two rounds above to arrive
+        __syncthreads();
+        sel.count = c;
+        sel.x = active ? (big_replaced(s_draw, tid, sel_base) ? sel_base + tid : (int)t) : 0;
+    }
+    sel.k = tid < sel.count ? (int32_t)s_v[sel.x] : LAB_UNSELECTED;
     __syncthreads();
     return sel;
 }
@@ -197,10 +241,6 @@ __device__ __forceinline__ void plan_big_update(const PlanArgs& a, uint32_t* lds
     // far), on its way while the class table is built; this workgroup owns that state and writes its next copy
     const bool strategy = a.eviction != RB_EVICT_UNIFORM;
     const int64_t aux0 = strategy && valid ? a.aux_old[k] : 0;
-    // table entry of the thread's candidate: its number in Floyd's emission order, or, with the Bernoulli
-    // selection, its number among the selected positions
-    int ent = tid, count = a.ce;
-    if (a.selection == RB_SELECT_BERNOULLI) ent = big_scan_excl(k != LAB_UNSELECTED ? 1 : 0, count, s_wave);
     // class table: keys in U[0, BIG_HASH), members per class in U[BIG_HASH, 2 BIG_HASH)
     uint32_t* ckey = s_u;
     uint32_t* ccnt = s_u + BIG_HASH;
@@ -283,15 +323,15 @@ __device__ __forceinline__ void plan_big_update(const PlanArgs& a, uint32_t* lds
     __syncthreads();
     // of the candidates that go to one slot the last of the mini-batch is stored
     const bool stored = placed && rmax[hr] == (uint32_t)x + 1u;
-    if (a.selection == RB_SELECT_BERNOULLI ? k != LAB_UNSELECTED : tid < a.ce) {
+    if (tid < sel.count) {
         PlanEntry e;
         e.pos = x;
         e.label = valid ? k : -1;
         e.row = stored ? row : -1;
-        entry[ent] = e;
+        entry[tid] = e;             // (its number in Floyd's emission order, or, with the Bernoulli selection, among the selected positions)
     }
     for (int i = tid; i < 2 * BIG_HASH; i += BIG_TPB) fwd[i] = s_v[i];
-    if (tid == 0) fwd[2 * BIG_HASH] = (uint32_t)count;
+    if (tid == 0) fwd[2 * BIG_HASH] = (uint32_t)sel.count;
 }
 
 // Mini-batch position of the candidate that the step stores in slot row `row`, -1 if the step does not write it.
@@ -335,6 +375,7 @@ __device__ __forceinline__ void plan_big_sample(const PlanArgs& a, uint32_t* lds
         atomicOr(&s_hit[k >> 5], 1u << (k & 31));
     }
     if (k == LAB_INVALID) atomicOr(&s_flags, (uint32_t)RB_FLAG_BAD_LABEL);
+    if (sel.lost && tid == 0) atomicOr(&s_flags, (uint32_t)RB_FLAG_PLAN_TIMEOUT);
     const uint64_t bits = tid < r ? draw64(a.sd, PURPOSE_SAMPLE, (uint32_t)tid) : 0;
     uint32_t* dkey = s_u;                            // values of the sampling draws
     uint32_t* dfirst = s_u + BIG_HASH;               // first draw with that value

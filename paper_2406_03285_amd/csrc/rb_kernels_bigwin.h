@@ -80,7 +80,7 @@ struct BwPlanArgs {
     int32_t eviction;                  // RB_EVICT_*
     uint32_t number;                   // the window's number (never 0): what its flags are set to
     int32_t selection;                 // RB_SELECT_*
-    int32_t ce;                        // candidate entries per step in the table: c, or b with the Bernoulli selection (one thread per position)
+    int32_t ce;                        // candidate entries per step in the table: c, or b with the Bernoulli selection
     const int32_t* aux_old;            // per class: FIFO: slot of the oldest sample; RESERVOIR: samples offered so far
     int32_t* aux_new;
 };
@@ -276,7 +276,7 @@ __device__ __forceinline__ PlanArgs bw_step_args(const BwPlanArgs& a, int s)
 
 // ---------------------------------------------------------------------------
 // Update planner of step s of the window (Alg. 1): thread i = candidate i of Floyd's emission order, or, with the
-// Bernoulli selection (mini-batches of at most BIG_MAX), mini-batch position i, which is a candidate if its coin says so.
+// Bernoulli selection, the i-th of the selected positions.
 // LDS as in plan_big_update.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void bw_plan_update(const BwPlanArgs& a, int s, uint32_t* lds)
@@ -303,11 +303,7 @@ __device__ __forceinline__ void bw_plan_update(const BwPlanArgs& a, int s, uint3
     const int64_t before_window = valid ? s_fill[k] : 0;             // samples of the class stored before the window
     const int64_t aux_window = strategy && valid ? a.aux_old[k] : 0;  // the strategy's state before the window
     if (tid < ce) bw_put(reinterpret_cast<uint32_t*>(t.classes) + s * BIG_MAX + tid, (uint32_t)k);   // LAB_INVALID: label outside [0, K); LAB_UNSELECTED: tails
-    // table entry of the thread's candidate: its number in Floyd's emission order, or its number among the selected positions
-    int ent = tid, count = ce;
-    if (a.selection == RB_SELECT_BERNOULLI) ent = big_scan_excl(k != LAB_UNSELECTED ? 1 : 0, count, s_wave);
-    const bool has_entry = a.selection == RB_SELECT_BERNOULLI ? k != LAB_UNSELECTED : tid < ce;
-    if (tid == 0) t.flags->count[s] = (uint32_t)count;
+    if (tid == 0) t.flags->count[s] = (uint32_t)sel.count;
     bw_publish(&t.flags->classes[s], a.number);
     bool ok = bw_await(t.flags->classes, 0, s, a.number, &s_ok);
     // the candidates that the steps before this one bring
@@ -395,9 +391,9 @@ __device__ __forceinline__ void bw_plan_update(const BwPlanArgs& a, int s, uint3
     // of the candidates of this step that go to one slot the last of the mini-batch is stored
     const bool stored = placed && rval[hr] == (uint32_t)x + 1u;
     __syncthreads();
-    if (stored) rval[hr] = ((uint32_t)x << 16) | (uint32_t)ent;
-    const int me = s * rows + ent;
-    if (has_entry) {
+    if (stored) rval[hr] = ((uint32_t)x << 16) | (uint32_t)tid;
+    const int me = s * rows + tid;             // table entry of the thread's candidate
+    if (tid < sel.count) {
         WinEntry e;
         e.src = x;
         e.label = valid ? k : -1;
@@ -406,7 +402,7 @@ __device__ __forceinline__ void bw_plan_update(const BwPlanArgs& a, int s, uint3
         e.handled = 0;
         e.pad[0] = 0; e.pad[1] = 0;
         t.entry[me] = e;
-        bw_put(t.first + s * BIG_MAX + ent, BW_NONE);          // nobody waits for the slot's old content yet
+        bw_put(t.first + s * BIG_MAX + tid, BW_NONE);          // nobody waits for the slot's old content yet
     }
     __syncthreads();
     for (int i = tid; i < BIG_HASH; i += BIG_TPB) bw_put64(t.wrote + (size_t)s * BIG_HASH + i, (uint64_t)rval[i] << 32 | rkey[i]);

@@ -546,12 +546,23 @@ def test_plan_ahead_steps_with_large_counts(w, steps):
     (wl.variant(wl.C2, name="C2-S3-bernoulli-ahead", S=3), 80),
     (wl.variant(wl.C4, name="C4-S8-bernoulli-ahead", S=8, shape=(3, 32, 32)), 60),              # 512 positions, Zipf head
     (wl.variant(wl.C5, name="C5-b1024-bernoulli-ahead", K=300, S=12, shape=(256,), b=1024, c=400, r=150), 30),   # the largest mini-batch this form takes
-    (wl.variant(wl.C5, name="C5-b1025-bernoulli-ahead", K=300, S=12, shape=(64,), b=1025, c=400, r=150), 10),    # one more: not eligible, announcement ignored
+    (wl.variant(wl.C5, name="C5-b1025-bernoulli-ahead", K=300, S=12, shape=(64,), b=1025, c=400, r=150), 10),    # one more: a planner's threads have several positions each
     (wl.variant(wl.C1, name="C1-c-equals-b-bernoulli-ahead", b=64, c=64, r=20, S=3), 30),       # every coin shows heads
 ], ids=["C1", "C2-S3", "C4-S8", "b1024", "b1025", "c=b"])
 def test_plan_ahead_with_the_bernoulli_selection(w, steps):
     run_ahead_parity(w, steps, policy=POLICIES["bernoulli-uniform"])
     run_many_parity(w, min(steps, 40), per_call=7, announce=True, policy=POLICIES["bernoulli-uniform"])
+
+
+# Mini-batches with more positions than a planner has threads: one, two and four positions per thread, the last ones ragged; one
+# candidate or none, as many as the form takes (512 expected) and one more, which it does not.
+@pytest.mark.parametrize("policy", ["bernoulli-uniform", "bernoulli-fifo", "bernoulli-reservoir"])
+@pytest.mark.parametrize("b,c,r,steps", [(1025, 1, 3, 30), (1940, 23, 25, 40), (2048, 300, 200, 12), (2049, 512, 70, 10), (3100, 64, 1024, 10),
+                                         (4096, 512, 512, 8), (4096, 513, 5, 6), (4095, 5, 1, 20)])
+def test_plan_ahead_with_the_bernoulli_selection_of_large_mini_batches(b, c, r, steps, policy):
+    w = wl.variant(wl.C5, name=f"coins-{b}-{c}", K=300, S=12, shape=(64,), b=b, c=c, r=r)
+    run_ahead_parity(w, steps, policy=POLICIES[policy])
+    run_many_parity(w, min(steps, 12), per_call=5, announce=True, policy=POLICIES[policy], store_bf16=policy == "bernoulli-fifo")
 
 
 @pytest.mark.parametrize("policy", ["exact-fifo", "exact-reservoir", "bernoulli-fifo", "bernoulli-reservoir"])
