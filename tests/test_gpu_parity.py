@@ -1207,6 +1207,47 @@ def test_moved_rows_counter_counts_stored_candidates_and_representatives():
         assert rb.rb_read_moved_rows(None)[0] == rb.RB_EINVAL
 
 
+@pytest.mark.parametrize("w,n", [(wl.variant(wl.C2, name="C2-pipeline-streams", S=6), 4),
+                                 (wl.variant(wl.C5, name="C5-pipeline-streams", K=300, S=12, shape=(256,), b=512, c=200, r=150), 3),
+                                 (wl.variant(wl.C2, name="C2-pipeline-streams-single", S=6), 1)], ids=["small", "large", "one-by-one"])
+def test_pipeline_makes_every_training_stream_wait(w, n):
+    """Whether rb_pipeline_drain has made it wait already or another stream, or none; the buffer's stream is always late."""
+    rb = _rb()
+    dev = torch.device("cuda:0")
+    side, train_a, train_b = (torch.cuda.Stream(dev) for _ in range(3))
+    buf = rb.RehearsalBuffer(w.K, w.S, w.shape, w.torch_dtype, device=dev, stream=side)
+    pipe = rb.Pipeline(buf)
+    calls = 9
+    batches = [wl.make_batch(w, t, dev) for t in range(calls * n)]
+    xs, ys = [x.contiguous() for x, _ in batches], [y.contiguous() for _, y in batches]
+    out_x = torch.zeros((calls * n, w.r, *w.shape), dtype=w.torch_dtype, device=dev)
+    out_y = torch.full((calls * n, w.r), -7, dtype=torch.int64, device=dev)
+    seen_x, seen_y = torch.zeros_like(out_x), torch.zeros_like(out_y)
+    sink = torch.empty(64 * 256, dtype=torch.float32, device=dev)
+    torch.cuda.synchronize()
+    for g in range(calls):
+        now, before = slice(g * n, (g + 1) * n), slice((g - 1) * n, g * n)
+        train = (train_a, train_b, train_a, train_a)[g % 4]
+        if g == 6:                                      # the buffer moves on to another stream
+            side = torch.cuda.Stream(dev)
+            buf.set_stream(side)
+        assert rb.rb_standin_compute(side, sink, 64, 50000) == rb.RB_OK         # this call's representatives are late
+        pipe.step_many(xs[now], ys[now], w.c, w.r, w.lib_seed, g * n, list(out_x[now]), list(out_y[now]), train)
+        if g > 0:
+            with torch.cuda.stream(train):
+                seen_x[before].copy_(out_x[before])
+                seen_y[before].copy_(out_y[before])
+        if g % 3 != 2:
+            pipe.drain(train_a)
+    torch.cuda.synchronize()
+    check = _rb().RehearsalBuffer(w.K, w.S, w.shape, w.torch_dtype, device=dev)          # the same steps, one after the other
+    for t in range(calls * n):
+        check.update_sample(xs[t], ys[t], w.c, w.r, w.lib_seed, t, seen_x[-1], seen_y[-1])
+        assert torch.equal(seen_y[-1], out_y[t]) and torch.equal(parity_util._bytes(seen_x[-1])[seen_y[-1] >= 0], parity_util._bytes(out_x[t])[out_y[t] >= 0])
+    assert torch.equal(seen_y[:-n], out_y[:-n]) and torch.equal(parity_util._bytes(seen_x[:-n]), parity_util._bytes(out_x[:-n]))
+    pipe.close()
+
+
 def test_pipeline_argument_checks_leave_it_unchanged():
     rb = _rb()
     w = wl.C1
