@@ -237,7 +237,7 @@ __device__ __forceinline__ int one_writer(const UpdateArgs& a, const uint32_t* s
 // the samples before a class from the old sums per chunk and the candidates that add to them (summing 10240 counts took 1.4 us),
 // the candidates' labels alone of a large mini-batch (2 us), a kernel per kind of selection and arguments read where they are used
 // (0.7 to 1 us: what did not fit the scalar registers went to vector lanes and back).  Measured on MI355X, us, before these and now:
-// 1024 + 1024 rows of 8 KB of 10000 classes 16.5 -> 14.2; Bernoulli selection with reservoir replacement, 90 + 75 rows of 49 KB kept as
+// 1024 + 1024 rows of 8 KB of 10000 classes 16.5 -> 13.6; Bernoulli selection with reservoir replacement, 90 + 75 rows of 49 KB kept as
 // bfloat16, 9.4 -> 8.6; Bernoulli, 9 + 20 rows of 59 KB kept as bfloat16 7.5 -> 6.4; FIFO, 563 + 150 rows of 1 KB of 2017 classes
 // 9.3 -> 8.6; 9 + 7 rows of 99 KB in 8 bits of 1160 classes 7.4 -> 6.6.  (Where the two launches are the faster form: step_form.)
 //
@@ -405,14 +405,17 @@ __global__ void __launch_bounds__(ONE_TPB) rb_step_one_kernel(const int64_t* bat
             for (int q = tid; q < c; q += ONE_TPB) s_kx[q] = s_lab[s_x[q]];
         } else {
             asm volatile("" : : "v"(near_label));
-            // (a thread's second label is requested once the first is there: the compiler moves it into its branch)
-            for (int i0 = tid; i0 < c; i0 += 2 * ONE_TPB) {
-                const int i1 = i0 + ONE_TPB;
-                const int x0 = s_x[i0], x1 = s_x[min(i1, c - 1)];
-                const int64_t y0 = batch_y[x0], y1 = batch_y[x1];
-                s_kx[i0] = listed(x0, y0);
-                if (i1 < c) s_kx[i1] = listed(x1, y1);
+            // (two at a time, both requested before either is waited for: 1024 + 1024 rows of 8 KB of a mini-batch of 4096 14.05 -> 13.57 us)
+            int i0 = 0;
+            for (; i0 + ONE_TPB < c; i0 += 2 * ONE_TPB) {
+                const int q0 = i0 + tid, q1 = q0 + ONE_TPB;
+                const int x0 = s_x[q0], x1 = s_x[min(q1, c - 1)];
+                int64_t y0 = batch_y[x0], y1 = batch_y[x1];
+                asm volatile("" : "+v"(y0), "+v"(y1));      // (the compiler would move the second request into its branch, behind the wait for the first)
+                s_kx[q0] = listed(x0, y0);
+                if (q1 < c) s_kx[q1] = listed(x1, y1);
             }
+            if (i0 + tid < c) s_kx[i0 + tid] = listed(s_x[i0 + tid], batch_y[s_x[i0 + tid]]);
         }
         lds_barrier();
     };

@@ -268,6 +268,11 @@ def test_single_launch_reads_and_checks_the_labels_of_large_mini_batches(b, c):
         compare_buffers(buf, orc, f"labels of large mini-batches, step {step}")
 
 
+@pytest.mark.parametrize("c", [512, 1024, 1025, 1537])     # a thread requests two candidates' labels at a time, or the last one alone
+def test_single_launch_reads_the_labels_of_many_candidates(c):
+    test_single_launch_reads_and_checks_the_labels_of_large_mini_batches(4096, c)
+
+
 @pytest.mark.parametrize("policy", ["exact-uniform", "exact-fifo", "bernoulli-reservoir"])
 @pytest.mark.parametrize("c,r", [(200, 70), (40, 64)])          # shapes of the single launches when the results lie elsewhere
 def test_single_call_may_replace_the_labels_of_the_mini_batch(c, r, policy):
