@@ -237,8 +237,8 @@ __device__ __forceinline__ int one_writer(const UpdateArgs& a, const uint32_t* s
 // the samples before a class from the old sums per chunk and the candidates that add to them (summing 10240 counts took 1.4 us),
 // the candidates' labels alone of a large mini-batch (2 us), a kernel per kind of selection and arguments read where they are used
 // (0.7 to 1 us: what did not fit the scalar registers went to vector lanes and back).  Measured on MI355X, us, before these and now:
-// 1024 + 1024 rows of 8 KB of 10000 classes 16.5 -> 13.6; Bernoulli selection with reservoir replacement, 90 + 75 rows of 49 KB kept as
-// bfloat16, 9.4 -> 8.6; Bernoulli, 9 + 20 rows of 59 KB kept as bfloat16 7.5 -> 6.4; FIFO, 563 + 150 rows of 1 KB of 2017 classes
+// 1024 + 1024 rows of 8 KB of 10000 classes 16.5 -> 13.0; Bernoulli selection with reservoir replacement, 90 + 75 rows of 49 KB kept as
+// bfloat16, 9.4 -> 8.0; Bernoulli, 9 + 20 rows of 59 KB kept as bfloat16 7.5 -> 6.4; FIFO, 563 + 150 rows of 1 KB of 2017 classes
 // 9.3 -> 8.6; 9 + 7 rows of 99 KB in 8 bits of 1160 classes 7.4 -> 6.6.  (Where the two launches are the faster form: step_form.)
 //
 // LDS (dynamic): s_fill[nchunks * CH] i32, s_hit[nchunks * CH / 32] u32 (bitmap of the classes with candidates), s_chunk[ONE_CHUNKS] i32,
@@ -309,15 +309,24 @@ __global__ void __launch_bounds__(ONE_TPB) rb_step_one_kernel(const int64_t* bat
     // ---- candidates: positions ----
     int m = c;                                  // number of candidates
     int at[ONE_PER];                            // Bernoulli: list index of position tid + u * ONE_TPB, -1: not selected
-    uint64_t bits[ONE_PER];                     // random bits of sampling draw tid + u * ONE_TPB
-    if (gather) {
+    // Sampling draws: thread `sid + u * ONE_TPB` of them.  A draw takes a wavefront twenty multiplications of a quarter of the rate, and the
+    // wavefronts of a compute unit share its four units: each makes those it has alone, the last wavefronts the first ones, while the
+    // first ones select or flip coins.  (Two each in any case, before the selection's: 10 + 4 rows of 1 KB, Bernoulli, 6.10 us, now 5.86;
+    // 64 + 26 of 11 KB of 1031 classes 6.78 : 6.52.  Of large mini-batches they are made while the candidates' labels travel: 1024 + 1024 of
+    // 8 KB 13.57 : 13.01.)
+    const int sid = tid ^ (ONE_TPB - WAVE);
+    uint64_t bits[ONE_PER];                     // random bits of sampling draw sid + u * ONE_TPB
+    const auto draw_bits = [&]() {
+        const int first = __builtin_amdgcn_readfirstlane(sid);
 #pragma unroll
-        for (int u = 0; u < ONE_PER; u += 2) {              // (two at a time: one draw is a chain of twenty dependent multiplications)
-            if (u * ONE_TPB >= r) break;
-            bits[u] = draw64(sd, PURPOSE_SAMPLE, (uint32_t)(tid + u * ONE_TPB));
-            bits[u + 1] = draw64(sd, PURPOSE_SAMPLE, (uint32_t)(tid + (u + 1) * ONE_TPB));
+        for (int u = 0; u < ONE_PER; u += 2) {              // (two at a time: one draw is a chain of dependent multiplications)
+            if (first + u * ONE_TPB >= r) break;
+            bits[u] = draw64(sd, PURPOSE_SAMPLE, (uint32_t)(sid + u * ONE_TPB));
+            if (first + (u + 1) * ONE_TPB < r) bits[u + 1] = draw64(sd, PURPOSE_SAMPLE, (uint32_t)(sid + (u + 1) * ONE_TPB));
+            asm volatile("" : "+v"(bits[u]), "+v"(bits[u + 1]));        // (here, not where they are used)
         }
-    }
+    };
+    if (gather && parked) draw_bits();
     if constexpr (BERNOULLI) {
         uint32_t heads = 0;                     // bit u: the coin of position tid + u * ONE_TPB
 #pragma unroll 1
@@ -353,11 +362,17 @@ __global__ void __launch_bounds__(ONE_TPB) rb_step_one_kernel(const int64_t* bat
 #pragma unroll 1
         for (int i0 = tid; i0 < c; i0 += 2 * ONE_TPB) {
             const int i1 = i0 + ONE_TPB;
-            const uint64_t d0 = draw64(sd, PURPOSE_SELECT, (uint32_t)i0), d1 = draw64(sd, PURPOSE_SELECT, (uint32_t)i1);
-            const uint32_t t0 = reduce32(d0, (uint32_t)(base + i0 + 1)), t1 = reduce32(d1, (uint32_t)(base + i1 + 1));
-            s_t[i0] = t0;
-            s_first[t0] = 0xFFFFFFFFu;
-            if (i1 < c) { s_t[i1] = t1; s_first[t1] = 0xFFFFFFFFu; }
+            if (__builtin_amdgcn_readfirstlane(i1) < c) {
+                const uint64_t d0 = draw64(sd, PURPOSE_SELECT, (uint32_t)i0), d1 = draw64(sd, PURPOSE_SELECT, (uint32_t)i1);
+                const uint32_t t0 = reduce32(d0, (uint32_t)(base + i0 + 1)), t1 = reduce32(d1, (uint32_t)(base + i1 + 1));
+                s_t[i0] = t0;
+                s_first[t0] = 0xFFFFFFFFu;
+                if (i1 < c) { s_t[i1] = t1; s_first[t1] = 0xFFFFFFFFu; }
+            } else {
+                const uint32_t t0 = reduce32(draw64(sd, PURPOSE_SELECT, (uint32_t)i0), (uint32_t)(base + i0 + 1));
+                s_t[i0] = t0;
+                s_first[t0] = 0xFFFFFFFFu;
+            }
         }
         lds_barrier();
         for (int i = tid; i < c; i += ONE_TPB) atomicMin(&s_first[s_t[i]], (uint32_t)i);
@@ -382,7 +397,8 @@ __global__ void __launch_bounds__(ONE_TPB) rb_step_one_kernel(const int64_t* bat
 
     // classes of the candidates; ends with a barrier after which the list is complete
     const auto listed = [&](int x, int64_t y) { return (uint64_t)y < (uint64_t)a.K ? ((uint32_t)y << ONE_POS_BITS) | (uint32_t)x : ONE_NO_CLASS; };
-    const auto classes = [&]() {
+    // (meanwhile: done while the labels travel, where they are requested only now)
+    const auto classes = [&](auto meanwhile) {
         for (int q = m + tid; q < one_padded(m); q += ONE_TPB) s_kx[q] = ONE_NO_CLASS;
         if constexpr (BERNOULLI) {
 #pragma unroll
@@ -411,11 +427,17 @@ __global__ void __launch_bounds__(ONE_TPB) rb_step_one_kernel(const int64_t* bat
                 const int q0 = i0 + tid, q1 = q0 + ONE_TPB;
                 const int x0 = s_x[q0], x1 = s_x[min(q1, c - 1)];
                 int64_t y0 = batch_y[x0], y1 = batch_y[x1];
+                if (i0 == 0) meanwhile();
                 asm volatile("" : "+v"(y0), "+v"(y1));      // (the compiler would move the second request into its branch, behind the wait for the first)
                 s_kx[q0] = listed(x0, y0);
                 if (q1 < c) s_kx[q1] = listed(x1, y1);
             }
-            if (i0 + tid < c) s_kx[i0 + tid] = listed(s_x[i0 + tid], batch_y[s_x[i0 + tid]]);
+            const int x0 = s_x[min(i0 + tid, c - 1)];
+            int64_t y0 = 0;
+            if (i0 < c) y0 = batch_y[x0];
+            if (i0 == 0) meanwhile();
+            asm volatile("" : "+v"(y0));
+            if (i0 + tid < c) s_kx[i0 + tid] = listed(x0, y0);
         }
         lds_barrier();
     };
@@ -438,7 +460,7 @@ __global__ void __launch_bounds__(ONE_TPB) rb_step_one_kernel(const int64_t* bat
             tile_bounds(it - i * a.tpr, a.tile_vec, a.tile_rem, a.row_vec, v_lo, v_hi);
             t.load(a.batch_x + (int64_t)__builtin_amdgcn_readfirstlane(s_x[i]) * a.row_vec * WIDE, v_lo, v_hi);
         }
-        classes();
+        classes([]() {});
         it = lo + wave;
         bool loaded = true;
         // (a second round only when the coins of the Bernoulli selection gave many times the candidates the grid was sized for)
@@ -485,7 +507,7 @@ __global__ void __launch_bounds__(ONE_TPB) rb_step_one_kernel(const int64_t* bat
         if (u * 4 * ONE_TPB >= nfill) break;
         if (4 * (tid + u * ONE_TPB) < nfill) *reinterpret_cast<int4*>(s_fill + 4 * (tid + u * ONE_TPB)) = fo[u];
     }
-    classes();
+    classes(draw_bits);
     const int32_t cap = (int32_t)a.S;
     for (int q = tid; q < m; q += 2 * ONE_TPB) {
         const uint32_t kx[2] = {s_kx[q], q + ONE_TPB < m ? s_kx[q + ONE_TPB] : ONE_NO_CLASS};
@@ -513,7 +535,7 @@ __global__ void __launch_bounds__(ONE_TPB) rb_step_one_kernel(const int64_t* bat
 #pragma unroll
     for (int u = 0; u < ONE_PER; ++u) {
         if (u * ONE_TPB >= n) break;
-        const int q = tid + u * ONE_TPB;
+        const int q = sid + u * ONE_TPB;
         if (q < n) s_t[q] = reduce32(bits[u], (uint32_t)(base + q + 1));
     }
     if (blockIdx.x == 0 && tid == 0) {
