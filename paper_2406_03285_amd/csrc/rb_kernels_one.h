@@ -620,7 +620,10 @@ __global__ void __launch_bounds__(ONE_TPB) rb_step_one_kernel(const int64_t* bat
     }
 
     // ---- books: new fill counts, their sums per chunk, the strategy's state (a chunk per wavefront, dealt over the workgroups) ----
-    for (int ch = wave * first_cand + blockIdx.x; ch < nchunks; ch += first_cand * ONE_NWAVE) {
+    // (by the last wavefronts where there are fewer tiles than wavefronts: they have none to wait for.  FIFO and reservoir replacement, whose
+    // state is read first, Bernoulli, 9 + 7 rows of 1.6 KB 5.96 -> 5.66 us; where all have tiles the first ones are done first)
+    const int keeper = hi - lo < ONE_NWAVE ? ONE_NWAVE - 1 - wave : wave;
+    for (int ch = keeper * first_cand + blockIdx.x; ch < nchunks; ch += first_cand * ONE_NWAVE) {
         const int k0 = ch * CH + 4 * lane;
         const int4 v = *reinterpret_cast<const int4*>(s_fill + k0);
         const int4 f = make_int4(min(v.x, cap), min(v.y, cap), min(v.z, cap), min(v.w, cap));
