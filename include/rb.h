@@ -126,7 +126,7 @@ int rb_set_storage(rb_buffer *rb, int32_t storage);
  * Every variant is served by every call, the Bernoulli selection by the
  * plan-ahead forms of the single launch (rb_announce_next) and by the
  * several-steps launches of rb_update_sample_many (the form for large counts)
- * for b <= 1024.  RB_EINVAL: unknown value.  RB_ESTATE: an rb_update was
+ * for b <= 1024 or c <= 512.  RB_EINVAL: unknown value.  RB_ESTATE: an rb_update was
  * already enqueued since the last rb_bind.
  */
 enum rb_selection { RB_SELECT_EXACT = 0, RB_SELECT_BERNOULLI = 1 };
@@ -205,8 +205,9 @@ int rb_sample_augment(rb_buffer *rb, int64_t r, uint64_t seed, uint64_t step,
  * in this very step is copied from the mini-batch row stored there) with
  * 1 <= c, r <= 64, up to 1024 classes and the exact selection, and beyond that,
  * for c, r >= 1 and up to 10240 classes, where it is the faster form:
- * while (c + r) * (sample + stored row bytes) is below 77 MB (30 MB with bfloat16
- * storage, 11 MB in 8 bits, less for some shapes), classes are neither many for
+ * while (c + r) * (sample + stored row bytes) is below 247 MB, r times that below
+ * 77 to 99 MB (with bfloat16 storage 110 and 33 to 44 MB, in 8 bits 22 to 30 and
+ * 16 MB; less for few rows and some other shapes), classes are neither many for
  * few rows nor few for many candidates, and r is not above the number of slots
  * (rb_query_launches tells).  Otherwise the two kernels are enqueued one
  * after the other, as they are when out_y lies over batch_y (the labels are
@@ -258,7 +259,7 @@ int rb_announce_next(rb_buffer *rb, const int64_t *next_batch_y);
  * steps.  Beyond those limits - and within them when a step's rows are so
  * short that they are moved sooner than one workgroup plans a step
  * (RB_OPT_PLANNERS) -, for up to 1024 candidates and representatives,
- * b <= 4096 (b <= 1024 with the Bernoulli selection) and up to 10240 classes,
+ * b <= 4096 (b <= 1024 or c <= 512 with the Bernoulli selection) and up to 10240 classes,
  * up to 16 steps share one launch in the same way; their plan is made by two
  * workgroups per step of the launch before, which work side by side (should
  * they ever fail to hear from each other within 2 s, that launch moves nothing

@@ -1193,34 +1193,50 @@ bool small_counts(const rb_buffer* rb, int64_t c, int64_t r)
 // (rb_step_one_kernel) or STEP_TWO (the two kernels of rb_update and rb_sample_augment).
 // STEP_ONE as long as the fill counts fit LDS, work items and a class's count with a step's candidates on top (not yet cut
 // off at the capacity) are counted in 32 bits, and the rows are moved soon enough: with one workgroup of planners and movers per
-// compute unit long rows move slower than in the general kernels, rows that are converted most of all.  Measured on MI355X, one
-// launch against two, 300 classes (in brackets the time the rows take at 5.5 TB/s): as they are, 300 + 300 rows of 12 KB [2.7 us]
-// 10.0 : 11.4, 200 + 200 of 49 KB [7.2] 14.0 : 15.8, 100 + 100 of 192 KB [14.0] 21.3 : 22.1, 200 + 200 [27.9] 37.0 : 35.6, 40 + 66
-// of 602 KB [23] 30.7 : 27.6; as bfloat16 200 + 200 of 49 KB [5.4] 13.0 : 13.7, 66 + 200 of 80 KB [5.8] 13.7 : 13.4, 70 + 70 of
-// 192 KB [7.3] 15.1 : 14.9, 40 + 66 of 602 KB [17.4] 27.5 : 23.9, but 1000 + 1000 of 12 KB [6.7] 16.7 : 18.3; in 8 bits 70 + 70 of
-// 49 KB [1.6] 9.2 : 9.8, 300 + 300 of 12 KB [1.7] 11.2 : 11.1, 300 + 300 of 4 KB [0.6] 11.1 : 10.5, 1000 + 1000 of 4 KB [1.9]
-// 14.1 : 14.7, 200 + 200 of 49 KB [4.5] 15.7 : 13.9, with the Bernoulli selection 300 + 300 of 12 KB 11.2 : 11.5, 150 + 150 of 4 KB
-// 10.0 : 10.3.
-// These figures, and those below, are of the kernels the lines were drawn with.  Both sides have become faster since (1 us for one launch,
-// up to 1.5 us for two launches of the small-count kernels), and the lines have not been moved: 1089 random shapes measured with the newer
-// kernels would put those of the row time further out (plain rows 22 us, 6 with two launches of the small-count kernels; bfloat16 20 and
-// 5.5; 8 bits 4, 5.5 with the Bernoulli selection, 3) and find no class count up to ONE_CLASSES where two launches are more than 4 %
-// faster.  On this side of the lines one launch loses more than 3 % in 3 of them (8-bit FIFO, 13 classes, 624 + 360 rows of 512 bytes
-// 13.0 : 11.8); what lies between the two is up to 28 % slower than it could be.
+// compute unit long rows move slower than in the general kernels, rows that are converted most of all, and of those the
+// representatives', whose workgroups have the longer plan in front of them.  The lines are drawn by the time the rows take at 5.5 TB/s, all of
+// them and the representatives', from 12800 random shapes (2 to 10000 classes, mini-batches of 16 to 4096, rows of 256 bytes to 602 KB, up
+// to 45 us of rows, all strategies) measured on MI355X both ways.  Two launches against one, geometric mean of the shapes in a range
+// and their 5th percentile, on this and on the far side of the lines:
+//   plain, exact           representatives 8 to 14 us   1.06 (0.98)      16 to 20 us   1.01 (0.96)     20 to 30   0.98 (0.91)
+//   plain, Bernoulli       12 to 18                     1.09 (1.01)      20 to 30      1.03 (0.98)
+//   bfloat16, exact        4 to 6                       1.11 (0.99)      10 to 12      1.02 (0.93)     12 to 14   1.00 (0.94)
+//   bfloat16, Bernoulli    6 to 8                       1.16 (1.05)      16 to 20      1.03 (0.93)     20 to 30   0.99 (0.92)
+//   8 bits, exact          2 to 3                       1.13 (0.99)      3 to 4        1.05 (0.89)     6 to 8     0.99 (0.89)
+//   8 bits, Bernoulli      2 to 3                       1.19 (0.99)      3 to 4        1.08 (0.82)     10 to 12   0.96 (0.84)
+// More than 1024 candidates: the two launches' search for class-mates grows with their square (plain rows beyond 14 us 1.54, bfloat16 beyond
+// 5.5 us 1.47, 8 bits beyond 4 us 1.40), and the lines lie further out.  Nearer they lie, or none are drawn further than before, for
+//   few long rows, up to 128: plain, exact, beyond 14 us 1.01 (0.95), up to 128 candidates 1.03; bfloat16, representatives beyond 3.3 us, up to 64 rows
+//     1.04; and up to 64 on either side, exact, when the two launches are those of the small-count kernels, a workgroup per tile: plain 5.5 to 7 us
+//     1.04 (0.91), 8 to 10 0.99; bfloat16 5.5 to 7 1.01 (0.94), 7 to 8 0.96; 8 bits 2 to 3 1.04, 3 to 4 1.01 (0.93);
+//   more than 1024 representatives of short rows, which the sampling kernel moves as well: rows of up to 13 KB, plain, beyond 14 us 7 of 10 slower
+//     in one launch, 8 bits beyond 2.8 us 8 of 10;
+//   converted rows of fewer than 32 classes, or more candidates than slots: those of candidates that lose their slot to a later one are read
+//     (8 bits, FIFO, 7 classes, 236 + 8 rows of 567 KB 48 : 37 us; more than 1.9 candidates per slot 4 of 5 slower).
+constexpr double ONE_MEASURED_US = 45.0;     // most time of rows the two forms were compared with
 enum { STEP_TWO = 0, STEP_SMALL = 1, STEP_ONE = 2 };
 int step_form(const rb_buffer* rb, int64_t c, int64_t r)
 {
     if (small_counts(rb, c, r)) return STEP_SMALL;
-    // (up to 64 rows on either side, with the exact selection, the two launches are those of the small-count kernels, a workgroup per
-    // tile: plain rows, 1378 classes, 30 + 30 rows of 371 KB [8.1 us] 14.5 : 14.2, 64 + 64 of 192 KB [8.9] 15.6 : 15.1, 60 + 10 of
-    // 371 KB [9.4] 15.9 : 14.5, 30 + 30 of 602 KB [13.1] 20.1 : 18.1, but 56 + 21 of 192 KB [5.4] 10.8 : 11.6)
-    const bool small_two = rb->selection == RB_SELECT_EXACT && c <= WAVE && r <= WAVE;
-    const double one_us = (double)(c + r) * (double)(rb->row_bytes + rb->sample_bytes) / 5.5e6;
-    const double one_most = rb->storage == RB_STORE_U8 ? 2.0 : rb->storage == RB_STORE_BF16 ? 5.5 : small_two ? 8.0 : 14.0;
-    // (bfloat16 rows that are mostly representatives': 27 + 107 rows of 127 KB, Bernoulli [4.7 us, 3.7 of them representatives] 13.8 : 13.0,
-    // 3 + 40 of 371 KB [4.4, 4.1] 11.9 : 11.5, 10 + 60 of 192 KB [3.7, 3.1] 10.5 : 10.5)
-    const double reps_most = rb->storage == RB_STORE_BF16 ? 3.3 : one_most;
-    if (one_us * (double)r / (double)(c + r) >= reps_most) return STEP_TWO;
+    const bool exact = rb->selection == RB_SELECT_EXACT, small_two = exact && c <= WAVE && r <= WAVE, many = c > BIG_MAX;
+    const double one_us = (double)(c + r) * (double)(rb->row_bytes + rb->sample_bytes) / 5.5e6;     // the rows, all and the representatives'
+    const double reps_us = (double)r * (double)(rb->row_bytes + rb->sample_bytes) / 5.5e6;
+    const bool further = !small_two && c + r > 2 * WAVE && r <= BIG_MAX && (rb->storage == RB_STORE_SAME || (rb->K >= 32 && c <= rb->K * rb->S));
+    double one_most, reps_most;
+    switch (rb->storage) {
+    case RB_STORE_U8:
+        one_most = !further ? 2.0 : many ? ONE_MEASURED_US : exact ? 4.0 : 5.5;
+        reps_most = !further ? 2.0 : many ? 8.0 : 3.0;
+        break;
+    case RB_STORE_BF16:
+        one_most = !further ? 5.5 : many ? ONE_MEASURED_US : 20.0;
+        reps_most = !further ? 3.3 : many ? 12.0 : exact ? 6.0 : 8.0;
+        break;
+    default:
+        one_most = small_two ? 8.0 : !further || (exact && c <= 2 * WAVE) ? 14.0 : ONE_MEASURED_US;
+        reps_most = !further || (exact && !many) ? 14.0 : 18.0;
+    }
+    if (one_us >= one_most || reps_us >= reps_most) return STEP_TWO;
     // Representatives that cannot exist leave the workgroups they are dealt to idle, and the others, planned by eight wavefronts
     // each, take longer than one wavefront per row of the two launches: 9 + 3754 rows of 128 bytes, 360 slots, 11.9 : 8.6 us;
     // 15 + 2593 of 1.5 KB, 120 slots, 10.6 : 8.2; 9 + 552 of 36 KB, 120 slots, 10.9 : 9.9; 17 + 185 in 8 bits, 160 slots, 10.0 : 9.3.
@@ -1243,14 +1259,15 @@ int step_form(const rb_buffer* rb, int64_t c, int64_t r)
     // 7.6 : 7.6 at 4000, 8.9 : 7.6 at 10000; 30 + 30 8.3 : 8.4, 8.6 : 8.2; 200 + 200 9.0 : 9.8, 9.5 : 9.9, 9.9 : 9.9.  In 8 bits 5 + 5
     // 8.5 : 8.3 at 4000, 10.1 : 8.3 at 10000; 200 + 200 10.1 : 10.2, 10.5 : 10.1; 1000 + 1000 15.1 : 15.1 at 10000.  Bernoulli
     // selection, as they are, 5 + 5 7.9 : 7.9, 8.4 : 7.9; 109 + 29 8.2 : 8.6, 8.6 : 8.7, 9.0 : 8.9; 200 + 200 9.5 : 10.0 at 10000; in
-    // 8 bits 30 + 30 9.3 : 9.5, 9.8 : 9.7, 10.2 : 9.5.
+    // 8 bits 30 + 30 9.3 : 9.5, 9.8 : 9.7, 10.2 : 9.5.  (With the old sums per chunk the counts cost 0.1 us per 1000 classes, and the line is
+    // nearer than it need be: beyond it two launches take 1.2 times as long with the general kernels, 1.02 to 1.08 with the small-count ones.)
     const bool u8 = rb->storage == RB_STORE_U8;
     const double rows = (double)(c + r);
     const double second_us = rb->selection == RB_SELECT_BERNOULLI ? (u8 ? 0.72 : 0.82) + 0.004 * rows
                            : small_two ? (rb->storage == RB_STORE_SAME ? 0.4 + 0.0085 * rows : 0.3 + 0.007 * rows)
                            : u8 ? 0.63 + 0.0005 * rows : 0.85 + 0.0019 * rows;
-    const bool many_classes = 0.21e-3 * (double)(rb->K - 2000) > second_us;
-    if (one_us < one_most && !many_classes && c >= 1 && r >= 1 && rb->K <= ONE_CLASSES && rb->opt_fuse &&
+    if (0.21e-3 * (double)(rb->K - 2000) > second_us) return STEP_TWO;
+    if (c >= 1 && r >= 1 && rb->K <= ONE_CLASSES && rb->opt_fuse &&
         rb->S <= INT32_MAX - RB_MAX_BATCH && (rb->row_vec + TILE_UNIT - 1) / TILE_UNIT <= INT32_MAX / 2 / RB_MAX_BATCH)
         return STEP_ONE;
     return STEP_TWO;

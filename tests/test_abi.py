@@ -416,6 +416,37 @@ def test_single_launch_with_long_rows(storage, selection, c, r, elems, launches)
     rb.rb_destroy(h)
 
 
+# ... and either side of where the time the rows take, or the representatives' rows, ends it: few or many candidates, either selection.
+@pytest.mark.parametrize("storage,selection,c,r,us,launches", [
+    (0, 0, 128, 66, 13.9, 1), (0, 0, 128, 66, 14.1, 2), (0, 0, 129, 66, 44.5, 2), (0, 0, 129, 10, 44.5, 1), (0, 0, 129, 10, 45.5, 2),
+    (0, 0, 300, 200, 34.0, 1), (0, 0, 300, 200, 36.0, 2), (0, 0, 1025, 1024, 35.5, 1), (0, 0, 1025, 1024, 36.5, 2),
+    (0, 0, 1025, 1025, 13.9, 1), (0, 0, 1025, 1025, 14.1, 2), (0, 1, 10, 119, 19.0, 1), (0, 1, 10, 119, 20.0, 2), (0, 1, 119, 10, 44.5, 1),
+    (0, 1, 119, 10, 45.5, 2), (0, 1, 64, 64, 13.9, 1), (0, 1, 64, 64, 14.1, 2),
+    (1, 0, 65, 195, 7.9, 1), (1, 0, 65, 195, 8.1, 2), (1, 0, 195, 65, 19.8, 1), (1, 0, 195, 65, 20.2, 2), (1, 0, 1025, 1024, 23.5, 1), (1, 0, 1025, 1024, 24.5, 2),
+    (1, 1, 32, 97, 10.5, 1), (1, 1, 32, 97, 10.8, 2), (1, 1, 4, 124, 3.35, 1), (1, 1, 4, 124, 3.5, 2),
+    (2, 0, 195, 65, 3.9, 1), (2, 0, 195, 65, 4.1, 2), (2, 0, 50, 200, 3.7, 1), (2, 0, 50, 200, 3.8, 2), (2, 0, 1025, 1024, 15.8, 1), (2, 0, 1025, 1024, 16.2, 2),
+    (2, 1, 100, 50, 5.4, 1), (2, 1, 100, 50, 5.6, 2), (2, 1, 64, 64, 1.9, 1), (2, 1, 64, 64, 2.1, 2),
+])
+def test_single_launch_ends_with_the_time_the_rows_take(storage, selection, c, r, us, launches):
+    import paper_2406_03285_amd as rb
+    elems = int(us * 5.5e6 / (c + r) / (8, 6, 5)[storage]) // 16 * 16
+    rc, h = rb.rb_create(1378, 4, (elems,), rb.RB_F32)
+    assert rb.rb_set_storage(h, storage) == rb.RB_OK and rb.rb_set_policy(h, selection, 0) == rb.RB_OK
+    assert rb.rb_query_launches(h, 2000, c, r) == (rb.RB_OK, launches)
+    rb.rb_destroy(h)
+
+
+# ... converted rows beyond the nearer lines: as many slots as candidates and 32 classes at least.
+@pytest.mark.parametrize("storage,elems", [(1, 32000), (2, 13000)])
+@pytest.mark.parametrize("classes,slots,launches", [(32, 7, 1), (31, 7, 2), (32, 6, 2), (39, 5, 1), (194, 1, 2), (195, 1, 1)])
+def test_single_launch_of_converted_rows_needs_slots(storage, elems, classes, slots, launches):
+    import paper_2406_03285_amd as rb
+    rc, h = rb.rb_create(classes, slots, (elems // 16 * 16,), rb.RB_F32)
+    assert rb.rb_set_storage(h, storage) == rb.RB_OK
+    assert rb.rb_query_launches(h, 400, 195, 65) == (rb.RB_OK, launches)
+    rb.rb_destroy(h)
+
+
 def test_single_launch_with_more_representatives_than_slots():
     import paper_2406_03285_amd as rb
     for selection in (0, 1):

@@ -145,6 +145,21 @@ def test_single_call_without_a_plan(K, S, vecs, b, c, r, store, labels, launches
     assert rb.rb_query_launches(buf.handle, b, c, r) == (rb.RB_OK, want)
 
 
+# ... whose rows take longest: several tiles per wavefront, of long rows and of many candidates' (exact, Bernoulli selection).
+@pytest.mark.parametrize("policy", ["exact-uniform"] + sorted(POLICIES))
+@pytest.mark.parametrize("K,S,vecs,b,c,r,store,labels,launches", [
+    (50, 6, 7501, 320, 300, 100, "same", "uniform", 1),         # ragged rows of 120 KB, 17.5 us of them
+    (300, 3, 37632, 130, 65, 70, "same", "zipf", (2, 1)),       # 30 us: the exact selection has too few candidates
+    (70, 4, 3003, 260, 200, 60, "bf16", "uniform", 1),          # 6.8 us
+    (300, 4, 5000, 100, 20, 120, "bf16", "active50", 1),        # mostly representatives
+    (40, 9, 2001, 200, 90, 40, "u8", "uniform", 1),             # 3.8 us
+    (300, 5, 256, 1200, 1100, 300, "u8", "zipf", 1),            # more than 1024 candidates, 5.2 us
+    (200, 8, 760, 1300, 1100, 100, "bf16", "uniform", 1),       # ... 8 us
+])
+def test_single_call_without_a_plan_and_long_rows(K, S, vecs, b, c, r, store, labels, launches, policy):
+    test_single_call_without_a_plan(K, S, vecs, b, c, r, store, labels, launches, policy)
+
+
 # ... with more candidates of a class than a wavefront has lanes: as many as the single launch takes with few classes, and skewed labels.
 @pytest.mark.parametrize("policy", ["exact-uniform"] + sorted(POLICIES))
 @pytest.mark.parametrize("K,S,vecs,b,c,r,store,labels", [
