@@ -293,29 +293,59 @@ hipError_t launch_sample_small(const SampleArgs& a, int storage, int unroll, dim
     }
 }
 
-template <bool NT>
-hipError_t launch_update(const UpdateArgs& a, int narrow, int unroll, dim3 grid, size_t lds, hipStream_t st)
+template <bool NT, int FORM>
+hipError_t launch_update_f(const UpdateArgs& a, int narrow, int unroll, dim3 grid, size_t lds, hipStream_t st)
 {
     if (narrow == 2) {                  // 8 bits per element: a lane holds four accesses per vector of the tile (at most four vectors)
-        if (unroll == 1) rb_update_kernel<1, NT, 2><<<grid, TPB, lds, st>>>(a);
-        else if (unroll == 2) rb_update_kernel<2, NT, 2><<<grid, TPB, lds, st>>>(a);
-        else rb_update_kernel<4, NT, 2><<<grid, TPB, lds, st>>>(a);
+        if (unroll == 1) rb_update_kernel<1, NT, 2, FORM><<<grid, TPB, lds, st>>>(a);
+        else if (unroll == 2) rb_update_kernel<2, NT, 2, FORM><<<grid, TPB, lds, st>>>(a);
+        else rb_update_kernel<4, NT, 2, FORM><<<grid, TPB, lds, st>>>(a);
         return hipGetLastError();
     }
     if (narrow == 1) {
         switch (unroll) {
-        case 1: rb_update_kernel<1, NT, 1><<<grid, TPB, lds, st>>>(a); break;
-        case 2: rb_update_kernel<2, NT, 1><<<grid, TPB, lds, st>>>(a); break;
-        case 4: rb_update_kernel<4, NT, 1><<<grid, TPB, lds, st>>>(a); break;
-        default: rb_update_kernel<8, NT, 1><<<grid, TPB, lds, st>>>(a); break;
+        case 1: rb_update_kernel<1, NT, 1, FORM><<<grid, TPB, lds, st>>>(a); break;
+        case 2: rb_update_kernel<2, NT, 1, FORM><<<grid, TPB, lds, st>>>(a); break;
+        case 4: rb_update_kernel<4, NT, 1, FORM><<<grid, TPB, lds, st>>>(a); break;
+        default: rb_update_kernel<8, NT, 1, FORM><<<grid, TPB, lds, st>>>(a); break;
         }
         return hipGetLastError();
     }
     switch (unroll) {
-    case 1: rb_update_kernel<1, NT, 0><<<grid, TPB, lds, st>>>(a); break;
-    case 2: rb_update_kernel<2, NT, 0><<<grid, TPB, lds, st>>>(a); break;
-    case 4: rb_update_kernel<4, NT, 0><<<grid, TPB, lds, st>>>(a); break;
-    default: rb_update_kernel<8, NT, 0><<<grid, TPB, lds, st>>>(a); break;
+    case 1: rb_update_kernel<1, NT, 0, FORM><<<grid, TPB, lds, st>>>(a); break;
+    case 2: rb_update_kernel<2, NT, 0, FORM><<<grid, TPB, lds, st>>>(a); break;
+    case 4: rb_update_kernel<4, NT, 0, FORM><<<grid, TPB, lds, st>>>(a); break;
+    default: rb_update_kernel<8, NT, 0, FORM><<<grid, TPB, lds, st>>>(a); break;
+    }
+    return hipGetLastError();
+}
+
+template <bool NT>
+hipError_t launch_update(const UpdateArgs& a, int narrow, int unroll, dim3 grid, size_t lds, hipStream_t st)
+{
+    if (a.selection == RB_SELECT_BERNOULLI) return launch_update_f<NT, GEN_COINS>(a, narrow, unroll, grid, lds, st);
+    return a.c <= GEN_FEW ? launch_update_f<NT, GEN_EXACT_FEW>(a, narrow, unroll, grid, lds, st) : launch_update_f<NT, GEN_EXACT_MANY>(a, narrow, unroll, grid, lds, st);
+}
+
+template <bool NT, bool MANY>
+hipError_t launch_sample_f(const SampleArgs& a, int widen, int unroll, dim3 grid, size_t lds, hipStream_t st)
+{
+    if (widen == 2) {
+        if (unroll == 1) rb_sample_kernel<1, NT, 2, MANY><<<grid, TPB, lds, st>>>(a);
+        else rb_sample_kernel<2, NT, 2, MANY><<<grid, TPB, lds, st>>>(a);
+        return hipGetLastError();
+    }
+    if (widen == 1) {
+        if (unroll == 1) rb_sample_kernel<1, NT, 1, MANY><<<grid, TPB, lds, st>>>(a);
+        else if (unroll == 2) rb_sample_kernel<2, NT, 1, MANY><<<grid, TPB, lds, st>>>(a);
+        else rb_sample_kernel<4, NT, 1, MANY><<<grid, TPB, lds, st>>>(a);
+        return hipGetLastError();
+    }
+    switch (unroll) {
+    case 1: rb_sample_kernel<1, NT, 0, MANY><<<grid, TPB, lds, st>>>(a); break;
+    case 2: rb_sample_kernel<2, NT, 0, MANY><<<grid, TPB, lds, st>>>(a); break;
+    case 4: rb_sample_kernel<4, NT, 0, MANY><<<grid, TPB, lds, st>>>(a); break;
+    default: rb_sample_kernel<8, NT, 0, MANY><<<grid, TPB, lds, st>>>(a); break;
     }
     return hipGetLastError();
 }
@@ -323,24 +353,7 @@ hipError_t launch_update(const UpdateArgs& a, int narrow, int unroll, dim3 grid,
 template <bool NT>
 hipError_t launch_sample(const SampleArgs& a, int widen, int unroll, dim3 grid, size_t lds, hipStream_t st)
 {
-    if (widen == 2) {
-        if (unroll == 1) rb_sample_kernel<1, NT, 2><<<grid, TPB, lds, st>>>(a);
-        else rb_sample_kernel<2, NT, 2><<<grid, TPB, lds, st>>>(a);
-        return hipGetLastError();
-    }
-    if (widen == 1) {
-        if (unroll == 1) rb_sample_kernel<1, NT, 1><<<grid, TPB, lds, st>>>(a);
-        else if (unroll == 2) rb_sample_kernel<2, NT, 1><<<grid, TPB, lds, st>>>(a);
-        else rb_sample_kernel<4, NT, 1><<<grid, TPB, lds, st>>>(a);
-        return hipGetLastError();
-    }
-    switch (unroll) {
-    case 1: rb_sample_kernel<1, NT, 0><<<grid, TPB, lds, st>>>(a); break;
-    case 2: rb_sample_kernel<2, NT, 0><<<grid, TPB, lds, st>>>(a); break;
-    case 4: rb_sample_kernel<4, NT, 0><<<grid, TPB, lds, st>>>(a); break;
-    default: rb_sample_kernel<8, NT, 0><<<grid, TPB, lds, st>>>(a); break;
-    }
-    return hipGetLastError();
+    return a.r > BIG_MAX && a.r <= a.K * a.S ? launch_sample_f<NT, true>(a, widen, unroll, grid, lds, st) : launch_sample_f<NT, false>(a, widen, unroll, grid, lds, st);
 }
 
 template <bool NT, int ST, bool AUX>
@@ -1608,7 +1621,7 @@ int rb_update(rb_buffer* rb, const void* batch_x, const int64_t* batch_y,
     a.aux_old = reinterpret_cast<const int32_t*>(rb->ws + rb->off_aux[rb->cur]);
     a.aux_new = reinterpret_cast<int32_t*>(rb->ws + rb->off_aux[rb->cur ^ 1]);
     const dim3 grid((unsigned)(rb->nchunks + (small ? sh.groups * sh.tpr : (rows * sh.tpr + NWAVE - 1) / NWAVE)));
-    const size_t lds = small ? small_lds_bytes(b, rb->nchunks) : (size_t)b * 4 + (size_t)a.cap * 8;
+    const size_t lds = small ? small_lds_bytes(b, rb->nchunks) : gen_update_lds_bytes((int)b, a.cap, rb->selection == RB_SELECT_BERNOULLI);
     const bool ordinary = ordinary_stores(rb, c, STORES_HALF);
     const hipError_t e = small ? (rb->opt_nt ? launch_update_small<true>(a, rb->storage, sh.unroll, grid, lds, rb->stream, ordinary)
                                              : launch_update_small<false>(a, rb->storage, sh.unroll, grid, lds, rb->stream, ordinary))
@@ -1645,7 +1658,7 @@ int rb_sample_augment(rb_buffer* rb, int64_t r, uint64_t seed, uint64_t step, vo
     a.row_vec = rb->row_vec;
     a.tpr = sh.tpr; a.tile_vec = sh.tile_vec; a.tile_rem = sh.tile_rem; a.rpb = sh.rpb;
     const dim3 grid((unsigned)(small ? sh.groups * sh.tpr : (r * sh.tpr + NWAVE - 1) / NWAVE));
-    const size_t lds = small ? 0 : ((size_t)rb->nchunks + (size_t)r) * 4;
+    const size_t lds = small ? 0 : gen_sample_lds_bytes((int)r, rb->nchunks);
     const bool ordinary = ordinary_stores(rb, r, STORES_HALF);
     const hipError_t e = small ? (rb->opt_nt ? launch_sample_small<true>(a, rb->storage, sh.unroll, grid, rb->stream, ordinary)
                                              : launch_sample_small<false>(a, rb->storage, sh.unroll, grid, rb->stream, ordinary))

@@ -148,6 +148,9 @@ __device__ __forceinline__ int lane_read(int v, int src)
     return __builtin_amdgcn_readlane(v, src);
 }
 
+// Lanes of one wavefront read what other lanes of it have written to LDS.
+__device__ __forceinline__ void wave_lds_wait() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
 // Workgroup barrier that orders LDS traffic only.  __syncthreads() also waits for every global load
 // and store the wavefront has in flight; the planners keep loads on their way in and table entries
 // and fill counts on their way out across these barriers (nobody in the same launch reads them).

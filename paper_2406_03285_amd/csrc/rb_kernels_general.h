@@ -26,27 +26,46 @@ __global__ void __launch_bounds__(TPB) rb_reset_kernel(uint32_t* __restrict__ ws
 // takes one work item (candidate row, tile of WAVE * U vectors) and works out
 // alone, with ballots over the candidate list, where that candidate goes.
 //
-// LDS (dynamic): s_first[b] u32 (lowest candidate index that drew a value;
-// with the Bernoulli selection: the class of every position whose coin came up heads),
-// s_k[cap] i32 (class per candidate, LAB_INVALID outside [0, K)), s_t[cap] u16
-// (Floyd draws), s_x[cap] u16 (candidate positions, Floyd emission order or,
-// with the Bernoulli selection, mini-batch order); cap = c, or b for Bernoulli.
+// LDS (dynamic): s_k[cap] i32 (class per candidate, LAB_INVALID outside [0, K), LAB_UNSELECTED behind the list's end),
+// s_x[cap] u16 (candidate positions, Floyd emission order or, with the Bernoulli selection, mini-batch order), both rounded up to GEN_LIST;
+// with the exact selection also s_first[b] u32 (lowest candidate index that drew a value) and s_t[cap] u16 (Floyd draws).  cap = c, or b for
+// Bernoulli.
+//
+// What bounds it, beside the rows: one wavefront per unit of a compute unit makes all draws, one chain of dependent multiplications behind the
+// other, and every wavefront passes over the whole list.  Hence two draws side by side, the list read four candidates per lane and
+// access, coins counted by ballots (a thread that walked its stretch of the mini-batch twice took 16 LDS accesses each time).
 //
 // Grid: `nchunks` bookkeeping workgroups (new fill counts and chunk sums for CH
 // classes each), then ceil(c * tpr / NWAVE) mover workgroups.
 // ---------------------------------------------------------------------------
 
-template <int U, bool NT, int NARROW>       // NARROW: binary32 mini-batch rows are stored 0 - as they come, 1 - as bfloat16, 2 - in 8 bits per element
+constexpr int GEN_LIST = 4 * WAVE;          // the candidate list and the sampling draws are read this many at a time
+__host__ __device__ inline int gen_padded(int n) { return (n + GEN_LIST - 1) / GEN_LIST * GEN_LIST; }
+inline size_t gen_update_lds_bytes(int b, int cap, bool bernoulli) { return (size_t)gen_padded(cap) * 6 + (bernoulli ? 0 : (size_t)b * 4 + (size_t)cap * 2); }
+inline size_t gen_sample_lds_bytes(int r, int nchunks) { return 4 * (size_t)(nchunks + r > ((r + 3) & ~3) ? nchunks + r : (r + 3) & ~3); }
+
+// Lane `lane` looks at four consecutive candidates of every GEN_LIST: number `bit` of its candidates is this one of the list.
+__device__ __forceinline__ int gen_entry(int bit, int lane) { return (bit >> 2) * GEN_LIST + 4 * lane + (bit & 3); }
+
+// A kernel per form of the selection: exact with up to GEN_FEW candidates, exact with more, Bernoulli.  (Two draws side by side and four
+// candidates per access: 300 to 500 candidates 3 % faster, 500 to 2048 9 to 12 %, more 30 %, but 65 to 128 2 % slower, 128 to 200 1 %, 200 to 300 equal.
+// Coins counted by ballots: mini-batches of 256 to 1024 5 % faster, 1024 to 2048 7 %, more 12 %, smaller ones equal.)
+enum { GEN_EXACT_FEW = 0, GEN_EXACT_MANY = 1, GEN_COINS = 2 };
+constexpr int GEN_FEW = 192;
+
+template <int U, bool NT, int NARROW, int FORM>       // NARROW: binary32 mini-batch rows are stored 0 - as they come, 1 - as bfloat16, 2 - in 8 bits per element
 __global__ void __launch_bounds__(TPB) rb_update_kernel(const UpdateArgs a)
 {
-    extern __shared__ uint32_t lds[];
-    uint32_t* s_first = lds;                                          // [b]
-    int32_t* s_k = reinterpret_cast<int32_t*>(lds + a.b);             // [cap]
-    uint16_t* s_t = reinterpret_cast<uint16_t*>(lds + a.b + a.cap);   // [cap]
-    uint16_t* s_x = s_t + a.cap;                                      // [cap]
+    extern __shared__ __align__(16) uint32_t lds[];
+    const int listed = gen_padded(a.cap);
+    int32_t* s_k = reinterpret_cast<int32_t*>(lds);                   // [listed]
+    uint16_t* s_x = reinterpret_cast<uint16_t*>(lds + listed);        // [listed]
+    uint32_t* s_first = lds + listed + listed / 2;                    // [b]
+    uint16_t* s_t = reinterpret_cast<uint16_t*>(s_first + a.b);       // [cap]
     __shared__ int s_wave[NWAVE];
     __shared__ int s_hist[CH];
-    __shared__ uint16_t s_pend[NWAVE][2 * WAVE];    // per wavefront: later class-mates waiting for their evict draw
+    __shared__ int s_seg[WAVE];                             // Bernoulli: heads per stretch of WAVE positions
+    __shared__ uint16_t s_pend[NWAVE][WAVE];                // per wavefront: the class-mates, one per lane
     __shared__ uint32_t s_cm[NWAVE][RB_MAX_BATCH / 32];     // per wavefront: bitmap of the class-mates' positions
     __shared__ uint16_t s_cmpre[NWAVE][RB_MAX_BATCH / 32];  // class-mates before each bitmap word
 
@@ -54,12 +73,10 @@ __global__ void __launch_bounds__(TPB) rb_update_kernel(const UpdateArgs a)
     const int b = a.b, c = a.c;
     int m;      // number of candidates of this step (the same in every workgroup)
 
-    if (a.selection == RB_SELECT_BERNOULLI) {
+    if constexpr (FORM == GEN_COINS) {
         // ---- one coin per sample, heads with probability c/b; candidates in mini-batch order ----
-        // s_lab[q] = class of sample q if its coin came up heads, LAB_UNSELECTED otherwise.  All labels
-        // are requested first (coalesced, MAX_PER = RB_MAX_BATCH / TPB per thread) so that their memory
-        // round trip overlaps the coin draws.
-        int32_t* s_lab = reinterpret_cast<int32_t*>(s_first);
+        // All labels are requested first (coalesced, MAX_PER = RB_MAX_BATCH / TPB per thread) so that their memory round trip overlaps
+        // the coin draws.
         constexpr int MAX_PER = RB_MAX_BATCH / TPB;
         int64_t yl[MAX_PER];
 #pragma unroll
@@ -68,28 +85,40 @@ __global__ void __launch_bounds__(TPB) rb_update_kernel(const UpdateArgs a)
             yl[u] = q < b ? a.batch_y[q] : -1;
         }
         uint32_t heads = 0;                    // bit u: the coin of sample tid + u * TPB
-        for (int q = tid, u = 0; q < b; q += TPB, ++u)
-            heads |= (uint32_t)((int64_t)below(a.sd, PURPOSE_COIN, (uint32_t)q, (uint64_t)b) < c) << u;
-#pragma unroll
-        for (int u = 0; u < MAX_PER; ++u) {
-            const int q = tid + u * TPB;
-            if (q < b) s_lab[q] = !((heads >> u) & 1u) ? LAB_UNSELECTED : (yl[u] >= 0 && yl[u] < a.K) ? (int32_t)yl[u] : LAB_INVALID;
-        }
-        __syncthreads();
-        const int per = (b + TPB - 1) / TPB;
-        const int q_lo = tid * per, q_hi = q_lo + per < b ? q_lo + per : b;
-        int mine = 0;
-        for (int q = q_lo; q < q_hi; ++q) mine += s_lab[q] != LAB_UNSELECTED;
-        int at = block_scan_excl(mine, m, s_wave);
-        for (int q = q_lo; q < q_hi; ++q) {
-            const int32_t k = s_lab[q];
-            if (k != LAB_UNSELECTED) {
-                s_x[at] = (uint16_t)q;
-                s_k[at] = k;
-                ++at;
+#pragma unroll 1
+        for (int u = 0; u * TPB < b; u += 2) {
+            const int q0 = tid + u * TPB, q1 = q0 + TPB;
+            uint64_t d0, d1 = 0;
+            const bool second = (u + 1) * TPB < b;
+            if (second) {                      // (two at a time)
+                d0 = draw64(a.sd, PURPOSE_COIN, (uint32_t)q0);
+                d1 = draw64(a.sd, PURPOSE_COIN, (uint32_t)q1);
+            } else {
+                d0 = draw64(a.sd, PURPOSE_COIN, (uint32_t)q0);
+            }
+            const bool head0 = q0 < b && (int)reduce32(d0, (uint32_t)b) < c, head1 = q1 < b && (int)reduce32(d1, (uint32_t)b) < c;
+            heads |= (uint32_t)head0 << u | (uint32_t)head1 << (u + 1);
+            const int in0 = __popcll(__ballot(head0)), in1 = __popcll(__ballot(head1));
+            if (lane == 0) {
+                s_seg[u * NWAVE + wave] = in0;
+                s_seg[(u + 1) * NWAVE + wave] = in1;
             }
         }
         __syncthreads();
+        static_assert(MAX_PER * NWAVE == WAVE && MAX_PER % 2 == 0, "one lane per stretch of positions, pairs of them");
+        const int incl = wave_scan_incl(lane < (b + TPB - 1) / TPB * NWAVE ? s_seg[lane] : 0);
+        m = lane_read(incl, WAVE - 1);
+#pragma unroll
+        for (int u = 0; u < MAX_PER; ++u) {
+            if (u * TPB >= b) break;
+            const bool mine = (heads >> u) & 1;
+            const uint64_t seg_heads = __ballot(mine);
+            const int at = lane_read(incl, u * NWAVE + __builtin_amdgcn_readfirstlane(wave)) - __popcll(seg_heads >> lane);     // (the sum less this one and the heads behind it)
+            if (mine) {
+                s_x[at] = (uint16_t)(tid + u * TPB);
+                s_k[at] = yl[u] >= 0 && yl[u] < a.K ? (int32_t)yl[u] : LAB_INVALID;
+            }
+        }
     } else {
         // ---- candidate selection: Floyd's c-subset of [0, b), all draws at once --
         // Draw i is t_i in [0, b-c+i]; it is "taken" iff an earlier draw had the same
@@ -99,10 +128,35 @@ __global__ void __launch_bounds__(TPB) rb_update_kernel(const UpdateArgs a)
         const int base = b - c;
         // s_first[v] = lowest candidate index that drew v: only the entries that are drawn at all
         // are initialised (by every thread that drew them), then minimised
-        for (int i = tid; i < c; i += TPB) {
-            uint32_t t = (uint32_t)below(a.sd, PURPOSE_SELECT, (uint32_t)i, (uint64_t)(base + i + 1));
-            s_t[i] = (uint16_t)t;
-            s_first[t] = 0xFFFFFFFFu;
+        // (of a large mini-batch the labels are near when the candidates' are asked for: one load per 64 bytes)
+        static_assert(RB_MAX_BATCH * sizeof(int64_t) / 64 <= 2 * TPB, "two loads per thread");
+        int64_t near0 = 0, near1 = 0;
+        if (FORM == GEN_EXACT_MANY && b > 4 * TPB) {
+            near0 = a.batch_y[min(8 * tid, b - 1)];
+            near1 = a.batch_y[min(8 * (tid + TPB), b - 1)];
+        }
+        if constexpr (FORM == GEN_EXACT_FEW) {
+            for (int i = tid; i < c; i += TPB) {
+                uint32_t t = (uint32_t)below(a.sd, PURPOSE_SELECT, (uint32_t)i, (uint64_t)(base + i + 1));
+                s_t[i] = (uint16_t)t;
+                s_first[t] = 0xFFFFFFFFu;
+            }
+        } else {
+#pragma unroll 1
+            for (int i0 = tid; i0 < c; i0 += 2 * TPB) {
+                const int i1 = i0 + TPB;
+                if (__builtin_amdgcn_readfirstlane(i1) < c) {       // (two at a time)
+                    const uint64_t d0 = draw64(a.sd, PURPOSE_SELECT, (uint32_t)i0), d1 = draw64(a.sd, PURPOSE_SELECT, (uint32_t)i1);
+                    const uint32_t t0 = reduce32(d0, (uint32_t)(base + i0 + 1)), t1 = reduce32(d1, (uint32_t)(base + i1 + 1));
+                    s_t[i0] = (uint16_t)t0;
+                    s_first[t0] = 0xFFFFFFFFu;
+                    if (i1 < c) { s_t[i1] = (uint16_t)t1; s_first[t1] = 0xFFFFFFFFu; }
+                } else {
+                    const uint32_t t0 = reduce32(draw64(a.sd, PURPOSE_SELECT, (uint32_t)i0), (uint32_t)(base + i0 + 1));
+                    s_t[i0] = (uint16_t)t0;
+                    s_first[t0] = 0xFFFFFFFFu;
+                }
+            }
         }
         __syncthreads();
         for (int i = tid; i < c; i += TPB) atomicMin(&s_first[s_t[i]], (uint32_t)i);
@@ -120,6 +174,7 @@ __global__ void __launch_bounds__(TPB) rb_update_kernel(const UpdateArgs a)
             s_x[i] = (uint16_t)(taken ? base + i : (int)s_t[i]);
         }
         // the candidates' labels, four loads in flight per thread
+        if (FORM == GEN_EXACT_MANY) asm volatile("" : : "v"(near0), "v"(near1));
         for (int i0 = tid; i0 < c; i0 += 4 * TPB) {
             int64_t y[4];
 #pragma unroll
@@ -133,8 +188,10 @@ __global__ void __launch_bounds__(TPB) rb_update_kernel(const UpdateArgs a)
                 if (i < c) s_k[i] = (y[u] >= 0 && y[u] < a.K) ? (int32_t)y[u] : LAB_INVALID;
             }
         }
-        __syncthreads();
     }
+    if (FORM != GEN_EXACT_FEW)
+        for (int q = m + tid; q < gen_padded(m); q += TPB) s_k[q] = LAB_UNSELECTED;
+    __syncthreads();
 
     if ((int)blockIdx.x < a.nchunks) {
         // ---- bookkeeping: fill_new = min(fill_old + candidates of the class, S) ----
@@ -192,17 +249,32 @@ __global__ void __launch_bounds__(TPB) rb_update_kernel(const UpdateArgs a)
         t.load(a.batch_x + (int64_t)p * a.row_vec * (NARROW == 2 ? 4 : NARROW ? 2 : 1), v_lo, v_hi);
 
         // Candidates of class ki, in mini-batch order: the one with `rank` class-mates before it is
-        // insertion number fill0 + rank of the class.  Each lane looks at every WAVE-th candidate,
+        // insertion number fill0 + rank of the class.  Each lane looks at four of every GEN_LIST candidates,
         // remembers in a bit mask which of them are class-mates, and the counts are summed over the
         // wavefront once at the end (no ballot, hence no scalar dependency, per round).
-        uint64_t hit = 0;                      // bit `round`: candidate round * WAVE + lane is a class-mate (m <= 64 * WAVE)
+        uint64_t hit = 0;                      // bit i: candidate entry(i) is a class-mate (m <= 64 * WAVE)
         int my_rank = 0;
-        for (int m0 = 0, round = 0; m0 < m; m0 += WAVE, ++round) {
-            const int q = m0 + lane;
-            const bool same = q < m && s_k[q] == ki;
-            const int xq = q < m ? s_x[q] : 0;
-            hit |= (uint64_t)same << round;
-            my_rank += same && xq < p;
+        // (a list of up to two candidates per lane: one of every WAVE, else few lanes hold most class-mates; 72 candidates of 2 classes
+        // 5.66 us, 5.95 with four per lane)
+        const bool wide = FORM == GEN_EXACT_MANY || (FORM == GEN_COINS && m > 2 * WAVE);
+        const auto entry = [&](int bit) { return wide ? gen_entry(bit, lane) : bit * WAVE + lane; };
+        if (wide) {
+#pragma unroll 2
+            for (int m0 = 0; m0 < m; m0 += GEN_LIST) {
+                const int4 kq = *reinterpret_cast<const int4*>(s_k + m0 + 4 * lane);
+                const ushort4 xq = *reinterpret_cast<const ushort4*>(s_x + m0 + 4 * lane);
+                const uint32_t same = (kq.x == ki ? 1u : 0u) | (kq.y == ki ? 2u : 0u) | (kq.z == ki ? 4u : 0u) | (kq.w == ki ? 8u : 0u);
+                hit |= (uint64_t)same << (m0 / WAVE);
+                my_rank += (kq.x == ki && xq.x < p) + (kq.y == ki && xq.y < p) + (kq.z == ki && xq.z < p) + (kq.w == ki && xq.w < p);
+            }
+        } else {
+            for (int m0 = 0, round = 0; m0 < m; m0 += WAVE, ++round) {
+                const int q = m0 + lane;
+                const bool same = q < m && s_k[q] == ki;
+                const int xq = q < m ? s_x[q] : 0;
+                hit |= (uint64_t)same << round;
+                my_rank += same && xq < p;
+            }
         }
         const int mine = __popcll(hit);
         const int incl = wave_scan_incl(mine | (my_rank << 16));      // both sums are <= 4096
@@ -225,7 +297,8 @@ __global__ void __launch_bounds__(TPB) rb_update_kernel(const UpdateArgs a)
             const bool reservoir = a.eviction == RB_EVICT_RESERVOIR;
             uint16_t* pend = s_pend[wave];
             int at = (incl & 0xFFFF) - mine;
-            for (uint64_t h = hit; h != 0; h &= h - 1) pend[at++] = s_x[__builtin_ctzll(h) * WAVE + lane];
+            for (uint64_t h = hit; h != 0; h &= h - 1) pend[at++] = s_x[entry(__builtin_ctzll(h))];
+            wave_lds_wait();
             const bool has = lane < total;
             const int xl = has ? pend[lane] : 0;
             int rl = 0;
@@ -258,44 +331,33 @@ __global__ void __launch_bounds__(TPB) rb_update_kernel(const UpdateArgs a)
             uint16_t* cmpre = s_cmpre[wave];
             cm[2 * lane] = 0u;
             cm[2 * lane + 1] = 0u;
-            for (int m0 = 0; m0 < m; m0 += WAVE) {
-                const int q = m0 + lane;
-                if (q < m && s_k[q] == ki) atomicOr(&cm[s_x[q] >> 5], 1u << (s_x[q] & 31));
+            wave_lds_wait();                   // (else a lane without class-mates takes its words for the zeros it wrote)
+            for (uint64_t h = hit; h != 0; h &= h - 1) {
+                const int x = s_x[entry(__builtin_ctzll(h))];
+                atomicOr(&cm[x >> 5], 1u << (x & 31));
             }
+            wave_lds_wait();
             {
                 const int p0 = __popc(cm[2 * lane]), p1 = __popc(cm[2 * lane + 1]);
                 const int before = wave_scan_incl(p0 + p1) - (p0 + p1);
                 cmpre[2 * lane] = (uint16_t)before;
                 cmpre[2 * lane + 1] = (uint16_t)(before + p0);
             }
-            // later class-mates are gathered WAVE at a time so that their draws are made with full wavefronts
-            uint16_t* pend = s_pend[wave];
-            int npend = 0;
+            wave_lds_wait();
+            // every lane draws for the later class-mates it holds: the list is dealt to the lanes evenly
             bool beaten = false;
-            for (int m0 = 0; m0 < m + WAVE; m0 += WAVE) {
-                if (m0 < m) {
-                    const int q = m0 + lane;
-                    const int xq = q < m ? s_x[q] : 0;
-                    const bool later = q < m && s_k[q] == ki && xq > p;
-                    const uint64_t mask = __ballot(later);
-                    if (later) pend[npend + __popcll(mask & ((1ull << lane) - 1))] = (uint16_t)xq;
-                    npend += __popcll(mask);
-                }
-                if (npend >= WAVE || (m0 >= m && npend > 0)) {
-                    const int take = npend < WAVE ? npend : WAVE;
-                    const int xr = lane < take ? pend[lane] : 0;
+            for (uint64_t h = hit; !beaten && __ballot(h != 0) != 0; h &= h - 1) {
+                const int x = h != 0 ? (int)s_x[entry(__builtin_ctzll(h))] : -1;
+                bool takes = false;
+                if (x > p) {
                     // the rival's insertion number decides whether it overwrites at all, and (reservoir) its odds
-                    const int rank_r = cmpre[xr >> 5] + __popc(cm[xr >> 5] & ((1u << (xr & 31)) - 1u));
-                    bool hit = false;
-                    if (lane < take && fill0 + rank_r >= a.S) {
+                    const int rank_r = cmpre[x >> 5] + __popc(cm[x >> 5] & ((1u << (x & 31)) - 1u));
+                    if (fill0 + rank_r >= a.S) {
                         const int64_t offers = aux0 + rank_r < INT32_MAX ? aux0 + rank_r : INT32_MAX;
-                        hit = (int64_t)below(a.sd, PURPOSE_EVICT, (uint32_t)xr, reservoir ? (uint64_t)offers + 1 : (uint64_t)a.S) == own;
+                        takes = (int64_t)below(a.sd, PURPOSE_EVICT, (uint32_t)x, reservoir ? (uint64_t)offers + 1 : (uint64_t)a.S) == own;
                     }
-                    beaten |= __ballot(hit) != 0;
-                    const int rest = lane + take < npend ? pend[lane + take] : 0;    // at most WAVE - 1 left over
-                    if (lane + take < npend) pend[lane] = (uint16_t)rest;
-                    npend -= take;
                 }
+                beaten = __ballot(takes) != 0;
             }
             if (beaten) continue;
             slot = own;
@@ -317,26 +379,37 @@ __global__ void __launch_bounds__(TPB) rb_update_kernel(const UpdateArgs a)
 // draw is taken, finds the chunk that holds the wanted sample, reads that
 // chunk's CH fill counts (four consecutive classes per lane) and moves its tile.
 //
-// LDS (dynamic): s_cpre[nchunks] i32, s_t[r] u32.
+// What bounds it, beside the rows: the draws (up to 16 per thread; of more than BIG_MAX two at a time, the first two while the chunk sums
+// travel: 2000 rows of 4 KB 12.3 -> 9.6 us) and the chain draw -> chunk -> fill counts -> row.
+//
+// LDS (dynamic): s_t[r] u32, s_cpre[nchunks] i32.
 // Grid: ceil(r * tpr / NWAVE) workgroups.
 // ---------------------------------------------------------------------------
 
-template <int U, bool NT, int WIDEN>        // WIDEN: rows are handed out 0 - as stored, 1 - widened from bfloat16, 2 - from 8 bits per element to binary32
+// MANY: of more than BIG_MAX representatives, of as many slots at least (1024 to 2048 7 % faster, more 14 %; up to 256 as fast or 1 % slower; of
+// fewer slots most draws are never needed: 747 of 18 slots 6.2 us, 8.7 with the first ones made in front).
+template <int U, bool NT, int WIDEN, bool MANY>        // WIDEN: rows are handed out 0 - as stored, 1 - widened from bfloat16, 2 - from 8 bits per element to binary32
 __global__ void __launch_bounds__(TPB) rb_sample_kernel(const SampleArgs a)
 {
-    extern __shared__ uint32_t lds[];
-    int32_t* s_cpre = reinterpret_cast<int32_t*>(lds);    // [nchunks]
-    uint32_t* s_t = lds + a.nchunks;                      // [r]
+    extern __shared__ __align__(16) uint32_t lds[];
+    uint32_t* s_t = lds;                                  // [r]
+    int32_t* s_cpre = reinterpret_cast<int32_t*>(lds + a.r);    // [nchunks]
     __shared__ int s_wave[NWAVE];
 
-    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = MANY ? __builtin_amdgcn_readfirstlane(tid / WAVE) : tid / WAVE;
 
-    // ---- F and the number of stored samples before every chunk -----------------
+    // ---- F and the number of stored samples before every chunk, with many the random bits of the first draws meanwhile ----
     const int cper = (a.nchunks + TPB - 1) / TPB;
+    uint64_t bits0 = 0, bits1 = 0;                        // of the draws tid and tid + TPB
     int csum = 0;
     for (int u = 0; u < cper; ++u) {
         int ch = tid * cper + u;
         if (ch < a.nchunks) csum += a.chunk[ch];
+    }
+    if constexpr (MANY) {
+        bits0 = draw64(a.sd, PURPOSE_SAMPLE, (uint32_t)tid);
+        bits1 = draw64(a.sd, PURPOSE_SAMPLE, (uint32_t)(tid + TPB));
+        asm volatile("" : "+v"(bits0), "+v"(bits1));      // (here, not where they are used)
     }
     int F;
     int cbefore = block_scan_excl(csum, F, s_wave);
@@ -352,8 +425,24 @@ __global__ void __launch_bounds__(TPB) rb_sample_kernel(const SampleArgs a)
 
     // ---- Floyd's n-subset of [0, F): all draws ----------------------------------
     const int base = F - n;
-    for (int i = tid; i < n; i += TPB)
-        s_t[i] = (uint32_t)below(a.sd, PURPOSE_SAMPLE, (uint32_t)i, (uint64_t)base + i + 1);
+    if constexpr (MANY) {
+        if (tid < n) s_t[tid] = reduce32(bits0, (uint32_t)base + (uint32_t)tid + 1u);
+        if (tid + TPB < n) s_t[tid + TPB] = reduce32(bits1, (uint32_t)(base + tid + TPB) + 1u);
+#pragma unroll 1
+        for (int u = 2; wave * WAVE + u * TPB < n; u += 2) {
+            const int i0 = tid + u * TPB, i1 = i0 + TPB;
+            if (wave * WAVE + (u + 1) * TPB < n) {
+                const uint64_t d0 = draw64(a.sd, PURPOSE_SAMPLE, (uint32_t)i0), d1 = draw64(a.sd, PURPOSE_SAMPLE, (uint32_t)i1);
+                s_t[i0] = reduce32(d0, (uint32_t)base + (uint32_t)i0 + 1u);
+                if (i1 < n) s_t[i1] = reduce32(d1, (uint32_t)base + (uint32_t)i1 + 1u);
+            } else if (i0 < n) {
+                s_t[i0] = reduce32(draw64(a.sd, PURPOSE_SAMPLE, (uint32_t)i0), (uint32_t)base + (uint32_t)i0 + 1u);
+            }
+        }
+    } else {
+        for (int i = tid; i < n; i += TPB)
+            s_t[i] = (uint32_t)below(a.sd, PURPOSE_SAMPLE, (uint32_t)i, (uint64_t)base + i + 1);
+    }
     __syncthreads();
 
     // ---- one work item per wavefront, no workgroup barrier from here on ---------
@@ -375,7 +464,16 @@ __global__ void __launch_bounds__(TPB) rb_sample_kernel(const SampleArgs a)
     for (;;) {
         const uint32_t t = s_t[cur];
         bool same = false;
-        for (int q = lane; q < cur; q += WAVE) same |= (s_t[q] == t);
+        if constexpr (MANY) {
+#pragma unroll 2
+            for (int q0 = 0; q0 < cur; q0 += GEN_LIST) {      // (lanes behind the last draw read its words again; none of theirs counts)
+                const int at = q0 + 4 * lane, left = cur - at;        // of the lane's words, those before draw `cur`
+                const uint4 v = *reinterpret_cast<const uint4*>(s_t + min(at, (n - 1) & ~3));
+                same |= (v.x == t && left > 0) | (v.y == t && left > 1) | (v.z == t && left > 2) | (v.w == t && left > 3);
+            }
+        } else {
+            for (int q = lane; q < cur; q += WAVE) same |= (s_t[q] == t);
+        }
         if (__ballot(same) != 0) { taken = true; break; }
         const int64_t q = (int64_t)t - base;
         if (q < 0 || q >= cur) break;
@@ -385,6 +483,7 @@ __global__ void __launch_bounds__(TPB) rb_sample_kernel(const SampleArgs a)
 
     // chunk holding g: the last one with s_cpre <= g
     int lo = 0, hi = a.nchunks - 1;
+    if (MANY && a.nchunks <= WAVE) lo = hi = __popcll(__ballot(lane < a.nchunks && s_cpre[lane] <= g)) - 1;
     while (lo < hi) {
         int mid = (lo + hi + 1) >> 1;
         if (s_cpre[mid] <= g) lo = mid; else hi = mid - 1;

@@ -22,9 +22,6 @@ constexpr uint32_t ONE_NO_CLASS = 0xFFFFFFFFu;      // ... of a candidate whose 
 static_assert(RB_MAX_BATCH <= 1 << ONE_POS_BITS && ONE_CLASSES < 1 << (31 - ONE_POS_BITS), "class and position in one word");
 constexpr int ONE_WORDS = RB_MAX_BATCH / 32;        // words of a bitmap over the mini-batch's positions
 
-// Lanes of one wavefront read what other lanes of it have written to LDS.
-__device__ __forceinline__ void wave_lds_wait() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
-
 struct OneArgs {
     UpdateArgs u;                       // (u.tpr, u.tile_vec, u.tile_rem: tiles of the candidates' rows)
     vec16* out_x;

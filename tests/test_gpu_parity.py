@@ -115,6 +115,17 @@ def test_policy_variant_through_the_single_call_and_at_full_size():
     run_parity(wl.C4, steps=30, policy=POLICIES["bernoulli-fifo"], single_call=True, progress=10)
 
 
+# The two calls' general kernels: 256 threads make two draws at a time and read their lists 256 at a time.  Odd numbers of draws, of
+# coins and of words in a list's last round, fewer stored samples than asked for, chunks of classes beyond a wavefront's and a workgroup's.
+@pytest.mark.parametrize("policy", ["exact-uniform"] + sorted(POLICIES))
+@pytest.mark.parametrize("K,S,b,c,r", [(40, 30, 256, 65, 65), (40, 30, 257, 256, 257), (40, 30, 513, 257, 512), (40, 30, 1024, 513, 514), (40, 30, 1025, 768, 769),
+                                       (100, 50, 2049, 1025, 1027), (30, 200, 4095, 3841, 4093), (3, 500, 1500, 1300, 1025), (3, 4, 600, 500, 4096),
+                                       (16640, 2, 300, 70, 66), (66000, 1, 1030, 300, 63)])
+def test_general_kernels_at_the_edges_of_their_rounds(K, S, b, c, r, policy):
+    w = wl.Workload(f"edges-K{K}-b{b}-c{c}-r{r}", 9, K, S, (8,), "f32", b, c, r, 4, "uniform", "uniform")
+    run_parity(w, check_state_every=2, policy=POLICIES.get(policy))
+
+
 # The single call without a plan: small counts (one launch, any strategy and storage form) and the shapes beyond them.
 # launches: what the call has to take, (exact, Bernoulli selection) where they differ.
 @pytest.mark.parametrize("policy", ["exact-uniform"] + sorted(POLICIES))
