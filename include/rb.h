@@ -342,7 +342,9 @@ int rb_query_launches(const rb_buffer *rb, int64_t b, int64_t c, int64_t r, int6
  * call's work as said in (1).  The mini-batch must stay unchanged until that
  * work is complete, i.e. until train_stream has passed the wait of the next
  * rb_pipeline_step or rb_pipeline_drain.  If train_stream is the bound stream
- * itself the call degenerates to rb_update_sample.
+ * itself the call degenerates to rb_update_sample; a later call or drain with
+ * another train_stream makes that one wait for everything enqueued on the
+ * bound stream until then.
  *
  * rb_pipeline_create makes the two events (no device memory); the pipeline
  * borrows `rb`, which must outlive it.  rb_pipeline_drain only does (1): it

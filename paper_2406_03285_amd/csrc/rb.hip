@@ -1372,6 +1372,7 @@ struct rb_pipeline {
     rb_buffer* rb;
     hipEvent_t ready;     // on the training stream: mini-batch produced, earlier representatives consumed
     hipEvent_t done;      // on the buffer's stream: the latest step's update and sampling are complete
+    bool recorded;        // `done` has been recorded behind that step (wait_done)
     int64_t prev_r;       // rows the latest step asked for
     bool started;         // at least one step has been enqueued
     uint64_t stream_number;   // the buffer's stream then (rb_buffer::stream_number)
@@ -1385,18 +1386,30 @@ static bool captured(hipStream_t stream)
     return true;                                // no telling
 }
 
+// Makes `train` wait for the latest step.  A call whose training stream is the buffer's own records no event, which nobody may ever wait
+// for; then it is recorded here, behind whatever else has gone to that stream (the caller has ordered it behind the stream the step ran on
+// if the handle has been given another one since).
+static bool wait_done(rb_pipeline* p, hipStream_t train)
+{
+    if (!p->recorded) {
+        if (hipEventRecord(p->done, p->rb->stream) != hipSuccess) return false;
+        p->recorded = true;
+    }
+    return hipStreamWaitEvent(train, p->done, 0) == hipSuccess;
+}
+
 // The two streams' hand-over before a call's steps: the training stream goes on once the previous call's representatives are complete,
 // the buffer's stream starts these steps once the training stream has got this far.  The latter need not wait for the former, which
 // the buffer's stream has behind it: after rb_pipeline_drain, when the training stream waits a second time, that wait is not in the
 // way of the steps (32 iterations of 8 + 8 rows of 602 KB a call 121.5 -> 116.5 us).  It goes first where the handle has been given
 // another stream since, and into a graph that is being captured (it is refused if those representatives come from outside, and
 // then nothing has been captured).
-static bool hand_over(const rb_pipeline* p, hipStream_t train)
+static bool hand_over(rb_pipeline* p, hipStream_t train)
 {
-    const bool first = p->started && (p->stream_number != p->rb->stream_number || captured(train));
-    if (first && hipStreamWaitEvent(train, p->done, 0) != hipSuccess) return false;
+    const bool first = p->started && (!p->recorded || p->stream_number != p->rb->stream_number || captured(train));
+    if (first && !wait_done(p, train)) return false;
     if (hipEventRecord(p->ready, train) != hipSuccess || hipStreamWaitEvent(p->rb->stream, p->ready, 0) != hipSuccess) return false;
-    return first || !p->started || hipStreamWaitEvent(train, p->done, 0) == hipSuccess;
+    return first || !p->started || wait_done(p, train);
 }
 
 extern "C" {
@@ -1817,6 +1830,7 @@ int rb_pipeline_create(rb_pipeline** out, rb_buffer* rb)
     if (!p) return RB_ENOMEM;
     p->rb = rb;
     p->prev_r = 0;
+    p->recorded = false;
     p->started = false;
     p->stream_number = 0;
     if (hipEventCreateWithFlags(&p->ready, hipEventDisableTiming) != hipSuccess) {
@@ -1850,6 +1864,7 @@ int rb_pipeline_step(rb_pipeline* p, const void* batch_x, const int64_t* batch_y
     if (two_streams && hipEventRecord(p->done, rb->stream) != hipSuccess) return RB_EHIP;
     if (ready_rows) *ready_rows = p->started ? p->prev_r : 0;
     p->prev_r = r;
+    p->recorded = two_streams;
     p->started = true;
     p->stream_number = rb->stream_number;
     return RB_OK;
@@ -1859,7 +1874,7 @@ int rb_pipeline_drain(rb_pipeline* p, void* train_stream, int64_t* ready_rows)
 {
     if (!p) return RB_EINVAL;
     hipStream_t train = static_cast<hipStream_t>(train_stream);
-    if (p->started && train != p->rb->stream && hipStreamWaitEvent(train, p->done, 0) != hipSuccess) return RB_EHIP;
+    if (p->started && train != p->rb->stream && !wait_done(p, train)) return RB_EHIP;
     if (ready_rows) *ready_rows = p->started ? p->prev_r : 0;
     return RB_OK;
 }
@@ -1895,6 +1910,7 @@ int rb_pipeline_step_many(rb_pipeline* p, int64_t n, const void* const* batch_x,
     if (two_streams && !recorded && hipEventRecord(p->done, rb->stream) != hipSuccess) return RB_EHIP;
     if (ready_rows) *ready_rows = p->started ? p->prev_r : 0;
     p->prev_r = r;
+    p->recorded = two_streams;
     p->started = true;
     p->stream_number = rb->stream_number;
     return RB_OK;

@@ -1279,6 +1279,41 @@ def test_pipeline_makes_every_training_stream_wait(w, n):
     pipe.close()
 
 
+@pytest.mark.parametrize("n", [1, 4])
+def test_pipeline_on_the_buffers_stream_is_waited_for_by_another(n):
+    """Calls whose training stream is the buffer's own, each late and then drained by another stream that copies the representatives."""
+    rb = _rb()
+    w = wl.variant(wl.C2, name="C2-pipeline-own-stream", S=6)
+    dev = torch.device("cuda:0")
+    own, other = torch.cuda.Stream(dev), torch.cuda.Stream(dev)
+    buf = rb.RehearsalBuffer(w.K, w.S, w.shape, w.torch_dtype, device=dev, stream=own)
+    pipe = rb.Pipeline(buf)
+    calls = 6
+    batches = [wl.make_batch(w, t, dev) for t in range(calls * n)]
+    xs, ys = [x.contiguous() for x, _ in batches], [y.contiguous() for _, y in batches]
+    out_x = torch.zeros((calls * n, w.r, *w.shape), dtype=w.torch_dtype, device=dev)
+    out_y = torch.full((calls * n, w.r), -7, dtype=torch.int64, device=dev)
+    seen_x, seen_y = torch.zeros_like(out_x), torch.zeros_like(out_y)
+    sink = torch.empty(64 * 256, dtype=torch.float32, device=dev)
+    torch.cuda.synchronize()
+    for g in range(calls):
+        now = slice(g * n, (g + 1) * n)
+        train = other if g % 3 == 2 else own            # (events of calls on two streams lie in between)
+        assert rb.rb_standin_compute(own, sink, 64, 50000) == rb.RB_OK
+        if n == 1:
+            pipe.step(xs[g], ys[g], w.c, w.r, w.lib_seed, g, out_x[g], out_y[g], train)
+        else:
+            pipe.step_many(xs[now], ys[now], w.c, w.r, w.lib_seed, g * n, list(out_x[now]), list(out_y[now]), train)
+        pipe.drain(other)
+        with torch.cuda.stream(other):
+            seen_x[now].copy_(out_x[now])
+            seen_y[now].copy_(out_y[now])
+    torch.cuda.synchronize()
+    assert torch.equal(seen_y, out_y) and torch.equal(parity_util._bytes(seen_x), parity_util._bytes(out_x))
+    assert int((out_y >= 0).sum()) > 0
+    pipe.close()
+
+
 def test_pipeline_argument_checks_leave_it_unchanged():
     rb = _rb()
     w = wl.C1

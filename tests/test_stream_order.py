@@ -1,0 +1,71 @@
+"""What a pipeline's calls ask of the two streams, on a runtime that writes it down (tests/recorded.py): orders that results only show
+when they go wrong at the right moment."""
+import pytest
+
+from recorded import kernels, run
+
+BUFFER, TRAIN, OTHER = 100, 200, 300                      # streams
+X, Y, OUT_X, OUT_Y = (1 << k for k in (43, 44, 45, 46))    # device memory
+
+
+def step(at, train, b=64, c=8, r=8):
+    return ["rb_pipeline_step", "pipe", X, Y, b, c, r, 1, at, OUT_X, OUT_Y, train]
+
+
+def step_many(n, at, train, b=64, c=8, r=8):
+    return ["rb_pipeline_step_many", "pipe", n, [X] * n, [Y + 8 * b * i for i in range(n)], b, c, r, 1, at, [OUT_X] * n, [OUT_Y] * n, train]
+
+
+def drain(train):
+    return ["rb_pipeline_drain", "pipe", train]
+
+
+def on_a_pipeline(calls, classes=1000):
+    """Results and lines of the calls on a new pipeline of a buffer on stream BUFFER."""
+    results = run([["create", classes, 4, 3072, 0, 0, 0, BUFFER], ["rb_pipeline_create"], *calls])
+    assert results[0][0] == 0 and results[1][0] == 0
+    return results[2:]
+
+
+def waits_for_the_steps_before(lines, train):
+    """Whether, behind these lines in order, stream `train` has waited for an event recorded behind the last launch on BUFFER."""
+    behind = {}                                            # event -> launches on BUFFER when it was recorded
+    launches = seen = 0
+    for line in lines:
+        what, *rest = line.split()
+        if what == "launch" and rest[1] == str(BUFFER):
+            launches += 1
+            if len(rest) == 6:
+                behind[rest[5]] = launches
+        elif what == "record" and rest[1] == str(BUFFER):
+            behind[rest[0]] = launches
+        elif what == "wait" and rest[0] == str(train):
+            seen = max(seen, behind.get(rest[1], 0))
+    return launches > 0 and seen == launches
+
+
+# A call whose training stream is the buffer's own needs no event; whoever has to wait for it from another stream does.
+@pytest.mark.parametrize("before", [[], [step(0, TRAIN)], [step_many(4, 0, TRAIN), drain(TRAIN)]], ids=["first", "after-a-step", "after-many"])
+@pytest.mark.parametrize("one_stream", [step(4, BUFFER), step_many(4, 4, BUFFER)], ids=["step", "many"])
+def test_representatives_collected_on_the_training_stream_are_waited_for_by_another(before, one_stream):
+    for then in (drain(TRAIN), step(8, TRAIN), step_many(4, 8, TRAIN)):
+        *earlier, (result, last) = on_a_pipeline([*before, one_stream, then, drain(OTHER)])[:-1]
+        assert result[0] == 0
+        lines = [line for _, some in earlier for line in some]
+        # (up to where the call's own steps start)
+        first = next((i for i, line in enumerate(last) if line.startswith("launch")), len(last))
+        assert waits_for_the_steps_before(lines + last[:first], TRAIN), (lines, last)
+    results = on_a_pipeline([*before, one_stream, drain(TRAIN), drain(OTHER)])
+    assert waits_for_the_steps_before([line for _, some in results for line in some], OTHER)
+
+
+def test_a_pipeline_on_one_stream_makes_no_stream_wait():
+    for result, lines in on_a_pipeline([step(0, BUFFER), step_many(4, 1, BUFFER), drain(BUFFER)]):
+        assert result[0] == 0 and kernels(lines) == [line.split()[1] for line in lines]
+
+
+def test_the_buffers_next_stream_stands_for_the_one_the_representatives_were_collected_on():
+    NEXT = 400                                             # (ordered behind BUFFER by the caller)
+    results = on_a_pipeline([step(0, BUFFER), ["rb_set_stream", "rb", NEXT], drain(NEXT), drain(OTHER), step(1, OTHER)])
+    assert [lines for _, lines in results[2:4]] == [[], [f"record 2 {NEXT}", f"wait {OTHER} 2"]]
+    assert results[4][1][0] == f"wait {OTHER} 2"
