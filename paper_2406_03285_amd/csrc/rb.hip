@@ -124,6 +124,18 @@ inline bool in_host_memory(const void* p)
 }
 inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
+// Launches a kernel; the result is this launch's own.  (`<<<>>>` drops it, and hipGetLastError, asked behind it, also tells of calls of
+// anybody's that have failed on this thread before: a step that runs would be taken for one that does not.)
+template <typename T> struct as_is { using type = T; };
+template <typename... P>
+hipError_t launch(void (*kernel)(P...), dim3 grid, int threads, size_t lds, hipStream_t st, const typename as_is<P>::type&... arguments)
+{
+    void* args[] = {const_cast<void*>(static_cast<const void*>(&arguments))...};
+    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, dim3((unsigned)threads), args, lds, st);
+    if (e != hipSuccess) (void)hipGetLastError();       // (nor is it left for others)
+    return e;
+}
+
 // How rb_update_sample_many carries out a call: step by step, or several steps per launch planned by one workgroup per
 // launch (rb_kernels_window.h) or by two per step (rb_kernels_bigwin.h).
 enum { MANY_SINGLE = 0, MANY_SMALL = 1, MANY_LARGE = 2 };
@@ -231,20 +243,18 @@ template <bool NT, int ST, bool AUX>
 hipError_t launch_update_small_s(const UpdateArgs& a, int unroll, dim3 grid, size_t lds, hipStream_t st, bool ordinary)
 {
     const auto go = [&](auto kernel) {
-        kernel<<<grid, TPB, lds, st>>>(a.batch_y, a.fill_old, a.sd.seed_lo, a.sd.seed_hi, a.sd.step_lo, a.sd.step_hi,
-                                       (uint32_t)(a.b | a.c << 16), a.nchunks, a);
+        return launch(kernel, grid, TPB, lds, st, a.batch_y, a.fill_old, a.sd.seed_lo, a.sd.seed_hi, a.sd.step_lo, a.sd.step_hi,
+                      (uint32_t)(a.b | a.c << 16), a.nchunks, a);
     };
     switch (unroll) {
-    case 1: go(rb_update_small_kernel<1, NT, ST, AUX>); break;
-    case 2: go(rb_update_small_kernel<2, NT, ST, AUX>); break;
+    case 1: return go(rb_update_small_kernel<1, NT, ST, AUX>);
+    case 2: return go(rb_update_small_kernel<2, NT, ST, AUX>);
     default:
         if constexpr (ST == RB_STORE_U8) return hipErrorInvalidValue;
-        else if (unroll == 4) go(rb_update_small_kernel<4, NT, ST, AUX>);
-        else if (ST == RB_STORE_SAME && ordinary) go(rb_update_small_kernel<8, NT, ST, AUX, NT && ST != RB_STORE_SAME>);
-        else go(rb_update_small_kernel<8, NT, ST, AUX>);
-        break;
+        else if (unroll == 4) return go(rb_update_small_kernel<4, NT, ST, AUX>);
+        else if (ST == RB_STORE_SAME && ordinary) return go(rb_update_small_kernel<8, NT, ST, AUX, NT && ST != RB_STORE_SAME>);
+        else return go(rb_update_small_kernel<8, NT, ST, AUX>);
     }
-    return hipGetLastError();
 }
 
 template <bool NT>
@@ -265,22 +275,19 @@ template <bool NT, int ST>
 hipError_t launch_sample_small_s(const SampleArgs& a, int unroll, dim3 grid, hipStream_t st, bool ordinary)
 {
     const auto go = [&](auto kernel) {
-        kernel<<<grid, TPB, 0, st>>>(a.fill, a.chunk, a.sd.seed_lo, a.sd.seed_hi, a.sd.step_lo, a.sd.step_hi, a.r, a.nchunks, a);
+        return launch(kernel, grid, TPB, 0, st, a.fill, a.chunk, a.sd.seed_lo, a.sd.seed_hi, a.sd.step_lo, a.sd.step_hi, a.r, a.nchunks, a);
     };
     switch (unroll) {
-    case 1: go(rb_sample_small_kernel<1, NT, ST>); break;
+    case 1: return go(rb_sample_small_kernel<1, NT, ST>);
     case 2:
-        if (ST == RB_STORE_U8 && grid.x > THREE_EACH) go(rb_sample_small_kernel<2, NT, ST, NT, ST == RB_STORE_U8 ? 2 : step_pace(ST, 2)>);
-        else go(rb_sample_small_kernel<2, NT, ST>);
-        break;
+        if (ST == RB_STORE_U8 && grid.x > THREE_EACH) return go(rb_sample_small_kernel<2, NT, ST, NT, ST == RB_STORE_U8 ? 2 : step_pace(ST, 2)>);
+        else return go(rb_sample_small_kernel<2, NT, ST>);
     default:
         if constexpr (ST == RB_STORE_U8) return hipErrorInvalidValue;
-        else if (unroll == 4) go(rb_sample_small_kernel<4, NT, ST>);
-        else if (ST == RB_STORE_SAME && ordinary) go(rb_sample_small_kernel<8, NT, ST, NT && ST != RB_STORE_SAME>);
-        else go(rb_sample_small_kernel<8, NT, ST>);
-        break;
+        else if (unroll == 4) return go(rb_sample_small_kernel<4, NT, ST>);
+        else if (ST == RB_STORE_SAME && ordinary) return go(rb_sample_small_kernel<8, NT, ST, NT && ST != RB_STORE_SAME>);
+        else return go(rb_sample_small_kernel<8, NT, ST>);
     }
-    return hipGetLastError();
 }
 
 template <bool NT>
@@ -297,27 +304,24 @@ template <bool NT, int FORM>
 hipError_t launch_update_f(const UpdateArgs& a, int narrow, int unroll, dim3 grid, size_t lds, hipStream_t st)
 {
     if (narrow == 2) {                  // 8 bits per element: a lane holds four accesses per vector of the tile (at most four vectors)
-        if (unroll == 1) rb_update_kernel<1, NT, 2, FORM><<<grid, TPB, lds, st>>>(a);
-        else if (unroll == 2) rb_update_kernel<2, NT, 2, FORM><<<grid, TPB, lds, st>>>(a);
-        else rb_update_kernel<4, NT, 2, FORM><<<grid, TPB, lds, st>>>(a);
-        return hipGetLastError();
+        if (unroll == 1) return launch(rb_update_kernel<1, NT, 2, FORM>, grid, TPB, lds, st, a);
+        if (unroll == 2) return launch(rb_update_kernel<2, NT, 2, FORM>, grid, TPB, lds, st, a);
+        return launch(rb_update_kernel<4, NT, 2, FORM>, grid, TPB, lds, st, a);
     }
     if (narrow == 1) {
         switch (unroll) {
-        case 1: rb_update_kernel<1, NT, 1, FORM><<<grid, TPB, lds, st>>>(a); break;
-        case 2: rb_update_kernel<2, NT, 1, FORM><<<grid, TPB, lds, st>>>(a); break;
-        case 4: rb_update_kernel<4, NT, 1, FORM><<<grid, TPB, lds, st>>>(a); break;
-        default: rb_update_kernel<8, NT, 1, FORM><<<grid, TPB, lds, st>>>(a); break;
+        case 1: return launch(rb_update_kernel<1, NT, 1, FORM>, grid, TPB, lds, st, a);
+        case 2: return launch(rb_update_kernel<2, NT, 1, FORM>, grid, TPB, lds, st, a);
+        case 4: return launch(rb_update_kernel<4, NT, 1, FORM>, grid, TPB, lds, st, a);
+        default: return launch(rb_update_kernel<8, NT, 1, FORM>, grid, TPB, lds, st, a);
         }
-        return hipGetLastError();
     }
     switch (unroll) {
-    case 1: rb_update_kernel<1, NT, 0, FORM><<<grid, TPB, lds, st>>>(a); break;
-    case 2: rb_update_kernel<2, NT, 0, FORM><<<grid, TPB, lds, st>>>(a); break;
-    case 4: rb_update_kernel<4, NT, 0, FORM><<<grid, TPB, lds, st>>>(a); break;
-    default: rb_update_kernel<8, NT, 0, FORM><<<grid, TPB, lds, st>>>(a); break;
+    case 1: return launch(rb_update_kernel<1, NT, 0, FORM>, grid, TPB, lds, st, a);
+    case 2: return launch(rb_update_kernel<2, NT, 0, FORM>, grid, TPB, lds, st, a);
+    case 4: return launch(rb_update_kernel<4, NT, 0, FORM>, grid, TPB, lds, st, a);
+    default: return launch(rb_update_kernel<8, NT, 0, FORM>, grid, TPB, lds, st, a);
     }
-    return hipGetLastError();
 }
 
 template <bool NT>
@@ -331,23 +335,20 @@ template <bool NT, bool MANY>
 hipError_t launch_sample_f(const SampleArgs& a, int widen, int unroll, dim3 grid, size_t lds, hipStream_t st)
 {
     if (widen == 2) {
-        if (unroll == 1) rb_sample_kernel<1, NT, 2, MANY><<<grid, TPB, lds, st>>>(a);
-        else rb_sample_kernel<2, NT, 2, MANY><<<grid, TPB, lds, st>>>(a);
-        return hipGetLastError();
+        if (unroll == 1) return launch(rb_sample_kernel<1, NT, 2, MANY>, grid, TPB, lds, st, a);
+        return launch(rb_sample_kernel<2, NT, 2, MANY>, grid, TPB, lds, st, a);
     }
     if (widen == 1) {
-        if (unroll == 1) rb_sample_kernel<1, NT, 1, MANY><<<grid, TPB, lds, st>>>(a);
-        else if (unroll == 2) rb_sample_kernel<2, NT, 1, MANY><<<grid, TPB, lds, st>>>(a);
-        else rb_sample_kernel<4, NT, 1, MANY><<<grid, TPB, lds, st>>>(a);
-        return hipGetLastError();
+        if (unroll == 1) return launch(rb_sample_kernel<1, NT, 1, MANY>, grid, TPB, lds, st, a);
+        if (unroll == 2) return launch(rb_sample_kernel<2, NT, 1, MANY>, grid, TPB, lds, st, a);
+        return launch(rb_sample_kernel<4, NT, 1, MANY>, grid, TPB, lds, st, a);
     }
     switch (unroll) {
-    case 1: rb_sample_kernel<1, NT, 0, MANY><<<grid, TPB, lds, st>>>(a); break;
-    case 2: rb_sample_kernel<2, NT, 0, MANY><<<grid, TPB, lds, st>>>(a); break;
-    case 4: rb_sample_kernel<4, NT, 0, MANY><<<grid, TPB, lds, st>>>(a); break;
-    default: rb_sample_kernel<8, NT, 0, MANY><<<grid, TPB, lds, st>>>(a); break;
+    case 1: return launch(rb_sample_kernel<1, NT, 0, MANY>, grid, TPB, lds, st, a);
+    case 2: return launch(rb_sample_kernel<2, NT, 0, MANY>, grid, TPB, lds, st, a);
+    case 4: return launch(rb_sample_kernel<4, NT, 0, MANY>, grid, TPB, lds, st, a);
+    default: return launch(rb_sample_kernel<8, NT, 0, MANY>, grid, TPB, lds, st, a);
     }
-    return hipGetLastError();
 }
 
 template <bool NT>
@@ -361,21 +362,19 @@ hipError_t launch_step_s(const StepArgs& sa, int unroll, dim3 grid, size_t lds, 
 {
     const UpdateArgs& a = sa.u;
     const auto go = [&](auto kernel) {
-        kernel<<<grid, TPB, lds, st>>>(a.batch_y, a.fill_old, a.sd.seed_lo, a.sd.seed_hi, a.sd.step_lo, a.sd.step_hi,
-                                       (uint32_t)(a.b | a.c << 16), (uint32_t)(sa.r | a.nchunks << 16), a.tpr, a.nchunks + a.c * a.tpr, sa);
+        return launch(kernel, grid, TPB, lds, st, a.batch_y, a.fill_old, a.sd.seed_lo, a.sd.seed_hi, a.sd.step_lo, a.sd.step_hi,
+                      (uint32_t)(a.b | a.c << 16), (uint32_t)(sa.r | a.nchunks << 16), a.tpr, a.nchunks + a.c * a.tpr, sa);
     };
     switch (unroll) {
-    case 1: go(rb_step_small_kernel<1, NT, ST, AUX>); break;
-    case 2: go(rb_step_small_kernel<2, NT, ST, AUX>); break;
+    case 1: return go(rb_step_small_kernel<1, NT, ST, AUX>);
+    case 2: return go(rb_step_small_kernel<2, NT, ST, AUX>);
     default:
         if constexpr (ST == RB_STORE_U8) return hipErrorInvalidValue;
-        else if (unroll == 4) go(rb_step_small_kernel<4, NT, ST, AUX>);
+        else if (unroll == 4) return go(rb_step_small_kernel<4, NT, ST, AUX>);
         else if constexpr (ST != RB_STORE_SAME) return hipErrorInvalidValue;
-        else if (ordinary) go(rb_step_small_kernel<8, NT, ST, AUX, false>);
-        else go(rb_step_small_kernel<8, NT, ST, AUX>);
-        break;
+        else if (ordinary) return go(rb_step_small_kernel<8, NT, ST, AUX, false>);
+        else return go(rb_step_small_kernel<8, NT, ST, AUX>);
     }
-    return hipGetLastError();
 }
 
 template <bool NT>
@@ -398,12 +397,11 @@ hipError_t launch_copy(vec16* dst, const vec16* src, int64_t nvec, int unroll, h
     const int64_t cap = (int64_t)TPB * unroll;
     dim3 grid((unsigned)((nvec + cap - 1) / cap));
     switch (unroll) {
-    case 1: rb_copy_kernel<1, NT, PACE><<<grid, TPB, 0, st>>>(dst, src, nvec); break;
-    case 2: rb_copy_kernel<2, NT, PACE><<<grid, TPB, 0, st>>>(dst, src, nvec); break;
-    case 4: rb_copy_kernel<4, NT, PACE><<<grid, TPB, 0, st>>>(dst, src, nvec); break;
-    default: rb_copy_kernel<8, NT, PACE><<<grid, TPB, 0, st>>>(dst, src, nvec); break;
+    case 1: return launch(rb_copy_kernel<1, NT, PACE>, grid, TPB, 0, st, dst, src, nvec);
+    case 2: return launch(rb_copy_kernel<2, NT, PACE>, grid, TPB, 0, st, dst, src, nvec);
+    case 4: return launch(rb_copy_kernel<4, NT, PACE>, grid, TPB, 0, st, dst, src, nvec);
+    default: return launch(rb_copy_kernel<8, NT, PACE>, grid, TPB, 0, st, dst, src, nvec);
     }
-    return hipGetLastError();
 }
 
 Seed make_seed(uint64_t seed, uint64_t step)
@@ -420,23 +418,20 @@ template <bool NT, int ST>
 hipError_t launch_planned_s(const MoveArgs& m, const PlanArgs& next, int unroll, dim3 grid, size_t lds, hipStream_t st, bool ordinary)
 {
     const auto go = [&](auto kernel) {
-        kernel<<<grid, TPB, lds, st>>>(m.table, m.batch_x, m.buf_x, m.out_x, m.row_vec, (uint32_t)(m.c | m.r << 16),
-                                       (uint32_t)m.tpr | (uint32_t)m.plan_next << 31, m.tile_vec, m.tile_rem, m, next);
+        return launch(kernel, grid, TPB, lds, st, m.table, m.batch_x, m.buf_x, m.out_x, m.row_vec, (uint32_t)(m.c | m.r << 16),
+                      (uint32_t)m.tpr | (uint32_t)m.plan_next << 31, m.tile_vec, m.tile_rem, m, next);
     };
     switch (unroll) {
-    case 1: go(rb_step_planned_kernel<1, NT, ST>); break;
-    case 2: go(rb_step_planned_kernel<2, NT, ST>); break;
+    case 1: return go(rb_step_planned_kernel<1, NT, ST>);
+    case 2: return go(rb_step_planned_kernel<2, NT, ST>);
     case 4:
         if constexpr (ST == RB_STORE_U8) return hipErrorInvalidValue;    // (at most two vectors per lane: step_planned)
-        else go(rb_step_planned_kernel<4, NT, ST>);
-        break;
+        else return go(rb_step_planned_kernel<4, NT, ST>);
     default:
         if constexpr (ST != RB_STORE_SAME) return hipErrorInvalidValue;  // (bfloat16 rows: at most four)
-        else if (ordinary) go(rb_step_planned_kernel<8, NT, ST, false>);
-        else go(rb_step_planned_kernel<8, NT, ST>);
-        break;
+        else if (ordinary) return go(rb_step_planned_kernel<8, NT, ST, false>);
+        else return go(rb_step_planned_kernel<8, NT, ST>);
     }
-    return hipGetLastError();
 }
 
 template <bool NT>
@@ -534,8 +529,7 @@ int step_planned(rb_buffer* rb, const void* batch_x, const int64_t* batch_y, int
 {
     if (!rb->plan_valid) {
         const PlanArgs now = make_plan(rb, batch_y, b, c, r, seed, step);
-        rb_plan_kernel<<<dim3(1), TPB, (size_t)b * 8, rb->stream>>>(now);
-        if (hipGetLastError() != hipSuccess) return RB_EHIP;
+        if (launch(rb_plan_kernel, dim3(1), TPB, (size_t)b * 8, rb->stream, now) != hipSuccess) return RB_EHIP;
         plan_enqueued(rb, batch_y, b, c, r, seed, step);
     }
     // (rows that are converted do better with fewer vectors per thread: 64 + 64 rows of 602 KB in 8 bits 25.6 us with four,
@@ -596,10 +590,8 @@ hipError_t launch_big_u(const MoveArgs& m, const PlanArgs& next, const uint32_t*
             const hipError_t e = allow_big_lds<&rb_step_big_kernel<U, NT, ST>>();
             if (e != hipSuccess) return e;
         }
-        rb_step_big_kernel<U, NT, ST><<<grid, BIG_TPB, lds, st>>>(m.table, m.batch_x, m.buf_x, m.out_x, m.row_vec, (uint32_t)(m.cgrid | m.r << 16),
-                                                                  (uint32_t)m.tpr | (uint32_t)m.plan_next << 31,
-                                                                  m.tile_vec, m.tile_rem, m, next, fwd, fwd_next);
-        return hipGetLastError();
+        return launch(rb_step_big_kernel<U, NT, ST>, grid, BIG_TPB, lds, st, m.table, m.batch_x, m.buf_x, m.out_x, m.row_vec, (uint32_t)(m.cgrid | m.r << 16),
+                      (uint32_t)m.tpr | (uint32_t)m.plan_next << 31, m.tile_vec, m.tile_rem, m, next, fwd, fwd_next);
     }
 }
 
@@ -686,8 +678,7 @@ int step_big(rb_buffer* rb, const void* batch_x, const int64_t* batch_y, int64_t
         PlanArgs now = make_plan(rb, batch_y, b, c, r, seed, step);
         now.table = rb->ws + rb->off_wtbl[rb->tbl_next];
         if (allow_big_lds<&rb_big_plan_kernel>() != hipSuccess) return RB_EHIP;
-        rb_big_plan_kernel<<<dim3(2), BIG_TPB, BIG_LDS_BYTES, rb->stream>>>(now, reinterpret_cast<uint32_t*>(rb->ws + rb->off_bfwd[rb->tbl_next]));
-        if (hipGetLastError() != hipSuccess) return RB_EHIP;
+        if (launch(rb_big_plan_kernel, dim3(2), BIG_TPB, BIG_LDS_BYTES, rb->stream, now, reinterpret_cast<uint32_t*>(rb->ws + rb->off_bfwd[rb->tbl_next])) != hipSuccess) return RB_EHIP;
         plan_enqueued(rb, batch_y, b, c, r, seed, step);
     }
     // candidate entries of the table, and how many of them the grid covers: all c, or, with the Bernoulli selection
@@ -737,10 +728,11 @@ hipError_t launch_recorded(K kernel, dim3 grid, int threads, size_t lds, hipStre
 {
     if (done != nullptr) {
         void* args[] = {const_cast<M*>(&m), const_cast<P*>(&next)};
-        return hipExtLaunchKernel(reinterpret_cast<const void*>(kernel), grid, dim3((unsigned)threads), args, lds, st, nullptr, done, 0);
+        const hipError_t e = hipExtLaunchKernel(reinterpret_cast<const void*>(kernel), grid, dim3((unsigned)threads), args, lds, st, nullptr, done, 0);
+        if (e != hipSuccess) (void)hipGetLastError();
+        return e;
     }
-    kernel<<<grid, threads, lds, st>>>(m, next);
-    return hipGetLastError();
+    return launch(kernel, grid, threads, lds, st, m, next);
 }
 
 // The event of the call being made, if its last launch is the one about to go out.
@@ -876,9 +868,8 @@ int steps_windowed(rb_buffer* rb, int64_t n, const void* const* batch_x, const i
         nat = w0;
         tbl = 0;
         const WinPlanArgs p = window_plan_args(rb, batch_y, 0, w, b, c, r, seed, first_step, tbl);
-        if (rb->eviction != RB_EVICT_UNIFORM) rb_window_plan_kernel<true><<<dim3(1), TPB, 0, rb->stream>>>(p);
-        else rb_window_plan_kernel<false><<<dim3(1), TPB, 0, rb->stream>>>(p);
-        if (hipGetLastError() != hipSuccess) return RB_EHIP;
+        const auto kernel = rb->eviction != RB_EVICT_UNIFORM ? rb_window_plan_kernel<true> : rb_window_plan_kernel<false>;
+        if (launch(kernel, dim3(1), TPB, 0, rb->stream, p) != hipSuccess) return RB_EHIP;
         rb->cur ^= 1;
     }
     while (at < n) {
@@ -1060,8 +1051,7 @@ int steps_bigwin(rb_buffer* rb, int64_t n, const void* const* batch_x, const int
         w = std::min(w0, n);
         tbl = 0;
         const BwPlanArgs p = bigwin_plan_args(rb, batch_y, 0, w, b, c, r, seed, first_step, tbl);
-        rb_bigwin_plan_kernel<<<dim3((unsigned)(2 * w)), BIG_TPB, BIG_LDS_BYTES, rb->stream>>>(p);
-        if (hipGetLastError() != hipSuccess) return RB_EHIP;
+        if (launch(rb_bigwin_plan_kernel, dim3((unsigned)(2 * w)), BIG_TPB, BIG_LDS_BYTES, rb->stream, p) != hipSuccess) return RB_EHIP;
         rb->cur ^= 1;
     }
     while (at < n) {
@@ -1145,9 +1135,8 @@ hipError_t launch_one_u(const OneArgs& a, dim3 grid, size_t lds, hipStream_t st)
         const hipError_t e = allow_big_lds<kernel, most>();
         if (e != hipSuccess) return e;
         const UpdateArgs& u = a.u;
-        kernel<<<grid, ONE_TPB, lds, st>>>(u.batch_y, u.fill_old, a.chunk_old, u.sd.seed_lo, u.sd.seed_hi, u.sd.step_lo, u.sd.step_hi,
-                                           (uint32_t)(u.b | u.c << 16), (uint32_t)(a.r | u.nchunks << 16), a.first_cand, a);
-        return hipGetLastError();
+        return launch(kernel, grid, ONE_TPB, lds, st, u.batch_y, u.fill_old, a.chunk_old, u.sd.seed_lo, u.sd.seed_hi, u.sd.step_lo, u.sd.step_hi,
+                      (uint32_t)(u.b | u.c << 16), (uint32_t)(a.r | u.nchunks << 16), a.first_cand, a);
     }
 }
 
@@ -1378,12 +1367,17 @@ struct rb_pipeline {
     uint64_t stream_number;   // the buffer's stream then (rb_buffer::stream_number)
 };
 
+// What a failed operation on streams or events leaves is not left for others either (launch).
+static bool succeeded(hipError_t e)
+{
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e == hipSuccess;
+}
+
 static bool captured(hipStream_t stream)
 {
     hipStreamCaptureStatus status;
-    if (hipStreamIsCapturing(stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
-    (void)hipGetLastError();
-    return true;                                // no telling
+    return !succeeded(hipStreamIsCapturing(stream, &status)) || status != hipStreamCaptureStatusNone;       // (no telling: taken for captured)
 }
 
 // Makes `train` wait for the latest step.  A call whose training stream is the buffer's own records no event, which nobody may ever wait
@@ -1392,10 +1386,10 @@ static bool captured(hipStream_t stream)
 static bool wait_done(rb_pipeline* p, hipStream_t train)
 {
     if (!p->recorded) {
-        if (hipEventRecord(p->done, p->rb->stream) != hipSuccess) return false;
+        if (!succeeded(hipEventRecord(p->done, p->rb->stream))) return false;
         p->recorded = true;
     }
-    return hipStreamWaitEvent(train, p->done, 0) == hipSuccess;
+    return succeeded(hipStreamWaitEvent(train, p->done, 0));
 }
 
 // The two streams' hand-over before a call's steps: the training stream goes on once the previous call's representatives are complete,
@@ -1408,7 +1402,7 @@ static bool hand_over(rb_pipeline* p, hipStream_t train)
 {
     const bool first = p->started && (!p->recorded || p->stream_number != p->rb->stream_number || captured(train));
     if (first && !wait_done(p, train)) return false;
-    if (hipEventRecord(p->ready, train) != hipSuccess || hipStreamWaitEvent(p->rb->stream, p->ready, 0) != hipSuccess) return false;
+    if (!succeeded(hipEventRecord(p->ready, train)) || !succeeded(hipStreamWaitEvent(p->rb->stream, p->ready, 0))) return false;
     return first || !p->started || wait_done(p, train);
 }
 
@@ -1514,9 +1508,8 @@ int rb_bind(rb_buffer* rb, void* buf_x, int64_t* buf_y, void* workspace, void* h
     int64_t blocks = (slots + TPB - 1) / TPB;
     if (blocks > 4096) blocks = 4096;
     if (blocks < 1) blocks = 1;
-    rb_reset_kernel<<<dim3((unsigned)blocks), TPB, 0, st>>>(static_cast<uint32_t*>(workspace),
-                                                           (int64_t)(rb->ws_bytes / 4), buf_y, slots);
-    if (hipGetLastError() != hipSuccess) return RB_EHIP;
+    if (launch(rb_reset_kernel, dim3((unsigned)blocks), TPB, 0, st, static_cast<uint32_t*>(workspace), (int64_t)(rb->ws_bytes / 4), buf_y, slots) != hipSuccess)
+        return RB_EHIP;
     rb->buf_x = buf_x;
     rb->buf_y = buf_y;
     rb->ws = static_cast<char*>(workspace);
@@ -1833,11 +1826,11 @@ int rb_pipeline_create(rb_pipeline** out, rb_buffer* rb)
     p->recorded = false;
     p->started = false;
     p->stream_number = 0;
-    if (hipEventCreateWithFlags(&p->ready, hipEventDisableTiming) != hipSuccess) {
+    if (!succeeded(hipEventCreateWithFlags(&p->ready, hipEventDisableTiming))) {
         delete p;
         return RB_EHIP;
     }
-    if (hipEventCreateWithFlags(&p->done, hipEventDisableTiming) != hipSuccess) {
+    if (!succeeded(hipEventCreateWithFlags(&p->done, hipEventDisableTiming))) {
         (void)hipEventDestroy(p->ready);
         delete p;
         return RB_EHIP;
@@ -1861,7 +1854,7 @@ int rb_pipeline_step(rb_pipeline* p, const void* batch_x, const int64_t* batch_y
     // (2) update with this mini-batch, then collect the next representatives
     const int rc = rb_update_sample(rb, batch_x, batch_y, b, c, r, seed, step, next_x, next_y);
     if (rc != RB_OK) return rc;
-    if (two_streams && hipEventRecord(p->done, rb->stream) != hipSuccess) return RB_EHIP;
+    if (two_streams && !succeeded(hipEventRecord(p->done, rb->stream))) return RB_EHIP;
     if (ready_rows) *ready_rows = p->started ? p->prev_r : 0;
     p->prev_r = r;
     p->recorded = two_streams;
@@ -1907,7 +1900,7 @@ int rb_pipeline_step_many(rb_pipeline* p, int64_t n, const void* const* batch_x,
     const bool recorded = asked && rb->done == nullptr;
     rb->done = nullptr;
     if (rc != RB_OK) return rc;
-    if (two_streams && !recorded && hipEventRecord(p->done, rb->stream) != hipSuccess) return RB_EHIP;
+    if (two_streams && !recorded && !succeeded(hipEventRecord(p->done, rb->stream))) return RB_EHIP;
     if (ready_rows) *ready_rows = p->started ? p->prev_r : 0;
     p->prev_r = r;
     p->recorded = two_streams;
@@ -2012,8 +2005,8 @@ const char* rb_strerror(int status)
 int rb_standin_compute(void* hip_stream, float* sink, int64_t blocks, int64_t iters)
 {
     if (!sink || blocks < 1 || blocks > (1 << 20) || iters < 0) return RB_EINVAL;
-    rb_standin_kernel<<<dim3((unsigned)blocks), TPB, 0, static_cast<hipStream_t>(hip_stream)>>>(sink, iters);
-    return hipGetLastError() == hipSuccess ? RB_OK : RB_EHIP;
+    const hipError_t e = launch(rb_standin_kernel, dim3((unsigned)blocks), TPB, 0, static_cast<hipStream_t>(hip_stream), sink, iters);
+    return e == hipSuccess ? RB_OK : RB_EHIP;
 }
 
 int rb_copy_bytes(void* hip_stream, void* dst, const void* src, size_t bytes, int32_t unroll, int32_t nontemporal)

@@ -56,6 +56,8 @@ static int is_capturing(uintptr_t stream)
 const char* recorder_lines(void) { return lines; }
 void recorder_clear(void) { used = 0; lines[0] = 0; }
 void recorder_fail(const char* function, int after) { snprintf(failing, sizeof failing, "%s", function); failing_after = after; }
+void recorder_pend(int error) { last_error = error; }
+int recorder_pending(void) { return last_error; }
 void recorder_capture(uintptr_t stream)
 {
     for (int i = 0; i < MAX_STREAMS; ++i)

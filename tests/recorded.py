@@ -7,6 +7,7 @@ array of device pointers), or one of
 
     ["create", classes, slots, elems, storage, selection, eviction, stream]   makes and binds a buffer
     ["fail", hip_function, after]      its calls fail, after so many that succeed; "" ends that
+    ["pend", error], ["pending"]       a call of somebody else's has failed before; the error that hipGetLastError would tell of
     ["capture", stream], ["end_capture"]
 """
 import ctypes as C
@@ -60,6 +61,11 @@ def _child(recorder, calls):
         if name == "fail":
             R.recorder_fail(args[0].encode(), args[1])
             result = 0
+        elif name == "pend":
+            R.recorder_pend(args[0])
+            result = 0
+        elif name == "pending":
+            result = R.recorder_pending()
         elif name == "capture":
             R.recorder_capture(u64(args[0]))
             result = 0

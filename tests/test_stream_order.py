@@ -4,6 +4,7 @@ import pytest
 
 from recorded import kernels, run
 
+RB_EHIP = -4
 BUFFER, TRAIN, OTHER = 100, 200, 300                      # streams
 X, Y, OUT_X, OUT_Y = (1 << k for k in (43, 44, 45, 46))    # device memory
 
@@ -69,3 +70,38 @@ def test_the_buffers_next_stream_stands_for_the_one_the_representatives_were_col
     results = on_a_pipeline([step(0, BUFFER), ["rb_set_stream", "rb", NEXT], drain(NEXT), drain(OTHER), step(1, OTHER)])
     assert [lines for _, lines in results[2:4]] == [[], [f"record 2 {NEXT}", f"wait {OTHER} 2"]]
     assert results[4][1][0] == f"wait {OTHER} 2"
+
+
+CALLS = {
+    "update": [["rb_update", "rb", X, Y, 64, 8, 1, 0]],
+    "update-general": [["rb_update", "rb", X, Y, 640, 300, 1, 0]],
+    "sample": [["rb_sample_augment", "rb", 8, 1, 0, OUT_X, OUT_Y]],
+    "sample-general": [["rb_sample_augment", "rb", 80, 1, 0, OUT_X, OUT_Y]],
+    "small": [["rb_update_sample", "rb", X, Y, 64, 8, 8, 1, 0, OUT_X, OUT_Y]],
+    "one": [["rb_update_sample", "rb", X, Y, 640, 300, 200, 1, 0, OUT_X, OUT_Y]],
+    "planned": [["rb_announce_next", "rb", Y], ["rb_update_sample", "rb", X, Y, 64, 8, 8, 1, 0, OUT_X, OUT_Y]],
+    "planned-large": [["rb_announce_next", "rb", Y], ["rb_update_sample", "rb", X, Y, 640, 300, 200, 1, 0, OUT_X, OUT_Y]],
+    "many": [step_many(4, 0, TRAIN)],
+    "many-large": [step_many(4, 0, TRAIN, 640, 300, 200)],
+    "bind": [["rb_bind", "rb", 1 << 40, 1 << 41, 1 << 42, BUFFER]],
+    "standin": [["rb_standin_compute", BUFFER, X, 4, 1]],
+    "copy": [["rb_copy_bytes", BUFFER, X, Y, 4096, 4, 1]],
+}
+
+
+# hipGetLastError tells of any call that has failed on the thread before; what it has to say is neither taken for a launch's nor taken away.
+@pytest.mark.parametrize("name", sorted(CALLS))
+def test_errors_that_others_have_left_are_left_alone(name):
+    *results, pending = on_a_pipeline([["pend", 98], *CALLS[name], ["pending"]])
+    last = results[-1][0]
+    assert (last[0] if isinstance(last, list) else last) == 0
+    assert [r for r in results[1:]] == on_a_pipeline(CALLS[name])
+    assert pending[0] == (98 if name != "bind" else 0)     # (rb_bind asks whether memory is the host's, which fails where it is nobody's)
+
+
+@pytest.mark.parametrize("name", sorted(CALLS))
+def test_a_failed_launch_is_reported_once_and_can_be_made_again(name):
+    function = "hipExtLaunchKernel" if name.startswith("many") else "hipLaunchKernel"
+    *_, (failed, _), pending, _, again = on_a_pipeline([["fail", function, 0], *CALLS[name], ["pending"], ["fail", "", 0], CALLS[name][-1]])
+    assert (failed[0] if isinstance(failed, list) else failed) == RB_EHIP and pending[0] == 0
+    assert (again[0][0] if isinstance(again[0], list) else again[0]) == 0
