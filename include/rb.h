@@ -124,10 +124,10 @@ int rb_set_storage(rb_buffer *rb, int32_t storage);
  * slots_per_class / n and is dropped otherwise (exact while a class has been
  * offered fewer than 2^31 - 1 samples).
  * Every variant is served by every call, the Bernoulli selection by the
- * plan-ahead forms of the single launch (rb_announce_next) and by the
- * several-steps launches of rb_update_sample_many (the form for large counts)
- * for b <= 1024 or c <= 512.  RB_EINVAL: unknown value.  RB_ESTATE: an rb_update was
- * already enqueued since the last rb_bind.
+ * plan-ahead form of the single launch (rb_announce_next) for b <= 1024 or
+ * c <= 512 and by the several-steps launches of rb_update_sample_many (the form
+ * for large counts) for b <= 1024.  RB_EINVAL: unknown value.  RB_ESTATE: an
+ * rb_update was already enqueued since the last rb_bind.
  */
 enum rb_selection { RB_SELECT_EXACT = 0, RB_SELECT_BERNOULLI = 1 };
 enum rb_eviction { RB_EVICT_UNIFORM = 0, RB_EVICT_FIFO = 1, RB_EVICT_RESERVOIR = 2 };
@@ -259,7 +259,7 @@ int rb_announce_next(rb_buffer *rb, const int64_t *next_batch_y);
  * steps.  Beyond those limits - and within them when a step's rows are so
  * short that they are moved sooner than one workgroup plans a step
  * (RB_OPT_PLANNERS) -, for up to 1024 candidates and representatives,
- * b <= 4096 (b <= 1024 or c <= 512 with the Bernoulli selection) and up to 10240 classes,
+ * b <= 4096 (b <= 1024 with the Bernoulli selection) and up to 10240 classes,
  * up to 16 steps share one launch in the same way; their plan is made by two
  * workgroups per step of the launch before, which work side by side (should
  * they ever fail to hear from each other within 2 s, that launch moves nothing

@@ -975,7 +975,9 @@ Shape bigwin_shape(const rb_buffer* rb, int64_t rows, int& width)
 }
 
 // Whether rb_update_sample_many puts several steps of this shape into one launch of the large-count form, and how
-// many at most (1: it does not).  Shapes that the small form takes (window_limit) are not meant.
+// many at most (1: it does not).  Shapes that the small form takes (window_limit) are not meant.  (Bernoulli selection: mini-batches that
+// cannot bring more candidates than a planner has threads, so that no step of a window can lose any; the single step's plan is made for
+// larger ones as well, big_coins.)
 int64_t bigwin_limit(const rb_buffer* rb, int64_t b, int64_t c, int64_t r)
 {
     const bool eligible = c >= 1 && c <= BIG_MAX && r >= 1 && r <= BIG_MAX && b <= BIG_BATCH &&
@@ -1003,7 +1005,7 @@ BwPlanArgs bigwin_plan_args(rb_buffer* rb, const int64_t* const* batch_y, int64_
     p.S = rb->S;
     p.eviction = rb->eviction;
     p.selection = rb->selection;
-    p.ce = (int32_t)(rb->selection == RB_SELECT_BERNOULLI ? b : c);     // with the Bernoulli selection one thread and one entry per position
+    p.ce = (int32_t)(rb->selection == RB_SELECT_BERNOULLI ? b : c);     // (b <= BIG_MAX then, bigwin_limit: the tables have room for BIG_MAX a step)
     rb->bw_number += 1;
     if (rb->bw_number == 0) rb->bw_number = 1;          // 0 is what a cleared flag shows
     p.number = rb->bw_number;

@@ -80,7 +80,7 @@ struct BwPlanArgs {
     int32_t eviction;                  // RB_EVICT_*
     uint32_t number;                   // the window's number (never 0): what its flags are set to
     int32_t selection;                 // RB_SELECT_*
-    int32_t ce;                        // candidate entries per step in the table: c, or b with the Bernoulli selection
+    int32_t ce;                        // candidate entries per step in the table, at most BIG_MAX: c, or b with the Bernoulli selection
     const int32_t* aux_old;            // per class: FIFO: slot of the oldest sample; RESERVOIR: samples offered so far
     int32_t* aux_new;
 };

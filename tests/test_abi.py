@@ -325,6 +325,7 @@ def test_variant_setters_validate_on_the_host():
     assert rb.rb_set_policy(h, rb.RB_SELECT_EXACT, rb.RB_EVICT_FIFO) == rb.RB_OK and rb.rb_query_steps_per_launch(h, 64, 8, 8) == (rb.RB_OK, 5)
     assert rb.rb_set_policy(h, rb.RB_SELECT_BERNOULLI, rb.RB_EVICT_FIFO) == rb.RB_OK and rb.rb_query_steps_per_launch(h, 64, 8, 8) == (rb.RB_OK, 5)   # the large-count form takes it
     assert rb.rb_query_steps_per_launch(h, 1025, 8, 8) == (rb.RB_OK, 1)         # ... for mini-batches of at most 1024
+    assert rb.rb_query_steps_per_launch(h, 1025, 400, 25) == (rb.RB_OK, 1) and rb.rb_query_steps_per_launch(h, 1024, 400, 25) == (rb.RB_OK, 5)
     rb.rb_destroy(h)
     # the library's choice between the two forms follows the time a step's rows take to move
     rc, h = rb.rb_create(10, 4, (3, 224, 224), rb.RB_F32)
