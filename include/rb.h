@@ -269,8 +269,8 @@ int rb_announce_next(rb_buffer *rb, const int64_t *next_batch_y);
  * batch_x[i], batch_y[i], step number first_step + i and writes to out_x[i],
  * out_y[i]; b, c, r and seed are common.  The four pointer arrays are HOST
  * arrays of n device pointers, read before the call returns.  All n steps are
- * validated first; on an error nothing was enqueued.  Results are those of n
- * separate calls, bit for bit.
+ * validated first: on any error but RB_EHIP nothing was enqueued.  Results are
+ * those of n separate calls, bit for bit.
  * The outputs and mini-batches of any 32 consecutive steps must not overlap.
  * The workspace behind the handle is used by the launches of this call while
  * they run: one stream of calls per handle.
@@ -351,8 +351,10 @@ int rb_query_launches(const rb_buffer *rb, int64_t b, int64_t c, int64_t r, int6
  * makes train_stream wait for the last step's representatives (end of
  * training, or before the caller touches the buffer's state).  Arguments,
  * limits and errors of rb_pipeline_step are those of rb_update_sample;
- * ready_rows may be null.  On an error nothing was enqueued and the pipeline
- * is unchanged.
+ * ready_rows may be null.  On an error of the arguments or of the handle's state
+ * nothing was enqueued and the pipeline is unchanged.  On RB_EHIP the streams may
+ * have been made to wait for each other and a part of the work may have been
+ * enqueued; whoever waits next (a call or rb_pipeline_drain) waits for that too.
  */
 typedef struct rb_pipeline rb_pipeline;
 int rb_pipeline_create(rb_pipeline **out, rb_buffer *rb);
@@ -379,8 +381,8 @@ int rb_pipeline_drain(rb_pipeline *p, void *train_stream, int64_t *ready_rows);
  * complete then), and trains the remaining n - 1 iterations of the group.
  * Every iteration thus trains on exactly the representatives that
  * rb_pipeline_step would have given it.  Arguments, limits and errors are those
- * of rb_update_sample_many; *ready_rows as in rb_pipeline_step.  n = 0 does
- * nothing.  On an error nothing was enqueued and the pipeline is unchanged.
+ * of rb_update_sample_many; *ready_rows as in rb_pipeline_step, and so is what an
+ * error leaves.  n = 0 does nothing.
  */
 int rb_pipeline_step_many(rb_pipeline *p, int64_t n, const void *const *batch_x, const int64_t *const *batch_y,
                           int64_t b, int64_t c, int64_t r, uint64_t seed, uint64_t first_step,

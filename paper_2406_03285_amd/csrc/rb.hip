@@ -1853,6 +1853,7 @@ int rb_pipeline_step(rb_pipeline* p, const void* batch_x, const int64_t* batch_y
     const bool two_streams = train != rb->stream;
     // (1) the training stream may go on once the previous step's representatives are complete
     if (two_streams && !hand_over(p, train)) return RB_EHIP;
+    p->recorded = false;                        // (should anything fail from here on, wait_done is for all that the buffer's stream has got)
     // (2) update with this mini-batch, then collect the next representatives
     const int rc = rb_update_sample(rb, batch_x, batch_y, b, c, r, seed, step, next_x, next_y);
     if (rc != RB_OK) return rc;
@@ -1894,6 +1895,7 @@ int rb_pipeline_step_many(rb_pipeline* p, int64_t n, const void* const* batch_x,
     const bool two_streams = train != rb->stream;
     // (1) the training stream may go on once the previous call's representatives are complete
     if (two_streams && !hand_over(p, train)) return RB_EHIP;
+    p->recorded = false;                        // (as in rb_pipeline_step)
     // (2) the n updates, each followed by the collection of the next representatives
     // (their last launch records the event, except into a graph that is being captured, and when the steps go out one by one)
     if (two_streams && !captured(rb->stream)) rb->done = p->done;

@@ -105,3 +105,23 @@ def test_a_failed_launch_is_reported_once_and_can_be_made_again(name):
     *_, (failed, _), pending, _, again = on_a_pipeline([["fail", function, 0], *CALLS[name], ["pending"], ["fail", "", 0], CALLS[name][-1]])
     assert (failed[0] if isinstance(failed, list) else failed) == RB_EHIP and pending[0] == 0
     assert (again[0][0] if isinstance(again[0], list) else again[0]) == 0
+
+
+# A call that fails on the way may have enqueued a part of its work, and nothing says where that ends: whoever waits next waits for all of it.
+@pytest.mark.parametrize("function,after,failing,launched", [
+    ("hipEventRecord", 1, step(1, TRAIN), 1),                          # the step is on its way, its event is not
+    ("hipEventRecord", 1, step_many(3, 1, TRAIN, 2000, 1100, 40), 3),  # the same for steps that go out one by one
+    ("hipLaunchKernel", 1, step(1, TRAIN, 3000, 2, 1500), 1),          # the second of two launches
+    ("hipLaunchKernel", 2, step_many(3, 1, TRAIN, 2000, 1100, 40), 2), # the third step of three
+    ("hipExtLaunchKernel", 0, step_many(4, 1, TRAIN), 1),              # the last launch of several steps
+], ids=["step-event", "many-event", "step-launch", "many-launch", "many-last-launch"])
+def test_a_pipeline_call_that_fails_on_the_way_is_waited_for(function, after, failing, launched):
+    for before in ([], [step(0, TRAIN)]):
+        results = on_a_pipeline([*before, ["fail", function, after], failing, ["fail", "", 0], step(0, TRAIN)], classes=300)
+        (result, lines), (again, next_lines) = results[len(before) + 1], results[-1]
+        assert result[0] == RB_EHIP and len(kernels(lines)) >= launched, (result, lines)
+        assert again[0] == 0
+        if before:
+            results = on_a_pipeline([*before, ["fail", function, after], failing, ["fail", "", 0], drain(OTHER)], classes=300)
+            assert results[-1][0] == [0, 8]                            # the representatives of the last call that succeeded
+            assert waits_for_the_steps_before([line for _, some in results for line in some], OTHER), results
