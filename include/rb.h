@@ -346,6 +346,13 @@ int rb_query_launches(const rb_buffer *rb, int64_t b, int64_t c, int64_t r, int6
  * another train_stream makes that one wait for everything enqueued on the
  * bound stream until then.
  *
+ * A call may be captured into a HIP graph by way of train_stream, which the
+ * bound stream joins; the capture has to be drained before it ends, and
+ * representatives that a call outside of it collects are refused (RB_EHIP).  A
+ * graph repeats its steps with the arguments and books they were captured with:
+ * it is replayed on the state the capture found, e.g. behind an rb_bind of its
+ * own.
+ *
  * rb_pipeline_create makes the two events (no device memory); the pipeline
  * borrows `rb`, which must outlive it.  rb_pipeline_drain only does (1): it
  * makes train_stream wait for the last step's representatives (end of

@@ -1418,6 +1418,53 @@ def test_binding_while_a_stream_is_being_captured(storage, static):
         buf.buf_y.fill_(5)
 
 
+@pytest.mark.parametrize("n,planners", [(1, 0), (4, 0), (4, 1)], ids=["one-step", "planners-side-by-side", "one-planner"])
+def test_pipeline_calls_in_a_graph(n, planners):
+    """Two calls of a new pipeline on two streams, captured with the binding in front and drained at the end: every replay gives the plain calls' bytes."""
+    rb = _rb()
+    K, S, b, c, r, seed = 9, 4, 40, 20, 10, 3
+    dev = torch.device("cuda:0")
+    train, side = torch.cuda.Stream(dev), torch.cuda.Stream(dev)
+    buf = rb.RehearsalBuffer(K, S, (64,), torch.float32, device=dev, stream=side)
+    buf.set_option(rb.RB_OPT_PLANNERS, planners)
+    pipe = rb.Pipeline(buf)
+    steps = 2 * n
+    xs = [torch.randn((b, 64), device=dev) for _ in range(steps)]
+    ys = [torch.randint(0, K, (b,), device=dev) for _ in range(steps)]
+    out_x = torch.zeros((steps, r, 64), device=dev)
+    out_y = torch.zeros((steps, r), dtype=torch.int64, device=dev)
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=train):
+        side.wait_stream(train)
+        assert rb.rb_bind(buf.handle, buf.buf_x, buf.buf_y, buf.workspace, side) == rb.RB_OK
+        for at in range(0, steps, n):
+            now = slice(at, at + n)
+            if n == 1:
+                pipe.step(xs[at], ys[at], c, r, seed, at, out_x[at], out_y[at], train)
+            else:
+                assert buf.steps_per_launch(b, c, r) > 1
+                pipe.step_many(xs[now], ys[now], c, r, seed, at, list(out_x[now]), list(out_y[now]), train)
+        assert pipe.drain(train) == r
+    orc = rbo.Buffer(K, S, 256)
+    want = []
+    for t in range(steps):
+        orc.update(xs[t].cpu().numpy().view(np.uint8).reshape(b, 256), ys[t].cpu().numpy(), c, seed, t)
+        want.append(orc.sample_augment(r, seed, t, out_x=np.zeros((r, 256), dtype=np.uint8)))
+    for replay in range(3):
+        out_x.zero_()
+        out_y.fill_(-7)
+        graph.replay()
+        torch.cuda.synchronize()
+        for t, (rows, want_x, want_y) in enumerate(want):
+            assert np.array_equal(out_y[t].cpu().numpy(), want_y), (replay, t)
+            assert np.array_equal(out_x[t].cpu().numpy().view(np.uint8).reshape(r, 256)[:rows], want_x[:rows]), (replay, t)
+        compare_buffers(buf, orc, f"pipeline in a graph, replay {replay}")
+        buf.buf_y.fill_(5)
+        torch.cuda.synchronize()
+    pipe.close()
+
+
 # ------------------------------------------------------ random configurations ---
 
 def _random_workload(rng, i):

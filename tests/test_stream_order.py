@@ -125,3 +125,27 @@ def test_a_pipeline_call_that_fails_on_the_way_is_waited_for(function, after, fa
             results = on_a_pipeline([*before, ["fail", function, after], failing, ["fail", "", 0], drain(OTHER)], classes=300)
             assert results[-1][0] == [0, 8]                            # the representatives of the last call that succeeded
             assert waits_for_the_steps_before([line for _, some in results for line in some], OTHER), results
+
+
+# Calls that a stream captures: the buffer's stream joins, no launch carries an event, and the training stream ends up behind all of it.
+@pytest.mark.parametrize("call,n", [(step, 1), (step_many, 4)], ids=["step", "many"])
+def test_a_captured_pipeline_call_keeps_to_what_a_graph_takes(call, n):
+    make = (lambda at: step(at, TRAIN)) if n == 1 else (lambda at: step_many(n, at, TRAIN))
+    results = on_a_pipeline([["capture", TRAIN], make(0), make(n), drain(TRAIN), ["end_capture"], make(2 * n)])
+    assert [r[0] for r, _ in results[1:4]] == [0, 0, 0] and results[-1][0][0] == 0
+    lines = [line for _, some in results[:4] for line in some]
+    assert kernels(lines) and all(len(line.split()) == 6 for line in lines if line.startswith("launch"))
+    assert lines[:2] == [f"record 1 {TRAIN}", f"wait {BUFFER} 1"] and waits_for_the_steps_before(lines, TRAIN)
+    # the second call's steps come behind the wait for the first one's
+    second = results[2][1]
+    assert second[:3] == [f"wait {TRAIN} 2", f"record 1 {TRAIN}", f"wait {BUFFER} 1"]
+
+
+# ... and representatives from outside are refused before anything has gone into the graph.
+@pytest.mark.parametrize("started", [step(0, TRAIN), step_many(4, 0, TRAIN)], ids=["by-step", "by-many"])
+@pytest.mark.parametrize("then", [step(4, TRAIN), step_many(4, 4, TRAIN), drain(TRAIN)], ids=["step", "many", "drain"])
+def test_a_capture_takes_no_representatives_from_outside(started, then):
+    results = on_a_pipeline([started, ["capture", TRAIN], then, ["pending"], ["end_capture"], then])
+    assert results[2][0][0] == RB_EHIP and results[2][1] == [] and results[3][0] == 0
+    assert results[-1][0] == [0, 8]
+    assert results[-1][1] == on_a_pipeline([started, then])[-1][1]
