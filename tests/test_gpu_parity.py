@@ -126,6 +126,14 @@ def test_general_kernels_at_the_edges_of_their_rounds(K, S, b, c, r, policy):
     run_parity(w, check_state_every=2, policy=POLICIES.get(policy))
 
 
+# More than 1024 representatives: one ballot finds the chunk of up to 64, a search of more; stored rows of each form, of less and more than a tile.
+@pytest.mark.parametrize("store,per_vec", [("same", 4), ("bf16", 8), ("u8", 16)])
+@pytest.mark.parametrize("K,S,b,c,r,vecs", [(16384, 2, 4096, 1500, 1025, 65), (16385, 2, 4096, 1500, 1537, 9), (66000, 1, 4096, 2000, 2050, 3), (300, 20, 2048, 1700, 1281, 513)])
+def test_many_representatives_of_many_classes(K, S, b, c, r, vecs, store, per_vec):
+    w = wl.Workload(f"many-K{K}-r{r}-{store}", 9, K, S, (vecs * per_vec,), "f32", b, c, r, 4, "uniform", "uniform")
+    run_parity(w, check_state_every=2, store_bf16=store == "bf16", store_u8=store == "u8")
+
+
 # The single call without a plan: small counts (one launch, any strategy and storage form) and the shapes beyond them.
 # launches: what the call has to take, (exact, Bernoulli selection) where they differ.
 @pytest.mark.parametrize("policy", ["exact-uniform"] + sorted(POLICIES))
