@@ -60,7 +60,9 @@ enum rb_status {
 #define RB_FLAG_BAD_LABEL 1u       /* state flag: a candidate's label was outside [0, K)   */
 #define RB_FLAG_PLAN_TIMEOUT 2u    /* state flag: the workgroups that plan a several-steps launch for large counts
                                       did not hear from each other within 2 s; that launch moved nothing and the
-                                      buffer's state is no longer defined (bind again) */
+                                      buffer's state is no longer defined (bind again).  Also: a step planned ahead
+                                      (rb_announce_next) with the Bernoulli selection, b > 1024 and c <= 512 had more
+                                      than 1024 candidates and left out those beyond (a chance below 2e-86 a step) */
 
 /*
  * Describe a buffer of `classes` sub-buffers of `slots_per_class` samples each
