@@ -206,12 +206,12 @@ int rb_sample_augment(rb_buffer *rb, int64_t r, uint64_t seed, uint64_t step,
  * halves run as ONE kernel launch (a representative whose slot is being written
  * in this very step is copied from the mini-batch row stored there) with
  * 1 <= c, r <= 64, up to 1024 classes and the exact selection, and beyond that,
- * for c, r >= 1 and up to 10240 classes, where it is the faster form:
- * while (c + r) * (sample + stored row bytes) is below 247 MB, r times that below
- * 77 to 99 MB (with bfloat16 storage 110 and 33 to 44 MB, in 8 bits 22 to 30 and
- * 16 MB; less for few rows and some other shapes), classes are neither many for
- * few rows nor few for many candidates, and r is not above the number of slots
- * (rb_query_launches tells).  Otherwise the two kernels are enqueued one
+ * for c, r >= 1 and up to 10240 classes, where it is the faster form.  The
+ * library decides that by the sizes, the storage form and the policy alone:
+ * never for rows that take long to move ((c + r) * (sample + stored row bytes)
+ * of 247 MB and more in any storage form, much less for most shapes), for
+ * classes that are many for few rows or few for many candidates, or for an r
+ * above the number of slots; rb_query_launches tells.  Otherwise the two kernels are enqueued one
  * after the other, as they are when out_y lies over batch_y (the labels are
  * read before they are replaced).  out_x must not overlap batch_x.
  */
