@@ -1,4 +1,4 @@
-"""Thin binding of the C ABI in include/rb.h (argument marshalling only): ctypes, and a native one for the calls of every step.
+"""Thin binding of the C ABI in include/rb.h (argument marshalling only): ctypes, and a native one for most calls of a training loop.
 
 Every function has the name and argument order of its C counterpart; tensors
 are passed as device pointers.  PyTorch is used for device memory and streams
