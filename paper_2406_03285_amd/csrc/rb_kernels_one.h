@@ -308,9 +308,9 @@ __global__ void __launch_bounds__(ONE_TPB) rb_step_one_kernel(const int64_t* bat
     int at[ONE_PER];                            // Bernoulli: list index of position tid + u * ONE_TPB, -1: not selected
     // Sampling draws: thread `sid + u * ONE_TPB` of them.  A draw takes a wavefront twenty multiplications of a quarter of the rate, and the
     // wavefronts of a compute unit share its four units: each makes those it has alone, the last wavefronts the first ones, while the
-    // first ones select or flip coins.  (Two each in any case, before the selection's: 10 + 4 rows of 1 KB, Bernoulli, 6.10 us, now 5.86;
-    // 64 + 26 of 11 KB of 1031 classes 6.78 : 6.52.  Of large mini-batches they are made while the candidates' labels travel: 1024 + 1024 of
-    // 8 KB 13.57 : 13.01.)
+    // first ones select or flip coins.  (Two each in any case, before the selection's, and the books by the first wavefronts (below): 10 + 4 rows of
+    // 1 KB, Bernoulli, 5.92 us, now 5.85; 64 + 26 of 1031 classes, of 5 KB 6.62 : 6.32, of 11 KB 6.67 : 6.36.  Of large
+    // mini-batches they are made while the candidates' labels travel: 1024 + 1024 of 8 KB 13.57 : 13.01.)
     const int sid = tid ^ (ONE_TPB - WAVE);
     uint64_t bits[ONE_PER];                     // random bits of sampling draw sid + u * ONE_TPB
     const auto draw_bits = [&]() {
