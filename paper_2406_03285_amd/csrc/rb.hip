@@ -1607,10 +1607,11 @@ int rb_update(rb_buffer* rb, const void* batch_x, const int64_t* batch_y,
     // keep those.  Both calls, r = 64, large against small tiles: bfloat16 rows of 49 KB 600 candidates 18.5 : 18.5 us,
     // 800 23.1 : 22.9, 900 24.7 : 26.1, 1000 25.4 : 28.1; of 192 KB 600 44.7 : 43.9, 800 55.8 : 57.6, 1000 66.5 : 71.8; 8 bits,
     // 49 KB, 700 21.0 : 20.4, 900 22.9 : 25.1; rows of 12 KB, one large tile, 1024 as bfloat16 15.4 : 14.5, 8 bits 16.5 : 15.2)
-    // (Bernoulli selection: a coin per position of the mini-batch in every workgroup, and 12 bytes of LDS for it, so the size of the
-    // mini-batch counts as well: large against small tiles, bfloat16 rows of 602 KB, r = 8, mini-batch of 512 / 1024 / 2048 / 4096,
-    // c = 10 [537 workgroups of small tiles] 12.7 : 11.6, 13.2 : 12.0, 14.1 : 13.2, 16.5 : 19.1, c = 60 [1980] 20.2 : 19.8, 21.0 : 21.3,
-    // 23.2 : 25.2, 31.1 : 43.4; of 192 KB, c = 60 [642] 12.7 : 12.1, 13.1 : 12.8, 14.1 : 14.2, 16.6 : 23.0; in 8 bits alike)
+    // (Bernoulli selection: a coin per position of the mini-batch in every workgroup, and 6 bytes of LDS for it, so the size of the
+    // mini-batch counts as well: large against small tiles, rb_update alone, bfloat16 rows of 602 KB, mini-batch of 512 / 1024 / 2048 / 4096,
+    // c = 10 [537 workgroups of small tiles] 6.3 : 5.6, 6.8 : 6.0, 7.7 : 7.0, 9.2 : 10.2, c = 60 [1980] 14.3 : 14.0, 15.1 : 15.4, 17.0 : 19.0,
+    // 21.4 : 25.7; of 192 KB, c = 60 [642] 7.0 : 7.2, 7.5 : 7.6, 8.6 : 8.9, 10.2 : 11.4; in 8 bits alike.  The chosen form is within 3 % of
+    // the better one at each of 72 shapes, 49 to 602 KB, c = 10, 60 and 200)
     const int64_t small_tiles = (rb->row_vec + WAVE * (narrow == 2 ? 2 : 4) - 1) / (WAVE * (narrow == 2 ? 2 : 4));
     const bool coins = rb->selection == RB_SELECT_BERNOULLI && (b >= 3072 || (b >= 1024 && rows * small_tiles > 1024 * NWAVE));
     const bool many = !small && (c > BIG_MAX || coins || (rows > 768 && rb->row_vec > WAVE * (narrow == 2 ? 4 : 8)));
