@@ -47,11 +47,24 @@ inline size_t gen_sample_lds_bytes(int r, int nchunks) { return 4 * (size_t)(nch
 // Lane `lane` looks at four consecutive candidates of every GEN_LIST: number `bit` of its candidates is this one of the list.
 __device__ __forceinline__ int gen_entry(int bit, int lane) { return (bit >> 2) * GEN_LIST + 4 * lane + (bit & 3); }
 
-// A kernel per form of the selection: exact with up to GEN_FEW candidates, exact with more, Bernoulli.  (Two draws side by side and four
+// A kernel per form of the selection: exact with few candidates (gen_few), exact with more, Bernoulli.  (Two draws side by side and four
 // candidates per access: 300 to 500 candidates 3 % faster, 500 to 2048 9 to 12 %, more 30 %, but 65 to 128 2 % slower, 128 to 200 1 %, 200 to 300 equal.
 // Coins counted by ballots: mini-batches of 256 to 1024 5 % faster, 1024 to 2048 7 %, more 12 %, smaller ones equal.)
 enum { GEN_EXACT_FEW = 0, GEN_EXACT_MANY = 1, GEN_COINS = 2 };
-constexpr int GEN_FEW = 192;
+// Few are more when rows are long: the wavefronts of GEN_EXACT_MANY, sooner done with the list, get in each other's way where 300 to 700
+// workgroups move rows of 16 KB and more (the same rows with plain stores take as long as before; 430 of 47 KB 9.6 us : 10.8, 595 of 22 KB
+// 8.7 : 9.9, but 289 of 26 KB 6.9 : 6.7).  Over 1400 shapes of such rows and 193 to 384 candidates the two are equal on average, with 385 to 512
+// plain ones GEN_EXACT_MANY is 3 % ahead and up to one in seven shapes more than 3 % behind.
+constexpr int GEN_FEW = 192, GEN_FEW_LONG = 512, GEN_FEW_LONG_CONVERTED = 384;
+constexpr int64_t GEN_LONG_VEC = 1024;
+inline bool gen_few(int c, int64_t row_vec, bool converted)
+{
+    return c <= (row_vec < GEN_LONG_VEC ? GEN_FEW : converted ? GEN_FEW_LONG_CONVERTED : GEN_FEW_LONG);
+}
+// Lists of this many candidates: the later class-mates of a class with many in this step are gathered for their draws.  They are dealt to the lanes
+// unevenly, and of 300 candidates of three classes a lane holds up to eight: 283 + 3 classes 10.1 us, 11.1 with a draw per candidate a lane holds
+// (which is as fast from about 400 on, where the list's passes count).
+constexpr int GEN_GATHERED = 384;
 
 template <int U, bool NT, int NARROW, int FORM>       // NARROW: binary32 mini-batch rows are stored 0 - as they come, 1 - as bfloat16, 2 - in 8 bits per element
 __global__ void __launch_bounds__(TPB) rb_update_kernel(const UpdateArgs a)
@@ -65,7 +78,7 @@ __global__ void __launch_bounds__(TPB) rb_update_kernel(const UpdateArgs a)
     __shared__ int s_wave[NWAVE];
     __shared__ int s_hist[CH];
     __shared__ int s_seg[WAVE];                             // Bernoulli: heads per stretch of WAVE positions
-    __shared__ uint16_t s_pend[NWAVE][WAVE];                // per wavefront: the class-mates, one per lane
+    __shared__ uint16_t s_pend[NWAVE][2 * WAVE];            // per wavefront: the class-mates, one per lane, or later ones waiting for their evict draw
     __shared__ uint32_t s_cm[NWAVE][RB_MAX_BATCH / 32];     // per wavefront: bitmap of the class-mates' positions
     __shared__ uint16_t s_cmpre[NWAVE][RB_MAX_BATCH / 32];  // class-mates before each bitmap word
 
@@ -344,20 +357,43 @@ __global__ void __launch_bounds__(TPB) rb_update_kernel(const UpdateArgs a)
                 cmpre[2 * lane + 1] = (uint16_t)(before + p0);
             }
             wave_lds_wait();
-            // every lane draws for the later class-mates it holds: the list is dealt to the lanes evenly
+            const auto takes = [&](int x) {    // whether the later class-mate at x overwrites this candidate's slot
+                // the rival's insertion number decides whether it overwrites at all, and (reservoir) its odds
+                const int rank_r = cmpre[x >> 5] + __popc(cm[x >> 5] & ((1u << (x & 31)) - 1u));
+                if (fill0 + rank_r < a.S) return false;
+                const int64_t offers = aux0 + rank_r < INT32_MAX ? aux0 + rank_r : INT32_MAX;
+                return (int64_t)below(a.sd, PURPOSE_EVICT, (uint32_t)x, reservoir ? (uint64_t)offers + 1 : (uint64_t)a.S) == own;
+            };
             bool beaten = false;
-            for (uint64_t h = hit; !beaten && __ballot(h != 0) != 0; h &= h - 1) {
-                const int x = h != 0 ? (int)s_x[entry(__builtin_ctzll(h))] : -1;
-                bool takes = false;
-                if (x > p) {
-                    // the rival's insertion number decides whether it overwrites at all, and (reservoir) its odds
-                    const int rank_r = cmpre[x >> 5] + __popc(cm[x >> 5] & ((1u << (x & 31)) - 1u));
-                    if (fill0 + rank_r >= a.S) {
-                        const int64_t offers = aux0 + rank_r < INT32_MAX ? aux0 + rank_r : INT32_MAX;
-                        takes = (int64_t)below(a.sd, PURPOSE_EVICT, (uint32_t)x, reservoir ? (uint64_t)offers + 1 : (uint64_t)a.S) == own;
+            if (FORM == GEN_EXACT_FEW || m <= GEN_GATHERED) {
+                // they are gathered WAVE at a time so that their draws are made with full wavefronts
+                uint16_t* pend = s_pend[wave];
+                int npend = 0;
+                for (int m0 = 0; m0 < m + WAVE && !beaten; m0 += WAVE) {
+                    if (m0 < m) {
+                        const int q = m0 + lane;
+                        const int xq = q < m ? s_x[q] : 0;
+                        const bool later = q < m && s_k[q] == ki && xq > p;
+                        const uint64_t mask = __ballot(later);
+                        if (later) pend[npend + __popcll(mask & ((1ull << lane) - 1))] = (uint16_t)xq;
+                        npend += __popcll(mask);
+                    }
+                    if (npend >= WAVE || (m0 >= m && npend > 0)) {
+                        wave_lds_wait();
+                        const int take = npend < WAVE ? npend : WAVE;
+                        beaten = __ballot(lane < take && takes(pend[lane])) != 0;
+                        const int rest = lane + take < npend ? pend[lane + take] : 0;    // at most WAVE - 1 left over
+                        wave_lds_wait();
+                        if (lane + take < npend) pend[lane] = (uint16_t)rest;
+                        npend -= take;
                     }
                 }
-                beaten = __ballot(takes) != 0;
+            } else {
+                // every lane draws for those it holds: the list is dealt to the lanes evenly
+                for (uint64_t h = hit; !beaten && __ballot(h != 0) != 0; h &= h - 1) {
+                    const int x = h != 0 ? (int)s_x[entry(__builtin_ctzll(h))] : -1;
+                    beaten = __ballot(x > p && takes(x)) != 0;
+                }
             }
             if (beaten) continue;
             slot = own;
