@@ -126,8 +126,8 @@ int rb_set_storage(rb_buffer *rb, int32_t storage);
  * slots_per_class / n and is dropped otherwise (exact while a class has been
  * offered fewer than 2^31 - 1 samples).
  * Every variant is served by every call, the Bernoulli selection by the
- * plan-ahead form of the single launch (rb_announce_next) for b <= 1024 or
- * c <= 512 and by the several-steps launches of rb_update_sample_many (the form
+ * plan-ahead form of the single launch (rb_announce_next) for b <= 1024, or
+ * c <= 512 where that is the faster form, and by the several-steps launches of rb_update_sample_many (the form
  * for large counts) for b <= 1024.  RB_EINVAL: unknown value.  RB_ESTATE: an
  * rb_update was already enqueued since the last rb_bind.
  */
@@ -236,8 +236,9 @@ int rb_update_sample(rb_buffer *rb, const void *batch_x, const int64_t *batch_y,
  * not be given other contents and passed as the next step's labels.  Used for 1 <= c <= 64,
  * 1 <= r <= 64, classes <= 1024 and the exact selection, and also for up to
  * 1024 candidates and representatives, b <= 4096 (with the Bernoulli selection
- * b <= 1024 or c <= 512) and up to 10240 classes (the step is then one launch
- * that moves rows by the plan, instead of two kernels); ignored otherwise.
+ * b <= 1024, or c <= 512 unless the rows are moved sooner than their step is
+ * planned) and up to 10240 classes (the step is then one launch that moves rows
+ * by the plan, instead of two kernels); ignored otherwise.
  * next_batch_y: device, b int64 labels that must be in place, as far as the
  * bound stream is concerned, when the announcing step is enqueued, and stay
  * unchanged until the step they belong to has run; null withdraws an

@@ -720,6 +720,22 @@ int step_big(rb_buffer* rb, const void* batch_x, const int64_t* batch_y, int64_t
     return RB_OK;
 }
 
+// Whether an announced step with the Bernoulli selection goes through the planners of large counts.  Mini-batches of up to BIG_MAX positions
+// always do.  Of larger ones the step that was not announced is the other form, and a plan takes longer than short rows: the update
+// planner's threads meet at one counter for a class with many candidates (labels, which the host cannot see), and with FIFO and
+// reservoir replacement it keeps the strategy's state of all classes, 0.4 us per 1000.  Unannounced steps' time over announced ones', singly
+// and 16 a call, 12400 random shapes of 1025 to 4096 positions:
+//   rows of 4 us and more            1.41, 1 of 100 more than 3 % slower when announced;
+//   shorter, up to 320 candidates    1.18 (0.2), FIFO and reservoir beyond 4000 classes 1.06 (21; 365 + 9 rows of 160 bytes of 7580 9.4 : 12.1 us);
+//   shorter, 321 to 512              1.10 (14; 512 + 10 rows of 704 bytes of 3 classes, bfloat16, FIFO 9.7 : 15.7 us).
+bool plans_coins(const rb_buffer* rb, int64_t b, int64_t c, int64_t r)
+{
+    if (!big_coins(b, c)) return false;
+    if (b <= BIG_MAX) return true;
+    const double rows_us = (double)(c + r) * (double)(rb->row_bytes + rb->sample_bytes) / 5.5e6;
+    return rows_us >= 4.0 || (c <= 320 && (rb->eviction == RB_EVICT_UNIFORM || rb->K <= 4000));
+}
+
 // A launch that records `done` (null: none) when it ends: its own completion is the event, without a packet of its own behind it in
 // the stream.  Two streams that wait for each other's events, 200 us of kernel a round: 237.0 us a round with the event recorded
 // behind the kernel, 233.7 so.
@@ -1692,9 +1708,9 @@ int rb_update_sample(rb_buffer* rb, const void* batch_x, const int64_t* batch_y,
 
     const bool plannable = small_counts(rb, c, r);
     // larger counts have a plan-ahead form of their own
-    // (with the Bernoulli selection, whose number of candidates is only bounded by b, where big_coins says so)
+    // (with the Bernoulli selection, whose number of candidates is only bounded by b, where plans_coins says so)
     const bool big = !plannable && c >= 1 && c <= BIG_MAX && r >= 1 && r <= BIG_MAX && b <= BIG_BATCH &&
-                     rb->K <= BIG_CLASSES && rb->opt_fuse && (rb->selection == RB_SELECT_EXACT || big_coins(b, c)) &&
+                     rb->K <= BIG_CLASSES && rb->opt_fuse && (rb->selection == RB_SELECT_EXACT || plans_coins(rb, b, c, r)) &&
                      rb->K * rb->S <= INT64_C(0x7FFFFFFF) && rb->S <= INT32_MAX - RB_MAX_BATCH;
     const int64_t* next_y = rb->next_y;
     rb->next_y = nullptr;                        // an announcement serves one call

@@ -1,6 +1,6 @@
 // Plan-ahead kernels for the single-launch step with up to 1024 candidates and representatives and up
 // to 10240 classes (any replacement strategy, any storage form; exact selection, or the Bernoulli
-// selection where big_coins says so): as in rb_kernels_planned.h the plan of a step is worked out by
+// selection where big_coins and plans_coins say so): as in rb_kernels_planned.h the plan of a step is worked out by
 // extra workgroups of the previous step's launch and left in a table, and the step's own launch only
 // moves rows by that table - but the planning workgroups (two: update, sampling) have 1024 threads
 // (one per candidate, resp. representative) and find class-mates, shared slots and repeated draws
@@ -23,9 +23,9 @@ constexpr int BIG_BATCH = 4096;               // largest mini-batch (words of th
 // Bernoulli selection: a step's candidates, a random number of them, get one thread each.  There are never more than BIG_MAX in a
 // mini-batch of that size; of a larger one c are expected, and with c <= BIG_COINS the chance of more than BIG_MAX is at most
 // exp(-1024 ln(1024 / 512) + 1024 - 512) = 1.3e-86 in a step (Chernoff's bound).  Such a step would leave out
-// the candidates beyond the BIG_MAX-th and raise RB_FLAG_PLAN_TIMEOUT.  (Within the line the planned launch is the faster form: 306 shapes,
-// 1025 to 4096 positions, 64 to 512 candidates, 16 to 512 representatives, rows of 1 to 192 KB in each storage form, 1.27 times as fast as
-// the step that was not announced, 0.99 times at worst; c = 512 and r = 16 of 2048, rows of 192 KB plain 46.7 : 41.3 us, bfloat16
+// the candidates beyond the BIG_MAX-th and raise RB_FLAG_PLAN_TIMEOUT.  (Which of these are planned: plans_coins.  306 shapes of 300 classes, uniform
+// replacement, 1025 to 4096 positions, 64 to 512 candidates, 16 to 512 representatives, rows of 1 to 192 KB in each storage form: 1.27 times as
+// fast as the step that was not announced, 0.99 times at worst; c = 512 and r = 16 of 2048, rows of 192 KB plain 46.7 : 41.3 us, bfloat16
 // 39.7 : 32.8, 8 bits 37.7 : 31.4.)
 constexpr int BIG_COINS = BIG_MAX / 2;
 __host__ __device__ constexpr bool big_coins(int64_t b, int64_t c) { return b <= BIG_MAX || (b <= BIG_BATCH && c <= BIG_COINS); }

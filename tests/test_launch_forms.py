@@ -5,11 +5,13 @@ import pytest
 from recorded import kernels, run
 
 X, Y, NEXT_Y, OUT_X, OUT_Y = (1 << k for k in (43, 44, 45, 46, 47))     # device memory
-SAME, EXACT, BERNOULLI, UNIFORM = 0, 0, 1, 0
+SAME, BF16, U8 = 0, 1, 2
+EXACT, BERNOULLI = 0, 1
+UNIFORM, FIFO, RESERVOIR = 0, 1, 2
 
 
-def forms(calls, selection, classes=300, slots=12, elems=64):
-    results = run([["create", classes, slots, elems, SAME, selection, UNIFORM, 100], *calls])
+def forms(calls, selection, classes=300, slots=12, elems=64, storage=SAME, eviction=UNIFORM):
+    results = run([["create", classes, slots, elems, storage, selection, eviction, 100], *calls])
     assert all(result == 0 for result, _ in results)
     return [kernels(lines) for _, lines in results[1:]]
 
@@ -18,15 +20,28 @@ def forms(calls, selection, classes=300, slots=12, elems=64):
 @pytest.mark.parametrize("selection,b,c,r,planned", [
     (EXACT, 4096, 1024, 1024, True), (EXACT, 4096, 1025, 40, False), (EXACT, 4096, 40, 1025, False),
     (BERNOULLI, 1024, 1024, 70, True), (BERNOULLI, 1025, 512, 70, True), (BERNOULLI, 1025, 513, 70, False),
-    (BERNOULLI, 4096, 512, 1024, True), (BERNOULLI, 4096, 513, 70, False), (BERNOULLI, 4096, 1, 1, True),
+    (BERNOULLI, 4096, 512, 1024, True), (BERNOULLI, 4096, 513, 70, False), (BERNOULLI, 4096, 320, 1, True),
 ])
 def test_announced_steps_of_large_counts(selection, b, c, r, planned):
     calls = [["rb_announce_next", "rb", NEXT_Y], ["rb_update_sample", "rb", X, Y, b, c, r, 1, 0, OUT_X, OUT_Y],
              ["rb_update_sample", "rb", X, NEXT_Y, b, c, r, 1, 1, OUT_X, OUT_Y]]
-    _, first, second = forms(calls, selection)
+    elems = 16384 if c > 320 else 64                         # (rows of 6 us, or short ones)
+    _, first, second = forms(calls, selection, elems=elems)
     assert (first == ["rb_big_plan_kernel", "rb_step_big_kernel"] and second == ["rb_step_big_kernel"]) is planned, (first, second)
     if not planned:
-        assert first == second == forms([calls[1]], selection)[0]
+        assert first == second == forms([calls[1]], selection, elems=elems)[0]
+
+
+# Mini-batches of more than 1024 with the Bernoulli selection: not where the rows are moved sooner than a step is planned.
+@pytest.mark.parametrize("eviction", [UNIFORM, FIFO, RESERVOIR])
+@pytest.mark.parametrize("b,c,classes,storage,elems,planned", [
+    (2000, 320, 4000, SAME, 64, True), (2000, 321, 4000, SAME, 64, False), (2000, 100, 4001, SAME, 64, None), (2000, 321, 300, BF16, 64, False),
+    (2000, 300, 4001, U8, 64, None), (1024, 500, 4001, SAME, 64, True), (2000, 400, 4001, SAME, 5840, False), (2000, 400, 4001, SAME, 5872, True),
+])
+def test_announced_steps_of_large_mini_batches_with_coins(b, c, classes, storage, elems, planned, eviction):
+    _, first, second = forms([["rb_announce_next", "rb", NEXT_Y], ["rb_update_sample", "rb", X, Y, b, c, 69, 1, 0, OUT_X, OUT_Y],
+                              ["rb_update_sample", "rb", X, NEXT_Y, b, c, 69, 1, 1, OUT_X, OUT_Y]], BERNOULLI, classes, 12, elems, storage, eviction)
+    assert (second == ["rb_step_big_kernel"]) is (eviction == UNIFORM if planned is None else planned), (first, second)
 
 
 # Four steps from one call: in one launch (behind the first one's plan), or one by one.
@@ -38,7 +53,7 @@ def test_several_steps_of_large_counts(selection, b, c, together):
     got = forms([call], selection)[0]
     if together:
         assert got[0] == "rb_bigwin_plan_kernel" and set(got[1:]) == {"rb_bigwin_kernel"} and len(got) <= n
-    elif c <= 512:
+    elif c <= 320:
         assert got == ["rb_big_plan_kernel"] + n * ["rb_step_big_kernel"]
     else:
         assert set(got) <= {"rb_step_one_kernel", "rb_update_kernel", "rb_sample_kernel"}
