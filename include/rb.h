@@ -236,9 +236,9 @@ int rb_update_sample(rb_buffer *rb, const void *batch_x, const int64_t *batch_y,
  * not be given other contents and passed as the next step's labels.  Used for 1 <= c <= 64,
  * 1 <= r <= 64, classes <= 1024 and the exact selection, and also for up to
  * 1024 candidates and representatives, b <= 4096 (with the Bernoulli selection
- * b <= 1024, or c <= 512 unless the rows are moved sooner than their step is
- * planned) and up to 10240 classes (the step is then one launch that moves rows
- * by the plan, instead of two kernels); ignored otherwise.
+ * b <= 1024, or c <= 512 unless a plan takes longer than it saves) and up to
+ * 10240 classes (the step is then one launch that moves rows by the plan,
+ * instead of two kernels); ignored otherwise.
  * next_batch_y: device, b int64 labels that must be in place, as far as the
  * bound stream is concerned, when the announcing step is enqueued, and stay
  * unchanged until the step they belong to has run; null withdraws an

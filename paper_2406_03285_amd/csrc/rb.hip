@@ -720,22 +720,6 @@ int step_big(rb_buffer* rb, const void* batch_x, const int64_t* batch_y, int64_t
     return RB_OK;
 }
 
-// Whether an announced step with the Bernoulli selection goes through the planners of large counts.  Mini-batches of up to BIG_MAX positions
-// always do.  Of larger ones the step that was not announced is the other form, and a plan takes longer than short rows: the update
-// planner's threads meet at one counter for a class with many candidates (labels, which the host cannot see), and with FIFO and
-// reservoir replacement it keeps the strategy's state of all classes, 0.4 us per 1000.  Unannounced steps' time over announced ones', singly
-// and 16 a call, 12400 random shapes of 1025 to 4096 positions:
-//   rows of 4 us and more            1.41, 1 of 100 more than 3 % slower when announced;
-//   shorter, up to 320 candidates    1.18 (0.2), FIFO and reservoir beyond 4000 classes 1.06 (21; 365 + 9 rows of 160 bytes of 7580 9.4 : 12.1 us);
-//   shorter, 321 to 512              1.10 (14; 512 + 10 rows of 704 bytes of 3 classes, bfloat16, FIFO 9.7 : 15.7 us).
-bool plans_coins(const rb_buffer* rb, int64_t b, int64_t c, int64_t r)
-{
-    if (!big_coins(b, c)) return false;
-    if (b <= BIG_MAX) return true;
-    const double rows_us = (double)(c + r) * (double)(rb->row_bytes + rb->sample_bytes) / 5.5e6;
-    return rows_us >= 4.0 || (c <= 320 && (rb->eviction == RB_EVICT_UNIFORM || rb->K <= 4000));
-}
-
 // A launch that records `done` (null: none) when it ends: its own completion is the event, without a packet of its own behind it in
 // the stream.  Two streams that wait for each other's events, 200 us of kernel a round: 237.0 us a round with the event recorded
 // behind the kernel, 233.7 so.
@@ -1297,6 +1281,31 @@ int step_form(const rb_buffer* rb, int64_t c, int64_t r)
         rb->S <= INT32_MAX - RB_MAX_BATCH && (rb->row_vec + TILE_UNIT - 1) / TILE_UNIT <= INT32_MAX / 2 / RB_MAX_BATCH)
         return STEP_ONE;
     return STEP_TWO;
+}
+
+// Whether an announced step with the Bernoulli selection goes through the planners of large counts.  Mini-batches of up to BIG_MAX positions
+// always do.  Of larger ones the step that was not announced is the other form: it makes all coins and draws in front of its rows, a plan is
+// made beside them, but takes longer than short rows where
+//   FIFO or reservoir replacement has the update planner keep the state of many classes, and its threads meet at the counters of classes
+//     with many candidates (labels, which the host cannot see), while the other form is a single launch.  What a plan saves and costs there,
+//     in us, is fitted to 11000 shapes, with 0.3 for labels that are in favour of a plan;
+//   a single class has all candidates: more than 300 of them 0.91, FIFO and reservoir replacement 0.80 times as fast when planned.
+// Unannounced steps' time over announced ones' (singly or 16 a call, the worse), random shapes of 1025 to 4096 positions, a quarter each of
+// them with labels of three classes, of fifty, skewed and uniform ones:
+//   all counts, classes, rows up to 8 us, strategies: 1.29, 1.0 % more than 3 % slower when announced (all of them planned: 1.4 %);
+//   FIFO and reservoir, 2500 to 10240 classes, 64 to 512 candidates, rows up to 6 us: 1.12, 11 % (1.10, 21 %);
+//   up to 3000 classes, 200 to 512 candidates, rows up to 5 us: 1.25, 7 % (1.24, 8 %).
+// The steps that are not planned would be 0.79 to 0.92 times as fast, one in nine of them more than 3 % faster.
+bool plans_coins(const rb_buffer* rb, int64_t b, int64_t c, int64_t r)
+{
+    if (!big_coins(b, c)) return false;
+    if (b <= BIG_MAX) return true;
+    const double rows_us = (double)(c + r) * (double)(rb->row_bytes + rb->sample_bytes) / 5.5e6;
+    if (rb->K == 1) return c <= 300 || rows_us >= 4.0;
+    if (rb->eviction == RB_EVICT_UNIFORM || rows_us >= 6.0 || step_form(rb, c, r) != STEP_ONE) return true;
+    const double saves_us = 1.2 + 0.22e-3 * (double)b + 2.5e-3 * (double)r + 0.6 * std::max(0.0, rows_us - 1.5);
+    const double costs_us = 0.67e-6 * (double)rb->K * (double)(c + 200) + 0.9e-3 * (double)c;
+    return saves_us >= costs_us;
 }
 
 // Update and sampling of one step in one launch without a plan (rb_kernels_one.h).

@@ -25,22 +25,26 @@ def forms(calls, selection, classes=300, slots=12, elems=64, storage=SAME, evict
 def test_announced_steps_of_large_counts(selection, b, c, r, planned):
     calls = [["rb_announce_next", "rb", NEXT_Y], ["rb_update_sample", "rb", X, Y, b, c, r, 1, 0, OUT_X, OUT_Y],
              ["rb_update_sample", "rb", X, NEXT_Y, b, c, r, 1, 1, OUT_X, OUT_Y]]
-    elems = 16384 if c > 320 else 64                         # (rows of 6 us, or short ones)
-    _, first, second = forms(calls, selection, elems=elems)
+    _, first, second = forms(calls, selection)
     assert (first == ["rb_big_plan_kernel", "rb_step_big_kernel"] and second == ["rb_step_big_kernel"]) is planned, (first, second)
     if not planned:
-        assert first == second == forms([calls[1]], selection, elems=elems)[0]
+        assert first == second == forms([calls[1]], selection)[0]
 
 
-# Mini-batches of more than 1024 with the Bernoulli selection: not where the rows are moved sooner than a step is planned.
+# Mini-batches of more than 1024 with the Bernoulli selection: not where the plan takes longer than what it saves.
 @pytest.mark.parametrize("eviction", [UNIFORM, FIFO, RESERVOIR])
-@pytest.mark.parametrize("b,c,classes,storage,elems,planned", [
-    (2000, 320, 4000, SAME, 64, True), (2000, 321, 4000, SAME, 64, False), (2000, 100, 4001, SAME, 64, None), (2000, 321, 300, BF16, 64, False),
-    (2000, 300, 4001, U8, 64, None), (1024, 500, 4001, SAME, 64, True), (2000, 400, 4001, SAME, 5840, False), (2000, 400, 4001, SAME, 5872, True),
+@pytest.mark.parametrize("b,c,r,classes,storage,elems,planned", [
+    (2000, 400, 69, 3613, SAME, 64, True), (2000, 400, 69, 3614, SAME, 64, None),          # many classes whose state is kept
+    (2000, 300, 69, 4600, U8, 64, True), (2000, 300, 69, 4700, BF16, 64, None),            # ... more with fewer candidates
+    (1024, 400, 69, 10240, SAME, 64, True),
+    (1171, 36, 12, 7541, BF16, 64, True),                                                  # the other form would be two launches
+    (1025, 512, 1, 10240, SAME, 8040, None), (1025, 512, 1, 10240, SAME, 8044, True),      # rows of 6 us
+    (2000, 300, 9, 1, SAME, 64, True), (2000, 301, 9, 1, SAME, 64, False),                 # one class of all candidates
+    (2000, 301, 1, 1, SAME, 9104, False), (2000, 301, 1, 1, SAME, 9108, True), (2000, 512, 9, 2, BF16, 64, True),
 ])
-def test_announced_steps_of_large_mini_batches_with_coins(b, c, classes, storage, elems, planned, eviction):
-    _, first, second = forms([["rb_announce_next", "rb", NEXT_Y], ["rb_update_sample", "rb", X, Y, b, c, 69, 1, 0, OUT_X, OUT_Y],
-                              ["rb_update_sample", "rb", X, NEXT_Y, b, c, 69, 1, 1, OUT_X, OUT_Y]], BERNOULLI, classes, 12, elems, storage, eviction)
+def test_announced_steps_of_large_mini_batches_with_coins(b, c, r, classes, storage, elems, planned, eviction):
+    _, first, second = forms([["rb_announce_next", "rb", NEXT_Y], ["rb_update_sample", "rb", X, Y, b, c, r, 1, 0, OUT_X, OUT_Y],
+                              ["rb_update_sample", "rb", X, NEXT_Y, b, c, r, 1, 1, OUT_X, OUT_Y]], BERNOULLI, classes, 12, elems, storage, eviction)
     assert (second == ["rb_step_big_kernel"]) is (eviction == UNIFORM if planned is None else planned), (first, second)
 
 
@@ -53,7 +57,7 @@ def test_several_steps_of_large_counts(selection, b, c, together):
     got = forms([call], selection)[0]
     if together:
         assert got[0] == "rb_bigwin_plan_kernel" and set(got[1:]) == {"rb_bigwin_kernel"} and len(got) <= n
-    elif c <= 320:
+    elif c <= 512:
         assert got == ["rb_big_plan_kernel"] + n * ["rb_step_big_kernel"]
     else:
         assert set(got) <= {"rb_step_one_kernel", "rb_update_kernel", "rb_sample_kernel"}
