@@ -1208,14 +1208,12 @@ bool small_counts(const rb_buffer* rb, int64_t c, int64_t r)
 //   bfloat16, Bernoulli    6 to 8                       1.16 (1.05)      16 to 20      1.03 (0.93)     20 to 30   0.99 (0.92)
 //   8 bits, exact          2 to 3                       1.13 (0.99)      3 to 4        1.05 (0.89)     6 to 8     0.99 (0.89)
 //   8 bits, Bernoulli      2 to 3                       1.19 (0.99)      3 to 4        1.08 (0.82)     10 to 12   0.96 (0.84)
+// (Long rows, more than 192 KB or 80 KB as bfloat16, exact selection with uniform or FIFO replacement, beyond the lines for few rows below: 553
+// shapes 1.04, half of them more than 3 % faster and 1 of 15 more than 3 % slower in one launch; bfloat16 rows beyond 130 KB 1.00.)
 // More than 1024 candidates: the two launches' search for class-mates grows with their square (plain rows beyond 14 us 1.54, bfloat16 beyond
 // 5.5 us 1.47, 8 bits beyond 4 us 1.40), and the lines lie further out.  Nearer they lie, or none are drawn further than before, for
 //   few long rows, up to 128: plain, exact, beyond 14 us 1.01 (0.95), up to 128 candidates 1.03; bfloat16, representatives beyond 3.3 us, up to 64 rows
-//     1.04;
-//   rows of more than 192 KB (stored as bfloat16: 80 KB), exact, uniform or FIFO replacement: 551 and 226 shapes on the far side of the nearer
-//     lines 1.01, a quarter of them more than 3 % slower in one launch (shorter ones: 1.09 and 1.10, 2 of 100).  With reservoir replacement
-//     1.13 and 1.10, and few are slower;
-//   up to 64 on either side, exact, when the two launches are those of the small-count kernels, a workgroup per tile: plain 5.5 to 7 us
+//     1.04; and up to 64 on either side, exact, when the two launches are those of the small-count kernels, a workgroup per tile: plain 5.5 to 7 us
 //     1.04 (0.91), 8 to 10 0.99; bfloat16 5.5 to 7 1.01 (0.94), 7 to 8 0.96; 8 bits 2 to 3 1.04, 3 to 4 1.01 (0.93);
 //   more than 1024 representatives of short rows, which the sampling kernel moves as well: rows of up to 13 KB, plain, beyond 14 us 7 of 10 slower
 //     in one launch, 8 bits beyond 2.8 us 8 of 10;
@@ -1229,9 +1227,7 @@ int step_form(const rb_buffer* rb, int64_t c, int64_t r)
     const bool exact = rb->selection == RB_SELECT_EXACT, small_two = exact && c <= WAVE && r <= WAVE, many = c > BIG_MAX;
     const double one_us = (double)(c + r) * (double)(rb->row_bytes + rb->sample_bytes) / 5.5e6;     // the rows, all and the representatives'
     const double reps_us = (double)r * (double)(rb->row_bytes + rb->sample_bytes) / 5.5e6;
-    const int64_t longest = rb->storage == RB_STORE_SAME ? 192 << 10 : rb->storage == RB_STORE_BF16 ? 80 << 10 : INT64_MAX;     // of a stored row, bytes
-    const bool few_long = exact && rb->eviction != RB_EVICT_RESERVOIR && !many && rb->row_bytes > longest;
-    const bool further = !small_two && !few_long && c + r > 2 * WAVE && r <= BIG_MAX && (rb->storage == RB_STORE_SAME || (rb->K >= 32 && c <= rb->K * rb->S));
+    const bool further = !small_two && c + r > 2 * WAVE && r <= BIG_MAX && (rb->storage == RB_STORE_SAME || (rb->K >= 32 && c <= rb->K * rb->S));
     double one_most, reps_most;
     switch (rb->storage) {
     case RB_STORE_U8:

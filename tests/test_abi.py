@@ -419,11 +419,11 @@ def test_single_launch_with_long_rows(storage, selection, c, r, elems, launches)
 
 # ... and either side of where the time the rows take, or the representatives' rows, ends it: few or many candidates, either selection.
 @pytest.mark.parametrize("storage,selection,c,r,us,launches", [
-    (0, 0, 128, 66, 13.9, 1), (0, 0, 128, 66, 14.1, 2), (0, 0, 129, 66, 44.5, 2), (0, 0, 630, 10, 44.5, 1), (0, 0, 630, 10, 45.5, 2), (0, 0, 129, 10, 13.9, 1), (0, 0, 129, 10, 14.1, 2),
+    (0, 0, 128, 66, 13.9, 1), (0, 0, 128, 66, 14.1, 2), (0, 0, 129, 66, 44.5, 2), (0, 0, 129, 10, 44.5, 1), (0, 0, 129, 10, 45.5, 2),
     (0, 0, 300, 200, 34.0, 1), (0, 0, 300, 200, 36.0, 2), (0, 0, 1025, 1024, 35.5, 1), (0, 0, 1025, 1024, 36.5, 2),
     (0, 0, 1025, 1025, 13.9, 1), (0, 0, 1025, 1025, 14.1, 2), (0, 1, 10, 119, 19.0, 1), (0, 1, 10, 119, 20.0, 2), (0, 1, 119, 10, 44.5, 1),
     (0, 1, 119, 10, 45.5, 2), (0, 1, 64, 64, 13.9, 1), (0, 1, 64, 64, 14.1, 2),
-    (1, 0, 65, 195, 7.9, 1), (1, 0, 65, 195, 8.1, 2), (1, 0, 390, 65, 19.8, 1), (1, 0, 390, 65, 20.2, 2), (1, 0, 1025, 1024, 23.5, 1), (1, 0, 1025, 1024, 24.5, 2),
+    (1, 0, 65, 195, 7.9, 1), (1, 0, 65, 195, 8.1, 2), (1, 0, 195, 65, 19.8, 1), (1, 0, 195, 65, 20.2, 2), (1, 0, 1025, 1024, 23.5, 1), (1, 0, 1025, 1024, 24.5, 2),
     (1, 1, 32, 97, 10.5, 1), (1, 1, 32, 97, 10.8, 2), (1, 1, 4, 124, 3.35, 1), (1, 1, 4, 124, 3.5, 2),
     (2, 0, 195, 65, 3.9, 1), (2, 0, 195, 65, 4.1, 2), (2, 0, 50, 200, 3.7, 1), (2, 0, 50, 200, 3.8, 2), (2, 0, 1025, 1024, 15.8, 1), (2, 0, 1025, 1024, 16.2, 2),
     (2, 1, 100, 50, 5.4, 1), (2, 1, 100, 50, 5.6, 2), (2, 1, 64, 64, 1.9, 1), (2, 1, 64, 64, 2.1, 2),
@@ -459,18 +459,3 @@ def test_single_launch_with_more_representatives_than_slots():
     rc, h = rb.rb_create(2, 3, (32,), rb.RB_F32)
     assert rb.rb_query_launches(h, 100, 9, 64) == (rb.RB_OK, 1)             # small counts: one launch in any case
     rb.rb_destroy(h)
-
-
-# Rows beyond 192 KB (stored as bfloat16: 80 KB) keep to the nearer lines, except where the two launches know late which rows they move.
-@pytest.mark.parametrize("storage,vecs", [(0, 12288), (1, 5120)])
-@pytest.mark.parametrize("selection,eviction,c,held", [(0, 0, 300, True), (0, 1, 300, True), (0, 2, 300, False), (1, 0, 300, False), (0, 0, 1025, False)])
-def test_single_launch_of_long_rows_ends_sooner(storage, vecs, selection, eviction, c, held):
-    import paper_2406_03285_amd as rb
-    for more in (0, 1):
-        row = 16 * (vecs + more)
-        r = 8 if c > 1024 else 20                                           # SAME: 22 and 74 us; bfloat16: 14 and 46 us
-        us = (c + r) * row * (2 if storage == 0 else 3) / 5.5e6
-        rc, h = rb.rb_create(200, 100, (row // 4 * (1 if storage == 0 else 2),), rb.RB_F32)
-        assert rb.rb_set_storage(h, storage) == rb.RB_OK and rb.rb_set_policy(h, selection, eviction) == rb.RB_OK
-        assert rb.rb_query_launches(h, 2000, c, r) == (rb.RB_OK, 2 if us > 45 or (held and more) else 1), us
-        rb.rb_destroy(h)
