@@ -328,7 +328,7 @@ template <bool NT>
 hipError_t launch_update(const UpdateArgs& a, int narrow, int unroll, dim3 grid, size_t lds, hipStream_t st)
 {
     if (a.selection == RB_SELECT_BERNOULLI) return launch_update_f<NT, GEN_COINS>(a, narrow, unroll, grid, lds, st);
-    return gen_few(a.c, a.row_vec, narrow != 0) ? launch_update_f<NT, GEN_EXACT_FEW>(a, narrow, unroll, grid, lds, st) : launch_update_f<NT, GEN_EXACT_MANY>(a, narrow, unroll, grid, lds, st);
+    return gen_few(a.c, a.row_vec, narrow != 0, a.eviction) ? launch_update_f<NT, GEN_EXACT_FEW>(a, narrow, unroll, grid, lds, st) : launch_update_f<NT, GEN_EXACT_MANY>(a, narrow, unroll, grid, lds, st);
 }
 
 template <bool NT, bool MANY>

@@ -52,14 +52,16 @@ __device__ __forceinline__ int gen_entry(int bit, int lane) { return (bit >> 2) 
 // Coins counted by ballots: mini-batches of 256 to 1024 5 % faster, 1024 to 2048 7 %, more 12 %, smaller ones equal.)
 enum { GEN_EXACT_FEW = 0, GEN_EXACT_MANY = 1, GEN_COINS = 2 };
 // Few are more when rows are long: the wavefronts of GEN_EXACT_MANY, sooner done with the list, get in each other's way where 300 to 700
-// workgroups move rows of 16 KB and more (the same rows with plain stores take as long as before; 430 of 47 KB 9.6 us : 10.8, 595 of 22 KB
-// 8.7 : 9.9, but 289 of 26 KB 6.9 : 6.7).  Over 1400 shapes of such rows and 193 to 384 candidates the two are equal on average, with 385 to 512
-// plain ones GEN_EXACT_MANY is 3 % ahead and up to one in seven shapes more than 3 % behind.
-constexpr int GEN_FEW = 192, GEN_FEW_LONG = 512, GEN_FEW_LONG_CONVERTED = 384;
+// workgroups move rows of 16 KB and more (the same rows with plain stores take as long as before).  Which kernel is ahead changes from shape to
+// shape.  Few against many over 16000 shapes of 193 to 512 candidates, rows of 16 KB and more: FIFO replacement, which makes no draws behind the
+// list, 1.01 to 1.03 by range and storage form, at most 3 of 100 more than 3 % slower (388 of 83 KB 14.5 : 15.8 us); else plain rows, up to 320 candidates, 1.00 to 1.01
+// (3 of 100), beyond 0.98 to 1.01 (up to 30 of 100); converted ones 0.99 to 1.00 (up to 16).
+constexpr int GEN_FEW = 192, GEN_FEW_LONG = 320, GEN_FEW_LONG_FIFO = 512;
 constexpr int64_t GEN_LONG_VEC = 1024;
-inline bool gen_few(int c, int64_t row_vec, bool converted)
+inline bool gen_few(int c, int64_t row_vec, bool converted, int eviction)
 {
-    return c <= (row_vec < GEN_LONG_VEC ? GEN_FEW : converted ? GEN_FEW_LONG_CONVERTED : GEN_FEW_LONG);
+    if (row_vec < GEN_LONG_VEC) return c <= GEN_FEW;
+    return c <= (eviction == RB_EVICT_FIFO ? GEN_FEW_LONG_FIFO : converted ? GEN_FEW : GEN_FEW_LONG);
 }
 // Lists of this many candidates: the later class-mates of a class with many in this step are gathered for their draws.  They are dealt to the lanes
 // unevenly, and of 300 candidates of three classes a lane holds up to eight: 283 + 3 classes 10.1 us, 11.1 with a draw per candidate a lane holds

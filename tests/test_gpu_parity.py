@@ -127,9 +127,9 @@ def test_general_kernels_at_the_edges_of_their_rounds(K, S, b, c, r, policy):
 
 
 # ... and where they take another form: by the number of candidates, sooner with short rows, and with classes of more candidates than lanes.
-@pytest.mark.parametrize("policy", ["exact-uniform", "exact-reservoir", "bernoulli-uniform"])
+@pytest.mark.parametrize("policy", ["exact-uniform", "exact-fifo", "exact-reservoir", "bernoulli-uniform"])
 @pytest.mark.parametrize("vecs,store", [(1023, "same"), (1024, "same"), (1024, "bf16")])
-@pytest.mark.parametrize("c", [192, 193, 384, 385, 512, 513])
+@pytest.mark.parametrize("c", [192, 193, 320, 321, 384, 385, 512, 513])
 def test_general_update_at_the_edges_of_its_forms(c, vecs, store, policy):
     w = wl.Workload(f"forms-{c}-{vecs}-{store}", 9, 3, 90, (vecs * (4 if store == "same" else 8),), "f32", 520, c, 20, 4, "uniform", "uniform")
     run_parity(w, check_state_every=2, policy=POLICIES.get(policy), store_bf16=store == "bf16")
