@@ -1284,7 +1284,7 @@ int step_form(const rb_buffer* rb, int64_t c, int64_t r)
 // made beside them, but takes longer than short rows where
 //   FIFO or reservoir replacement has the update planner keep the state of many classes, and its threads meet at the counters of classes
 //     with many candidates (labels, which the host cannot see), while the other form is a single launch.  What a plan saves and costs there,
-//     in us, is fitted to 11000 shapes, with 0.3 for labels that are in favour of a plan;
+//     in us, is fitted to 11300 shapes; 0.3 of the 1.2 are not, they leave shapes that are about equal to the plan;
 //   a single class has all candidates: more than 300 of them 0.91, FIFO and reservoir replacement 0.80 times as fast when planned.
 // Unannounced steps' time over announced ones' (singly or 16 a call, the worse), random shapes of 1025 to 4096 positions, a quarter each of
 // them with labels of three classes, of fifty, skewed and uniform ones:

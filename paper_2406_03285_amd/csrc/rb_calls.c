@@ -1,9 +1,10 @@
 /*
  * Native marshalling of the calls a training loop makes: rb_update, rb_sample_augment, rb_update_sample, rb_announce_next,
  * rb_update_sample_many, rb_announce_next_many, rb_pipeline_step_many and rb_pipeline_drain (rb_pipeline_step goes through ctypes).
- * One `Call` object per function: called with integers, None and tensors in the declared positions it goes straight
- * to the library; anything else (keywords, other number types, wrong argument counts) goes to the Python function it was made with, which says what is accepted and what is not.  A call through ctypes converts every argument through objects of its
- * own: 16 + 16 rows of 12 KB in one call take the host 4.2 us that way and 3.3 so (on a slower one 5.1 and 4.0), and the GPU 4.1.
+ * One `Call` object per function: called with integers, None and tensors in the declared positions it goes straight to the library;
+ * anything else (keywords, other number types, wrong argument counts) goes to the Python function it was made with, which says what is
+ * accepted and what is not.  A call through ctypes converts every argument through objects of its own: 16 + 16 rows of 12 KB in one call
+ * take the host 4.2 us that way and 3.3 so (on a slower one 5.1 and 4.0), and the GPU 4.1.
  * A call for many steps and its announcement make five arrays of pointers besides: for 20 steps through ctypes 28 us, which pipelines of
  * short steps wait for, and 4.3 so (16 steps of 21 + 7 rows of 44 KB on a stream of their own 54 -> 41 us a call).
  *
